@@ -253,18 +253,15 @@ int release_subset_slice(cleave::SubsetRing& r, int64_t begin, int64_t total, hi
   return CLEAVE_OK;
 }
 
-const char* kernel_name(int dtype, int cls, bool vec, int transA, int transB) {
-  static const char* names[2][2][5] = {
-      {{"execute_f32_256x256_nn", "execute_f32_256x256_nt", "execute_f32_256x256_tn", "execute_f32_256x256_tt",
-        "execute_f32_256x256_scalar"},
-       {"execute_f32_128x128_nn", "execute_f32_128x128_nt", "execute_f32_128x128_tn", "execute_f32_128x128_tt",
-        "execute_f32_128x128_scalar"}},
-      {{"execute_bf16_256x256_nn", "execute_bf16_256x256_nt", "execute_bf16_256x256_tn", "execute_bf16_256x256_tt",
-        "execute_bf16_256x256_scalar"},
-       {"execute_bf16_128x128_nn", "execute_bf16_128x128_nt", "execute_bf16_128x128_tn", "execute_bf16_128x128_tt",
-        "execute_bf16_128x128_scalar"}}};
-  const int mode = vec ? (transA ? 2 : 0) + (transB ? 1 : 0) : 4;
-  return names[dtype == CLEAVE_BF16 ? 1 : 0][cls][mode];
+const char* kernel_name(int dtype, cleave::ExecuteTile tile, int transA, int transB) {
+  static const char* names[2][3][4] = {
+      {{"execute_f32_128x128_nn", "execute_f32_128x128_nt", "execute_f32_128x128_tn", "execute_f32_128x128_tt"},
+       {"execute_f32_64x64_nn", "execute_f32_64x64_nt", "execute_f32_64x64_tn", "execute_f32_64x64_tt"},
+       {"execute_f32_element", "execute_f32_element", "execute_f32_element", "execute_f32_element"}},
+      {{"execute_bf16_128x128_nn", "execute_bf16_128x128_nt", "execute_bf16_128x128_tn", "execute_bf16_128x128_tt"},
+       {"execute_bf16_64x64_nn", "execute_bf16_64x64_nt", "execute_bf16_64x64_tn", "execute_bf16_64x64_tt"},
+       {"execute_bf16_element", "execute_bf16_element", "execute_bf16_element", "execute_bf16_element"}}};
+  return names[dtype == CLEAVE_BF16 ? 1 : 0][tile][(transA ? 2 : 0) + (transB ? 1 : 0)];
 }
 
 const char* direct_kernel_name(int cls, int transA, int transB) {
@@ -358,7 +355,9 @@ inline int subset_part(const cleave_task& t) { return t.k_len % cleave::kDirectK
 
 // Validates the ids (range, no repeats) and sizes the lists.  Uses the plan's
 // own stamp array for the repeat check: no allocation.  Caller holds subset.mu.
-int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int cus, SubsetLayout* out) {
+// always_fine: the launch takes small sub-tiles whatever their number.
+int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int cus, bool always_fine,
+                  SubsetLayout* out) {
   const int64_t n_tasks = static_cast<int64_t>(plan->tasks.size());
   if (++plan->seen_generation == 0) {   // wrapped: start over with clean stamps
     std::fill(plan->seen_stamp.begin(), plan->seen_stamp.end(), 0u);
@@ -374,7 +373,7 @@ int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int
   }
   // Few large items would leave most CUs idle: cut everything small instead
   // (the bits do not depend on the cut).
-  out->fine = large_items > 0 && large_items <= static_cast<size_t>(cus) / 2;
+  out->fine = always_fine || (large_items > 0 && large_items <= static_cast<size_t>(cus) / 2);
   for (int64_t i = 0; i < n_ids; ++i) {
     const cleave_task& t = plan->tasks[task_ids[i]];
     const cleave::SubTiling st = cleave::sub_tiling(t, out->fine);
@@ -410,6 +409,21 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
     }
   }
   return CLEAVE_OK;
+}
+
+// Workgroup tile of the general kernel for `items` 128 x 128 work items.  The
+// 64 x 64 tile gives four times as many workgroups, four of them per CU
+// instead of two, at twice the LDS traffic per flop.  fp32 MFMAs leave the LDS
+// mostly idle, so there the narrow tile wins until the wide one has several
+// rounds of workgroups (us, wide / narrow: 512^3 with 32 items 22 / 10,
+// 768x3072x2048 with 288 items 128 / 89, 2048x3072x768 with 768 items 90 / 92,
+// 4096^3 with 4096 items 999 / 1046).  bf16 MFMAs do not: narrow only while
+// the wide tile leaves half of the CUs without a workgroup (1000^3, 128 items
+// 13.8 / 11.3; 2001x768x3072, 192 items 27.4 / 29.7; 3001x2999x1001, 1152
+// items 44 / 55).
+cleave::ExecuteTile general_tile(int dtype, int64_t items, int cus) {
+  const int64_t narrow_up_to = dtype == CLEAVE_BF16 ? cus / 2 : int64_t{4} * cus - 1;
+  return items <= narrow_up_to ? cleave::kTileNarrow : cleave::kTileWide;
 }
 
 int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, const void* A,
@@ -455,6 +469,12 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
                    // in-tile byte offsets are kept in 32 bits
                    lda * eb < (int64_t{1} << 22) && ldb * eb < (int64_t{1} << 22) &&
                    offsets_multiple_of(bl.a, bl.shape, e) && offsets_multiple_of(bl.b, bl.shape, e);
+  const bool direct = vec && dtype == CLEAVE_BF16;
+  // the general kernel's 16-byte loads need that much between the start of a
+  // stored row and the end of any chunk (K-contiguous) or row (otherwise), and
+  // keep in-tile byte offsets (up to 128 rows) in 32 bits
+  const bool by_element = (transA ? plan->M : plan->min_k_end) < e || (transB ? plan->min_k_end : plan->N) < e ||
+                          lda * eb >= (int64_t{1} << 25) || ldb * eb >= (int64_t{1} << 25);
 
   const cleave::WorkItem* d_lists[cleave::kNumTileClasses] = {plan->d_items[0], plan->d_items[1]};
   int64_t counts[cleave::kNumTileClasses] = {static_cast<int64_t>(plan->items[0].size()),
@@ -464,7 +484,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
                                                   static_cast<int64_t>(plan->items_whole_steps[1])};
   // which of the plan's lists a class runs from (-1: a subset's own list)
   int list_of[cleave::kNumTileClasses] = {task_ids ? -1 : 0, task_ids ? -1 : 1};
-  if (!task_ids && prefers_fine(plan->items[cleave::kTileLarge].size())) {
+  if (!task_ids && (!direct || prefers_fine(plan->items[cleave::kTileLarge].size()))) {
     list_of[cleave::kTileSmall] = cleave::kNumTileClasses;
     d_lists[cleave::kTileLarge] = nullptr;
     counts[cleave::kTileLarge] = 0;
@@ -481,7 +501,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   if (task_ids) {
     subset_lock = std::unique_lock<std::mutex>(plan->subset.mu);
     SubsetLayout layout;
-    rc = layout_subset(plan, task_ids, n_ids, cus, &layout);
+    rc = layout_subset(plan, task_ids, n_ids, cus, !direct, &layout);
     if (rc != CLEAVE_OK) return rc;
     slice_total = layout.total();
     cleave::WorkItem* slice = nullptr;
@@ -533,6 +553,9 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     args.b_at = bl.b;
     args.c_at = bl.c;
     args.C = asm_to.C;
+    args.M = plan->M;
+    args.N = plan->N;
+    args.K = plan->K;
     args.ldc = asm_to.ldc;
     args.c_bf16 = asm_to.out_dtype == CLEAVE_BF16 ? 1 : 0;
     // block origins and row lengths are multiples of 8 elements whenever `vec` holds
@@ -541,10 +564,11 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
                                : (asm_to.ldc % 4 == 0 && aligned(asm_to.C, args.c_bf16 ? 8 : 16) &&
                                   offsets_multiple_of(bl.c, bl.shape, 4));
     // bf16 with 16-byte loads: items made of whole K steps go to the direct
-    // kernel, the others (if any) to the staged one.  Which kernel computes a
+    // kernel, the others (if any) to the general one.  Which kernel computes a
     // block depends only on the block's own task record.
-    const int64_t n_direct = (vec && dtype == CLEAVE_BF16) ? whole_steps[c] : 0;
-    const int64_t n_staged = counts[c] - n_direct;
+    const int64_t n_direct = direct ? whole_steps[c] : 0;
+    const int64_t n_general = counts[c] - n_direct;
+    cleave::ExecuteTile tile = cleave::kTileWide;
     if (n_direct > 0) {
       // Persistent workgroups, as many as the chip holds at once: each walks
       // the item list with the grid as stride and fetches the head of its next
@@ -560,21 +584,18 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       args.wg_ranges = nullptr;
       if (he != hipSuccess) return launch_failed(he);
     }
-    if (n_staged > 0) {
-      // One workgroup per work item (the kernel loops only if the grid is
-      // capped): the hardware dispatcher then balances uneven items and keeps
-      // the workgroups that share a CU out of phase.
+    if (n_general > 0) {
       args.items = d_lists[c] + n_direct;
-      args.n_items = n_staged;
-      constexpr int64_t kMaxGrid = int64_t{1} << 20;
-      const int grid = static_cast<int>(std::min<int64_t>(n_staged, kMaxGrid));
-      const hipError_t he = cleave::launch_execute(args, dtype, c, vec, grid, stream);
+      args.n_items = n_general;
+      tile = by_element ? cleave::kTileByElement
+                        : general_tile(dtype, n_general * (c == cleave::kTileLarge ? 4 : 1), cus);
+      const hipError_t he = cleave::launch_execute(args, dtype, c, tile, stream);
       if (he != hipSuccess) return launch_failed(he);
     }
     if (counts[c] > most) {
       most = counts[c];
-      plan->last_kernel = n_direct >= n_staged ? direct_kernel_name(c, transA, transB)
-                                               : kernel_name(dtype, c, vec, transA, transB);
+      plan->last_kernel = n_direct >= n_general ? direct_kernel_name(c, transA, transB)
+                                               : kernel_name(dtype, tile, transA, transB);
     }
   }
   if (task_ids && !static_scratch) return release_subset_slice(plan->subset, slice_begin, slice_total, stream);

@@ -2,27 +2,46 @@
 // rows of A with its columns of B; here restricted to its chunk of the inner
 // dimension, and the fp32 partial block goes to the task's slot in HBM).
 //
-// This is the staged executor: fp32 inputs, chunk lengths or tile edges the
-// bf16 direct-to-LDS path does not take, unaligned operands.  One workgroup
-// computes one work item: a 256 x 256 sub-tile (8 wave64 as 2 x 4, a wave owns
-// 128 x 64) or a 128 x 128 one (4 waves as 2 x 2, 64 x 64 each) of a task's
-// output block over the task's whole chunk [k0, k0 + k_len).  The inner loop
-// walks the chunk in ascending steps of 128 bytes of K per row (64 bf16 / 32
-// fp32 elements) and, inside a step, in ascending 32-byte sub-steps; the order
-// of the MFMA accumulation for an output element therefore depends only on
-// the task record, which is what makes a re-issued task bitwise reproducible.
+// This is the general executor: fp32 inputs, and every bf16 work item that the
+// direct-to-LDS kernel does not take (chunks that are no whole number of its K
+// steps, operands whose rows do not start on 16-byte boundaries, rows longer
+// than its 32-bit offsets).  One workgroup computes one TM x TN part of a work
+// item over the task's whole chunk [k0, k0 + k_len), in ascending steps of 128
+// bytes of K per row (64 bf16 / 32 fp32 elements) and, inside a step, in
+// ascending 32-byte sub-steps; the order of the MFMA accumulation for an
+// output element therefore depends only on the task record (and is the direct
+// kernel's), which is what makes a re-issued task bitwise reproducible.
 //
-// Data path per K step: global -> VGPR (16-byte chunks, issued one step
-// ahead) -> LDS (K-contiguous rows, 16 bytes of padding per row so that
-// fragment reads are bank-conflict free; operands whose storage is not
-// K-contiguous are transposed in registers on the way) -> 16-byte fragment
-// reads -> MFMA 32x32x16 bf16 (or 32x32x2 fp32) into fp32 accumulators ->
-// stores of the partial block.  The small class is sized so that two
-// workgroups share a CU: while one waits at a barrier, refills LDS or drains
-// its stores, the other keeps the matrix cores busy.
+// Data path per K step: global -> VGPR in 16-byte loads -> LDS -> fragments ->
+// MFMA 32x32x16 bf16 (or 32x32x2 fp32) into fp32 accumulators.
+//   * The loads need only the alignment of an element (global memory takes
+//     16-byte loads at any address), so an odd leading dimension or chunk
+//     start costs a second cache line per row, not sixteen-fold instructions.
+//     Elements beyond the chunk must be zero and loads must stay inside the
+//     operand, so the steps that touch an end (the last of a chunk) load the
+//     last 16 bytes that are inside and shift the wanted elements down.
+//   * Loads run SETS steps ahead in registers and LDS holds two steps, with one
+//     barrier per step: what bounds a launch with few workgroups is the latency
+//     of a step's loads, and SETS of them overlap.
+//     The waits on them count loads in flight, so the loads of a step past the
+//     last one are issued too (one line, already read) rather than skipped.
+//   * LDS images and fragment reads are the direct kernel's (swizzled
+//     K-contiguous rows; k rows read through the LDS transpose read for bf16,
+//     one dword per k for fp32), so nothing is transposed in registers.
+//
+// What bounds it: fp32, the matrix cores (64 cycles per 32x32x2): 4096^3 as
+// 512 x 512 x 1024 tasks runs at 138-141 TFLOP/s of 157 nominal.  bf16, the LDS
+// (a 64 x 64 wave tile reads 128 bytes per clock and CU at full MFMA rate, and
+// the tile's refill comes on top): the same with an odd leading dimension
+// 613-638 TFLOP/s.  Before, operands that were not 16-byte aligned were loaded
+// one element at a time and fp32 had one workgroup tile with one step in
+// flight.  Execute + reduce, before -> now: forward, dX and dW of 3001 x 1000 x
+// 2500 bf16 in 4 splits 1173 -> 169 us, of 2048 x 768 x 3072 fp32 403 -> 266
+// us, 512^3 fp32 26.7 -> 17.3 us.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "plan_internal.h"
 #include "kernels.h"
@@ -37,369 +56,492 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void* lds_void;
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+// 16 bytes at an address that is only a multiple of an element
+typedef uint32_t u32x4_at2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
 
-constexpr int kChunksPerRow = 8;                    // 128 bytes of K per tile row and step
-constexpr int kRowStride = 16 * kChunksPerRow + 16; // LDS bytes per tile row (padded)
+template <int V>
+using int_c = std::integral_constant<int, V>;
+
+// Kernel shape: element bytes, workgroup tile TM x TN computed by WM x WN
+// waves, SETS register sets of loads in flight, WPE waves per SIMD.
+template <int EB_, int TM_, int TN_, int WM_, int WN_, int SETS_, int WPE_>
+struct Shape {
+  static constexpr int EB = EB_, TM = TM_, TN = TN_, WM = WM_, WN = WN_, SETS = SETS_, WPE = WPE_;
+  static constexpr int NT = WM * WN * 64;
+  static constexpr int E = 16 / EB;             // elements per 16-byte chunk
+  static constexpr int KS = 128 / EB;           // elements of K per step
+  static constexpr int WTM = TM / WM, WTN = TN / WN;
+  static constexpr int MB = WTM / 32, NB = WTN / 32;
+  static constexpr int kSub = 4;                // 32-byte sub-steps per step
+  static constexpr int kATile = TM * 128, kBTile = TN * 128;   // bytes
+  static constexpr int kStage = kATile + kBTile;
+  static_assert(SETS == 1 || SETS == 2 || SETS == 4, "register sets rotate with the two LDS stages");
+};
+
+// All LDS accesses of this wave are done; then the workgroup barrier.  Loads
+// to registers stay in flight across it.
+#define CLEAVE_LDS_BARRIER() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
+
+// The elements of a 16-byte chunk moved down by `shift` elements, zeros above
+// (shift >= E: all zero).
+template <int EB>
+__device__ __forceinline__ u32x4 shift_down(u32x4 v, int shift) {
+  constexpr int E = 16 / EB;
+  const int bits = shift * EB * 8;
+  const uint64_t lo = v[0] | (static_cast<uint64_t>(v[1]) << 32);
+  const uint64_t hi = v[2] | (static_cast<uint64_t>(v[3]) << 32);
+  const uint64_t across = bits == 0 ? 0 : hi << ((64 - bits) & 63);
+  uint64_t l = bits < 64 ? (lo >> (bits & 63)) | across : hi >> ((bits - 64) & 63);
+  uint64_t h = bits < 64 ? hi >> (bits & 63) : 0;
+  if (shift >= E) l = h = 0;
+  return u32x4{static_cast<uint32_t>(l), static_cast<uint32_t>(l >> 32), static_cast<uint32_t>(h),
+               static_cast<uint32_t>(h >> 32)};
+}
 
 // ---------------------------------------------------------------------------
 // Operand tile: R rows (an m or n index) x 128 bytes of K, moved global ->
-// registers -> LDS by NT threads.  `row_stride` / `k_stride` are element
-// strides of the stored matrix along the tile's row index and along K.
+// registers -> LDS by NT threads, NV 16-byte chunks each.  Slot s of the LDS
+// image is written by thread s % NT.
+//   KCONTIG: tile rows of 128 bytes, slot = r * 8 + (chunk ^ ((r >> 1) & 7)).
+//   else:    KS k rows of R elements, slot = k * CH + (chunk ^ swizzle(k)); the
+//            swizzle spreads over the banks the four k rows of a transpose
+//            read (bf16) or the k rows of the two halves of a wave (fp32).
 // ---------------------------------------------------------------------------
-enum LoadMode : int { kVecKContig = 0, kVecTransposed = 1, kScalar = 2 };
-
-template <int EB, int R, int NT, int MODE>
+template <int EB, int R, int NT, bool KCONTIG, bool ELEMENTWISE>
 struct OperandTile {
-  static constexpr int E = 16 / EB;                 // elements per 16-byte chunk
-  static constexpr int NV = R * kChunksPerRow / NT; // 16-byte chunks held per thread
-  // Transposed mode: a thread owns KB consecutive k rows x E consecutive tile
-  // rows (one 16-byte load per k row) and writes E runs of KB elements.
-  static constexpr int KB = (EB == 2) ? (NV < 8 ? NV : 8) : 4;
-  static constexpr int kBlocksPerThread = NV / KB;
-  static constexpr int KG = kChunksPerRow * E / KB; // k groups per step
-  static_assert(NV >= 2 && NV % KB == 0, "unsupported tile / thread count");
+  static_assert(KCONTIG || !ELEMENTWISE, "element loads fill the K-contiguous image, whatever the storage");
+  static constexpr int E = 16 / EB;
+  static constexpr int KS = 128 / EB;
+  static constexpr int CH = R / E;                  // chunks per k row
+  static constexpr int NV = R * 8 / NT;
+  static_assert(R * 8 % NT == 0, "tile / thread count");
 
-  u32x4 v[NV];
-  uint32_t off[NV];   // vector modes: byte offset of each 16-byte load from the step base
+  static __device__ __forceinline__ int k_swizzle(int k) {
+    if constexpr (EB == 4) return 8 * ((k >> 2) & 1);
+    else if constexpr (CH == 8) return 4 * ((k >> 1) & 1);
+    else return 4 * (k & 3);
+  }
+  // (tile row, k) of the first element of this thread's chunk i
+  static __device__ __forceinline__ void where(int i, int t, int* r, int* k) {
+    const int slot = t + NT * i;
+    if constexpr (KCONTIG) {
+      *r = slot >> 3;
+      *k = ((slot & 7) ^ ((*r >> 1) & 7)) * E;
+    } else {
+      *k = slot / CH;
+      *r = ((slot % CH) ^ k_swizzle(*k)) * E;
+    }
+  }
 
-  // Vector modes: fixes this thread's load offsets for one work item.  Rows
-  // beyond r_valid are clamped to the last valid 16-byte run: they only feed
-  // output elements that are never stored.
-  __device__ __forceinline__ void init(int64_t row_stride, int64_t k_stride, int r_valid, int t) {
-    if constexpr (MODE == kVecKContig) {
+  const unsigned char* base;    // element (tile row 0, k0); wave-uniform
+  const unsigned char* next;    // where the next step's loads start from; wave-uniform
+  uint32_t off[NV];             // byte offset of each chunk from `next`
+  int64_t row_stride, k_stride; // bytes
+  int r_valid, k_len, steps;
+  int left_to_row_end;          // !KCONTIG: elements from tile row 0 to the end of a stored row (>= r_valid)
+  int edge_step;                // the step whose loads must be kept inside the operand (-1: none)
+
+  // k0: chunk start; k_total, r_total: extent of the operand; r0: tile row 0.
+  __device__ __forceinline__ void init(const unsigned char* b, int64_t rs, int64_t ks, int rv, int64_t r0,
+                                       int64_t r_total, int64_t k0, int len, int64_t k_total, int t) {
+    base = next = b;
+    row_stride = rs * EB;
+    k_stride = ks * EB;
+    r_valid = rv;
+    k_len = len;
+    steps = (len + KS - 1) / KS;
+    edge_step = len % KS ? steps - 1 : -1;
+    if constexpr (KCONTIG) {
+      left_to_row_end = 0;
+    } else {
+      const int64_t left = r_total - r0;
+      left_to_row_end = static_cast<int>(left < 2 * R ? left : 2 * R);
+      // a chunk that runs past the end of a stored row stays inside the operand
+      // except on the operand's last row
+      const bool past_end = (rv + E - 1) / E * E > left_to_row_end;
+      if (past_end && k0 + len == k_total) edge_step = steps - 1;
+    }
+    if constexpr (ELEMENTWISE) return;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      int r, k;
+      where(i, t, &r, &k);
+      // rows beyond the valid ones feed outputs that are never stored: any row of the tile will do
+      if constexpr (KCONTIG) r = min(r, rv - 1);
+      else r = r < rv ? r : 0;
+      off[i] = static_cast<uint32_t>(r * row_stride + k * k_stride);
+    }
+  }
+
+  // Chunk i of the edge step is loaded `shift` elements before the wanted
+  // element, so that the 16 bytes end inside the row (K-contiguous: inside the
+  // chunk, everything behind it being zero).  Returns the byte offset from 16
+  // bytes before the step's start.
+  __device__ __forceinline__ uint32_t edge_source(int i, int t, int* shift) const {
+    int r, k;
+    where(i, t, &r, &k);
+    const int k_left = k_len - edge_step * KS;    // 1 .. KS
+    int at;
+    int64_t row;
+    if constexpr (KCONTIG) {
+      row = min(r, r_valid - 1) * row_stride;
+      at = min(k, k_left - E);                    // > -E, and the row holds E elements up to the chunk's end
+      *shift = k - at;
+    } else {
+      row = min(k, k_left - 1) * k_stride;
+      r = r < r_valid ? r : 0;
+      at = min(r, left_to_row_end - E);           // > -E, and a stored row holds E elements
+      *shift = k < k_left ? r - at : E;
+    }
+    return static_cast<uint32_t>(row + (at + E) * EB);
+  }
+
+  // One element at a time, for operands whose stored rows hold less than a
+  // chunk (or end less than a chunk behind their start) and for rows too long
+  // for 32-bit offsets.
+  __device__ __forceinline__ void load_elements(u32x4 (&v)[NV], int s, int t) const {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      int r, k;
+      where(i, t, &r, &k);
+      k += s * KS;
+      u32x4 w = {0, 0, 0, 0};
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        if (r < r_valid && k + e < k_len) {
+          const unsigned char* q = base + r * row_stride + (k + e) * k_stride;
+          if constexpr (EB == 4) w[e] = *reinterpret_cast<const uint32_t*>(q);
+          else w[e >> 1] |= static_cast<uint32_t>(*reinterpret_cast<const uint16_t*>(q)) << (16 * (e & 1));
+        }
+      }
+      v[i] = w;
+    }
+  }
+
+  // Steps are loaded in ascending order, each once.  The number of loads in
+  // flight must not depend on the control flow (the compiler's waits count
+  // them), so a step past the last one is loaded too: one line, already read.
+  __device__ __forceinline__ void load(u32x4 (&v)[NV], int s, int t) {
+    if constexpr (ELEMENTWISE) {
+      load_elements(v, s, t);
+      return;
+    }
+    typedef typename std::conditional<EB == 2, u32x4_at2, u32x4_at4>::type chunk_t;
+    if (s == edge_step) {
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
-        const int c = t + NT * i;
-        const int row = min(c >> 3, r_valid - 1);
-        off[i] = static_cast<uint32_t>((row * row_stride + (c & 7) * E) * EB);
+        int shift;
+        off[i] = edge_source(i, t, &shift);
+        __builtin_amdgcn_sched_barrier(0);
       }
-    } else if constexpr (MODE == kVecTransposed) {
+      next = base + s * (k_stride * KS) - 16;
+    } else if (s == steps) {
 #pragma unroll
-      for (int b = 0; b < kBlocksPerThread; ++b) {
-        const int blk = t + NT * b;
-        const int kg = (blk >> 3) % KG;
-        const int rg = (blk / (8 * KG)) * 8 + (blk & 7);
-        const int r = min(rg * E, r_valid - E);
+      for (int i = 0; i < NV; ++i) off[i] = __builtin_amdgcn_readfirstlane(off[0]);
+    }
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk)
-          off[b * KB + kk] = static_cast<uint32_t>(((kg * KB + kk) * k_stride + r) * EB);
+    for (int i = 0; i < NV; ++i) v[i] = *reinterpret_cast<const chunk_t*>(next + off[i]);
+    if (s + 1 < steps) next += k_stride * KS;
+  }
+
+  // Before the edge step is written to LDS: the wanted elements into place.
+  __device__ __forceinline__ void settle(u32x4 (&v)[NV], int s, int t) const {
+    if (!ELEMENTWISE && s == edge_step) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        int shift;
+        edge_source(i, t, &shift);
+        v[i] = shift_down<EB>(v[i], shift);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
 
-  // k index (within the step) of load i, for the tail predicate.
-  static __device__ __forceinline__ int k_of(int i, int t) {
-    if constexpr (MODE == kVecKContig) {
-      return ((t + NT * i) & 7) * E;
-    } else {
-      const int blk = t + NT * (i / KB);
-      return ((blk >> 3) % KG) * KB + (i % KB);
-    }
-  }
-
-  // base: first element of the tile's row 0 at this step's first k (bytes,
-  // wave-uniform).  FULL: the whole step lies inside the chunk; otherwise
-  // k_left (>= 1) elements remain and loads beyond them yield zeros.
-  template <bool FULL>
-  __device__ __forceinline__ void load(const unsigned char* base, int64_t row_stride,
-                                       int64_t k_stride, int r_valid, int k_left, int t) {
-    if constexpr (MODE != kScalar) {
+  static __device__ __forceinline__ void store(const u32x4 (&v)[NV], unsigned char* lds, int t) {
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        if (FULL || k_of(i, t) < k_left) {
-          v[i] = *reinterpret_cast<const u32x4*>(base + off[i]);
-        } else {
-          v[i] = u32x4{0, 0, 0, 0};
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int c = t + NT * i;
-        const int row = c >> 3;
-        const int k = (c & 7) * E;
-        u32x4 w = {0, 0, 0, 0};
-        if (row < r_valid) {
-          const unsigned char* p = base + (static_cast<int64_t>(row) * row_stride +
-                                           static_cast<int64_t>(k) * k_stride) * EB;
-          if constexpr (EB == 4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (k + e < k_left) w[e] = *reinterpret_cast<const uint32_t*>(p + e * k_stride * 4);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              if (k + e < k_left) {
-                const uint32_t h = *reinterpret_cast<const uint16_t*>(p + e * k_stride * 2);
-                w[e >> 1] |= h << (16 * (e & 1));
-              }
-            }
-          }
-        }
-        v[i] = w;
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(unsigned char* lds, int t) const {
-    if constexpr (MODE != kVecTransposed) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int c = t + NT * i;
-        *reinterpret_cast<u32x4*>(lds + (c >> 3) * kRowStride + (c & 7) * 16) = v[i];
-      }
-    } else {
-#pragma unroll
-      for (int b = 0; b < kBlocksPerThread; ++b) {
-        const int blk = t + NT * b;
-        const int kg = (blk >> 3) % KG;
-        const int rg = (blk / (8 * KG)) * 8 + (blk & 7);
-        unsigned char* dst = lds + (rg * E) * kRowStride + kg * KB * EB;
-        if constexpr (EB == 4) {
-          // 4 x 4 transpose of dwords: pure renaming.
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const u32x4 w = {v[b * 4 + 0][j], v[b * 4 + 1][j], v[b * 4 + 2][j], v[b * 4 + 3][j]};
-            *reinterpret_cast<u32x4*>(dst + j * kRowStride) = w;
-          }
-        } else {
-          // KB x 8 transpose of 16-bit values: row j of the result collects
-          // halfword j of the KB loaded k rows.
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            uint32_t w[KB / 2];
-#pragma unroll
-            for (int p = 0; p < KB / 2; ++p) {
-              const uint32_t lo = v[b * KB + 2 * p][j >> 1];
-              const uint32_t hi = v[b * KB + 2 * p + 1][j >> 1];
-              w[p] = (j & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
-            }
-            if constexpr (KB == 8) {
-              *reinterpret_cast<u32x4*>(dst + j * kRowStride) = u32x4{w[0], w[1], w[2], w[3]};
-            } else if constexpr (KB == 4) {
-              *reinterpret_cast<u32x2*>(dst + j * kRowStride) = u32x2{w[0], w[1]};
-            } else {
-              *reinterpret_cast<uint32_t*>(dst + j * kRowStride) = w[0];
-            }
-          }
-        }
-      }
-    }
+    for (int i = 0; i < NV; ++i) *reinterpret_cast<u32x4*>(lds + (t + NT * i) * 16) = v[i];
   }
 };
 
-// ---------------------------------------------------------------------------
-// The kernel.  A TM x TN workgroup tile computed by WM x WN waves; one LDS
-// stage (A tile then B tile), refilled from registers between two barriers.
-// Two (or more) workgroups are resident per CU, so one workgroup's barriers,
-// LDS refills and partial-block stores overlap with the other's MFMAs.
-// ---------------------------------------------------------------------------
-template <int EB, int TM, int TN, int WM, int WN, int MODE_A, int MODE_B>
-__global__ __launch_bounds__(WM* WN * 64, (WM * WN > 4 ? 1 : 2)) void execute_kernel(ExecuteArgs args) {
-  constexpr int NT = WM * WN * 64;
-  constexpr int E = 16 / EB;
-  constexpr int kStepElems = kChunksPerRow * E;
-  constexpr int WTM = TM / WM;          // wave tile
-  constexpr int WTN = TN / WN;
-  constexpr int MB = WTM / 32;          // 32 x 32 MFMA blocks per wave tile
-  constexpr int NB = WTN / 32;
-  constexpr int kATileBytes = TM * kRowStride;
-  constexpr int kSub = kChunksPerRow / 2;   // 32-byte sub-steps per K step
+// A_K / B_K: the operand is stored K-contiguous (ELEMENTWISE: both true, any storage).
+template <typename S, bool A_K, bool B_K, bool ELEMENTWISE>
+__global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args) {
+  constexpr int EB = S::EB, TM = S::TM, TN = S::TN, MB = S::MB, NB = S::NB, E = S::E, SETS = S::SETS;
 
   extern __shared__ __align__(16) unsigned char smem[];
 
   const int t = threadIdx.x;
   const int lane = t & 63;
-  const int wave = t >> 6;
-  const int wm = wave / WN;
-  const int wn = wave % WN;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave / S::WN;
+  const int wn = wave % S::WN;
   const int l32 = lane & 31;
   const int lh = lane >> 5;
 
-  // Element strides of the stored operands along (tile row, K).
+  // Lane-constant fragment addresses inside a stage: K-contiguous operands one
+  // per sub-step (blocks are 32 rows apart), others one per block.
+  const int i16 = lane & 15, kq = i16 >> 2, cq = i16 & 3, nsub = (lane >> 4) & 1;
+  const auto frag_addr = [&](int row0, int x, int r_tile, bool kcontig) -> uint32_t {
+    if (kcontig) return (row0 + l32) * 128 + (((2 * x + lh) ^ ((l32 >> 1) & 7)) * 16);
+    if (EB == 4) return (4 * lh * r_tile + ((row0 + x * 32 + l32) ^ (32 * lh))) * 4;
+    const int ch = r_tile / 8;
+    const int k = 8 * lh + kq;
+    const int c = row0 / 8 + x * 4 + 2 * nsub + (cq >> 1);
+    const int sw = ch == 8 ? 4 * ((k >> 1) & 1) : 4 * (k & 3);
+    return (k * ch + (c ^ sw)) * 16 + (cq & 1) * 8;
+  };
+  uint32_t a_addr[A_K ? S::kSub : MB], b_addr[B_K ? S::kSub : NB];
+#pragma unroll
+  for (int x = 0; x < (A_K ? S::kSub : MB); ++x) a_addr[x] = frag_addr(wm * S::WTM, x, TM, A_K);
+#pragma unroll
+  for (int x = 0; x < (B_K ? S::kSub : NB); ++x) b_addr[x] = S::kATile + frag_addr(wn * S::WTN, x, TN, B_K);
+
   const int64_t a_rs = args.transA ? 1 : args.lda;
   const int64_t a_ks = args.transA ? args.lda : 1;
   const int64_t b_rs = args.transB ? args.ldb : 1;
   const int64_t b_ks = args.transB ? 1 : args.ldb;
 
-  const unsigned char* a_frag = smem + (wm * WTM + l32) * kRowStride + lh * 16;
-  const unsigned char* b_frag = smem + kATileBytes + (wn * WTN + l32) * kRowStride + lh * 16;
-
-  for (int64_t it = blockIdx.x; it < args.n_items; it += gridDim.x) {
-    const WorkItem item = args.items[it];
-    const int m_valid = static_cast<int>(item.m_valid);
-    const int n_valid = static_cast<int>(item.n_valid);
-    const int64_t m_base = item.m_base;
-    const int64_t n_base = item.n_base;
+  // Workgroups are dealt round-robin over the XCDs and list position i belongs
+  // to XCD i % 8: the parts of an item follow each other on the item's XCD.
+  const uint32_t parts = args.parts_m * args.parts_n;
+  const uint64_t total = (static_cast<uint64_t>(args.n_items) + 7) / 8 * 8 * parts;
+  for (uint64_t b = blockIdx.x; b < total; b += gridDim.x) {
+    const uint64_t j = b >> 3;
+    const uint64_t it = j / parts * 8 + (b & 7);
+    const uint32_t part = static_cast<uint32_t>(j % parts);
+    if (it >= static_cast<uint64_t>(args.n_items)) continue;
+    const WorkItem item = load_work_item(args.items, static_cast<int64_t>(it));
+    const int m_off = static_cast<int>(part / args.parts_n) * TM;
+    const int n_off = static_cast<int>(part % args.parts_n) * TN;
+    const int m_valid = min(static_cast<int>(item.m_valid) - m_off, TM);
+    const int n_valid = min(static_cast<int>(item.n_valid) - n_off, TN);
+    if (m_valid <= 0 || n_valid <= 0) continue;
+    const int64_t m_base = static_cast<int64_t>(item.m_base) + m_off;
+    const int64_t n_base = static_cast<int64_t>(item.n_base) + n_off;
     const int k_len = static_cast<int>(item.k_len);
 
-    const unsigned char* a_ptr =
-        static_cast<const unsigned char*>(args.A) +
-        (member_offset(args.a_at, args.batch, item.gemm_id) + m_base * a_rs +
-         static_cast<int64_t>(item.k0) * a_ks) * EB;
-    const unsigned char* b_ptr =
-        static_cast<const unsigned char*>(args.B) +
-        (member_offset(args.b_at, args.batch, item.gemm_id) + n_base * b_rs +
-         static_cast<int64_t>(item.k0) * b_ks) * EB;
+    OperandTile<EB, TM, S::NT, A_K, ELEMENTWISE> ta;
+    OperandTile<EB, TN, S::NT, B_K, ELEMENTWISE> tb;
+    ta.init(static_cast<const unsigned char*>(args.A) +
+                (member_offset(args.a_at, args.batch, item.gemm_id) + m_base * a_rs +
+                 static_cast<int64_t>(item.k0) * a_ks) * EB,
+            a_rs, a_ks, m_valid, m_base, args.M, item.k0, k_len, args.K, t);
+    tb.init(static_cast<const unsigned char*>(args.B) +
+                (member_offset(args.b_at, args.batch, item.gemm_id) + n_base * b_rs +
+                 static_cast<int64_t>(item.k0) * b_ks) * EB,
+            b_rs, b_ks, n_valid, n_base, args.N, item.k0, k_len, args.K, t);
 
     f32x16 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+      for (int jn = 0; jn < NB; ++jn) acc[i][jn] = f32x16{};
 
-    OperandTile<EB, TM, NT, MODE_A> ta;
-    OperandTile<EB, TN, NT, MODE_B> tb;
-    ta.init(a_rs, a_ks, m_valid, t);
-    tb.init(b_rs, b_ks, n_valid, t);
+    u32x4 va[SETS][ta.NV], vb[SETS][tb.NV];
+    auto fetch = [&](auto set_tag, int s) {
+      constexpr int set = decltype(set_tag)::value;
+      ta.load(va[set], s, t);
+      tb.load(vb[set], s, t);
+    };
+    auto commit = [&](auto set_tag, auto stage_tag, int s) {
+      constexpr int set = decltype(set_tag)::value, stage = decltype(stage_tag)::value;
+      ta.settle(va[set], s, t);
+      tb.settle(vb[set], s, t);
+      ta.store(va[set], smem + stage * S::kStage, t);
+      tb.store(vb[set], smem + stage * S::kStage + S::kATile, t);
+    };
 
-    // Global -> registers for step s; full steps take the unpredicated path.
-    auto load_step = [&](int s) {
-      const int64_t koff = static_cast<int64_t>(s) * kStepElems;
-      const int k_left = k_len - static_cast<int>(koff);
-      const unsigned char* pa = a_ptr + koff * a_ks * EB;
-      const unsigned char* pb = b_ptr + koff * b_ks * EB;
-      if (k_left >= kStepElems) {
-        ta.template load<true>(pa, a_rs, a_ks, m_valid, k_left, t);
-        tb.template load<true>(pb, b_rs, b_ks, n_valid, k_left, t);
+    u32x4 fa[2][MB], fb[2][NB];
+    auto tr_read = [&](const unsigned char* q) -> u32x2 {
+      return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)q));
+    };
+    auto read_frag = [&](const unsigned char* stage, const uint32_t* addr, auto kcontig_tag, auto rows_tag,
+                         auto ks_tag, int x) -> u32x4 {
+      constexpr bool KC = decltype(kcontig_tag)::value;
+      constexpr int R = decltype(rows_tag)::value, KSUB = decltype(ks_tag)::value;
+      if constexpr (KC) {
+        return *reinterpret_cast<const u32x4*>(stage + addr[KSUB] + x * 32 * 128);
+      } else if constexpr (EB == 2) {
+        const unsigned char* q = stage + addr[x] + KSUB * (16 * R * 2);
+        const u32x2 lo = tr_read(q), hi = tr_read(q + 4 * R * 2);
+        return u32x4{lo[0], lo[1], hi[0], hi[1]};
       } else {
-        ta.template load<false>(pa, a_rs, a_ks, m_valid, k_left, t);
-        tb.template load<false>(pb, b_rs, b_ks, n_valid, k_left, t);
+        const uint32_t* q = reinterpret_cast<const uint32_t*>(stage + addr[x] + KSUB * (8 * R * 4));
+        return u32x4{q[0], q[R], q[2 * R], q[3 * R]};
       }
     };
-    auto store_step = [&]() {
-      ta.store(smem, t);
-      tb.store(smem + kATileBytes, t);
-    };
-    u32x4 fa[2][MB], fb[2][NB];
-    auto read_frags = [&](int ks, int buf) {
+    auto read_frags = [&](int stage, auto ks_tag, int buf) {
 #pragma unroll
       for (int i = 0; i < MB; ++i)
-        fa[buf][i] = *reinterpret_cast<const u32x4*>(a_frag + i * 32 * kRowStride + ks * 32);
+        fa[buf][i] = read_frag(smem + stage * S::kStage, a_addr, std::bool_constant<A_K>{}, int_c<TM>{}, ks_tag, i);
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
-        fb[buf][j] = *reinterpret_cast<const u32x4*>(b_frag + j * 32 * kRowStride + ks * 32);
+      for (int i = 0; i < NB; ++i)
+        fb[buf][i] = read_frag(smem + stage * S::kStage, b_addr, std::bool_constant<B_K>{}, int_c<TN>{}, ks_tag, i);
     };
     auto mma = [&](int buf) {
+      if constexpr (EB == 2) {
 #pragma unroll
-      for (int i = 0; i < MB; ++i) {
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          if constexpr (EB == 2) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, fa[buf][i]), __builtin_bit_cast(bf16x8, fb[buf][j]),
-                acc[i][j], 0, 0, 0);
-          } else {
-            // (bit-cast the whole chunk first: a bit_cast of a single vector
-            // element lvalue is miscompiled into a read of element 0)
-            const f32x4 a4 = __builtin_bit_cast(f32x4, fa[buf][i]);
-            const f32x4 b4 = __builtin_bit_cast(f32x4, fb[buf][j]);
+          for (int jn = 0; jn < NB; ++jn)
+            acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8, fa[buf][i]), __builtin_bit_cast(bf16x8, fb[buf][jn]), acc[i][jn], 0, 0, 0);
+      } else {
+        // (bit-cast the whole chunk first: a bit_cast of a single vector
+        // element lvalue is miscompiled into a read of element 0)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4[e], b4[e], acc[i][j], 0, 0, 0);
-          }
-        }
+        for (int e = 0; e < E; ++e)
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int jn = 0; jn < NB; ++jn) {
+              const f32x4 a4 = __builtin_bit_cast(f32x4, fa[buf][i]);
+              const f32x4 b4 = __builtin_bit_cast(f32x4, fb[buf][jn]);
+              acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4[e], b4[e], acc[i][jn], 0, 0, 0);
+            }
       }
     };
 
-    const int steps = (k_len + kStepElems - 1) / kStepElems;
-    load_step(0);
-    // Every wave has finished reading the previous work item's last tile.
-    __syncthreads();
-    store_step();
-    __syncthreads();
+    const int steps = (k_len + S::KS - 1) / S::KS;
+    // Steps 0 .. SETS-1 into registers, step 0 on into LDS, step SETS behind it.
+    fetch(int_c<0>{}, 0);
+    if constexpr (SETS > 1) fetch(int_c<1>{}, 1);
+    if constexpr (SETS > 2) {
+      fetch(int_c<2>{}, 2);
+      fetch(int_c<3>{}, 3);
+    }
+    if (b != blockIdx.x) CLEAVE_LDS_BARRIER();   // every wave is past the previous item's last fragment reads
+    commit(int_c<0>{}, int_c<0>{}, 0);
+    fetch(int_c<0>{}, SETS);
+    CLEAVE_LDS_BARRIER();
+    read_frags(0, int_c<0>{}, 0);
 
-    for (int s = 0; s < steps; ++s) {
-      const bool more = s + 1 < steps;
-      read_frags(0, 0);
-      if (more) load_step(s + 1);
-#pragma unroll
-      for (int ks = 0; ks < kSub; ++ks) {
-        if (ks + 1 < kSub) read_frags(ks + 1, (ks + 1) & 1);
-        mma(ks & 1);
-        if constexpr (EB == 2) {
-          // Issue order inside a sub-step: one fragment read of the next
-          // sub-step between consecutive MFMAs of this one.
-          if (ks + 1 < kSub) {
-#pragma unroll
-            for (int x = 0; x < MB + NB; ++x) {
-              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, MB * NB - (MB + NB), 0);
-          }
-        }
+    // Step s sits in LDS stage s % 2; register set s % SETS holds step s until
+    // it is written to LDS at the end of step s - 1 (the stage's readers, step
+    // s - 2's, are past the barrier between), and then takes step s + SETS.
+    auto k_step = [&](auto phase_tag, int s) {
+      constexpr int P = decltype(phase_tag)::value;
+      constexpr int cur = P & 1, oth = cur ^ 1, next_set = (P + 1) % SETS;
+      read_frags(cur, int_c<1>{}, 1);
+      mma(0);
+      read_frags(cur, int_c<2>{}, 0);
+      mma(1);
+      read_frags(cur, int_c<3>{}, 1);
+      mma(0);
+      if (s + 1 < steps) {
+        commit(int_c<next_set>{}, int_c<oth>{}, s + 1);
+        fetch(int_c<next_set>{}, s + 1 + SETS);
+        CLEAVE_LDS_BARRIER();
+        read_frags(oth, int_c<0>{}, 0);
       }
-      if (more) {
-        __syncthreads();     // all fragment reads of this step are done
-        store_step();
-        __syncthreads();     // the next step's tile is visible
+      mma(1);
+    };
+    for (int s = 0; s < steps;) {
+      k_step(int_c<0>{}, s);
+      if (++s >= steps) break;
+      k_step(int_c<1>{}, s);
+      if (++s >= steps) break;
+      if constexpr (SETS == 4) {
+        k_step(int_c<2>{}, s);
+        if (++s >= steps) break;
+        k_step(int_c<3>{}, s);
+        ++s;
       }
     }
 
-    const int row0 = wm * WTM + lh * 4;
-    const int col0 = wn * WTN + l32;
-    store_tile<MB, NB>(acc, tile_target(args, item), args.C && args.c_bf16, row0, col0, m_valid,
-                       n_valid, m_valid == TM && n_valid == TN);
+    const int row0 = wm * S::WTM + lh * 4;
+    const int col0 = wn * S::WTN + l32;
+    TileTarget target = tile_target(args, item);
+    target.base += (m_off * target.ld + n_off) * (args.C && args.c_bf16 ? 2 : 4);
+    store_tile<MB, NB>(acc, target, args.C && args.c_bf16, row0, col0, m_valid, n_valid,
+                       m_valid == TM && n_valid == TN);
   }
 }
 
-template <int EB, int TM, int TN, int WM, int WN, int MODE_A, int MODE_B>
+template <typename S, bool A_K, bool B_K, bool ELEMENTWISE = false>
 hipError_t launch_one(const ExecuteArgs& args, int grid, hipStream_t stream) {
-  constexpr size_t lds = (TM + TN) * kRowStride;
-  hipLaunchKernelGGL((execute_kernel<EB, TM, TN, WM, WN, MODE_A, MODE_B>), dim3(grid),
-                     dim3(WM * WN * 64), lds, stream, args);
+  hipLaunchKernelGGL((execute_kernel<S, A_K, B_K, ELEMENTWISE>), dim3(grid), dim3(S::NT), 2 * S::kStage, stream,
+                     args);
   return hipGetLastError();
 }
 
-template <int EB, int TM, int TN, int WM, int WN, int MODE_A, int MODE_B>
+template <typename S, bool A_K, bool B_K, bool ELEMENTWISE = false>
 hipError_t configure_one() {
-  return hipFuncSetAttribute(
-      reinterpret_cast<const void*>(execute_kernel<EB, TM, TN, WM, WN, MODE_A, MODE_B>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>((TM + TN) * kRowStride));
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(execute_kernel<S, A_K, B_K, ELEMENTWISE>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, 2 * S::kStage);
 }
 
-template <int EB, int TM, int TN, int WM, int WN>
-hipError_t configure_modes() {
-  hipError_t e = configure_one<EB, TM, TN, WM, WN, kScalar, kScalar>();
-  if (e == hipSuccess) e = configure_one<EB, TM, TN, WM, WN, kVecKContig, kVecKContig>();
-  if (e == hipSuccess) e = configure_one<EB, TM, TN, WM, WN, kVecKContig, kVecTransposed>();
-  if (e == hipSuccess) e = configure_one<EB, TM, TN, WM, WN, kVecTransposed, kVecKContig>();
-  if (e == hipSuccess) e = configure_one<EB, TM, TN, WM, WN, kVecTransposed, kVecTransposed>();
+template <typename S>
+hipError_t configure_layouts() {
+  hipError_t e = configure_one<S, true, true>();
+  if (e == hipSuccess) e = configure_one<S, true, false>();
+  if (e == hipSuccess) e = configure_one<S, false, true>();
+  if (e == hipSuccess) e = configure_one<S, false, false>();
   return e;
 }
 
-template <int EB, int TM, int TN, int WM, int WN>
-hipError_t launch_modes(const ExecuteArgs& args, bool vec, int grid, hipStream_t stream) {
-  if (!vec) return launch_one<EB, TM, TN, WM, WN, kScalar, kScalar>(args, grid, stream);
+// Grid of a launch over work items of one class, and the workgroup tiles per item.
+template <typename S>
+int cut_items(ExecuteArgs* args, int tile_class) {
+  static_assert(kSmallTileRows % S::TM == 0 && kLargeTileRows % S::TM == 0 && kSmallTileCols % S::TN == 0 &&
+                kLargeTileCols % S::TN == 0, "a work item is cut into whole workgroup tiles");
+  args->parts_m = tile_rows(tile_class) / S::TM;
+  args->parts_n = tile_cols(tile_class) / S::TN;
+  const int64_t blocks = (args->n_items + 7) / 8 * 8 * args->parts_m * args->parts_n;
+  constexpr int64_t kMaxGrid = int64_t{1} << 20;   // the kernel loops beyond that
+  return static_cast<int>(blocks < kMaxGrid ? blocks : kMaxGrid);
+}
+
+template <typename S>
+hipError_t launch_layouts(ExecuteArgs args, int tile_class, hipStream_t stream) {
+  const int grid = cut_items<S>(&args, tile_class);
   const bool a_k = !args.transA;   // A stored M x K: K-contiguous
   const bool b_k = args.transB;    // B stored N x K: K-contiguous
-  if (a_k && b_k) return launch_one<EB, TM, TN, WM, WN, kVecKContig, kVecKContig>(args, grid, stream);
-  if (a_k && !b_k) return launch_one<EB, TM, TN, WM, WN, kVecKContig, kVecTransposed>(args, grid, stream);
-  if (!a_k && b_k) return launch_one<EB, TM, TN, WM, WN, kVecTransposed, kVecKContig>(args, grid, stream);
-  return launch_one<EB, TM, TN, WM, WN, kVecTransposed, kVecTransposed>(args, grid, stream);
+  if (a_k && b_k) return launch_one<S, true, true>(args, grid, stream);
+  if (a_k && !b_k) return launch_one<S, true, false>(args, grid, stream);
+  if (!a_k && b_k) return launch_one<S, false, true>(args, grid, stream);
+  return launch_one<S, false, false>(args, grid, stream);
+}
+
+template <int EB>
+using Wide = Shape<EB, 128, 128, 2, 2, 2, 2>;
+template <int EB>
+using Narrow = Shape<EB, 64, 64, 2, 2, 2, 4>;
+template <int EB>
+using ByElement = Shape<EB, 64, 64, 2, 2, 1, 4>;
+
+template <int EB>
+hipError_t configure_type() {
+  hipError_t e = configure_layouts<Wide<EB>>();
+  if (e == hipSuccess) e = configure_layouts<Narrow<EB>>();
+  if (e == hipSuccess) e = configure_one<ByElement<EB>, true, true, true>();
+  return e;
+}
+
+template <int EB>
+hipError_t launch_type(ExecuteArgs args, int tile_class, ExecuteTile tile, hipStream_t stream) {
+  if (tile == kTileByElement) {
+    const int grid = cut_items<ByElement<EB>>(&args, tile_class);
+    return launch_one<ByElement<EB>, true, true, true>(args, grid, stream);
+  }
+  return tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, stream)
+                             : launch_layouts<Wide<EB>>(args, tile_class, stream);
 }
 
 }  // namespace
 
 hipError_t configure_execute_kernels() {
-  hipError_t e = configure_modes<2, kLargeTileRows, kLargeTileCols, 2, kLargeTileCols / 64>();
-  if (e == hipSuccess) e = configure_modes<2, 128, 128, 2, 2>();
-  if (e == hipSuccess) e = configure_modes<4, kLargeTileRows, kLargeTileCols, 2, kLargeTileCols / 64>();
-  if (e == hipSuccess) e = configure_modes<4, 128, 128, 2, 2>();
-  return e;
+  const hipError_t e = configure_type<2>();
+  return e != hipSuccess ? e : configure_type<4>();
 }
 
-hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, bool vec, int grid,
-                          hipStream_t stream) {
-  if (dtype == CLEAVE_BF16) {
-    return tile_class == kTileLarge ? launch_modes<2, kLargeTileRows, kLargeTileCols, 2, kLargeTileCols / 64>(args, vec, grid, stream)
-                                    : launch_modes<2, 128, 128, 2, 2>(args, vec, grid, stream);
-  }
-  return tile_class == kTileLarge ? launch_modes<4, kLargeTileRows, kLargeTileCols, 2, kLargeTileCols / 64>(args, vec, grid, stream)
-                                  : launch_modes<4, 128, 128, 2, 2>(args, vec, grid, stream);
+hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, ExecuteTile tile, hipStream_t stream) {
+  return dtype == CLEAVE_BF16 ? launch_type<2>(args, tile_class, tile, stream)
+                              : launch_type<4>(args, tile_class, tile, stream);
 }
 
 }  // namespace cleave

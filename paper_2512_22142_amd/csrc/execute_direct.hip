@@ -215,24 +215,7 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
     TileTarget out;               // where this sub-tile's accumulators go
     int steps, m_valid, n_valid;
   };
-  // A work item record into scalar registers.  The table is never written by
-  // this kernel: read through the constant address space, a wave-uniform
-  // address becomes scalar loads whose completion the compiler tracks, even
-  // though the kernel also stores to global memory.
-  auto load_item = [&](int64_t idx) -> WorkItem {
-    typedef const __attribute__((address_space(4))) u32x4* const_words;
-    const_words src = (const_words)(args.items + idx);
-    uint32_t words[12];
-#pragma unroll
-    for (int v = 0; v < 3; ++v) {
-      const u32x4 q = src[v];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) words[4 * v + e] = q[e];
-    }
-    WorkItem w;
-    __builtin_memcpy(&w, words, sizeof(w));
-    return w;
-  };
+  auto load_item = [&](int64_t idx) -> WorkItem { return load_work_item(args.items, idx); };
   auto make_ctx = [&](const WorkItem& w) -> ItemCtx {
     ItemCtx c;
     c.m_valid = static_cast<int>(w.m_valid);

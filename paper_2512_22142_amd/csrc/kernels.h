@@ -53,15 +53,23 @@ struct ExecuteArgs {
   // The output (partials, or C in assemble mode) takes a 16-byte (fp32) or
   // 8-byte (bf16) store at every fourth column of every sub-tile row.
   int out_vec;
+  // General kernel only: extent of the logical operands (loads stay inside them)
+  // and the workgroup tiles per work item (filled in at the launch).
+  int64_t M, N, K;
+  int parts_m, parts_n;
   // Direct kernel only.  Null: workgroup b takes items b, b + grid, ...
   // Otherwise grid + 1 entries: workgroup b takes items [wg_ranges[b], wg_ranges[b + 1]).
   const uint32_t* wg_ranges;
 };
 
-// Enqueues the execute kernel for one tile class.  `vec` selects the 16-byte
-// load path (caller has checked alignment and divisibility).
-hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, bool vec, int grid,
-                          hipStream_t stream);
+// Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, or 64 x 64
+// with operands loaded one element at a time (what operands with rows shorter
+// than 16 bytes need).
+enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileByElement = 2 };
+
+// Enqueues the general execute kernel over work items of one tile class: any
+// element type, size and alignment.
+hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, ExecuteTile tile, hipStream_t stream);
 
 // Enqueues the bf16 direct-to-LDS execute kernel for one tile class.  The
 // caller has checked the 16-byte load conditions and that the chunk length of

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <limits>
 #include <mutex>
 #include <vector>
 
@@ -210,6 +211,7 @@ struct cleave_plan {
   bool all_k_mult4 = true;
   bool all_mn_mult8 = true;  // every m0, m_len, n0, n_len is a multiple of 8
   bool all_mn_mult4 = true;
+  int64_t min_k_end = std::numeric_limits<int64_t>::max();   // smallest k0 + k_len of a task
   bool all_n_mult4 = true;   // every n0, n_len multiple of 4 (vector path of reduce)
   std::vector<cleave_task> tasks;
   // All tasks, launch order.  Each list starts with the items whose chunk is a
