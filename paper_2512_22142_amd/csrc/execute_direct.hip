@@ -262,12 +262,14 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
   static_assert(STAGES == 2, "the hand-over between items is written for a ring of two stages");
   // Store instructions per lane: a full sub-tile whose target takes 16-byte
   // stores goes through the wave's block image in LDS (behind the ring).
-  constexpr int kTileStores = MB * staged_stores_per_block_row<NB>();
-  constexpr int kHalfStores = kTileStores / 2;
+  // bf16 outputs take half as many, and the waits that count them come in both
+  // kinds (a launch writes one type, so the choice is the same for all items).
+  constexpr int kStoresF32 = MB * staged_stores_per_block_row<NB, false>();
+  constexpr int kStoresBf16 = MB * staged_stores_per_block_row<NB, true>();
   // "at most n operations outstanding" for n stores issued last: the counter holds 63 at most
-  constexpr int kBehindCheck = kHalfStores < 63 ? kHalfStores : 63;
-  constexpr int kBehindTile = kTileStores < 63 ? kTileStores : 63;
+  static_assert(kStoresF32 <= 63, "all of a sub-tile's stores can be outstanding");
   static_assert(MB % 2 == 0, "the epilogue stores a sub-tile in two halves of block rows");
+  const bool bf16_out = args.C && args.c_bf16;
   unsigned char* const image = smem + STAGES * kStage + wave * kBlockImageBytes;
 
   // This workgroup's items: first, first + stride, ... below it_end.
@@ -290,10 +292,10 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
   WorkItem after_next;
   // How the current item's first two steps got into the ring.
   //   kFilled:             ring filled from empty, nothing issued since.
-  //   kFilledBehindStores: ring filled from empty, then exactly kTileStores
-  //     stores of the previous item: the counter retires in issue order, so the
-  //     loads have landed once at most that many operations are outstanding
-  //     (or 63, all the counter can hold, if the stores are more than that).
+  //   kFilledBehindStores: ring filled from empty, then exactly the kStoresF32
+  //     or kStoresBf16 stores of the previous item: the counter retires in issue
+  //     order, so the loads have landed once at most that many operations are
+  //     outstanding.
   //   kPrefetched:         fetched during the previous item's last two steps;
   //     step 0 was waited for at that item's last barrier (its first fragments
   //     are already in registers), step 1 between the two halves of its stores.
@@ -380,7 +382,8 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
     // completed before the previous item's final barrier.
     if (entry != kPrefetched) {
       if (entry == kFilledBehindStores) {
-        CLEAVE_WAIT_BARRIER(kBehindTile);
+        if (bf16_out) CLEAVE_WAIT_BARRIER(kStoresBf16);
+        else CLEAVE_WAIT_BARRIER(kStoresF32);
       } else if (steps >= STAGES) {
         CLEAVE_WAIT_BARRIER(LPS);
       } else {
@@ -427,10 +430,12 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
           // wait for the previous item's stores either
           CLEAVE_WAIT_BARRIER(63);
         } else if (s == 0 && entry == kFilledBehindStores) {
-          CLEAVE_WAIT_BARRIER(kBehindTile);
+          if (bf16_out) CLEAVE_WAIT_BARRIER(kStoresBf16);
+          else CLEAVE_WAIT_BARRIER(kStoresF32);
         } else if (s == 0 && entry == kPrefetched) {
-          // step 1 was waited for before the second half of the previous item's stores
-          CLEAVE_WAIT_BARRIER(kBehindCheck);
+          // step 1 was waited for before the second half of the previous item's
+          // stores: nothing to wait for but those stores, and they may drain
+          CLEAVE_WAIT_BARRIER(kStoresF32 / 2);
         } else {
           CLEAVE_WAIT_BARRIER(0);
         }
@@ -456,17 +461,21 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
     const int col0 = wn * S::WTN + l32;
     const TileTarget target = c.out;
     const int m_valid = c.m_valid, n_valid = c.n_valid;
-    const bool bf16_out = args.C && args.c_bf16;
+    auto store_rows = [&](auto from_tag, auto to_tag) {
+      constexpr int I0 = decltype(from_tag)::value, I1 = decltype(to_tag)::value;
+      if (bf16_out) store_tile_rows_staged_bf16<MB, NB, I0, I1>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
+      else store_tile_rows_staged_f32<MB, NB, I0, I1>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
+    };
     if (cont) {
       // The next item's step 1 went out at the last barrier; wait for it
       // between the two halves of the stores: the first half keeps the memory
-      // pipeline busy meanwhile, and the second half then trails the check, so
-      // that the next item's first barrier finds at most kBehindCheck
-      // operations outstanding without any store having to complete.  The
-      // block image is this wave's own: no barrier between the halves.
-      store_tile_rows_staged<MB, NB, 0, MB / 2>(acc, target, bf16_out, image, wm * S::WTM, wn * S::WTN, lane);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBehindCheck) : "memory");
-      store_tile_rows_staged<MB, NB, MB / 2, MB>(acc, target, bf16_out, image, wm * S::WTM, wn * S::WTN, lane);
+      // pipeline busy meanwhile, the second half trails the check, and the next
+      // item's first barrier has no load to wait for.  The block image is this
+      // wave's own: no barrier between the halves.
+      store_rows(int_c<0>{}, int_c<MB / 2>{});
+      if (bf16_out) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kStoresBf16 / 2) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kStoresF32 / 2) : "memory");
+      store_rows(int_c<MB / 2>{}, int_c<MB>{});
       entry = kPrefetched;
       phase = (phase + steps) & 1;
     } else {
@@ -474,7 +483,7 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
       // item's stores so that its latency hides behind them.
       if (has_next) fill_ring(nx);
       if (wide) {
-        store_tile_rows_staged<MB, NB, 0, MB>(acc, target, bf16_out, image, wm * S::WTM, wn * S::WTN, lane);
+        store_rows(int_c<0>{}, int_c<MB>{});
       } else {
         store_tile<MB, NB>(acc, target, bf16_out, row0, col0, m_valid, n_valid, interior);
       }

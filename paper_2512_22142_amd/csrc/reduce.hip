@@ -14,6 +14,7 @@
 
 #include <cstdint>
 
+#include "bf16_round.h"
 #include "kernels.h"
 
 namespace cleave {
@@ -24,14 +25,6 @@ constexpr int kThreads = 256;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-// Round-to-nearest-even fp32 -> bf16 (NaN stays a quiet NaN).
-__device__ __forceinline__ uint32_t to_bf16_bits(float x) {
-  uint32_t u = __builtin_bit_cast(uint32_t, x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
 
 // What happens to an aggregated value.  An epilogue sees the sum of a tile's
 // partials (the left fold, unchanged by what follows) for four consecutive
@@ -46,8 +39,8 @@ struct StoreEpilogue {
   __device__ __forceinline__ void apply4(int64_t off, f32x4 acc) const {
     if constexpr (OUT_BF16) {
       u32x2 w;
-      w[0] = to_bf16_bits(acc[0]) | (to_bf16_bits(acc[1]) << 16);
-      w[1] = to_bf16_bits(acc[2]) | (to_bf16_bits(acc[3]) << 16);
+      w[0] = pack_bf16(acc[0], acc[1]);
+      w[1] = pack_bf16(acc[2], acc[3]);
       *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(C) + off) = w;
     } else {
       *reinterpret_cast<f32x4*>(static_cast<float*>(C) + off) = acc;
@@ -55,7 +48,7 @@ struct StoreEpilogue {
   }
   __device__ __forceinline__ void apply1(int64_t off, float acc) const {
     if constexpr (OUT_BF16) {
-      static_cast<uint16_t*>(C)[off] = static_cast<uint16_t>(to_bf16_bits(acc));
+      static_cast<uint16_t*>(C)[off] = to_bf16_bits(acc);
     } else {
       static_cast<float*>(C)[off] = acc;
     }
@@ -136,7 +129,7 @@ struct AdamEpilogue {
     w[off] = w1;
     m[off] = me;
     v[off] = ve;
-    if (w_bf16) w_bf16[off] = static_cast<uint16_t>(to_bf16_bits(w1));
+    if (w_bf16) w_bf16[off] = to_bf16_bits(w1);
   }
 };
 

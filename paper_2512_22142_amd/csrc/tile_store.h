@@ -6,6 +6,7 @@
 
 #include <cstdint>
 
+#include "bf16_round.h"
 #include "kernels.h"
 
 namespace cleave {
@@ -59,14 +60,6 @@ __device__ __forceinline__ TileTarget tile_target(const ExecuteArgs& args, const
   return t;
 }
 
-// Round-to-nearest-even fp32 -> bf16 (NaN stays a quiet NaN).
-__device__ __forceinline__ uint16_t tile_to_bf16(float x) {
-  uint32_t u = __builtin_bit_cast(uint32_t, x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return static_cast<uint16_t>((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return static_cast<uint16_t>(u >> 16);
-}
-
 // Stores a wave's MB x NB grid of 32 x 32 MFMA accumulator blocks.  A block
 // leaves lane l with column l % 32 and rows 8*q + 4*(l / 32) + r, so half a
 // wave writes one aligned run of 32 elements per store.  row0 / col0: this
@@ -106,71 +99,41 @@ __device__ __forceinline__ void store_blocks(const tile_f32x16 (&acc)[MB][NB], T
   }
 }
 
-// Block rows [I0, I1) of a full sub-tile (no bounds checks), same order and
-// addresses as store_blocks: lets a caller put other work between two parts
-// of a sub-tile's stores.
-template <int MB, int NB, int I0, int I1, typename T, typename Cvt>
-__device__ __forceinline__ void store_block_rows(const tile_f32x16 (&acc)[MB][NB], T* tp, int64_t ld,
-                                                 Cvt cvt) {
-#pragma unroll
-  for (int i = I0; i < I1; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        T* p = tp + static_cast<int64_t>(i * 32 + q * 8 + r) * ld;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) p[j * 32] = cvt(acc[i][j][q * 4 + r]);
-      }
-}
-
-template <int MB, int NB, int I0, int I1>
-__device__ __forceinline__ void store_tile_rows(const tile_f32x16 (&acc)[MB][NB], const TileTarget& t,
-                                                bool bf16, int row0, int col0) {
-  if (!bf16) {
-    float* tp = reinterpret_cast<float*>(t.base) + row0 * t.ld + col0;
-    store_block_rows<MB, NB, I0, I1>(acc, tp, t.ld, [](float x) { return x; });
-  } else {
-    uint16_t* tp = reinterpret_cast<uint16_t*>(t.base) + row0 * t.ld + col0;
-    store_block_rows<MB, NB, I0, I1>(acc, tp, t.ld, [](float x) { return tile_to_bf16(x); });
-  }
-}
-
-// Number of store instructions a lane issues for a full sub-tile.
-template <int MB, int NB>
-__device__ __forceinline__ constexpr int full_tile_stores() {
-  return MB * NB * 16;
-}
-
-// Block rows [I0, I1) of a full sub-tile, each 32 x 32 block turned through a
-// 4 KB row-major image in LDS that belongs to this wave alone (`image`), so
-// that a lane leaves with four consecutive columns of one row: a store
-// instruction then writes eight whole 128-byte lines (fp32) instead of 64
-// dwords in two rows -- a quarter of the store instructions and half the
-// address-unit cycles of store_block_rows.  The values and their addresses are
-// the same.  wave_row0 / wave_col0: first row and column of the wave's part
-// of the sub-tile.  The target must allow 16-byte (fp32) or 8-byte (bf16)
-// stores at every fourth column.  LDS executes a wave's accesses in issue
-// order, and the compiler is kept from reordering them by the asm statements;
-// no other wave touches the image, so no barrier is involved.
+// Block rows [I0, I1) of a full sub-tile, turned through a 4 KB row-major image
+// in LDS that belongs to this wave alone (`image`), so that a lane leaves with
+// 16 consecutive bytes of one row and a store instruction writes eight whole
+// 128-byte lines instead of 64 elements in two rows.  The image holds one
+// 32 x 32 block of fp32 or two neighbouring ones of bf16 (32 rows x 64
+// columns), which therefore take half the LDS traffic and store instructions.
+// The values and their addresses are those of store_blocks.  wave_row0 /
+// wave_col0: first row and column of the wave's part of the sub-tile.  The
+// target must allow 16-byte (fp32) or 8-byte (bf16) stores at every fourth
+// column.  LDS executes a wave's accesses in issue order, and the compiler is
+// kept from reordering them by the asm statements; no other wave touches the
+// image, so no barrier is involved.
+//
+// bf16 values are rounded where they are, two rows of a column per
+// instruction; one lane exchange then turns the pairs of two neighbouring
+// columns round, so that a lane writes two neighbouring columns of one row as
+// one dword.  Rounding on the way out of the image, four values per lane in
+// integer arithmetic, and 8-byte stores had made the store phase the longer
+// half of a work item of two K steps: 128 products of 1024 x 1024 x 128 into
+// bf16 followed by 128 of 1024 x 128 x 1024 into fp32, 200 -> 182 us.
 constexpr int kBlockImageBytes = 32 * 32 * 4;
-template <int NB>
+template <int NB, bool BF16>
 __device__ __forceinline__ constexpr int staged_stores_per_block_row() {
-  return NB * 4;
+  return NB * (BF16 ? 2 : 4);
 }
 
 template <int MB, int NB, int I0, int I1>
-__device__ __forceinline__ void store_tile_rows_staged(const tile_f32x16 (&acc)[MB][NB],
-                                                       const TileTarget& t, bool bf16,
-                                                       unsigned char* image, int wave_row0,
-                                                       int wave_col0, int lane) {
+__device__ __forceinline__ void store_tile_rows_staged_f32(const tile_f32x16 (&acc)[MB][NB],
+                                                           const TileTarget& t, unsigned char* image,
+                                                           int wave_row0, int wave_col0, int lane) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   float* wr = reinterpret_cast<float*>(image) + (4 * (lane >> 5)) * 32 + (lane & 31);
   const f32x4* rd = reinterpret_cast<const f32x4*>(image) + lane;   // row lane / 8 (+ 8 k), columns 4 (lane % 8) ..
-  const int64_t at = static_cast<int64_t>(wave_row0 + (lane >> 3)) * t.ld + wave_col0 + (lane & 7) * 4;
-  float* gp32 = reinterpret_cast<float*>(t.base) + at;
-  uint16_t* gp16 = reinterpret_cast<uint16_t*>(t.base) + at;
+  float* gp = reinterpret_cast<float*>(t.base) + static_cast<int64_t>(wave_row0 + (lane >> 3)) * t.ld + wave_col0 +
+              (lane & 7) * 4;
 #pragma unroll
   for (int i = I0; i < I1; ++i)
 #pragma unroll
@@ -183,19 +146,53 @@ __device__ __forceinline__ void store_tile_rows_staged(const tile_f32x16 (&acc)[
 #pragma unroll
       for (int k = 0; k < 4; ++k) v[k] = rd[64 * k];
       asm volatile("" ::: "memory");
-      const int64_t block_at = static_cast<int64_t>(i * 32) * t.ld + j * 32;
-      if (!bf16) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) *reinterpret_cast<f32x4*>(gp32 + block_at + 8 * k * t.ld) = v[k];
-      } else {
+      for (int k = 0; k < 4; ++k)
+        *reinterpret_cast<f32x4*>(gp + static_cast<int64_t>(i * 32 + 8 * k) * t.ld + j * 32) = v[k];
+    }
+}
+
+template <int MB, int NB, int I0, int I1>
+__device__ __forceinline__ void store_tile_rows_staged_bf16(const tile_f32x16 (&acc)[MB][NB],
+                                                            const TileTarget& t, unsigned char* image,
+                                                            int wave_row0, int wave_col0, int lane) {
+  static_assert(NB % 2 == 0, "the image takes two blocks side by side");
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x4_at8 __attribute__((ext_vector_type(4), aligned(8)));   // rows start on 8 bytes
+  // Image rows are 32 dwords (64 columns).  An even lane writes columns
+  // (l32, l32 + 1) of its rows 8 q + 4 lh + 2 p, an odd lane columns
+  // (l32 - 1, l32) of the rows behind them.  The two halves of a wave are four
+  // rows apart, which is the same banks: rows with bit 2 set are kept with
+  // their 16-dword halves exchanged.
+  const int lh = lane >> 5, odd = lane & 1;
+  const uint32_t select = odd ? 0x03020706u : 0x05040100u;   // (other high, own high) : (own low, other low)
+  uint32_t* wr = reinterpret_cast<uint32_t*>(image) + (4 * lh + odd) * 32 + ((lane & 31) >> 1);
+  uint32_t* wr_half[2] = {wr + 16 * lh, wr + 16 * (1 - lh)};
+  const int row = lane >> 3, quad = (lane & 7) ^ (4 * ((row >> 2) & 1));
+  const u32x4* rd = reinterpret_cast<const u32x4*>(image) + row * 8 + quad;
+  uint16_t* gp = reinterpret_cast<uint16_t*>(t.base) + static_cast<int64_t>(wave_row0 + row) * t.ld + wave_col0 +
+                 (lane & 7) * 8;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          u32x2 w;
-          w[0] = tile_to_bf16(v[k][0]) | (static_cast<uint32_t>(tile_to_bf16(v[k][1])) << 16);
-          w[1] = tile_to_bf16(v[k][2]) | (static_cast<uint32_t>(tile_to_bf16(v[k][3])) << 16);
-          *reinterpret_cast<u32x2*>(gp16 + block_at + 8 * k * t.ld) = w;
+  for (int i = I0; i < I1; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; j += 2) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {   // rows 8 * (p / 2) + 4 lh + 2 * (p % 2), and the next
+          const uint32_t own = pack_bf16(acc[i][j + h][2 * p], acc[i][j + h][2 * p + 1]);
+          const uint32_t other = __builtin_amdgcn_update_dpp(0u, own, 0xB1, 0xF, 0xF, true);   // lane ^ 1
+          wr_half[h][(8 * (p >> 1) + 2 * (p & 1)) * 32] = __builtin_amdgcn_perm(other, own, select);
         }
-      }
+      asm volatile("" ::: "memory");
+      u32x4 v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = rd[64 * k];
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        *reinterpret_cast<u32x4_at8*>(gp + static_cast<int64_t>(i * 32 + 8 * k) * t.ld + j * 32) = v[k];
     }
 }
 
@@ -210,7 +207,7 @@ __device__ __forceinline__ void store_tile(const tile_f32x16 (&acc)[MB][NB], con
   } else {
     uint16_t* tp = reinterpret_cast<uint16_t*>(t.base) + row0 * t.ld + col0;
     store_blocks<MB, NB>(acc, tp, t.ld, row0, col0, m_valid, n_valid, interior,
-                         [](float x) { return tile_to_bf16(x); });
+                         [](float x) { return to_bf16_bits(x); });
   }
 }
 

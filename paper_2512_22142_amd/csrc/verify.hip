@@ -25,6 +25,7 @@
 
 #include <cstdint>
 
+#include "bf16_round.h"
 #include "kernels.h"
 
 namespace cleave {
@@ -323,14 +324,6 @@ __global__ __launch_bounds__(kThreads) void verify_pass_kernel(VerifyPassArgs a)
   }
 }
 
-// Round-to-nearest-even fp32 -> bf16 (NaN stays a quiet NaN).
-__device__ __forceinline__ uint32_t to_bf16_bits(float x) {
-  uint32_t u = __builtin_bit_cast(uint32_t, x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
 // The bilinear items of all S splits of a tile over one run of rows, and the
 // tile's aggregated rows into C (paper Sec. 3.2 and Sec. 6: the PS checks the
 // returned blocks and aggregates them).  Per split the arithmetic and the
@@ -398,8 +391,8 @@ __device__ __forceinline__ void aggregate_item(const BilinearArgs& a, const Aggr
           const int64_t off = c_at + static_cast<int64_t>(rows[u]) * g.ldc + cols[u];
           if (g.out_bf16) {
             u32x2 w;
-            w[0] = to_bf16_bits(sum[0]) | (to_bf16_bits(sum[1]) << 16);
-            w[1] = to_bf16_bits(sum[2]) | (to_bf16_bits(sum[3]) << 16);
+            w[0] = pack_bf16(sum[0], sum[1]);
+            w[1] = pack_bf16(sum[2], sum[3]);
             *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(g.C) + off) = w;
           } else {
             *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + off) = sum;
@@ -421,7 +414,7 @@ __device__ __forceinline__ void aggregate_item(const BilinearArgs& a, const Aggr
         sum = sp == 0 ? pv : sum + pv;
       }
       const int64_t off = c_at + static_cast<int64_t>(row) * g.ldc + col;
-      if (g.out_bf16) static_cast<uint16_t*>(g.C)[off] = static_cast<uint16_t>(to_bf16_bits(sum));
+      if (g.out_bf16) static_cast<uint16_t*>(g.C)[off] = to_bf16_bits(sum);
       else static_cast<float*>(g.C)[off] = sum;
     }
   }

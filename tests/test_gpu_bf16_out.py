@@ -1,0 +1,70 @@
+"""bf16 outputs of the execute kernels' full sub-tiles and of the aggregation,
+bit for bit: integer-valued inputs make every sum exact in fp32, so the output
+must be the nearest-even rounding of the oracle's value; infinities and NaN in
+the inputs must come out as such."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_22142_amd as cleave
+from oracle import gemm as og
+from workloads.tensors import make_matrix
+
+pytestmark = pytest.mark.gpu
+
+
+def _rounded(ref):
+    return torch.from_numpy(ref).to(torch.bfloat16).view(torch.int16).numpy()
+
+
+# ld pad / origin in elements: rows on 16 bytes, on 8 bytes only (both the widest store the
+# sub-tile takes), and an origin that only takes element stores
+@pytest.mark.parametrize("pad,origin", [(8, 0), (4, 4), (12, 0), (8, 4), (4, 2)])
+@pytest.mark.parametrize("tile,steps", [(256, 1), (256, 2), (512, 3), (128, 1), (128, 2), (128, 5)])
+def test_assembled_bf16_rounds_and_stays_inside(tile, steps, pad, origin):
+    # several work items per workgroup for the short chains, clipped sub-tiles at the right edge
+    M, N, K = (4096, 4232, 64 * steps) if steps < 3 else (1024, 1160, 64 * steps)
+    a = make_matrix(901 + steps, M, K, "bf16", integer_valued=True)
+    b = make_matrix(902 + steps, K, N, "bf16", integer_valued=True)
+    b[:, 0] *= 64                                     # sums with more than eight significant bits
+    plan = cleave.plan_uniform(M, N, K, tile, tile, 1)
+    ld = N + pad
+    flat = torch.full((M * ld + origin,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide = flat[origin:].view(M, ld)
+    C = wide[:, :N]
+    cleave.execute_assemble(plan, a.cuda(), b.cuda(), C)
+    assert "direct" in plan.last_kernel
+    torch.cuda.synchronize()
+    ref = og.gemm(og.widen(a), og.widen(b))
+    assert np.array_equal(C.contiguous().view(torch.int16).cpu().numpy(), _rounded(ref))
+    assert bool(torch.isnan(wide[:, N:].float()).all()) and bool(torch.isnan(flat[:origin].float()).all())
+
+
+@pytest.mark.parametrize("assembled", [True, False])
+def test_non_finite_sums_keep_their_class(assembled):
+    M = N = 256
+    K = 128
+    a = make_matrix(911, M, K, "bf16", integer_valued=True)
+    b = make_matrix(912, K, N, "bf16", integer_valued=True)
+    a[3, 5], a[70, 9], a[200, 1] = float("inf"), float("-inf"), float("nan")
+    big = torch.finfo(torch.bfloat16).max
+    a[129, :], b[:, 131] = big, big                   # overflows to infinity in fp32 already
+    plan = cleave.plan_uniform(M, N, K, 256, 256, 1)
+    C = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    if assembled:
+        cleave.execute_assemble(plan, a.cuda(), b.cuda(), C)
+    else:
+        parts = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
+        cleave.execute(plan, a.cuda(), b.cuda(), parts)
+        cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    got = C.float().cpu()
+    ref = a.double() @ b.double()
+    cols = torch.arange(N) != 131                     # there fp32 sums overflow either way before an infinity joins
+    assert torch.equal(torch.isnan(got)[[3, 70, 200]][:, cols], torch.isnan(ref)[[3, 70, 200]][:, cols])
+    inf = torch.isinf(ref[[3, 70]]) & cols
+    assert torch.equal(got[[3, 70]][inf].double(), ref[[3, 70]][inf])
+    assert got[129, 131] == float("inf")
+    rest = torch.ones(M, dtype=torch.bool)
+    rest[[3, 70, 129, 200]] = False
+    assert torch.equal(got[rest][:, cols], ref[rest][:, cols].to(torch.bfloat16).float())
