@@ -21,7 +21,7 @@
 //     the 16-byte fragment reads are conflict free.
 //   * operand stored with the tile-row index contiguous (read "transposed"):
 //     the tile is kept as BK k rows of R/8 chunks,
-//       slot = k*(R/8) + (chunk ^ (4*(k & 3)));
+//       slot = k*(R/8) + (chunk ^ (4*(k & 3))),  for R = 64 ^ (4*((k >> 1) & 1));
 //     fragments are gathered with the LDS transpose read (ds_read_b64_tr_b16:
 //     within 16 lanes, lane i supplies the address of 4 consecutive elements of
 //     k row i/4 and receives column i of the 4 x 16 block), two reads per
@@ -75,9 +75,14 @@ struct Shape {
   static constexpr int kLoadsA = kATile / 1024 / NW;   // wave-wide loads per wave and step
   static constexpr int kLoadsB = kBTile / 1024 / NW;
   static constexpr int kLoadsPerStep = kLoadsA + kLoadsB;
+  // A tile smaller than the small class's: a workgroup computes one of the
+  // PARTS_M x PARTS_N parts of a work item, and only that.
+  static constexpr int PARTS_M = TM < kSmallTileRows ? kSmallTileRows / TM : 1;
+  static constexpr int PARTS_N = TN < kSmallTileCols ? kSmallTileCols / TN : 1;
+  static constexpr int PARTS = PARTS_M * PARTS_N;
   static_assert(kATile % (1024 * NW) == 0 && kBTile % (1024 * NW) == 0, "tile / wave count");
   static_assert(kSub % 2 == 0 && (CPR == 4 || CPR == 8), "BK must be 32 or 64");
-  static_assert(WTM % 32 == 0 && WTN % 32 == 0 && STAGES >= 2, "shape");
+  static_assert(WTM % 32 == 0 && WTN % 32 == 0 && STAGES >= 2 && (STAGES & (STAGES - 1)) == 0, "shape");
 };
 
 // Waits until at most `n` vector-memory operations of this wave are still in
@@ -99,6 +104,13 @@ __device__ __forceinline__ int row_swizzle(int r) {
   return CPR == 4 ? ((r >> 2) & 3) : ((r >> 1) & 7);
 }
 
+// XOR applied to the chunk index of k row `k` of a tile kept as k rows of CH
+// chunks: spreads over the banks the four k rows of a transpose read.
+template <int CH>
+__device__ __forceinline__ int k_swizzle(int k) {
+  return CH == 8 ? 4 * ((k >> 1) & 1) : 4 * (k & 3);
+}
+
 template <typename S, bool KCONTIG, int R>
 struct DirectTile {
   static constexpr int kLoads = R * S::BK * 2 / 1024 / S::NW;
@@ -116,7 +128,7 @@ struct DirectTile {
         goff[i] = static_cast<uint32_t>((min(r, r_valid - 1) * row_stride + c * 8) * 2);
       } else {
         const int k = slot / CH;
-        const int c = (slot % CH) ^ (4 * (k & 3));
+        const int c = (slot % CH) ^ k_swizzle<CH>(k);
         goff[i] = static_cast<uint32_t>((k * k_stride + min(c * 8, r_valid - 8)) * 2);
       }
     }
@@ -150,7 +162,7 @@ struct DirectTile {
 };
 
 template <typename S, bool A_K, bool B_K>
-__global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteArgs args) {
+__global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(ExecuteArgs args) {
   constexpr int TM = S::TM, TN = S::TN, MB = S::MB, NB = S::NB, CPR = S::CPR, kSub = S::kSub;
   constexpr int kStage = S::kStage, kATile = S::kATile, STAGES = S::STAGES, LPS = S::kLoadsPerStep;
   constexpr int kRowBytes = CPR * 16;        // K-contiguous tile row
@@ -186,7 +198,7 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int c = wm * (S::WTM / 8) + i * 4 + 2 * nsub + (cq >> 1);
-      a_addr[i] = ((8 * lh + kq) * CHA + (c ^ (4 * kq))) * 16 + (cq & 1) * 8;
+      a_addr[i] = ((8 * lh + kq) * CHA + (c ^ k_swizzle<CHA>(kq))) * 16 + (cq & 1) * 8;
     }
   }
   if constexpr (B_K) {
@@ -198,7 +210,7 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int c = wn * (S::WTN / 8) + j * 4 + 2 * nsub + (cq >> 1);
-      b_addr[j] = kATile + ((8 * lh + kq) * CHB + (c ^ (4 * kq))) * 16 + (cq & 1) * 8;
+      b_addr[j] = kATile + ((8 * lh + kq) * CHB + (c ^ k_swizzle<CHB>(kq))) * 16 + (cq & 1) * 8;
     }
   }
 
@@ -215,7 +227,25 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
     TileTarget out;               // where this sub-tile's accumulators go
     int steps, m_valid, n_valid;
   };
-  auto load_item = [&](int64_t idx) -> WorkItem { return load_work_item(args.items, idx); };
+  auto load_item = [&](int64_t idx) -> WorkItem {
+    if constexpr (S::PARTS == 1) {
+      return load_work_item(args.items, idx);
+    } else {
+      // workgroups are dealt round-robin over the XCDs and list position i belongs to
+      // XCD i % 8: the parts of an item follow each other on the item's XCD
+      const uint32_t part = static_cast<uint32_t>(idx >> 3) % S::PARTS;
+      const int64_t it = (idx >> 3) / S::PARTS * 8 + (idx & 7);
+      WorkItem w = load_work_item(args.items, it < args.n_items ? it : 0);
+      const uint32_t mo = part / S::PARTS_N * TM, no = part % S::PARTS_N * TN;
+      const bool empty = it >= args.n_items || mo >= w.m_valid || no >= w.n_valid;
+      w.m_valid = empty ? 0 : min(w.m_valid - mo, static_cast<uint32_t>(TM));
+      w.n_valid = empty ? 0 : min(w.n_valid - no, static_cast<uint32_t>(TN));
+      w.m_base += mo;
+      w.n_base += no;
+      w.out_off += static_cast<uint64_t>(mo) * w.out_ld + no;
+      return w;
+    }
+  };
   auto make_ctx = [&](const WorkItem& w) -> ItemCtx {
     ItemCtx c;
     c.m_valid = static_cast<int>(w.m_valid);
@@ -252,24 +282,19 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
 
   // A workgroup walks its work items -- every grid-th one, or a run of its own
   // when the launch comes with a balanced schedule.  The ring runs on across
-  // items: when the current item and the next one are both full sub-tiles, the
-  // next item's first two K steps are fetched into the ring stages that this
-  // item's last two steps free, exactly as this item's own later steps would
-  // be, so the next K loop starts without a ring fill and without waiting for
-  // this item's stores.  Otherwise (clipped sub-tiles need other lane offsets,
-  // one-step items free no stage early) the ring is filled from empty after the
-  // item's last step, ahead of its stores.
-  static_assert(STAGES == 2, "the hand-over between items is written for a ring of two stages");
-  // Store instructions per lane: a full sub-tile whose target takes 16-byte
-  // stores goes through the wave's block image in LDS (behind the ring).
-  // bf16 outputs take half as many, and the waits that count them come in both
-  // kinds (a launch writes one type, so the choice is the same for all items).
-  constexpr int kStoresF32 = MB * staged_stores_per_block_row<NB, false>();
-  constexpr int kStoresBf16 = MB * staged_stores_per_block_row<NB, true>();
-  // "at most n operations outstanding" for n stores issued last: the counter holds 63 at most
-  static_assert(kStoresF32 <= 63, "all of a sub-tile's stores can be outstanding");
-  static_assert(MB % 2 == 0, "the epilogue stores a sub-tile in two halves of block rows");
+  // items: when the current item and the next one are both full sub-tiles of at
+  // least a ring's worth of steps, the next item's first steps are fetched into
+  // the stages that this item's last steps free, exactly as this item's own
+  // later steps would be, so the next K loop starts without a ring fill and
+  // without waiting for this item's stores.  Otherwise (clipped sub-tiles need
+  // other lane offsets) the ring is filled from empty after the item's last
+  // step, ahead of its stores.
+  //
+  // Store instructions per lane of a full sub-tile whose target takes 16-byte
+  // stores: it goes through the wave's block image in LDS (behind the ring).
+  // bf16 outputs take half as many.
   const bool bf16_out = args.C && args.c_bf16;
+  const int tile_stores = MB * (bf16_out ? staged_stores_per_block_row<NB, true>() : staged_stores_per_block_row<NB, false>());
   unsigned char* const image = smem + STAGES * kStage + wave * kBlockImageBytes;
 
   // This workgroup's items: first, first + stride, ... below it_end.
@@ -279,8 +304,10 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
     it_end = args.wg_ranges[blockIdx.x + 1];
     stride = 1;
   }
+  if constexpr (S::PARTS > 1) it_end = it_first + 1;
   if (it_first >= it_end) return;
   ItemCtx c = make_ctx(load_item(it_first));
+  if (S::PARTS > 1 && c.m_valid == 0) return;
   fill_ring(c);
   int64_t it_next = it_first + stride;
   // Item records are read two items ahead (scalar loads through the constant
@@ -288,20 +315,41 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
   // the current item's first barrier, a whole K step before the next wait
   // that covers it.  `last_item` stands in for records past the end.
   const int64_t last_item = it_end - 1;
-  ItemCtx nx = make_ctx(load_item(it_next < it_end ? it_next : last_item));
+  ItemCtx nx = S::PARTS > 1 ? c : make_ctx(load_item(it_next < it_end ? it_next : last_item));
   WorkItem after_next;
-  // How the current item's first two steps got into the ring.
-  //   kFilled:             ring filled from empty, nothing issued since.
-  //   kFilledBehindStores: ring filled from empty, then exactly the kStoresF32
-  //     or kStoresBf16 stores of the previous item: the counter retires in issue
-  //     order, so the loads have landed once at most that many operations are
-  //     outstanding.
-  //   kPrefetched:         fetched during the previous item's last two steps;
-  //     step 0 was waited for at that item's last barrier (its first fragments
-  //     are already in registers), step 1 between the two halves of its stores.
+  // How the current item's first steps got into the ring.
+  //   kFilled:             ring filled from empty; what has been issued since, if
+  //     anything, is not counted.
+  //   kFilledBehindStores: ring filled from empty, then exactly the tile_stores
+  //     stores of the previous item.
+  //   kPrefetched:         fetched during the previous item's last steps, then its
+  //     tile_stores stores; step 0 was waited for at that item's last barrier
+  //     (its first fragments are already in registers).
+  // The counter of outstanding operations retires in issue order, so a step has
+  // landed once at most the operations issued behind it are outstanding: the
+  // later steps in the ring and, for the steps fetched ahead of them, the
+  // stores, none of which has to complete for that.
   enum Entry : int { kFilled = 0, kFilledBehindStores = 1, kPrefetched = 2 };
   int entry = kFilled;
   int phase = 0;   // ring stage that holds the current item's step 0
+  // Barrier once at most `steps_behind` steps' loads and `stores` stores are
+  // outstanding.  (The counts are multiples of four; the counter holds 63.)
+  static_assert(LPS % 4 == 0 && (STAGES - 1) * LPS + MB * NB * 4 <= 40, "the wait counts below");
+  auto wait_behind = [&](int steps_behind, int stores) {
+    switch ((steps_behind * LPS + stores) >> 2) {
+      case 0: CLEAVE_WAIT_BARRIER(0); break;
+      case 1: CLEAVE_WAIT_BARRIER(4); break;
+      case 2: CLEAVE_WAIT_BARRIER(8); break;
+      case 3: CLEAVE_WAIT_BARRIER(12); break;
+      case 4: CLEAVE_WAIT_BARRIER(16); break;
+      case 5: CLEAVE_WAIT_BARRIER(20); break;
+      case 6: CLEAVE_WAIT_BARRIER(24); break;
+      case 7: CLEAVE_WAIT_BARRIER(28); break;
+      case 8: CLEAVE_WAIT_BARRIER(32); break;
+      case 9: CLEAVE_WAIT_BARRIER(36); break;
+      default: CLEAVE_WAIT_BARRIER(40); break;
+    }
+  };
 
   f32x16 acc[MB][NB];
   u32x4 fa[2][MB], fb[2][NB];
@@ -372,42 +420,37 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
 
   for (;;) {
     const int steps = c.steps;
-    const bool has_next = it_next < it_end;
+    const bool has_next = S::PARTS == 1 && it_next < it_end;
     const bool interior = c.m_valid == TM && c.n_valid == TN;
     const bool wide = interior && args.out_vec;   // stores of whole lines through the block image
     // hand the ring over without draining it
-    const bool cont = has_next && wide && nx.m_valid == TM && nx.n_valid == TN && steps >= 2;
+    const bool cont = has_next && wide && nx.m_valid == TM && nx.n_valid == TN && steps >= STAGES && nx.steps >= STAGES;
+    // stores between the steps fetched ahead of the item and its own
+    const int stores_behind = entry == kFilled ? 0 : tile_stores;
 
     // Step 0 must have landed.  All earlier fragment reads of this workgroup
     // completed before the previous item's final barrier.
     if (entry != kPrefetched) {
-      if (entry == kFilledBehindStores) {
-        if (bf16_out) CLEAVE_WAIT_BARRIER(kStoresBf16);
-        else CLEAVE_WAIT_BARRIER(kStoresF32);
-      } else if (steps >= STAGES) {
-        CLEAVE_WAIT_BARRIER(LPS);
-      } else {
-        CLEAVE_WAIT_BARRIER(0);
-      }
+      wait_behind(min(STAGES, steps) - 1, stores_behind);
       read_frags(0u, int_c<0>{}, 0);   // a ring filled from empty starts at stage 0
     }
 
-    // One K step; step s sits in ring stage (s + phase) % 2.  Sub-step j
+    // One K step; step s sits in ring stage (s + phase) % STAGES.  Sub-step j
     // multiplies register set j & 1 while the fragments of sub-step j+1 are
     // fetched into the other set.  The barrier sits before the last sub-step's
     // MFMAs: by then this wave holds all fragments of step s and the step
     // after it has landed (loads return in order), so the stage is refilled
-    // with the step after next -- this item's, or the next item's first or
-    // second -- and the first fragments of the following step are fetched
-    // while the last sub-step multiplies.  MID: a step with at least two more
-    // steps of this item behind it and not the item's first -- no case
-    // distinctions, the loop body of long chunks.
+    // with the step STAGES further on -- this item's, or one of the next item's
+    // first -- and the first fragments of the following step are fetched while
+    // the last sub-step multiplies.  MID: a step with at least STAGES more steps
+    // of this item behind it and none of the steps fetched ahead of the item in
+    // the ring -- no case distinctions, the loop body of long chunks.
     auto k_step = [&](auto mid_tag, auto first_tag, int s) {
       constexpr bool MID = decltype(mid_tag)::value;
       constexpr bool FIRST = decltype(first_tag)::value;   // the item's step 0
-      const int st = (s + phase) & 1;
-      const uint32_t cur = st ? kStage : 0;
-      const uint32_t oth = st ? 0 : kStage;
+      const int st = (s + phase) & (STAGES - 1);
+      const uint32_t cur = st * kStage;
+      const uint32_t oth = ((st + 1) & (STAGES - 1)) * kStage;
       auto sub = [&](auto j_tag) {
         constexpr int J = decltype(j_tag)::value;
         read_frags(cur, int_c<J + 1>{}, (J + 1) & 1);
@@ -420,7 +463,7 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
         sub(int_c<2>{});
       }
       if constexpr (MID) {
-        CLEAVE_WAIT_BARRIER(0);
+        CLEAVE_WAIT_BARRIER((STAGES - 2) * LPS);
         issue(c, s + STAGES, st);
         read_frags(oth, int_c<0>{}, 0);
       } else {
@@ -429,22 +472,15 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
           // no step follows in the ring: nothing to wait for, and no reason to
           // wait for the previous item's stores either
           CLEAVE_WAIT_BARRIER(63);
-        } else if (s == 0 && entry == kFilledBehindStores) {
-          if (bf16_out) CLEAVE_WAIT_BARRIER(kStoresBf16);
-          else CLEAVE_WAIT_BARRIER(kStoresF32);
-        } else if (s == 0 && entry == kPrefetched) {
-          // step 1 was waited for before the second half of the previous item's
-          // stores: nothing to wait for but those stores, and they may drain
-          CLEAVE_WAIT_BARRIER(kStoresF32 / 2);
         } else {
-          CLEAVE_WAIT_BARRIER(0);
+          wait_behind(cont ? STAGES - 2 : min(STAGES - 2, steps - 2 - s), s + 1 < STAGES ? stores_behind : 0);
         }
         if (s + STAGES < steps) {
           issue(c, s + STAGES, st);
-        } else if (cont && s + STAGES - steps < nx.steps) {
+        } else if (cont) {
           issue(nx, s + STAGES - steps, st);
         }
-        if (s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
+        if (S::PARTS == 1 && s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
         if (!last || cont) read_frags(oth, int_c<0>{}, 0);
       }
       mma((kSub - 1) & 1, std::false_type{});
@@ -452,6 +488,8 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
     };
     k_step(std::false_type{}, std::true_type{}, 0);
     int s = 1;
+    if constexpr (STAGES > 2)
+      for (; s < STAGES - 1 && s < steps; ++s) k_step(std::false_type{}, std::false_type{}, s);
     for (; s + STAGES < steps; ++s) k_step(std::true_type{}, std::false_type{}, s);
     for (; s < steps; ++s) k_step(std::false_type{}, std::false_type{}, s);
 
@@ -461,35 +499,18 @@ __global__ __launch_bounds__(S::NT, S::WGS) void execute_direct_kernel(ExecuteAr
     const int col0 = wn * S::WTN + l32;
     const TileTarget target = c.out;
     const int m_valid = c.m_valid, n_valid = c.n_valid;
-    auto store_rows = [&](auto from_tag, auto to_tag) {
-      constexpr int I0 = decltype(from_tag)::value, I1 = decltype(to_tag)::value;
-      if (bf16_out) store_tile_rows_staged_bf16<MB, NB, I0, I1>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
-      else store_tile_rows_staged_f32<MB, NB, I0, I1>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
-    };
-    if (cont) {
-      // The next item's step 1 went out at the last barrier; wait for it
-      // between the two halves of the stores: the first half keeps the memory
-      // pipeline busy meanwhile, the second half trails the check, and the next
-      // item's first barrier has no load to wait for.  The block image is this
-      // wave's own: no barrier between the halves.
-      store_rows(int_c<0>{}, int_c<MB / 2>{});
-      if (bf16_out) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kStoresBf16 / 2) : "memory");
-      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kStoresF32 / 2) : "memory");
-      store_rows(int_c<MB / 2>{}, int_c<MB>{});
-      entry = kPrefetched;
-      phase = (phase + steps) & 1;
+    // The ring is free unless it was handed over: the next item's ring fill is
+    // issued before this item's stores so that its latency hides behind them.
+    if (!cont && has_next) fill_ring(nx);
+    if (!wide) {
+      store_tile<MB, NB>(acc, target, bf16_out, row0, col0, m_valid, n_valid, interior);
+    } else if (bf16_out) {
+      store_tile_staged_bf16<MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
     } else {
-      // The ring is free: the next item's ring fill is issued before this
-      // item's stores so that its latency hides behind them.
-      if (has_next) fill_ring(nx);
-      if (wide) {
-        store_rows(int_c<0>{}, int_c<MB>{});
-      } else {
-        store_tile<MB, NB>(acc, target, bf16_out, row0, col0, m_valid, n_valid, interior);
-      }
-      entry = wide ? kFilledBehindStores : kFilled;
-      phase = 0;
+      store_tile_staged_f32<MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
     }
+    entry = cont ? kPrefetched : wide ? kFilledBehindStores : kFilled;
+    phase = cont ? (phase + steps) & (STAGES - 1) : 0;
     if (!has_next) break;
     c = nx;
     nx = make_ctx(after_next);
@@ -520,22 +541,25 @@ hipError_t configure_layouts() {
   return e;
 }
 
-// Large class: 256 x 256 tile, 8 waves (2 x 4, each 128 x 64), 64 elements of
-// K per step, two 64 KB stages, one workgroup per CU.  Small class: 128 x 128
-// tile, 4 waves (each 64 x 64), same K step, two 32 KB stages, two workgroups
-// per CU.  Both fetch full 128-byte lines of K-contiguous operands.
-#ifndef CLEAVE_DIRECT_SHAPE_LARGE
-#define CLEAVE_DIRECT_SHAPE_LARGE Shape<kLargeTileRows, kLargeTileCols, 2, 4, 64, 2, 1>
-#endif
-using LargeShape = CLEAVE_DIRECT_SHAPE_LARGE;
-#ifndef CLEAVE_DIRECT_SHAPE_SMALL
-#define CLEAVE_DIRECT_SHAPE_SMALL Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 2, 2>
-#endif
-using SmallShape = CLEAVE_DIRECT_SHAPE_SMALL;
-static_assert(LargeShape::TM == kLargeTileRows && LargeShape::TN == kLargeTileCols,
-              "the kernel's tile must be the host's sub-tile of the large class");
-static_assert(kDirectKStep % LargeShape::BK == 0 && kDirectKStep % SmallShape::BK == 0,
-              "the host hands this kernel the work items whose chunk is a multiple of kDirectKStep");
+// All shapes fetch full 128-byte lines of K-contiguous operands (64 elements of
+// K per step).
+//   large class: 256 x 256 tile, 8 waves (2 x 4, each 128 x 64), two 64 KB
+//     stages, one workgroup per CU;
+//   small class: 128 x 128 tile, 4 waves (each 64 x 64), two 32 KB stages, two
+//     workgroups per CU;
+//   parts: a launch of few small items has one short-lived workgroup per CU, or
+//     none, and what bounds it is the time one K step takes a lone workgroup:
+//     0.62 us at 128 x 128, of which its matrix instructions are 0.21.  64 x 64
+//     parts (4 waves of 32 x 32) spread an item over four CUs, read and fill a
+//     third of the LDS per step, and four 16 KB stages keep three steps' loads
+//     in flight: 0.27 us per step.  Execute, 128 x 128 items -> parts: 24 items
+//     of 6 steps 7.0 -> 5.0 us, 64 of 64 39 -> 17, 72 of 64 42 -> 28, 128 of
+//     172 105 -> 73 us.  Full launches do better with the larger tile (4096
+//     items of 16 steps 164 / 237 us).
+using LargeShape = Shape<kLargeTileRows, kLargeTileCols, 2, 4, 64, 2, 1>;
+using SmallShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 2, 2>;
+using PartsShape = Shape<64, 64, 2, 2, 64, 4, 2>;
+static_assert(kDirectKStep == LargeShape::BK && kDirectKStep == SmallShape::BK && kDirectKStep == PartsShape::BK, "the host hands this kernel the work items of whole K steps");
 
 template <typename S>
 hipError_t launch_layouts(const ExecuteArgs& args, int grid, hipStream_t stream) {
@@ -551,18 +575,21 @@ hipError_t launch_layouts(const ExecuteArgs& args, int grid, hipStream_t stream)
 
 
 hipError_t configure_execute_direct_kernels() {
-  const hipError_t e = configure_layouts<LargeShape>();
-  return e != hipSuccess ? e : configure_layouts<SmallShape>();
+  hipError_t e = configure_layouts<LargeShape>();
+  if (e == hipSuccess) e = configure_layouts<SmallShape>();
+  if (e == hipSuccess) e = configure_layouts<PartsShape>();
+  return e;
 }
 
-int direct_workgroups_per_cu(int tile_class) {
-  return tile_class == kTileLarge ? LargeShape::WGS : SmallShape::WGS;
-}
-
-hipError_t launch_execute_direct(const ExecuteArgs& args, int tile_class, int grid,
-                                 hipStream_t stream) {
-  return tile_class == kTileLarge ? launch_layouts<LargeShape>(args, grid, stream)
-                                  : launch_layouts<SmallShape>(args, grid, stream);
+hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, int grid, hipStream_t stream) {
+  switch (shape) {
+    case kDirectLarge: return launch_layouts<LargeShape>(args, grid, stream);
+    case kDirectSmall: return launch_layouts<SmallShape>(args, grid, stream);
+    default: {   // one workgroup per part of an item; the list is padded to whole rounds of the XCDs
+      const int64_t parts = (args.n_items + 7) / 8 * 8 * PartsShape::PARTS;
+      return launch_layouts<PartsShape>(args, static_cast<int>(parts), stream);
+    }
+  }
 }
 
 }  // namespace cleave

@@ -71,13 +71,17 @@ enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileByElement = 2 };
 // element type, size and alignment.
 hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, ExecuteTile tile, hipStream_t stream);
 
-// Enqueues the bf16 direct-to-LDS execute kernel for one tile class.  The
-// caller has checked the 16-byte load conditions and that the chunk length of
-// every item is a multiple of kDirectKStep elements.
-hipError_t launch_execute_direct(const ExecuteArgs& args, int tile_class, int grid,
-                                 hipStream_t stream);
-// Workgroups of the direct kernel that one CU holds at a time, per tile class.
-int direct_workgroups_per_cu(int tile_class);
+// Shape of the direct kernel: one for the large class, two for the small one
+// (128 x 128 items; 64 x 64 parts of them, one workgroup each).  The bits do not
+// depend on it.
+enum DirectShape : int { kDirectLarge = 0, kDirectSmall = 1, kDirectParts = 2 };
+// Workgroups one CU holds at a time.
+constexpr int direct_workgroups_per_cu(DirectShape shape) { return shape == kDirectLarge ? 1 : 2; }
+// Enqueues the bf16 direct-to-LDS execute kernel.  The caller has checked the
+// 16-byte load conditions and that the chunk length of every item is a multiple
+// of kDirectKStep elements.  `grid` persistent workgroups (kDirectParts: one
+// workgroup per part, whatever `grid`).
+hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, int grid, hipStream_t stream);
 
 // Raises the dynamic-LDS limit of every execute kernel on the current device
 // (needed once per device and process, before the first launch).

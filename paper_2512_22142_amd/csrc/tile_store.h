@@ -99,7 +99,7 @@ __device__ __forceinline__ void store_blocks(const tile_f32x16 (&acc)[MB][NB], T
   }
 }
 
-// Block rows [I0, I1) of a full sub-tile, turned through a 4 KB row-major image
+// A full sub-tile, turned through a 4 KB row-major image
 // in LDS that belongs to this wave alone (`image`), so that a lane leaves with
 // 16 consecutive bytes of one row and a store instruction writes eight whole
 // 128-byte lines instead of 64 elements in two rows.  The image holds one
@@ -125,8 +125,8 @@ __device__ __forceinline__ constexpr int staged_stores_per_block_row() {
   return NB * (BF16 ? 2 : 4);
 }
 
-template <int MB, int NB, int I0, int I1>
-__device__ __forceinline__ void store_tile_rows_staged_f32(const tile_f32x16 (&acc)[MB][NB],
+template <int MB, int NB>
+__device__ __forceinline__ void store_tile_staged_f32(const tile_f32x16 (&acc)[MB][NB],
                                                            const TileTarget& t, unsigned char* image,
                                                            int wave_row0, int wave_col0, int lane) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -135,7 +135,7 @@ __device__ __forceinline__ void store_tile_rows_staged_f32(const tile_f32x16 (&a
   float* gp = reinterpret_cast<float*>(t.base) + static_cast<int64_t>(wave_row0 + (lane >> 3)) * t.ld + wave_col0 +
               (lane & 7) * 4;
 #pragma unroll
-  for (int i = I0; i < I1; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       asm volatile("" ::: "memory");
@@ -152,47 +152,49 @@ __device__ __forceinline__ void store_tile_rows_staged_f32(const tile_f32x16 (&a
     }
 }
 
-template <int MB, int NB, int I0, int I1>
-__device__ __forceinline__ void store_tile_rows_staged_bf16(const tile_f32x16 (&acc)[MB][NB],
-                                                            const TileTarget& t, unsigned char* image,
-                                                            int wave_row0, int wave_col0, int lane) {
-  static_assert(NB % 2 == 0, "the image takes two blocks side by side");
+template <int MB, int NB>
+__device__ __forceinline__ void store_tile_staged_bf16(const tile_f32x16 (&acc)[MB][NB],
+                                                       const TileTarget& t, unsigned char* image,
+                                                       int wave_row0, int wave_col0, int lane) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   typedef uint32_t u32x4_at8 __attribute__((ext_vector_type(4), aligned(8)));   // rows start on 8 bytes
-  // Image rows are 32 dwords (64 columns).  An even lane writes columns
-  // (l32, l32 + 1) of its rows 8 q + 4 lh + 2 p, an odd lane columns
-  // (l32 - 1, l32) of the rows behind them.  The two halves of a wave are four
-  // rows apart, which is the same banks: rows with bit 2 set are kept with
-  // their 16-dword halves exchanged.
+  constexpr int W = NB % 2 == 0 ? 2 : 1;      // blocks side by side in the image
+  constexpr int RW = 16 * W;                  // dwords of an image row
+  constexpr int QR = RW / 4;                  // 16-byte pieces of an image row
+  constexpr int RR = 64 / QR;                 // rows per read of the whole wave
+  // An even lane writes columns (l32, l32 + 1) of its rows 8 q + 4 lh + 2 p, an
+  // odd lane columns (l32 - 1, l32) of the rows behind them.  The two halves of
+  // a wave are four rows apart, which is the same banks: with two blocks, rows
+  // with bit 2 set are kept with their 16-dword halves exchanged.
   const int lh = lane >> 5, odd = lane & 1;
   const uint32_t select = odd ? 0x03020706u : 0x05040100u;   // (other high, own high) : (own low, other low)
-  uint32_t* wr = reinterpret_cast<uint32_t*>(image) + (4 * lh + odd) * 32 + ((lane & 31) >> 1);
-  uint32_t* wr_half[2] = {wr + 16 * lh, wr + 16 * (1 - lh)};
-  const int row = lane >> 3, quad = (lane & 7) ^ (4 * ((row >> 2) & 1));
-  const u32x4* rd = reinterpret_cast<const u32x4*>(image) + row * 8 + quad;
+  uint32_t* wr = reinterpret_cast<uint32_t*>(image) + (4 * lh + odd) * RW + ((lane & 31) >> 1);
+  uint32_t* wr_half[2] = {wr + (W == 2 ? 16 * lh : 0), wr + 16 * (1 - lh)};
+  const int row = lane / QR, quad = (lane % QR) ^ (W == 2 ? 4 * ((row >> 2) & 1) : 0);
+  const u32x4* rd = reinterpret_cast<const u32x4*>(image) + row * QR + quad;
   uint16_t* gp = reinterpret_cast<uint16_t*>(t.base) + static_cast<int64_t>(wave_row0 + row) * t.ld + wave_col0 +
-                 (lane & 7) * 8;
+                 (lane % QR) * 8;
 #pragma unroll
-  for (int i = I0; i < I1; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; j += 2) {
+    for (int j = 0; j < NB; j += W) {
       asm volatile("" ::: "memory");
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < W; ++h)
 #pragma unroll
         for (int p = 0; p < 8; ++p) {   // rows 8 * (p / 2) + 4 lh + 2 * (p % 2), and the next
           const uint32_t own = pack_bf16(acc[i][j + h][2 * p], acc[i][j + h][2 * p + 1]);
           const uint32_t other = __builtin_amdgcn_update_dpp(0u, own, 0xB1, 0xF, 0xF, true);   // lane ^ 1
-          wr_half[h][(8 * (p >> 1) + 2 * (p & 1)) * 32] = __builtin_amdgcn_perm(other, own, select);
+          wr_half[h][(8 * (p >> 1) + 2 * (p & 1)) * RW] = __builtin_amdgcn_perm(other, own, select);
         }
       asm volatile("" ::: "memory");
-      u32x4 v[4];
+      u32x4 v[32 / RR];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = rd[64 * k];
+      for (int k = 0; k < 32 / RR; ++k) v[k] = rd[64 * k];
       asm volatile("" ::: "memory");
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        *reinterpret_cast<u32x4_at8*>(gp + static_cast<int64_t>(i * 32 + 8 * k) * t.ld + j * 32) = v[k];
+      for (int k = 0; k < 32 / RR; ++k)
+        *reinterpret_cast<u32x4_at8*>(gp + static_cast<int64_t>(i * 32 + RR * k) * t.ld + j * 32) = v[k];
     }
 }
 
