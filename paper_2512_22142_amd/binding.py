@@ -1,4 +1,5 @@
-"""ctypes binding of libcleave.so: argument marshalling only.
+"""Binding of libcleave.so: argument marshalling only (ctypes, and for the calls
+that come once or twice per GEMM the checks in csrc/native.cpp).
 
 Every step of the path (task generation, sub-GEMM execution, aggregation) runs
 inside the library; torch tensors are used here solely as owners of device
@@ -12,6 +13,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcleave.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 F32 = 0
 BF16 = 1
@@ -58,9 +60,9 @@ class CleaveError(RuntimeError):
 
 
 def _load():
-    if not os.path.exists(LIB_PATH):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(NATIVE_PATH)):
         raise ImportError(
-            "libcleave.so is not built: run `python -m paper_2512_22142_amd.build` "
+            "libcleave.so and _native.so are not built: run `python -m paper_2512_22142_amd.build` "
             "(or __graft_entry__.build()) first")
     # Device pointers and streams come from PyTorch, so the library must bind to
     # the HIP runtime instance PyTorch has loaded: import torch first, whatever
@@ -150,6 +152,7 @@ def _load():
 
 
 _lib = _load()
+from . import _native  # noqa: E402  (needs torch and the library, both loaded by now)
 
 
 def _check(status, where):
@@ -220,12 +223,7 @@ def plan_explicit(M, N, K, band_h, col_w, ksplit_per_tile, gemm_id=0):
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if hasattr(stream, "cuda_stream"):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+    return ctypes.c_void_p(_native.stream(stream))
 
 
 def _dtype_code(t):
@@ -238,36 +236,26 @@ def _dtype_code(t):
 
 
 def _matrix(t, what):
-    if t.dim() != 2 or t.stride(1) != 1 or not t.is_cuda:
-        raise ValueError("%s must be a 2-D device tensor with unit column stride" % what)
-    return ctypes.c_void_p(t.data_ptr()), int(t.stride(0))
+    ptr, ld = _native.matrix(t, what)
+    return ctypes.c_void_p(ptr), ld
+
+
+def _plan_addr(plan):
+    return plan._h.value if plan._h is not None else None
 
 
 def execute(plan, A, B, partials, transA=0, transB=0, task_ids=None, stream=None, noalloc=False):
     """cleave_execute (or, with noalloc=True, cleave_execute_noalloc): A, B stored
     device matrices (torch), partials a flat fp32 device tensor of
     plan.partial_elems elements."""
-    import torch
-    a_ptr, lda = _matrix(A, "A")
-    b_ptr, ldb = _matrix(B, "B")
-    if A.dtype != B.dtype:
-        raise TypeError("A and B must have the same dtype")
-    if partials.dtype != torch.float32 or not partials.is_cuda or not partials.is_contiguous() \
-            or partials.numel() < plan.partial_elems:
-        raise ValueError("partials must be a contiguous fp32 device tensor of partial_elems elements")
-    # Stored shapes must hold the logical operands.
-    a_rows, a_cols = (plan.K, plan.M) if transA else (plan.M, plan.K)
-    b_rows, b_cols = (plan.N, plan.K) if transB else (plan.K, plan.N)
-    if tuple(A.shape) != (a_rows, a_cols) or tuple(B.shape) != (b_rows, b_cols):
-        raise ValueError("operand shapes %s, %s do not match the plan" % (tuple(A.shape), tuple(B.shape)))
     ids_ptr, n_ids = None, 0
     if task_ids is not None:
         ids = np.ascontiguousarray(task_ids, dtype=np.int64)
-        ids_ptr, n_ids = ctypes.c_void_p(ids.ctypes.data), len(ids)
-    entry = _lib.cleave_execute_noalloc if noalloc else _lib.cleave_execute
-    _check(entry(plan._h, ids_ptr, n_ids, a_ptr, lda, int(transA), b_ptr, ldb,
-                 int(transB), _dtype_code(A), ctypes.c_void_p(partials.data_ptr()),
-                 _stream_ptr(stream)), "cleave_execute_noalloc" if noalloc else "cleave_execute")
+        ids_ptr, n_ids = ids.ctypes.data, len(ids)
+    status = _native.execute(_plan_addr(plan), plan.M, plan.N, plan.K, plan.partial_elems, A, B, partials,
+                             transA, transB, ids_ptr, n_ids, stream, noalloc)
+    if status != OK:
+        raise CleaveError(status, "cleave_execute_noalloc" if noalloc else "cleave_execute")
 
 
 def execute_noalloc(plan, A, B, partials, transA=0, transB=0, task_ids=None, stream=None):
@@ -277,11 +265,7 @@ def execute_noalloc(plan, A, B, partials, transA=0, transB=0, task_ids=None, str
 
 def reduce(plan, partials, C, stream=None):
     """cleave_reduce: C an M x N device matrix (fp32 or bf16)."""
-    c_ptr, ldc = _matrix(C, "C")
-    if tuple(C.shape) != (plan.M, plan.N):
-        raise ValueError("C must be M x N")
-    _check(_lib.cleave_reduce(plan._h, ctypes.c_void_p(partials.data_ptr()), c_ptr, ldc,
-                              _dtype_code(C), _stream_ptr(stream)), "cleave_reduce")
+    _check(_native.reduce(_plan_addr(plan), plan.M, plan.N, partials, C, stream), "cleave_reduce")
 
 
 def plan_batched(M, N, K, tile_m, tile_n, ksplit, n_batch):
@@ -291,10 +275,7 @@ def plan_batched(M, N, K, tile_m, tile_n, ksplit, n_batch):
     return Plan(h.value)
 
 
-def _device_2d(t, what):
-    if t.dim() != 2 or t.stride(1) != 1 or not t.is_cuda:
-        raise ValueError("%s must be a 2-D device tensor with unit column stride" % what)
-    return ctypes.c_void_p(t.data_ptr()), int(t.stride(0))
+_device_2d = _matrix
 
 
 def execute_batched(plan, A, a_strides, B, b_strides, n_inner, partials, transA=0, transB=0,
@@ -393,13 +374,7 @@ def reduce_grouped(plan, partials, C_list, stream=None):
 
 def reduce_residual(plan, partials, R, C, stream=None):
     """cleave_reduce_residual: C = sum of partials + R (R may be C)."""
-    c_ptr, ldc = _matrix(C, "C")
-    r_ptr, ldr = _matrix(R, "R")
-    if tuple(C.shape) != (plan.M, plan.N) or tuple(R.shape) != (plan.M, plan.N) or ldr != ldc \
-            or R.dtype != C.dtype:
-        raise ValueError("R and C must be M x N with the same dtype and leading dimension")
-    _check(_lib.cleave_reduce_residual(plan._h, ctypes.c_void_p(partials.data_ptr()), r_ptr, c_ptr,
-                                       ldc, _dtype_code(C), _stream_ptr(stream)),
+    _check(_native.reduce_residual(_plan_addr(plan), plan.M, plan.N, partials, R, C, stream),
            "cleave_reduce_residual")
 
 

@@ -1,4 +1,5 @@
-"""Builds libcleave.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc."""
+"""Builds libcleave.so (HIP kernels + C ABI, hipcc for gfx950) and _native.so (the
+binding's argument checks) in-tree."""
 import os
 import subprocess
 import sys
@@ -9,6 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcleave.so")
+NATIVE = os.path.join(HERE, "_native.so")
 
 SOURCES = ["plan.cpp", "scheduler.cpp", "api.cpp", "execute.hip", "execute_direct.hip", "reduce.hip", "verify.hip", "subset.hip"]
 
@@ -31,6 +33,28 @@ def _compile(src):
     return src, obj, res
 
 
+def _compile_native():
+    """The binding's argument checks (host code against torch's headers), linked
+    to the library beside it; the HIP runtime is the one torch has loaded."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           os.path.join(CSRC, "native.cpp"), "-o", NATIVE]
+    for d in inc + [os.path.join(rocm, "include")]:
+        cmd += ["-isystem", d]
+    for d in cpp_extension.library_paths():
+        cmd += ["-L" + d]
+    cmd += ["-L" + HERE, "-l:libcleave.so", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed on native.cpp:\n%s" % (res.stdout + res.stderr))
+
+
 def build(verbose=True, extra=None):
     """Compiles every source (always; the call is the build check) and links."""
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -48,13 +72,14 @@ def build(verbose=True, extra=None):
             print(text, file=sys.stderr)
         objs.append(obj)
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    _compile_native()
     return LIB
 
 
 def ensure_built(verbose=False):
     """Builds the library only if none is there (tests, the smoke check and the
     benchmark use what is built; after a change to a source, build again)."""
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(NATIVE)):
         build(verbose=verbose)
     return LIB
 

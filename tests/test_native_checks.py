@@ -1,0 +1,79 @@
+"""What the binding's native argument checks accept and refuse."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_22142_amd as cleave
+
+
+def _plan():
+    return cleave.plan_uniform(64, 32, 48, 32, 32, 1)
+
+
+def test_host_tensors_and_non_tensors_are_refused():
+    plan = _plan()
+    A, B, P, C = torch.zeros(64, 48), torch.zeros(48, 32), torch.zeros(plan.partial_elems), torch.zeros(64, 32)
+    for call in (lambda: cleave.execute(plan, A, B, P), lambda: cleave.reduce(plan, P, C),
+                 lambda: cleave.reduce_residual(plan, P, C, C)):
+        with pytest.raises(ValueError, match="2-D device tensor"):
+            call()
+    with pytest.raises(TypeError):
+        cleave.execute(plan, np.zeros((64, 48)), B, P)
+    with pytest.raises(TypeError):
+        cleave.reduce(plan, P, None)
+
+
+@pytest.mark.gpu
+def test_device_tensors_that_do_not_fit_are_refused():
+    plan = _plan()
+    dev = dict(device="cuda")
+    A, B, C = torch.zeros(64, 48, **dev), torch.zeros(48, 32, **dev), torch.zeros(64, 32, **dev)
+    P = torch.zeros(plan.partial_elems, **dev)
+    refused = [
+        (ValueError, lambda: cleave.execute(plan, A, B, P, 1, 0)),             # shapes of the other layout
+        (ValueError, lambda: cleave.execute(plan, A.t(), B, P, 1, 0)),         # column stride
+        (ValueError, lambda: cleave.execute(plan, A.view(-1), B, P)),
+        (ValueError, lambda: cleave.execute(plan, A, B, P[1:])),               # too short
+        (ValueError, lambda: cleave.execute(plan, A, B, P.double())),
+        (TypeError, lambda: cleave.execute(plan, A, B.bfloat16(), P)),
+        (TypeError, lambda: cleave.execute(plan, A.half(), B.half(), P)),
+        (cleave.CleaveError, lambda: cleave.execute(plan, A, B, P, task_ids=[0, 0])),
+        (cleave.CleaveError, lambda: cleave.execute(plan, A, B, P, transA=0, task_ids=[plan.num_tasks])),
+        (ValueError, lambda: cleave.reduce(plan, P, C.t())),
+        (TypeError, lambda: cleave.reduce(plan, P, C.half())),
+        (ValueError, lambda: cleave.reduce_residual(plan, P, C.bfloat16(), C)),
+        (ValueError, lambda: cleave.reduce_residual(plan, P, torch.zeros(64, 64, **dev)[:, :32], C)),
+    ]
+    for error, call in refused:
+        with pytest.raises(error):
+            call()
+    plan.close()
+    with pytest.raises(cleave.CleaveError):
+        cleave.execute(plan, A, B, P)
+
+
+@pytest.mark.gpu
+def test_streams_flags_and_ids_in_every_accepted_form():
+    plan = _plan()
+    g = torch.Generator().manual_seed(3)
+    A, B = torch.randint(-4, 5, (64, 48), generator=g).float(), torch.randint(-4, 5, (48, 32), generator=g).float()
+    want = A @ B
+    A, B = A.cuda(), torch.nn.Parameter(B.cuda())
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    every = list(range(plan.num_tasks))
+    for stream in (None, side, side.cuda_stream, np.int64(side.cuda_stream)):
+        for flag in (0, False, np.int32(0)):
+            for ids in (None, every, np.asarray(every, dtype=np.int32)):
+                P = torch.full((plan.partial_elems,), float("nan"), device="cuda")
+                C = torch.full((64, 32), float("nan"), device="cuda")
+                torch.cuda.synchronize()
+                cleave.execute(plan, A, B, P, flag, flag, task_ids=ids, stream=stream)
+                cleave.reduce(plan, P, C, stream=stream)
+                torch.cuda.synchronize()
+                assert torch.equal(C.cpu(), want)
+    with torch.cuda.stream(side):                        # torch's current stream is the default
+        C = torch.zeros(64, 32, device="cuda")
+        cleave.execute(plan, A, B, P)
+        cleave.reduce(plan, P, C)
+        assert torch.equal(C.cpu(), want)
