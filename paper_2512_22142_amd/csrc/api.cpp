@@ -727,7 +727,6 @@ int reduce_impl(cleave_plan* plan, const float* partials, void* C, int64_t ldc, 
     vec = vec && aligned(epi.adam->m, 16) && aligned(epi.adam->v, 16) &&
           (!epi.adam->w_bf16 || aligned(epi.adam->w_bf16, 8));
   cleave::ReduceArgs args{};
-  args.tasks = plan->d_tasks;
   args.items = plan->d_reduce_items;
   args.n_items = static_cast<int64_t>(plan->reduce_items.size());
   args.partials = partials;

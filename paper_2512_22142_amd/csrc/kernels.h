@@ -109,7 +109,6 @@ static_assert(sizeof(ExpandArgs) <= 4096, "kernel arguments stay within 4 KB");
 hipError_t launch_expand_subset(const ExpandArgs& args, hipStream_t stream);
 
 struct ReduceArgs {
-  const cleave_task* tasks;
   const ReduceItem* items;
   int64_t n_items;
   const float* partials;

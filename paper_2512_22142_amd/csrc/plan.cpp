@@ -140,6 +140,21 @@ void order_work_items(cleave_plan* p) {
   }
 }
 
+// Elements per reduce item of a tile with S splits (a multiple of 1024: 256
+// threads, four elements each).  Short runs, one or two loads of every split per
+// thread and no loop, start and end a small launch sooner and keep more
+// workgroups in flight in a large one; they stop paying where a thread's few
+// loads no longer cover a workgroup's start.  us, runs of 4096 / 2048 / 1024
+// elements: S = 2, 768 x 3072 6.5 / 4.6 / 5.0, 8192 x 3072 47.1 / 46.3 / 48.0;
+// S = 4, 1024 x 1024 4.9 / 3.6 / 3.7, 4096 x 4096 56 / 54 / 52.6, 3001 x 2500
+// 28.0 / 26.2 / 24.9; S = 5, 4096 x 4096 80 / - / 74; S = 8, 4096 x 4096
+// 107 / 103 / 113, 8192 x 8192 417 / 419 / 443; S = 1 (a copy), 4096 x 4096
+// 23.2 / 23.7 / 26.2 and 24.6 in runs of 16384, 1024 x 1024 3.3 against 7.2.
+uint64_t reduce_run(uint32_t S) {
+  if (S == 1) return 4096;
+  return S == 2 || S >= 8 ? 2048 : 1024;
+}
+
 // Emits the task records of `tiles` in canonical order and fills the derived
 // tables.  Returns a status code.
 // With n_batch > 0 the tile list is emitted n_batch times, once per batch
@@ -228,15 +243,22 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
     // and column panels of B, at the same chunk of the inner dimension.
     order_work_items(p);
 
-    constexpr uint32_t kReduceElemsPerItem = 4096;
-    for (uint32_t i = 0; i < p->tasks.size(); ++i) {
-      const cleave_task& t = p->tasks[i];
+    for (const cleave_task& t : p->tasks) {
       if (t.ksplit_idx != 0) continue;
-      // a single split is a plain copy: fewer, longer items do better there
-      const uint32_t elems = t.ksplit_cnt == 1 ? 4 * kReduceElemsPerItem : kReduceElemsPerItem;
-      const uint32_t rows_per = std::max<uint32_t>(1, elems / t.n_len);
-      for (uint32_t r = 0; r < t.m_len; r += rows_per) {
-        p->reduce_items.push_back(ReduceItem{i, r, std::min(rows_per, t.m_len - r), 0});
+      const uint64_t block = static_cast<uint64_t>(t.m_len) * t.n_len;
+      const uint64_t run = reduce_run(t.ksplit_cnt);
+      for (uint64_t e = 0; e < block; e += run) {
+        ReduceItem item{};
+        item.partial_off = t.partial_off + e;
+        item.block = block;
+        item.m0 = t.m0 + static_cast<uint32_t>(e / t.n_len);
+        item.n0 = t.n0;
+        item.col0 = static_cast<uint32_t>(e % t.n_len);
+        item.n_len = t.n_len;
+        item.count = static_cast<uint32_t>(std::min(run, block - e));
+        item.ksplit_cnt = t.ksplit_cnt;
+        item.gemm_id = t.gemm_id;
+        p->reduce_items.push_back(item);
       }
     }
   } catch (const std::bad_alloc&) {

@@ -95,14 +95,21 @@ __host__ __device__ inline WorkItem make_work_item(const cleave_task& t, uint32_
   return w;
 }
 
-// One unit of work of the reduce kernel: a run of rows of one output tile.
-struct ReduceItem {
-  uint32_t task;    // index of the tile's chunk-0 task
-  uint32_t row0;    // first row within the tile
-  uint32_t rows;    // number of rows
+// One unit of work of the reduce kernel: a run of elements of one output tile,
+// in the tile's row-major order.  The record carries everything the kernel needs
+// from the tile's chunk-0 task.
+struct alignas(16) ReduceItem {
+  uint64_t partial_off;   // the run's first element in the tile's first block
+  uint64_t block;         // elements between two splits' blocks
+  uint32_t m0, n0;        // row and column of C where the tile row the run starts in begins
+  uint32_t col0;          // the run's first column in that tile row
+  uint32_t n_len;         // elements per tile row
+  uint32_t count;         // elements of the run
+  uint32_t ksplit_cnt;
+  uint32_t gemm_id;       // batch member (batched plans)
   uint32_t pad;
 };
-static_assert(sizeof(ReduceItem) == 16, "ReduceItem is 16 bytes");
+static_assert(sizeof(ReduceItem) == 48, "ReduceItem is 48 bytes");
 
 // Tables of the returned-block check.  A row segment is a distinct (m0, m_len)
 // of the task list, a column segment a distinct (n0, n_len): the projections

@@ -6,16 +6,19 @@
 // instead feed one of the streaming operators the paper keeps on the PS
 // (residual add, Adam update) without being stored first: see the epilogues.
 //
-// One workgroup handles one reduce item (a run of rows of one tile, ~4K
-// elements).  The S blocks of a tile are adjacent in the partial buffer and
-// each block is contiguous, so every load of the vector path is a 16-byte
-// access into a contiguous stream.
+// One workgroup handles one reduce item (a run of 1024 to 4096 elements of one
+// tile).  Its record is read through scalar loads and holds everything that the
+// loads of the partials need; looking the tile's task up behind it took another
+// 0.1-0.2 us of a 3 us launch.  The S blocks of a tile are adjacent in the
+// partial buffer and each block is contiguous, so every load of the vector path
+// is a 16-byte access into a contiguous stream.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
 #include "bf16_round.h"
 #include "kernels.h"
+#include "load_record.h"
 
 namespace cleave {
 
@@ -149,13 +152,20 @@ struct GroupedAdamEpilogue {
   }
 };
 
+// Offset from the start of a tile row of the element x places behind it in the
+// tile's row-major order.
+__device__ __forceinline__ int64_t place(uint32_t x, uint32_t n_len, int64_t ldc) {
+  const uint32_t r = x / n_len;
+  return r * ldc + (x - r * n_len);
+}
+
 // Vector path for a compile-time split count: all S loads of two output
 // float4s are issued before the first add, so every thread keeps 2*S 16-byte
 // loads in flight.  The adds stay a left fold in ascending split order.
 template <int S, typename Epi>
 __device__ __forceinline__ void reduce_item_fixed(const float* p0, uint64_t block, uint32_t count,
-                                                  uint32_t n_len, const Epi& epi, int64_t c_base,
-                                                  int64_t ldc) {
+                                                  uint32_t col0, uint32_t n_len, const Epi& epi,
+                                                  int64_t c_base, int64_t ldc) {
   constexpr uint32_t kStride = kThreads * 4;
   uint32_t e = threadIdx.x * 4;
   for (; e + kStride < count; e += 2 * kStride) {
@@ -171,9 +181,8 @@ __device__ __forceinline__ void reduce_item_fixed(const float* p0, uint64_t bloc
       acc0 = acc0 + a[s];
       acc1 = acc1 + b[s];
     }
-    const uint32_t r0 = e / n_len, r1 = (e + kStride) / n_len;
-    epi.apply4(c_base + r0 * ldc + (e - r0 * n_len), acc0);
-    epi.apply4(c_base + r1 * ldc + (e + kStride - r1 * n_len), acc1);
+    epi.apply4(c_base + place(col0 + e, n_len, ldc), acc0);
+    epi.apply4(c_base + place(col0 + e + kStride, n_len, ldc), acc1);
   }
   if (e < count) {
     f32x4 a[S];
@@ -183,47 +192,42 @@ __device__ __forceinline__ void reduce_item_fixed(const float* p0, uint64_t bloc
     f32x4 acc = a[0];
 #pragma unroll
     for (int s = 1; s < S; ++s) acc = acc + a[s];
-    const uint32_t r = e / n_len;
-    epi.apply4(c_base + r * ldc + (e - r * n_len), acc);
+    epi.apply4(c_base + place(col0 + e, n_len, ldc), acc);
   }
 }
 
 template <typename Epi, bool VEC>
 __global__ __launch_bounds__(kThreads) void reduce_kernel(ReduceArgs args, Epi all_members) {
   for (int64_t it = blockIdx.x; it < args.n_items; it += gridDim.x) {
-    const ReduceItem item = args.items[it];
-    const cleave_task task = args.tasks[item.task];
-    const auto epi = all_members.for_member(task.gemm_id);
-    const uint32_t n_len = task.n_len;
-    const uint32_t S = task.ksplit_cnt;
-    const uint64_t block = static_cast<uint64_t>(task.m_len) * n_len;   // elements per partial
-    const float* p0 = args.partials + task.partial_off + static_cast<uint64_t>(item.row0) * n_len;
-    const uint32_t count = item.rows * n_len;
-    const int64_t c_row0 = static_cast<int64_t>(task.m0) + item.row0;
-    const int64_t c_base = member_offset(args.c_at, args.batch, task.gemm_id) +
-                           c_row0 * args.ldc + task.n0;
+    const ReduceItem item = load_record(args.items, it);
+    const auto epi = all_members.for_member(item.gemm_id);
+    const uint32_t n_len = item.n_len, col0 = item.col0;
+    const uint32_t S = item.ksplit_cnt;
+    const uint64_t block = item.block;
+    const float* p0 = args.partials + item.partial_off;
+    const uint32_t count = item.count;
+    const int64_t c_base = member_offset(args.c_at, args.batch, item.gemm_id) +
+                           static_cast<int64_t>(item.m0) * args.ldc + item.n0;
 
     if constexpr (VEC) {
       switch (S) {
-        case 1: reduce_item_fixed<1>(p0, block, count, n_len, epi, c_base, args.ldc); break;
-        case 2: reduce_item_fixed<2>(p0, block, count, n_len, epi, c_base, args.ldc); break;
-        case 4: reduce_item_fixed<4>(p0, block, count, n_len, epi, c_base, args.ldc); break;
-        case 8: reduce_item_fixed<8>(p0, block, count, n_len, epi, c_base, args.ldc); break;
+        case 1: reduce_item_fixed<1>(p0, block, count, col0, n_len, epi, c_base, args.ldc); break;
+        case 2: reduce_item_fixed<2>(p0, block, count, col0, n_len, epi, c_base, args.ldc); break;
+        case 4: reduce_item_fixed<4>(p0, block, count, col0, n_len, epi, c_base, args.ldc); break;
+        case 8: reduce_item_fixed<8>(p0, block, count, col0, n_len, epi, c_base, args.ldc); break;
         default:
           for (uint32_t e = threadIdx.x * 4; e < count; e += kThreads * 4) {
             f32x4 acc = *reinterpret_cast<const f32x4*>(p0 + e);
             for (uint32_t s = 1; s < S; ++s)
               acc = acc + *reinterpret_cast<const f32x4*>(p0 + s * block + e);
-            const uint32_t r = e / n_len;
-            epi.apply4(c_base + r * args.ldc + (e - r * n_len), acc);
+            epi.apply4(c_base + place(col0 + e, n_len, args.ldc), acc);
           }
       }
     } else {
       for (uint32_t e = threadIdx.x; e < count; e += kThreads) {
         float acc = p0[e];
         for (uint32_t s = 1; s < S; ++s) acc = acc + p0[s * block + e];
-        const uint32_t r = e / n_len;
-        epi.apply1(c_base + r * args.ldc + (e - r * n_len), acc);
+        epi.apply1(c_base + place(col0 + e, n_len, args.ldc), acc);
       }
     }
   }

@@ -8,28 +8,9 @@
 
 #include "bf16_round.h"
 #include "kernels.h"
+#include "load_record.h"
 
 namespace cleave {
-
-// A work item record into scalar registers.  The table is never written by the
-// execute kernels: read through the constant address space, a wave-uniform
-// address becomes scalar loads whose completion the compiler tracks, even
-// though the kernels also store to global memory.
-__device__ __forceinline__ WorkItem load_work_item(const WorkItem* items, int64_t idx) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  typedef const __attribute__((address_space(4))) u32x4* const_words;
-  const_words src = (const_words)(items + idx);
-  uint32_t words[12];
-#pragma unroll
-  for (int v = 0; v < 3; ++v) {
-    const u32x4 q = src[v];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) words[4 * v + e] = q[e];
-  }
-  WorkItem w;
-  __builtin_memcpy(&w, words, sizeof(w));
-  return w;
-}
 
 typedef float tile_f32x16 __attribute__((ext_vector_type(16)));
 
