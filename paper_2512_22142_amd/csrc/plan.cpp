@@ -294,7 +294,7 @@ void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
       if (b % kXcds == home && (best_home < 0 || load[b] < load[best_home])) best_home = b;
     }
     const double c = cost(i);
-    const int b = (best_home >= 0 && load[best_home] <= load[best_any] + c) ? best_home : best_any;
+    const int b = (best_home >= 0 && load[best_home] <= load[best_any] + 0.25 * c) ? best_home : best_any;
     load[b] += c;
     owned[b].push_back(i);
   }

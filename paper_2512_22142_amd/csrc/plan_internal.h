@@ -192,9 +192,11 @@ struct SubsetRing {
 // [ranges[b], ranges[b + 1]) and the runs have nearly equal cost: longest items
 // first, each to the least-loaded workgroup of the XCD the item's position
 // belongs to (position mod 8, as the list was laid out) unless a workgroup of
-// another XCD is behind by more than the item's own cost; inside a run the
-// original order is kept.  Returns with `ranges` empty, and the list
-// untouched, when all items cost the same or no workgroup gets a second item.
+// another XCD is behind by more than a quarter of the item's own cost (a whole
+// item let the largest load of a 4096 x 11008 x 4096 tiling grow to 1.38 times
+// the mean, 1.17 now); inside a run the original order is kept.  Returns with
+// `ranges` empty, and the list untouched, when all items cost the same or no
+// workgroup gets a second item.
 void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
                         std::vector<uint32_t>* ranges);
 // Cost of a work item in the schedule's unit (one K step of the fast kernel):
