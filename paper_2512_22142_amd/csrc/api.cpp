@@ -265,11 +265,13 @@ const char* kernel_name(int dtype, cleave::ExecuteTile tile, int transA, int tra
 }
 
 const char* direct_kernel_name(cleave::DirectShape shape, int transA, int transB) {
-  static const char* names[3][4] = {
+  static const char* names[4][4] = {
       {"execute_direct_bf16_256x256_nn", "execute_direct_bf16_256x256_nt",
        "execute_direct_bf16_256x256_tn", "execute_direct_bf16_256x256_tt"},
       {"execute_direct_bf16_128x128_nn", "execute_direct_bf16_128x128_nt",
        "execute_direct_bf16_128x128_tn", "execute_direct_bf16_128x128_tt"},
+      {"execute_direct_bf16_128x128_deep_nn", "execute_direct_bf16_128x128_deep_nt",
+       "execute_direct_bf16_128x128_deep_tn", "execute_direct_bf16_128x128_deep_tt"},
       {"execute_direct_bf16_64x64_nn", "execute_direct_bf16_64x64_nt",
        "execute_direct_bf16_64x64_tn", "execute_direct_bf16_64x64_tt"}};
   return names[shape][(transA ? 2 : 0) + (transB ? 1 : 0)];
@@ -351,6 +353,7 @@ struct AssembleTarget {
 struct SubsetLayout {
   bool fine = false;                                  // every block cut into small-class sub-tiles
   int64_t counts[cleave::kNumTileClasses][2] = {};    // work items per (class, part)
+  int64_t direct_steps[cleave::kNumTileClasses] = {};   // K steps of the items of part 0, together
   int64_t total() const { return counts[0][0] + counts[0][1] + counts[1][0] + counts[1][1]; }
 };
 inline int subset_part(const cleave_task& t) { return t.k_len % cleave::kDirectKStep == 0 ? 0 : 1; }
@@ -380,6 +383,7 @@ int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int
     const cleave_task& t = plan->tasks[task_ids[i]];
     const cleave::SubTiling st = cleave::sub_tiling(t, out->fine);
     out->counts[st.cls][subset_part(t)] += st.count();
+    if (subset_part(t) == 0) out->direct_steps[st.cls] += int64_t{st.count()} * (t.k_len / cleave::kDirectKStep);
   }
   return CLEAVE_OK;
 }
@@ -428,13 +432,16 @@ cleave::ExecuteTile general_tile(int dtype, int64_t items, int cus) {
   return items <= narrow_up_to ? cleave::kTileNarrow : cleave::kTileWide;
 }
 
-// Shape of the direct kernel for `items` work items of a class.  Small items run
-// as 64 x 64 parts while that leaves them about two workgroups per CU: at 128
-// items parts are 9-25 % faster whatever the chain's length (1 to 24 K steps),
-// at 192 the two are within 8 % of each other, at 256 parts are slower.
-cleave::DirectShape direct_shape(int cls, int64_t items, int cus) {
+// Shape of the direct kernel for `items` work items of a class with `steps` K
+// steps between them.  Small items run as 64 x 64 parts while that leaves them
+// about two workgroups per CU: at 128 items parts are 9-25 % faster whatever the
+// chain's length (1 to 24 K steps), at 192 the two are within 8 % of each other,
+// at 256 parts are slower.  From there to one item per CU the deep ring wins
+// when chains are long (24 steps: 16 %, 12: nothing).
+cleave::DirectShape direct_shape(int cls, int64_t items, int64_t steps, int cus) {
   if (cls == cleave::kTileLarge) return cleave::kDirectLarge;
-  return items * 8 <= int64_t{5} * cus ? cleave::kDirectParts : cleave::kDirectSmall;
+  if (items * 8 <= int64_t{5} * cus) return cleave::kDirectParts;
+  return items <= cus && steps >= 16 * items ? cleave::kDirectDeep : cleave::kDirectSmall;
 }
 
 int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, const void* A,
@@ -493,6 +500,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   // leading items of each list whose chunk is a whole number of direct-kernel K steps
   int64_t whole_steps[cleave::kNumTileClasses] = {static_cast<int64_t>(plan->items_whole_steps[0]),
                                                   static_cast<int64_t>(plan->items_whole_steps[1])};
+  int64_t direct_steps[cleave::kNumTileClasses] = {plan->items_direct_steps[0], plan->items_direct_steps[1]};   // of those
   // which of the plan's lists a class runs from (-1: a subset's own list)
   int list_of[cleave::kNumTileClasses] = {task_ids ? -1 : 0, task_ids ? -1 : 1};
   if (!task_ids && (!direct || prefers_fine(plan->items[cleave::kTileLarge].size()))) {
@@ -503,6 +511,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     d_lists[cleave::kTileSmall] = plan->d_items_fine;
     counts[cleave::kTileSmall] = static_cast<int64_t>(plan->items_fine.size());
     whole_steps[cleave::kTileSmall] = static_cast<int64_t>(plan->items_fine_whole_steps);
+    direct_steps[cleave::kTileSmall] = plan->items_direct_steps[cleave::kNumTileClasses];
   }
   // Subset launches: the work-item lists are written on the device, from the
   // task records, into a slice of memory the plan set aside when its tables
@@ -536,6 +545,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     for (int c = 0; c < cleave::kNumTileClasses; ++c) {
       d_lists[c] = slice + pos;
       whole_steps[c] = layout.counts[c][0];
+      direct_steps[c] = layout.direct_steps[c];
       counts[c] = layout.counts[c][0] + layout.counts[c][1];
       pos += counts[c];
     }
@@ -580,7 +590,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     const int64_t n_direct = direct ? whole_steps[c] : 0;
     const int64_t n_general = counts[c] - n_direct;
     cleave::ExecuteTile tile = cleave::kTileWide;
-    const cleave::DirectShape shape = direct_shape(c, n_direct, cus);
+    const cleave::DirectShape shape = direct_shape(c, n_direct, direct_steps[c], cus);
     if (n_direct > 0) {
       // Persistent workgroups, as many as the chip holds at once: each walks
       // the item list with the grid as stride and fetches the head of its next

@@ -547,6 +547,12 @@ hipError_t configure_layouts() {
 //     stages, one workgroup per CU;
 //   small class: 128 x 128 tile, 4 waves (each 64 x 64), two 32 KB stages, two
 //     workgroups per CU;
+//   deep: a launch with at most one small item per CU leaves half of the LDS
+//     unused and a lone workgroup waiting for its loads, one step ahead, when
+//     the operands come from HBM.  Four stages, three steps ahead, one workgroup
+//     per CU: 216 items of 64 steps 55 -> 42 us, 192 of 24 25.7 -> 21.6 us (inputs
+//     not in any cache); 256 of 12 steps 14.3 / 14.6 us, full launches lose the
+//     second workgroup (4096 items of 16 steps 187 / 221 us);
 //   parts: a launch of few small items has one short-lived workgroup per CU, or
 //     none, and what bounds it is the time one K step takes a lone workgroup:
 //     0.62 us at 128 x 128, of which its matrix instructions are 0.21.  64 x 64
@@ -558,8 +564,10 @@ hipError_t configure_layouts() {
 //     items of 16 steps 164 / 237 us).
 using LargeShape = Shape<kLargeTileRows, kLargeTileCols, 2, 4, 64, 2, 1>;
 using SmallShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 2, 2>;
+using DeepShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 4, 1>;
 using PartsShape = Shape<64, 64, 2, 2, 64, 4, 2>;
-static_assert(kDirectKStep == LargeShape::BK && kDirectKStep == SmallShape::BK && kDirectKStep == PartsShape::BK, "the host hands this kernel the work items of whole K steps");
+static_assert(kDirectKStep == LargeShape::BK && kDirectKStep == SmallShape::BK &&
+              kDirectKStep == DeepShape::BK && kDirectKStep == PartsShape::BK, "the host hands this kernel the work items of whole K steps");
 
 template <typename S>
 hipError_t launch_layouts(const ExecuteArgs& args, int grid, hipStream_t stream) {
@@ -577,6 +585,7 @@ hipError_t launch_layouts(const ExecuteArgs& args, int grid, hipStream_t stream)
 hipError_t configure_execute_direct_kernels() {
   hipError_t e = configure_layouts<LargeShape>();
   if (e == hipSuccess) e = configure_layouts<SmallShape>();
+  if (e == hipSuccess) e = configure_layouts<DeepShape>();
   if (e == hipSuccess) e = configure_layouts<PartsShape>();
   return e;
 }
@@ -585,6 +594,7 @@ hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, int
   switch (shape) {
     case kDirectLarge: return launch_layouts<LargeShape>(args, grid, stream);
     case kDirectSmall: return launch_layouts<SmallShape>(args, grid, stream);
+    case kDirectDeep: return launch_layouts<DeepShape>(args, grid, stream);
     default: {   // one workgroup per part of an item; the list is padded to whole rounds of the XCDs
       const int64_t parts = (args.n_items + 7) / 8 * 8 * PartsShape::PARTS;
       return launch_layouts<PartsShape>(args, static_cast<int>(parts), stream);

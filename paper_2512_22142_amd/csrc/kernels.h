@@ -71,12 +71,15 @@ enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileByElement = 2 };
 // element type, size and alignment.
 hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, ExecuteTile tile, hipStream_t stream);
 
-// Shape of the direct kernel: one for the large class, two for the small one
-// (128 x 128 items; 64 x 64 parts of them, one workgroup each).  The bits do not
-// depend on it.
-enum DirectShape : int { kDirectLarge = 0, kDirectSmall = 1, kDirectParts = 2 };
+// Shape of the direct kernel: one for the large class, three for the small one
+// (128 x 128 items, two workgroups per CU; the same with twice the ring, one per
+// CU; 64 x 64 parts of an item, one workgroup each).  The bits do not depend on
+// it.
+enum DirectShape : int { kDirectLarge = 0, kDirectSmall = 1, kDirectDeep = 2, kDirectParts = 3 };
 // Workgroups one CU holds at a time.
-constexpr int direct_workgroups_per_cu(DirectShape shape) { return shape == kDirectLarge ? 1 : 2; }
+constexpr int direct_workgroups_per_cu(DirectShape shape) {
+  return shape == kDirectLarge || shape == kDirectDeep ? 1 : 2;
+}
 // Enqueues the bf16 direct-to-LDS execute kernel.  The caller has checked the
 // 16-byte load conditions and that the chunk length of every item is a multiple
 // of kDirectKStep elements.  `grid` persistent workgroups (kDirectParts: one

@@ -232,6 +232,8 @@ struct cleave_plan {
   // would leave most of the CUs without a work item.
   std::vector<cleave::WorkItem> items_fine;
   size_t items_fine_whole_steps = 0;
+  // K steps of the whole-step items of the three lists (large, small, fine), together.
+  int64_t items_direct_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};
   std::vector<cleave::ReduceItem> reduce_items;
 
   // Device copies (current device at first use).
