@@ -885,7 +885,6 @@ namespace {
 // device copies plus scratch (once per device the plan is used on).
 int ensure_verify_tables_host(cleave_plan* p) {
   using cleave::Segment;
-  using cleave::VerifyItem;
   if (!p->verify) {
     cleave::VerifyTables* v = new (std::nothrow) cleave::VerifyTables;
     if (!v) return CLEAVE_ENOMEM;
@@ -904,9 +903,8 @@ int ensure_verify_tables_host(cleave_plan* p) {
         if (ci.second) v->col_segs.push_back(Segment{t.n0, t.n_len});
         v->task_col_seg.push_back(ci.first->second);
         const uint32_t rows_per = std::max<uint32_t>(1, kElemsPerItem / t.n_len);
-        const uint32_t index = static_cast<uint32_t>(&t - p->tasks.data());
         for (uint32_t r0 = 0; r0 < t.m_len; r0 += rows_per)
-          v->items.push_back(VerifyItem{index, r0, std::min(rows_per, t.m_len - r0), 0});
+          v->items.push_back(cleave::make_verify_item(t, r0, std::min(rows_per, t.m_len - r0)));
         v->max_ksplit = std::max(v->max_ksplit, t.ksplit_cnt);
         if (v->items.size() > std::numeric_limits<uint32_t>::max()) {
           delete v;
@@ -955,7 +953,6 @@ int ensure_verify_tables(cleave_plan* p) {
 // Tables of the fused check + aggregation (first fused call on the plan, after
 // ensure_verify_tables): runs of rows of ~kAggElemsPerItem output elements.
 int ensure_aggregate_tables(cleave_plan* p) {
-  using cleave::VerifyItem;
   cleave::VerifyTables* v = p->verify;
   if (v->d_agg_items || p->tasks.empty()) return CLEAVE_OK;
   if (v->agg_first_item.empty()) {
@@ -965,13 +962,15 @@ int ensure_aggregate_tables(cleave_plan* p) {
       v->agg_first_item.push_back(0);
       for (const cleave_task& t : p->tasks) {
         const uint32_t rows_per = std::max<uint32_t>(1, kAggElemsPerItem / t.n_len);
-        const uint32_t index = static_cast<uint32_t>(&t - p->tasks.data());
-        for (uint32_t r0 = 0, j = 0; r0 < t.m_len; r0 += rows_per, ++j) {
-          if (t.ksplit_idx == 0)
-            v->agg_items.push_back(VerifyItem{index, r0, std::min(rows_per, t.m_len - r0),
-                                              static_cast<uint32_t>(slots) + j});
+        const uint32_t runs = (t.m_len + rows_per - 1) / rows_per;
+        for (uint32_t j = 0; t.ksplit_idx == 0 && j < runs; ++j) {
+          const uint32_t r0 = j * rows_per;
+          cleave::VerifyItem item = cleave::make_verify_item(t, r0, std::min(rows_per, t.m_len - r0));
+          item.slot = static_cast<uint32_t>(slots) + j;
+          item.slot_step = runs;
+          v->agg_items.push_back(item);
         }
-        slots += (t.m_len + rows_per - 1) / rows_per;
+        slots += runs;
         if (slots > std::numeric_limits<uint32_t>::max()) {
           v->agg_items.clear();
           v->agg_first_item.clear();
@@ -1068,7 +1067,7 @@ int verify_impl(cleave_plan* plan, const void* A, int64_t lda, int transA, const
                                n_members, r_stride, bl.shape, bl.a};
   pass.B = cleave::ProjectArgs{B, ldb, v->d_col_segs, static_cast<int>(v->col_segs.size()), s, V, V_abs, K,
                                n_members, s_stride, bl.shape, bl.b};
-  pass.bil = cleave::BilinearArgs{plan->d_tasks, v->d_items, static_cast<int64_t>(v->items.size()),
+  pass.bil = cleave::BilinearArgs{v->d_items, static_cast<int64_t>(v->items.size()),
                                   partials, r, s, v->d_item_sums, batched ? 1 : 0, r_stride, s_stride};
   const uint32_t* first_item = v->d_task_first_item;
   const double* item_sums = v->d_item_sums;
@@ -1084,8 +1083,7 @@ int verify_impl(cleave_plan* plan, const void* A, int64_t lda, int transA, const
     fused.B = pass.B;
     fused.bil = pass.bil;
     fused.bil.item_sums = v->d_agg_item_sums;
-    fused.agg = cleave::AggregateArgs{v->d_agg_items, static_cast<int64_t>(v->agg_items.size()),
-                                      v->d_agg_first_item, agg.C, agg.ldc, agg.out_dtype == CLEAVE_BF16 ? 1 : 0};
+    fused.agg = cleave::AggregateArgs{v->d_agg_items, static_cast<int64_t>(v->agg_items.size()), agg.C, agg.ldc, agg.out_dtype == CLEAVE_BF16 ? 1 : 0};
     CLEAVE_HIP(cleave::launch_verify_reduce_pass(fused, dtype, a_contig, b_contig,
                                                  a_vec && b_vec && p_vec && c_vec, stream));
   } else {

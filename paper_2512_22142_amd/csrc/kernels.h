@@ -178,10 +178,9 @@ struct ProjectArgs {
 };
 
 // item_sums[item] = sum_{rows of the item} r[m0 + i] * sum_j P[i][j] * s[n0 + j].
-// Batched plans (batched != 0): task.gemm_id selects the member's probe vectors,
+// Batched plans (batched != 0): the item's gemm_id selects the member's probe vectors,
 // r_stride / s_stride entries apart.
 struct BilinearArgs {
-  const cleave_task* tasks;
   const VerifyItem* items;
   int64_t n_items;
   const float* partials;
@@ -208,15 +207,13 @@ hipError_t launch_verify_pass(const VerifyPassArgs& args, int dtype, bool a_cont
 // adjacent, each m_len * n_len elements), so that every partial element is
 // read once for both its check and the sum.  The runs are shorter than the
 // bilinear items of the separate pass (the pass also writes; short items
-// measured 15-25 % faster).  An item names the tile's first task; its sum for
-// split s goes to item_sums[item.slot + s * ipt], ipt = the task's slot count
-// (first_item[task + 1] - first_item[task]); C gets the left fold
+// measured 15-25 % faster).  The sum for split s goes to
+// item_sums[item.slot + s * item.slot_step]; C gets the left fold
 // ((P0 + P1) + ...) + P_{S-1} in fp32.  Splits per tile: at most kMaxFusedSplits.
 constexpr int kMaxFusedSplits = 8;
 struct AggregateArgs {
   const VerifyItem* items;
   int64_t n_items;
-  const uint32_t* first_item;     // per task: first slot; n_tasks + 1 entries
   void* C;
   int64_t ldc;                    // elements
   int out_bf16;

@@ -118,13 +118,32 @@ static_assert(sizeof(ReduceItem) == 48, "ReduceItem is 48 bytes");
 struct Segment {
   uint32_t start, len;
 };
-// One unit of work of the bilinear-form kernel: a run of rows of one task's
-// partial block.
-struct VerifyItem {
-  uint32_t task, row0, rows;
-  uint32_t slot;   // fused pass only: where the item's sum for the tile's first split goes
+// One unit of work of the bilinear-form kernels: a run of rows of one task's
+// partial block, or (fused pass) of all splits' blocks of a tile.  The record
+// carries everything the kernels need from the (first split's) task.
+struct alignas(16) VerifyItem {
+  uint64_t partial_off;     // first element of the run in the (first split's) block
+  uint64_t block;           // fused pass: elements between two splits' blocks
+  uint32_t m0, n0;          // first row and column of the run in the output
+  uint32_t n_len;           // elements per row
+  uint32_t count;           // elements of the run
+  uint32_t gemm_id;         // batch member
+  uint32_t ksplit_cnt;      // fused pass: splits of the tile,
+  uint32_t slot, slot_step; // where the sum of its first split goes, and how much further on the next one's
 };
-static_assert(sizeof(VerifyItem) == 16, "VerifyItem is 16 bytes");
+static_assert(sizeof(VerifyItem) == 48, "VerifyItem is 48 bytes");
+inline VerifyItem make_verify_item(const cleave_task& t, uint32_t row0, uint32_t rows) {
+  VerifyItem item{};
+  item.partial_off = t.partial_off + static_cast<uint64_t>(row0) * t.n_len;
+  item.block = static_cast<uint64_t>(t.m_len) * t.n_len;
+  item.m0 = t.m0 + row0;
+  item.n0 = t.n0;
+  item.n_len = t.n_len;
+  item.count = rows * t.n_len;
+  item.gemm_id = t.gemm_id;
+  item.ksplit_cnt = t.ksplit_cnt;
+  return item;
+}
 
 struct VerifyTables {
   std::vector<Segment> row_segs, col_segs;

@@ -27,6 +27,7 @@
 
 #include "bf16_round.h"
 #include "kernels.h"
+#include "load_record.h"
 
 namespace cleave {
 
@@ -81,10 +82,31 @@ __device__ __forceinline__ void load_weights(const float* w, double (&out)[VEC])
   }
 }
 
-// Sum over the 64 lanes of a wave, same tree on every call.
+// v of the lane N places on (cyclically) in each row of 16 lanes.
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+  const uint64_t bits = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = static_cast<uint32_t>(bits), hi = static_cast<uint32_t>(bits >> 32);
+  const uint32_t rl = __builtin_amdgcn_update_dpp(0u, lo, 0x120 + N, 0xF, 0xF, true);
+  const uint32_t rh = __builtin_amdgcn_update_dpp(0u, hi, 0x120 + N, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, rl | (static_cast<uint64_t>(rh) << 32));
+}
+
+// Sum over the 64 lanes of a wave, same tree on every call: lanes 32 apart, then
+// 16, 8, 4, 2, 1.  Behind the first two levels the sums repeat every 16, 8, 4, 2
+// lanes, so the lane 2^n away in either direction holds the same value and a
+// rotation of 16 lanes (VALU) takes the place of an exchange through the LDS:
+// the tree stands at the end of every unit, where nothing overlaps it.  With the
+// units' records read through scalar loads (no task look-up), check + aggregation
+// of 4096 x 11008 x 4096 in 4 splits 197 -> 192 us, 4096 x 4096 x 11008 105 -> 99,
+// 512 x 2048 x 1024 17.0 -> 13.2 us.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  v += __shfl_xor(v, 32, 64);
+  v += __shfl_xor(v, 16, 64);
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  v += row_rotate<1>(v);
   return v;
 }
 
@@ -126,13 +148,22 @@ struct ProjectStrided {
         }
       }
     }
-    // lanes l, l + KT, l + 2 KT, ... of a wave hold the same k chunk
+    // lanes l, l + KT, l + 2 KT, ... of a wave hold the same k chunk (lanes 32,
+    // then 16, then 8 apart, as in wave_sum)
+    if constexpr (KT < 64) {
+      static_assert(KT == 8, "three levels");
 #pragma unroll
-    for (int m = 32; m >= KT; m >>= 1) {
+      for (int m = 32; m >= 16; m >>= 1) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          acc[e] += __shfl_xor(acc[e], m, 64);
+          acc_abs[e] += __shfl_xor(acc_abs[e], m, 64);
+        }
+      }
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        acc[e] += __shfl_xor(acc[e], m, 64);
-        acc_abs[e] += __shfl_xor(acc_abs[e], m, 64);
+        acc[e] += row_rotate<8>(acc[e]);
+        acc_abs[e] += row_rotate<8>(acc_abs[e]);
       }
     }
     const int wave = t >> 6, lane = t & 63;
@@ -214,14 +245,13 @@ struct ProjectRows {
 // 16-byte loads in flight; wave sums, then the four waves in order.
 template <bool VEC>
 __device__ __forceinline__ void bilinear_item(const BilinearArgs& a, int64_t it, double* smem) {
-  const VerifyItem item = a.items[it];
-  const cleave_task task = a.tasks[item.task];
-  const uint32_t n_len = task.n_len;
-  const float* P = a.partials + task.partial_off + static_cast<uint64_t>(item.row0) * n_len;
-  const int64_t member = a.batched ? task.gemm_id : 0;
-  const float* rr = a.r + member * a.r_stride + task.m0 + item.row0;
-  const float* ss = a.s + member * a.s_stride + task.n0;
-  const uint32_t count = item.rows * n_len;
+  const VerifyItem item = load_record(a.items, it);
+  const uint32_t n_len = item.n_len;
+  const float* P = a.partials + item.partial_off;
+  const int64_t member = a.batched ? item.gemm_id : 0;
+  const float* rr = a.r + member * a.r_stride + item.m0;
+  const float* ss = a.s + member * a.s_stride + item.n0;
+  const uint32_t count = item.count;
   double acc = 0.0;
   if constexpr (VEC) {
     constexpr uint32_t kStride = kThreads * 4;
@@ -288,6 +318,15 @@ struct pick { typedef T type; };
 template <typename T, typename F>
 struct pick<false, T, F> { typedef F type; };
 
+// Every so many-th unit of a pass is a projection unit until they are used up, so
+// that the compute-heavier projections are spread over the item stream.  An odd
+// number: workgroup u runs on XCD u mod 8, and an even period would leave the
+// projections to half of the XCDs or fewer.
+__device__ __forceinline__ int64_t projection_period(int64_t total, int64_t proj) {
+  const int64_t every = proj > 0 ? total / proj : 1;
+  return every > 1 ? (every - 1) | 1 : 1;
+}
+
 // One launch for the three independent jobs: projection units of A, of B, and
 // the bilinear items share one list of units that the workgroups walk with the
 // grid as stride.
@@ -305,9 +344,7 @@ __global__ __launch_bounds__(kThreads) void verify_pass_kernel(VerifyPassArgs a)
   const int64_t unitsB = kbB * a.B.n_segs * a.B.n_members;
   const int64_t proj = unitsA + unitsB;
   const int64_t total = proj + a.bil.n_items;
-  // every `every`-th unit is a projection unit until they are used up, so that
-  // the compute-heavier projections are spread over the item stream
-  const int64_t every = proj > 0 ? total / proj : 1;
+  const int64_t every = projection_period(total, proj);
   for (int64_t u = blockIdx.x; u < total; u += gridDim.x) {
     const int64_t slot = u / every;
     if (u % every == 0 && slot < proj) {
@@ -333,14 +370,13 @@ __global__ __launch_bounds__(kThreads) void verify_pass_kernel(VerifyPassArgs a)
 template <bool VEC, int S>
 __device__ __forceinline__ void aggregate_item(const BilinearArgs& a, const AggregateArgs& g,
                                                const VerifyItem& item, double* smem) {
-  const cleave_task task = a.tasks[item.task];            // the tile's first split
-  const uint32_t n_len = task.n_len;
-  const uint64_t block = static_cast<uint64_t>(task.m_len) * n_len;   // elements between two splits' blocks
-  const float* P = a.partials + task.partial_off + static_cast<uint64_t>(item.row0) * n_len;
-  const float* rr = a.r + task.m0 + item.row0;
-  const float* ss = a.s + task.n0;
-  const int64_t c_at = static_cast<int64_t>(task.m0 + item.row0) * g.ldc + task.n0;
-  const uint32_t count = item.rows * n_len;
+  const uint32_t n_len = item.n_len;
+  const uint64_t block = item.block;
+  const float* P = a.partials + item.partial_off;
+  const float* rr = a.r + item.m0;
+  const float* ss = a.s + item.n0;
+  const int64_t c_at = static_cast<int64_t>(item.m0) * g.ldc + item.n0;
+  const uint32_t count = item.count;
   double acc[S];
 #pragma unroll
   for (int sp = 0; sp < S; ++sp) acc[sp] = 0.0;
@@ -425,11 +461,10 @@ __device__ __forceinline__ void aggregate_item(const BilinearArgs& a, const Aggr
   }
   __syncthreads();
   if (threadIdx.x < S) {
-    const uint32_t ipt = g.first_item[item.task + 1] - g.first_item[item.task];   // slots per task
     double total = 0.0;
 #pragma unroll
     for (int w = 0; w < kThreads / 64; ++w) total += smem[threadIdx.x * (kThreads / 64) + w];
-    a.item_sums[item.slot + threadIdx.x * ipt] = total;
+    a.item_sums[item.slot + threadIdx.x * item.slot_step] = total;
   }
   __syncthreads();   // smem is reused by the workgroup's next unit
 }
@@ -437,8 +472,8 @@ __device__ __forceinline__ void aggregate_item(const BilinearArgs& a, const Aggr
 template <bool VEC>
 __device__ __forceinline__ void aggregate_item_any(const BilinearArgs& a, const AggregateArgs& g, int64_t idx,
                                                    double* smem) {
-  const VerifyItem it0 = g.items[idx];
-  switch (a.tasks[it0.task].ksplit_cnt) {               // uniform over the workgroup
+  const VerifyItem it0 = load_record(g.items, idx);
+  switch (it0.ksplit_cnt) {                             // uniform over the workgroup
     case 1: aggregate_item<VEC, 1>(a, g, it0, smem); break;
     case 2: aggregate_item<VEC, 2>(a, g, it0, smem); break;
     case 3: aggregate_item<VEC, 3>(a, g, it0, smem); break;
@@ -467,7 +502,7 @@ __global__ __launch_bounds__(kThreads) void verify_reduce_pass_kernel(VerifyRedu
   const int64_t unitsB = kbB * a.B.n_segs * a.B.n_members;
   const int64_t proj = unitsA + unitsB;
   const int64_t total = proj + a.agg.n_items;
-  const int64_t every = proj > 0 ? total / proj : 1;
+  const int64_t every = projection_period(total, proj);
   for (int64_t u = blockIdx.x; u < total; u += gridDim.x) {
     const int64_t slot = u / every;
     if (u % every == 0 && slot < proj) {
