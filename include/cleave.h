@@ -179,9 +179,10 @@ int cleave_execute(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids,
  *   - the work list of a subset (task_ids != NULL) is written into a fixed
  *     768 KB array that is part of the library's code object (one copy per
  *     GPU, held until the process ends) instead of plan-owned memory; a subset
- *     whose tasks are cut into more than 16384 work items (256 x 256 or
- *     128 x 128 sub-tiles of the tasks' blocks) is refused with CLEAVE_ELIMIT
- *     and nothing is enqueued;
+ *     whose tasks are cut into more than 16384 work items (256 x 256 sub-tiles
+ *     of blocks with both edges above 128, 128 x 128 ones of the others,
+ *     whatever dtype and alignment) is refused with CLEAVE_ELIMIT and nothing
+ *     is enqueued;
  *   - every call on a GPU uses that GPU's one array, from its start: two
  *     subset calls that may run at the same time on one GPU (different
  *     streams, or threads) race and must be ordered by the caller; calls on

@@ -360,9 +360,10 @@ inline int subset_part(const cleave_task& t) { return t.k_len % cleave::kDirectK
 
 // Validates the ids (range, no repeats) and sizes the lists.  Uses the plan's
 // own stamp array for the repeat check: no allocation.  Caller holds subset.mu.
-// always_fine: the launch takes small sub-tiles whatever their number.
-int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int cus, bool always_fine,
-                  SubsetLayout* out) {
+// The cut depends on the ids alone, not on which kernel runs the items (the
+// general one cuts large items into its workgroup tiles itself), so neither do
+// the work-list memory a subset takes and the limit on it.
+int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int cus, SubsetLayout* out) {
   const int64_t n_tasks = static_cast<int64_t>(plan->tasks.size());
   if (++plan->seen_generation == 0) {   // wrapped: start over with clean stamps
     std::fill(plan->seen_stamp.begin(), plan->seen_stamp.end(), 0u);
@@ -378,7 +379,7 @@ int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int
   }
   // Few large items would leave most CUs idle: cut everything small instead
   // (the bits do not depend on the cut).
-  out->fine = always_fine || (large_items > 0 && large_items <= static_cast<size_t>(cus) / 2);
+  out->fine = large_items > 0 && large_items <= static_cast<size_t>(cus) / 2;
   for (int64_t i = 0; i < n_ids; ++i) {
     const cleave_task& t = plan->tasks[task_ids[i]];
     const cleave::SubTiling st = cleave::sub_tiling(t, out->fine);
@@ -521,7 +522,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   if (task_ids) {
     subset_lock = std::unique_lock<std::mutex>(plan->subset.mu);
     SubsetLayout layout;
-    rc = layout_subset(plan, task_ids, n_ids, cus, !direct, &layout);
+    rc = layout_subset(plan, task_ids, n_ids, cus, &layout);
     if (rc != CLEAVE_OK) return rc;
     slice_total = layout.total();
     cleave::WorkItem* slice = nullptr;

@@ -101,3 +101,42 @@ def test_many_subset_launches_in_flight_wrap_the_work_list_memory():
         cleave.execute(plan, run.A, run.B, run.partials, task_ids=lost)
     torch.cuda.synchronize()
     assert torch.equal(run.partials.view(torch.int32), first.view(torch.int32))
+
+
+@pytest.mark.parametrize("dtype,ld_pad", [("f32", 0), ("bf16", 1), ("bf16", 0)])
+def test_captured_subsets_of_large_blocks_take_one_item_per_sub_tile(dtype, ld_pad):
+    """The memory set aside for captured calls holds the all-small cut of the task
+    list; a subset large enough for the 256 x 256 sub-tiles takes a quarter of it,
+    whatever the element type and alignment."""
+    M = N = 13 * 136
+    K = 64
+    plan = cleave.plan_uniform(M, N, K, 136, 136, 1)     # 169 tasks, one 256 x 256 or four 128 x 128 sub-tiles each
+    plan.upload()
+    g = torch.Generator().manual_seed(322)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    a = torch.randint(-4, 5, (M, K), generator=g).to(torch.float32)
+    b = torch.randint(-4, 5, (K, N), generator=g).to(torch.float32)
+    dA, dB = a.to(dt).cuda(), torch.zeros((K, N + ld_pad), dtype=dt, device="cuda")[:, :N]
+    dB.copy_(b.to(dt))
+    want = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
+    cleave.execute(plan, dA, dB, want)
+    every = list(range(plan.num_tasks))
+    bufs = [torch.empty_like(want) for _ in range(4)]
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    refused = []
+    with torch.cuda.graph(graph, stream=side):
+        for buf in bufs:
+            try:
+                cleave.execute(plan, dA, dB, buf, task_ids=every)
+            except cleave.CleaveError as e:
+                refused.append(e.status)
+    assert refused == []
+    for rep in range(3):
+        for buf in bufs:
+            buf.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(buf, want) for buf in bufs), rep

@@ -89,3 +89,28 @@ def test_noalloc_refuses_oversized_subsets_and_plans_not_uploaded():
     cleave.execute_noalloc(big, dA, b2, p2, task_ids=list(range(16384)))   # within the limit again
     torch.cuda.synchronize()
     assert not bool(torch.isnan(p2[:16384 * 64 * 64]).any())
+
+
+@pytest.mark.parametrize("dtype,ld_pad", [("f32", 0), ("bf16", 1)])
+def test_noalloc_counts_the_sub_tiles_of_the_mixed_cut_for_any_type_and_alignment(dtype, ld_pad):
+    """Tasks whose blocks are one 256 x 256 sub-tile each (four 128 x 128 ones):
+    up to 16384 of them fit the array, also on the general executor's path
+    (fp32; bf16 rows that do not start on 16 bytes)."""
+    edge, K = 132, 8
+    plan = cleave.plan_uniform(edge * 128, edge * 128, K, edge, edge, 1)      # 16384 tasks
+    plan.upload()
+    g = torch.Generator().manual_seed(321)
+    a = torch.randint(-4, 5, (edge * 128, K), generator=g).to(torch.float32)
+    b = torch.randint(-4, 5, (K, edge * 128), generator=g).to(torch.float32)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dA, dB = a.to(dt).cuda(), torch.zeros((K, edge * 128 + ld_pad), dtype=dt, device="cuda")[:, :edge * 128]
+    dB.copy_(b.to(dt))
+    got = torch.full((plan.partial_elems,), float("nan"), dtype=torch.float32, device="cuda")
+    want = torch.empty_like(got)
+    cleave.execute(plan, dA, dB, want)
+    for n in (5000, plan.num_tasks):
+        got.fill_(float("nan"))
+        cleave.execute_noalloc(plan, dA, dB, got, task_ids=list(range(n)))
+        torch.cuda.synchronize()
+        assert torch.equal(got[:n * edge * edge], want[:n * edge * edge])
+        assert bool(torch.isnan(got[n * edge * edge:]).all())
