@@ -253,7 +253,7 @@ int release_subset_slice(cleave::SubsetRing& r, int64_t begin, int64_t total, hi
   return CLEAVE_OK;
 }
 
-const char* kernel_name(int dtype, cleave::ExecuteTile tile, int transA, int transB) {
+const char* kernel_name(int dtype, const cleave::GeneralLoads& how, int transA, int transB) {
   static const char* names[2][3][4] = {
       {{"execute_f32_128x128_nn", "execute_f32_128x128_nt", "execute_f32_128x128_tn", "execute_f32_128x128_tt"},
        {"execute_f32_64x64_nn", "execute_f32_64x64_nt", "execute_f32_64x64_tn", "execute_f32_64x64_tt"},
@@ -261,7 +261,8 @@ const char* kernel_name(int dtype, cleave::ExecuteTile tile, int transA, int tra
       {{"execute_bf16_128x128_nn", "execute_bf16_128x128_nt", "execute_bf16_128x128_tn", "execute_bf16_128x128_tt"},
        {"execute_bf16_64x64_nn", "execute_bf16_64x64_nt", "execute_bf16_64x64_tn", "execute_bf16_64x64_tt"},
        {"execute_bf16_element", "execute_bf16_element", "execute_bf16_element", "execute_bf16_element"}}};
-  return names[dtype == CLEAVE_BF16 ? 1 : 0][tile][(transA ? 2 : 0) + (transB ? 1 : 0)];
+  const int row = how.a_elements || how.b_elements ? 2 : how.tile;
+  return names[dtype == CLEAVE_BF16 ? 1 : 0][row][(transA ? 2 : 0) + (transB ? 1 : 0)];
 }
 
 const char* direct_kernel_name(cleave::DirectShape shape, int transA, int transB) {
@@ -489,11 +490,11 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
                    lda * eb < (int64_t{1} << 22) && ldb * eb < (int64_t{1} << 22) &&
                    offsets_multiple_of(bl.a, bl.shape, e) && offsets_multiple_of(bl.b, bl.shape, e);
   const bool direct = vec && dtype == CLEAVE_BF16;
-  // the general kernel's 16-byte loads need that much between the start of a
+  // An operand of the general kernel's 16-byte loads needs that much between the start of a
   // stored row and the end of any chunk (K-contiguous) or row (otherwise), and
-  // keep in-tile byte offsets (up to 128 rows) in 32 bits
-  const bool by_element = (transA ? plan->M : plan->min_k_end) < e || (transB ? plan->min_k_end : plan->N) < e ||
-                          lda * eb >= (int64_t{1} << 25) || ldb * eb >= (int64_t{1} << 25);
+  // in-tile byte offsets (up to 128 rows) that fit 32 bits.
+  const bool a_elements = (transA ? plan->M : plan->min_k_end) < e || lda * eb >= (int64_t{1} << 25);
+  const bool b_elements = (transB ? plan->min_k_end : plan->N) < e || ldb * eb >= (int64_t{1} << 25);
 
   const cleave::WorkItem* d_lists[cleave::kNumTileClasses] = {plan->d_items[0], plan->d_items[1]};
   int64_t counts[cleave::kNumTileClasses] = {static_cast<int64_t>(plan->items[0].size()),
@@ -590,7 +591,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     // block depends only on the block's own task record.
     const int64_t n_direct = direct ? whole_steps[c] : 0;
     const int64_t n_general = counts[c] - n_direct;
-    cleave::ExecuteTile tile = cleave::kTileWide;
+    cleave::GeneralLoads how{cleave::kTileWide, a_elements, b_elements};
     const cleave::DirectShape shape = direct_shape(c, n_direct, direct_steps[c], cus);
     if (n_direct > 0) {
       // Persistent workgroups, as many as the chip holds at once: each walks
@@ -611,15 +612,14 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     if (n_general > 0) {
       args.items = d_lists[c] + n_direct;
       args.n_items = n_general;
-      tile = by_element ? cleave::kTileByElement
-                        : general_tile(dtype, n_general * (c == cleave::kTileLarge ? 4 : 1), cus);
-      const hipError_t he = cleave::launch_execute(args, dtype, c, tile, stream);
+      how.tile = general_tile(dtype, n_general * (c == cleave::kTileLarge ? 4 : 1), cus);
+      const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);
     }
     if (counts[c] > most) {
       most = counts[c];
       plan->last_kernel = n_direct >= n_general ? direct_kernel_name(shape, transA, transB)
-                                               : kernel_name(dtype, tile, transA, transB);
+                                               : kernel_name(dtype, how, transA, transB);
     }
   }
   if (task_ids && !static_scratch) return release_subset_slice(plan->subset, slice_begin, slice_total, stream);

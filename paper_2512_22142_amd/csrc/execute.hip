@@ -25,6 +25,14 @@
 //     of a step's loads, and SETS of them overlap.
 //     The waits on them count loads in flight, so the loads of a step past the
 //     last one are issued too (one line, already read) rather than skipped.
+//   * An operand whose rows hold less than 16 bytes is loaded one element at a
+//     time; the other operand, which is the large one then, still takes 16-byte
+//     loads.  With both by element and the guards per element (the loads of a
+//     chunk one behind the other, registers spilled) outputs one to seven
+//     columns wide took up to 1.3 times the 128 x 128 element tile that this one
+//     replaced: us, that tile / both by element / now, bf16 131072 x 1 x 512
+//     161 / 206 / 56, 64 x 1 x 4096 159 / 172 / 51, fp32 1 x 131072 x 512 with
+//     K x M and K x N operands 168 / 201 / 143.
 //   * LDS images and fragment reads are the direct kernel's (swizzled
 //     K-contiguous rows; k rows read through the LDS transpose read for bf16,
 //     one dword per k for fp32), so nothing is transposed in registers.
@@ -202,7 +210,8 @@ struct OperandTile {
 
   // One element at a time, for operands whose stored rows hold less than a
   // chunk (or end less than a chunk behind their start) and for rows too long
-  // for 32-bit offsets.
+  // for 32-bit offsets.  Elements beyond the chunk repeat the address of its
+  // last one and are dropped, so that a chunk's loads are in flight together.
   __device__ __forceinline__ void load_elements(u32x4 (&v)[NV], int s, int t) const {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -210,12 +219,16 @@ struct OperandTile {
       where(i, t, &r, &k);
       k += s * KS;
       u32x4 w = {0, 0, 0, 0};
+      if (r < r_valid) {
+        const int left = k_len - k;
+        const unsigned char* q = base + r * row_stride + min(k, k_len - 1) * k_stride;
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (r < r_valid && k + e < k_len) {
-          const unsigned char* q = base + r * row_stride + (k + e) * k_stride;
-          if constexpr (EB == 4) w[e] = *reinterpret_cast<const uint32_t*>(q);
-          else w[e >> 1] |= static_cast<uint32_t>(*reinterpret_cast<const uint16_t*>(q)) << (16 * (e & 1));
+        for (int e = 0; e < E; ++e) {
+          uint32_t x;
+          if constexpr (EB == 4) x = *reinterpret_cast<const uint32_t*>(q);
+          else x = *reinterpret_cast<const uint16_t*>(q);
+          w[e * EB / 4] |= e < left ? x << (e * EB % 4 * 8) : 0u;
+          q += e + 1 < left ? k_stride : 0;
         }
       }
       v[i] = w;
@@ -267,10 +280,15 @@ struct OperandTile {
   }
 };
 
-// A_K / B_K: the operand is stored K-contiguous (ELEMENTWISE: both true, any storage).
-template <typename S, bool A_K, bool B_K, bool ELEMENTWISE>
+// How an operand is stored and loaded: K-contiguous or tile-row-contiguous rows
+// in 16-byte loads, or one element at a time from either (into the
+// K-contiguous image).
+enum Storage : int { kByK = 0, kByRow = 1, kElements = 2 };
+
+template <typename S, Storage A, Storage B>
 __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args) {
   constexpr int EB = S::EB, TM = S::TM, TN = S::TN, MB = S::MB, NB = S::NB, E = S::E, SETS = S::SETS;
+  constexpr bool A_K = A != kByRow, B_K = B != kByRow;
 
   extern __shared__ __align__(16) unsigned char smem[];
 
@@ -324,8 +342,8 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
     const int64_t n_base = static_cast<int64_t>(item.n_base) + n_off;
     const int k_len = static_cast<int>(item.k_len);
 
-    OperandTile<EB, TM, S::NT, A_K, ELEMENTWISE> ta;
-    OperandTile<EB, TN, S::NT, B_K, ELEMENTWISE> tb;
+    OperandTile<EB, TM, S::NT, A_K, A == kElements> ta;
+    OperandTile<EB, TN, S::NT, B_K, B == kElements> tb;
     ta.init(static_cast<const unsigned char*>(args.A) +
                 (member_offset(args.a_at, args.batch, item.gemm_id) + m_base * a_rs +
                  static_cast<int64_t>(item.k0) * a_ks) * EB,
@@ -462,25 +480,34 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
   }
 }
 
-template <typename S, bool A_K, bool B_K, bool ELEMENTWISE = false>
+template <typename S, Storage A, Storage B>
 hipError_t launch_one(const ExecuteArgs& args, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL((execute_kernel<S, A_K, B_K, ELEMENTWISE>), dim3(grid), dim3(S::NT), 2 * S::kStage, stream,
-                     args);
+  hipLaunchKernelGGL((execute_kernel<S, A, B>), dim3(grid), dim3(S::NT), 2 * S::kStage, stream, args);
   return hipGetLastError();
 }
 
-template <typename S, bool A_K, bool B_K, bool ELEMENTWISE = false>
+template <typename S, Storage A, Storage B>
 hipError_t configure_one() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(execute_kernel<S, A_K, B_K, ELEMENTWISE>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(execute_kernel<S, A, B>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, 2 * S::kStage);
 }
 
 template <typename S>
 hipError_t configure_layouts() {
-  hipError_t e = configure_one<S, true, true>();
-  if (e == hipSuccess) e = configure_one<S, true, false>();
-  if (e == hipSuccess) e = configure_one<S, false, true>();
-  if (e == hipSuccess) e = configure_one<S, false, false>();
+  hipError_t e = configure_one<S, kByK, kByK>();
+  if (e == hipSuccess) e = configure_one<S, kByK, kByRow>();
+  if (e == hipSuccess) e = configure_one<S, kByRow, kByK>();
+  if (e == hipSuccess) e = configure_one<S, kByRow, kByRow>();
+  return e;
+}
+
+template <typename S>
+hipError_t configure_elements() {
+  hipError_t e = configure_one<S, kElements, kElements>();
+  if (e == hipSuccess) e = configure_one<S, kElements, kByK>();
+  if (e == hipSuccess) e = configure_one<S, kElements, kByRow>();
+  if (e == hipSuccess) e = configure_one<S, kByK, kElements>();
+  if (e == hipSuccess) e = configure_one<S, kByRow, kElements>();
   return e;
 }
 
@@ -501,10 +528,22 @@ hipError_t launch_layouts(ExecuteArgs args, int tile_class, hipStream_t stream) 
   const int grid = cut_items<S>(&args, tile_class);
   const bool a_k = !args.transA;   // A stored M x K: K-contiguous
   const bool b_k = args.transB;    // B stored N x K: K-contiguous
-  if (a_k && b_k) return launch_one<S, true, true>(args, grid, stream);
-  if (a_k && !b_k) return launch_one<S, true, false>(args, grid, stream);
-  if (!a_k && b_k) return launch_one<S, false, true>(args, grid, stream);
-  return launch_one<S, false, false>(args, grid, stream);
+  if (a_k && b_k) return launch_one<S, kByK, kByK>(args, grid, stream);
+  if (a_k && !b_k) return launch_one<S, kByK, kByRow>(args, grid, stream);
+  if (!a_k && b_k) return launch_one<S, kByRow, kByK>(args, grid, stream);
+  return launch_one<S, kByRow, kByRow>(args, grid, stream);
+}
+
+// a_elements / b_elements: at least one of them.
+template <typename S>
+hipError_t launch_elements(ExecuteArgs args, int tile_class, bool a_elements, bool b_elements, hipStream_t stream) {
+  const int grid = cut_items<S>(&args, tile_class);
+  if (a_elements && b_elements) return launch_one<S, kElements, kElements>(args, grid, stream);
+  if (a_elements)
+    return args.transB ? launch_one<S, kElements, kByK>(args, grid, stream)
+                       : launch_one<S, kElements, kByRow>(args, grid, stream);
+  return args.transA ? launch_one<S, kByRow, kElements>(args, grid, stream)
+                     : launch_one<S, kByK, kElements>(args, grid, stream);
 }
 
 template <int EB>
@@ -518,18 +557,16 @@ template <int EB>
 hipError_t configure_type() {
   hipError_t e = configure_layouts<Wide<EB>>();
   if (e == hipSuccess) e = configure_layouts<Narrow<EB>>();
-  if (e == hipSuccess) e = configure_one<ByElement<EB>, true, true, true>();
+  if (e == hipSuccess) e = configure_elements<ByElement<EB>>();
   return e;
 }
 
 template <int EB>
-hipError_t launch_type(ExecuteArgs args, int tile_class, ExecuteTile tile, hipStream_t stream) {
-  if (tile == kTileByElement) {
-    const int grid = cut_items<ByElement<EB>>(&args, tile_class);
-    return launch_one<ByElement<EB>, true, true, true>(args, grid, stream);
-  }
-  return tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, stream)
-                             : launch_layouts<Wide<EB>>(args, tile_class, stream);
+hipError_t launch_type(const ExecuteArgs& args, int tile_class, const GeneralLoads& how, hipStream_t stream) {
+  if (how.a_elements || how.b_elements)
+    return launch_elements<ByElement<EB>>(args, tile_class, how.a_elements, how.b_elements, stream);
+  return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, stream)
+                                 : launch_layouts<Wide<EB>>(args, tile_class, stream);
 }
 
 }  // namespace
@@ -539,9 +576,10 @@ hipError_t configure_execute_kernels() {
   return e != hipSuccess ? e : configure_type<4>();
 }
 
-hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, ExecuteTile tile, hipStream_t stream) {
-  return dtype == CLEAVE_BF16 ? launch_type<2>(args, tile_class, tile, stream)
-                              : launch_type<4>(args, tile_class, tile, stream);
+hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, const GeneralLoads& how,
+                          hipStream_t stream) {
+  return dtype == CLEAVE_BF16 ? launch_type<2>(args, tile_class, how, stream)
+                              : launch_type<4>(args, tile_class, how, stream);
 }
 
 }  // namespace cleave

@@ -62,14 +62,19 @@ struct ExecuteArgs {
   const uint32_t* wg_ranges;
 };
 
-// Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, or 64 x 64
-// with operands loaded one element at a time (what operands with rows shorter
-// than 16 bytes need).
-enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileByElement = 2 };
+// Workgroup tile of the general execute kernel: 128 x 128 or 64 x 64.
+enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1 };
+// An operand with rows shorter than 16 bytes is loaded one element at a time
+// (64 x 64 tile, whatever `tile`); the other one still takes 16-byte loads.
+struct GeneralLoads {
+  ExecuteTile tile;
+  bool a_elements, b_elements;
+};
 
 // Enqueues the general execute kernel over work items of one tile class: any
 // element type, size and alignment.
-hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, ExecuteTile tile, hipStream_t stream);
+hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, const GeneralLoads& how,
+                          hipStream_t stream);
 
 // Shape of the direct kernel: one for the large class, three for the small one
 // (128 x 128 items, two workgroups per CU; the same with twice the ring, one per

@@ -40,7 +40,8 @@ def check(M, N, K, tile, S, transA, transB, dtype, pad=0, kernel=None):
     tasks, elems = planner.plan_uniform(M, N, K, *tile, S)
     parts = torch.full((elems,), float("nan"), dtype=torch.float32, device="cuda")
     C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
-    dA, dB = tight(A, pad), tight(B, pad)
+    pads = pad if isinstance(pad, tuple) else (pad, pad)
+    dA, dB = tight(A, pads[0]), tight(B, pads[1])
     cleave.execute(plan, dA, dB, parts, transA, transB)
     if kernel:
         assert kernel in plan.last_kernel, plan.last_kernel
@@ -89,6 +90,20 @@ def test_wide_tiles_exact(dtype, transA, transB):
 def test_rows_shorter_than_a_load_exact(dtype, transA, transB):
     for M, N, K, S in ((1, 1, 1, 1), (3, 2, 5, 5), (2, 300, 70, 2), (130, 3, 65, 1), (40, 50, 6, 2), (5, 7, 100, 3)):
         check(M, N, K, (64, 64), S, transA, transB, dtype)
+
+
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_one_operand_by_elements_the_other_in_wide_loads_exact(dtype, transA, transB):
+    E, step = (8, 64) if dtype == "bf16" else (4, 32)
+    for short, other, K, pad in ((1, E, E, 0), (E - 1, 63, step - 1, 1), (2, 65, step + 1, 0), (1, 200, 2 * step + 7, 1),
+                                 (E - 1, 129, 3 * step, 0)):
+        check(short, other, K, (64, 64), 1, transA, transB, dtype, pad)
+        check(other, short, K, (128, 64), 1, transA, transB, dtype, pad)
+    # rows 32 MiB and more apart in one operand
+    far = (1 << 25) // (16 // E) + 3
+    check(9, 70, 9, (64, 64), 1, transA, transB, dtype, pad=(far, 1), kernel="element")
+    check(70, 9, 9, (64, 64), 1, transA, transB, dtype, pad=(1, far), kernel="element")
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
