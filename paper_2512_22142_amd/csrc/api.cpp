@@ -435,14 +435,22 @@ cleave::ExecuteTile general_tile(int dtype, int64_t items, int cus) {
 }
 
 // Shape of the direct kernel for `items` work items of a class with `steps` K
-// steps between them.  Small items run as 64 x 64 parts while that leaves them
-// about two workgroups per CU: at 128 items parts are 9-25 % faster whatever the
-// chain's length (1 to 24 K steps), at 192 the two are within 8 % of each other,
-// at 256 parts are slower.  From there to one item per CU the deep ring wins
-// when chains are long (24 steps: 16 %, 12: nothing).
+// steps between them.  Small items run as 64 x 64 parts while a part has a
+// place of its own, two on each CU (an item is four of them): there parts win
+// at every chain length.  From there to one item per CU the deep ring wins when
+// chains are long and the operands come from HBM.  Time against 128 x 128 items
+// with two stages, operands in L2 / from HBM, by K steps per item (256 CUs, all
+// layouts):
+//                    4 steps      8            16           24           48
+//   128 items parts  0.83 / 0.84  0.85 / 0.89  0.80 / 0.73  0.80 / 0.70  0.73 / 0.66
+//   130 items parts  1.04 / 1.00  1.15 / 1.06  1.07 / 0.88  0.93 / 0.82  0.86 / 0.78
+//             deep   1.10 / 1.12  1.14 / 1.08  1.09 / 0.88  0.92 / 0.83  0.78 / 0.76
+//   160 items parts  1.06 / 1.03  1.15 / 1.06  1.08 / 0.91  1.01 / 0.90  0.93 / 0.88
+//             deep   1.09 / 1.12  1.12 / 1.03  1.09 / 0.89  1.02 / 0.84  0.84 / 0.77
+//   256 items deep   1.09 / 1.09  1.10 / 0.99  1.05 / 0.87  0.91 / 0.84  0.86 / 0.78
 cleave::DirectShape direct_shape(int cls, int64_t items, int64_t steps, int cus) {
   if (cls == cleave::kTileLarge) return cleave::kDirectLarge;
-  if (items * 8 <= int64_t{5} * cus) return cleave::kDirectParts;
+  if (items * 2 <= cus) return cleave::kDirectParts;
   return items <= cus && steps >= 16 * items ? cleave::kDirectDeep : cleave::kDirectSmall;
 }
 

@@ -74,3 +74,14 @@ def test_parts_serve_a_batched_plan_exact():
     for g in range(n_batch):
         ref = og.gemm(og.widen(x)[:, g * d:(g + 1) * d].copy(), og.widen(y)[:, g * d:(g + 1) * d].T.copy())
         assert np.array_equal(C[g * L:(g + 1) * L].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("M,N,steps", [(1024, 2176, 8), (1280, 2040, 12)])   # 136 and 160 items
+def test_more_than_half_an_item_per_cu_is_not_cut_into_parts(M, N, steps):
+    K = 64 * steps
+    a = make_matrix(1031, M, K, "bf16", integer_valued=True)
+    b = make_matrix(1032, K, N, "bf16", integer_valued=True)
+    plan = cleave.plan_uniform(M, N, K, 128, 128, 1)
+    run = GpuGemm(plan, a, b).run()
+    assert "128x128" in plan.last_kernel
+    assert np.array_equal(run.C_host(), og.gemm(og.widen(a), og.widen(b)))
