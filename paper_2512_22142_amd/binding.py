@@ -240,6 +240,11 @@ def _matrix(t, what):
     return ctypes.c_void_p(ptr), ld
 
 
+def _partials(plan, partials):
+    """Address of the plan's partial blocks: a contiguous fp32 device tensor that holds them all."""
+    return ctypes.c_void_p(_native.partials(partials, plan.partial_elems))
+
+
 def _plan_addr(plan):
     return plan._h.value if plan._h is not None else None
 
@@ -265,7 +270,7 @@ def execute_noalloc(plan, A, B, partials, transA=0, transB=0, task_ids=None, str
 
 def reduce(plan, partials, C, stream=None):
     """cleave_reduce: C an M x N device matrix (fp32 or bf16)."""
-    _check(_native.reduce(_plan_addr(plan), plan.M, plan.N, partials, C, stream), "cleave_reduce")
+    _check(_native.reduce(_plan_addr(plan), plan.M, plan.N, plan.partial_elems, partials, C, stream), "cleave_reduce")
 
 
 def plan_batched(M, N, K, tile_m, tile_n, ksplit, n_batch):
@@ -326,7 +331,7 @@ def execute_assemble(plan, A, B, C, transA=0, transB=0, a_strides=(0, 0), b_stri
 def reduce_batched(plan, partials, C, c_strides, n_inner, stream=None):
     """cleave_reduce_batched: C the 2-D device tensor that holds every member's result."""
     c_ptr, ldc = _device_2d(C, "C")
-    _check(_lib.cleave_reduce_batched(plan._h, ctypes.c_void_p(partials.data_ptr()), c_ptr, ldc,
+    _check(_lib.cleave_reduce_batched(plan._h, _partials(plan, partials), c_ptr, ldc,
                                       int(c_strides[0]), int(c_strides[1]), int(n_inner),
                                       _dtype_code(C), _stream_ptr(stream)), "cleave_reduce_batched")
 
@@ -367,14 +372,14 @@ def execute_grouped(plan, A_list, B_list, partials, transA=0, transB=0, task_ids
 def reduce_grouped(plan, partials, C_list, stream=None):
     """cleave_reduce_grouped: member g's result goes to C_list[g]."""
     c_arr, ldc = _member_pointers(C_list, "C_list")
-    _check(_lib.cleave_reduce_grouped(plan._h, ctypes.c_void_p(partials.data_ptr()), len(C_list), c_arr, ldc,
+    _check(_lib.cleave_reduce_grouped(plan._h, _partials(plan, partials), len(C_list), c_arr, ldc,
                                       _dtype_code(C_list[0]), _stream_ptr(stream)),
            "cleave_reduce_grouped")
 
 
 def reduce_residual(plan, partials, R, C, stream=None):
     """cleave_reduce_residual: C = sum of partials + R (R may be C)."""
-    _check(_native.reduce_residual(_plan_addr(plan), plan.M, plan.N, partials, R, C, stream),
+    _check(_native.reduce_residual(_plan_addr(plan), plan.M, plan.N, plan.partial_elems, partials, R, C, stream),
            "cleave_reduce_residual")
 
 
@@ -395,7 +400,7 @@ def reduce_adam(plan, partials, w, m, v, lr, beta1, beta2, eps, weight_decay, st
         ptrs.append(q)
     if w.dtype != torch.float32 or tuple(w.shape) != (plan.M, plan.N):
         raise ValueError("w must be an M x N fp32 device tensor")
-    _check(_lib.cleave_reduce_adam(plan._h, ctypes.c_void_p(partials.data_ptr()), w_ptr, ptrs[0],
+    _check(_lib.cleave_reduce_adam(plan._h, _partials(plan, partials), w_ptr, ptrs[0],
                                    ptrs[1], ptrs[2], ld, lr, beta1, beta2, eps, weight_decay,
                                    int(step), _stream_ptr(stream)), "cleave_reduce_adam")
 
@@ -414,7 +419,7 @@ def reduce_adam_grouped(plan, partials, w_list, m_list, v_list, lr, beta1, beta2
             raise ValueError("w_bf16_list must match w_list")
     if ldm != ld or ldv != ld or not (len(w_list) == len(m_list) == len(v_list)):
         raise ValueError("w, m, v lists must have one entry per member and one leading dimension")
-    _check(_lib.cleave_reduce_adam_grouped(plan._h, ctypes.c_void_p(partials.data_ptr()), len(w_list), w_arr,
+    _check(_lib.cleave_reduce_adam_grouped(plan._h, _partials(plan, partials), len(w_list), w_arr,
                                            m_arr, v_arr, b_arr, ld, lr, beta1, beta2, eps, weight_decay,
                                            int(step), _stream_ptr(stream)), "cleave_reduce_adam_grouped")
 

@@ -53,6 +53,14 @@ Matrix matrix(PyObject* o, const char* what) {
   return Matrix{t.data_ptr(), t.stride(0), t.size(0), t.size(1), t.scalar_type()};
 }
 
+// The partial blocks of a plan, `elems` elements.
+float* partial_blocks(PyObject* o, int64_t elems) {
+  const at::Tensor& t = tensor(o, "partials");
+  if (t.scalar_type() != at::kFloat || !t.is_cuda() || !t.is_contiguous() || t.numel() < elems)
+    raise(PyExc_ValueError, "partials must be a contiguous fp32 device tensor of partial_elems elements");
+  return static_cast<float*>(t.data_ptr());
+}
+
 int dtype_code(at::ScalarType t) {
   if (t == at::kFloat) return CLEAVE_F32;
   if (t == at::kBFloat16) return CLEAVE_BF16;
@@ -134,10 +142,7 @@ PyObject* py_execute(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t M = integer(a[1]), N = integer(a[2]), K = integer(a[3]);
     const Matrix A = matrix(a[5], "A"), B = matrix(a[6], "B");
     if (A.type != B.type) raise(PyExc_TypeError, "A and B must have the same dtype");
-    const at::Tensor& parts = tensor(a[7], "partials");
-    if (parts.scalar_type() != at::kFloat || !parts.is_cuda() || !parts.is_contiguous() ||
-        parts.numel() < integer(a[4]))
-      raise(PyExc_ValueError, "partials must be a contiguous fp32 device tensor of partial_elems elements");
+    float* p = partial_blocks(a[7], integer(a[4]));
     // stored shapes must hold the logical operands
     const int ta = static_cast<int>(integer(a[8])), tb = static_cast<int>(integer(a[9]));
     if (A.rows != (ta ? K : M) || A.cols != (ta ? M : K) || B.rows != (tb ? N : K) || B.cols != (tb ? K : N)) {
@@ -150,7 +155,6 @@ PyObject* py_execute(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t* ids = static_cast<const int64_t*>(address(a[10]));
     const int64_t n_ids = integer(a[11]);
     const int dt = dtype_code(A.type);
-    float* p = static_cast<float*>(parts.data_ptr());
     void* stream = stream_of(a[12]);
     const int noalloc = PyObject_IsTrue(a[13]);
     if (noalloc < 0) throw Raised{};
@@ -163,16 +167,24 @@ PyObject* py_execute(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// reduce(plan address, M, N, partials, C, stream)
+// partials(t, elems) -> address
+PyObject* py_partials(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject* {
+    expect_args(n, 2);
+    return PyLong_FromVoidPtr(partial_blocks(a[0], integer(a[1])));
+  });
+}
+
+// reduce(plan address, M, N, partial_elems, partials, C, stream)
 PyObject* py_reduce(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
-    expect_args(n, 6);
-    const Matrix C = matrix(a[4], "C");
+    expect_args(n, 7);
+    const Matrix C = matrix(a[5], "C");
     if (C.rows != integer(a[1]) || C.cols != integer(a[2])) raise(PyExc_ValueError, "C must be M x N");
     cleave_plan* plan = static_cast<cleave_plan*>(address(a[0]));
-    const float* p = static_cast<const float*>(tensor(a[3], "partials").data_ptr());
+    const float* p = partial_blocks(a[4], integer(a[3]));
     const int dt = dtype_code(C.type);
-    void* stream = stream_of(a[5]);
+    void* stream = stream_of(a[6]);
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = cleave_reduce(plan, p, C.ptr, C.ld, dt, stream);
@@ -181,18 +193,18 @@ PyObject* py_reduce(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// reduce_residual(plan address, M, N, partials, R, C, stream)
+// reduce_residual(plan address, M, N, partial_elems, partials, R, C, stream)
 PyObject* py_reduce_residual(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
-    expect_args(n, 7);
-    const Matrix C = matrix(a[5], "C"), R = matrix(a[4], "R");
+    expect_args(n, 8);
+    const Matrix C = matrix(a[6], "C"), R = matrix(a[5], "R");
     const int64_t M = integer(a[1]), N = integer(a[2]);
     if (C.rows != M || C.cols != N || R.rows != M || R.cols != N || R.ld != C.ld || R.type != C.type)
       raise(PyExc_ValueError, "R and C must be M x N with the same dtype and leading dimension");
     cleave_plan* plan = static_cast<cleave_plan*>(address(a[0]));
-    const float* p = static_cast<const float*>(tensor(a[3], "partials").data_ptr());
+    const float* p = partial_blocks(a[4], integer(a[3]));
     const int dt = dtype_code(C.type);
-    void* stream = stream_of(a[6]);
+    void* stream = stream_of(a[7]);
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = cleave_reduce_residual(plan, p, R.ptr, C.ptr, C.ld, dt, stream);
@@ -209,6 +221,7 @@ PyCFunction as_function(F* f) {
 PyMethodDef kMethods[] = {
     {"matrix", as_function(py_matrix), METH_FASTCALL, nullptr},
     {"stream", py_stream, METH_O, nullptr},
+    {"partials", as_function(py_partials), METH_FASTCALL, nullptr},
     {"execute", as_function(py_execute), METH_FASTCALL, nullptr},
     {"reduce", as_function(py_reduce), METH_FASTCALL, nullptr},
     {"reduce_residual", as_function(py_reduce_residual), METH_FASTCALL, nullptr},

@@ -52,6 +52,43 @@ def test_device_tensors_that_do_not_fit_are_refused():
         cleave.execute(plan, A, B, P)
 
 
+def test_partial_blocks_on_the_host_are_refused():
+    plan = _plan()
+    with pytest.raises(ValueError, match="partials must be"):
+        cleave.binding._partials(plan, torch.zeros(plan.partial_elems))
+    with pytest.raises(TypeError):
+        cleave.binding._partials(plan, np.zeros(plan.partial_elems, dtype=np.float32))
+
+
+@pytest.mark.gpu
+def test_every_aggregation_refuses_partials_that_are_not_the_plans_blocks():
+    """A valid output and, in turn, partials on the host, one element short, of
+    another type and strided: refused before anything is enqueued, the outputs
+    untouched."""
+    dev = dict(device="cuda")
+    plan, batched = _plan(), cleave.plan_batched(64, 32, 48, 32, 32, 1, 2)
+    out = [torch.full((64, 32), 7.0, **dev) for _ in range(5)]
+    R, C, w, m, v = out
+    both = torch.full((128, 32), 7.0, **dev)
+    hyper = (1e-3, 0.9, 0.95, 1e-8, 0.1, 1)
+    calls = [(plan, lambda P: cleave.reduce(plan, P, C)),
+             (plan, lambda P: cleave.reduce_residual(plan, P, R, C)),
+             (plan, lambda P: cleave.reduce_adam(plan, P, w, m, v, *hyper)),
+             (batched, lambda P: cleave.reduce_batched(batched, P, both, (64 * 32, 0), 1)),
+             (batched, lambda P: cleave.reduce_grouped(batched, P, [C, R])),
+             (batched, lambda P: cleave.reduce_adam_grouped(batched, P, [w, C], [m, R], [v, both[:64]], *hyper))]
+    for which, call in calls:
+        n = which.partial_elems
+        good = torch.zeros(n, **dev)
+        for bad in (good.cpu(), good[1:], good.double(), good.bfloat16(), torch.zeros(2 * n, **dev)[::2]):
+            with pytest.raises(ValueError, match="partials must be"):
+                call(bad)
+    torch.cuda.synchronize()
+    assert all(bool((t == 7.0).all()) for t in out + [both])
+    for _, call in calls[:2] + calls[3:5]:                     # and the blocks themselves are taken, also as a matrix
+        call(torch.zeros(4 * batched.partial_elems, **dev).view(2, -1))
+
+
 @pytest.mark.gpu
 def test_streams_flags_and_ids_in_every_accepted_form():
     plan = _plan()
