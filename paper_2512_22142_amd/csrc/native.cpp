@@ -89,19 +89,25 @@ void* address(PyObject* o) {   // an int; None is null
   return p;
 }
 
-// None: torch's current stream; else an object with a `cuda_stream`, or an address.
+// None: torch's current stream; else an object with a `cuda_stream` (None there is
+// the null stream), or an address in any form that int() takes.
 void* stream_of(PyObject* o) {
   if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
   if (PyLong_Check(o)) return address(o);
   if (PyObject* s = PyObject_GetAttrString(o, "cuda_stream")) {
-    void* p = PyLong_AsVoidPtr(s);
+    void* p = s == Py_None ? nullptr : PyLong_AsVoidPtr(s);
     Py_DECREF(s);
     if (!p && PyErr_Occurred()) throw Raised{};
     return p;
   }
   if (!PyErr_ExceptionMatches(PyExc_AttributeError)) throw Raised{};
   PyErr_Clear();
-  return reinterpret_cast<void*>(static_cast<intptr_t>(integer(o)));
+  PyObject* n = PyNumber_Long(o);
+  if (!n) throw Raised{};
+  void* p = PyLong_AsVoidPtr(n);
+  Py_DECREF(n);
+  if (!p && PyErr_Occurred()) throw Raised{};
+  return p;
 }
 
 template <typename F>

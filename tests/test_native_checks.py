@@ -23,6 +23,26 @@ def test_host_tensors_and_non_tensors_are_refused():
         cleave.reduce(plan, P, None)
 
 
+class _Stream:
+    def __init__(self, address):
+        self.cuda_stream = address
+
+
+class _Address:
+    def __init__(self, address):
+        self.address = address
+
+    def __int__(self):
+        return self.address
+
+
+@pytest.mark.parametrize("stream,address", [
+    (_Stream(None), None), (_Stream(4096), 4096), (_Address(8192), 8192), (_Address((1 << 63) + 64), (1 << 63) + 64),
+    (np.uint64((1 << 63) + 64), (1 << 63) + 64), (0, None), ("4096", 4096)])
+def test_stream_arguments(stream, address):
+    assert cleave.binding._stream_ptr(stream).value == address
+
+
 @pytest.mark.gpu
 def test_device_tensors_that_do_not_fit_are_refused():
     plan = _plan()
