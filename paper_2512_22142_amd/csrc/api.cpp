@@ -86,6 +86,24 @@ int upload_vector(const std::vector<T>& v, T** dst) {
   return CLEAVE_OK;
 }
 
+// The aggregation's table, from the tasks already on the device and the tile list
+// (which goes behind the records).
+int make_reduce_table(cleave_plan* p) {
+  const int64_t n_tiles = static_cast<int64_t>(p->reduce_tiles.size());
+  const size_t records = static_cast<size_t>(p->reduce_runs) * sizeof(cleave::ReduceItem);
+  const size_t listed = p->reduce_tiles.size() * sizeof(cleave::ReduceTile);
+  unsigned char* table = nullptr;
+  const hipError_t e = hipMalloc(reinterpret_cast<void**>(&table), records + listed);
+  if (e == hipErrorOutOfMemory) return CLEAVE_ENOMEM;
+  if (e != hipSuccess) return hip_fail(e);
+  p->d_reduce_items = reinterpret_cast<cleave::ReduceItem*>(table);
+  cleave::ReduceTile* tiles = reinterpret_cast<cleave::ReduceTile*>(table + records);
+  CLEAVE_HIP(hipMemcpy(tiles, p->reduce_tiles.data(), listed, hipMemcpyHostToDevice));
+  CLEAVE_HIP(cleave::launch_expand_reduce(p->d_tasks, tiles, n_tiles, p->d_reduce_items, nullptr));
+  CLEAVE_HIP(hipStreamSynchronize(nullptr));   // streams that do not wait for the null stream read it next
+  return CLEAVE_OK;
+}
+
 // Work-list memory of cleave_execute_noalloc: a fixed array in the code
 // object, one copy per GPU the library runs on, held until the process ends
 // (768 KB).  In host code the name is only a handle for hipGetSymbolAddress;
@@ -178,7 +196,7 @@ int ensure_uploaded(cleave_plan* p) {
       p->wg_ranges_grid[list] = grid;
     }
   }
-  if (rc == CLEAVE_OK) rc = upload_vector(p->reduce_items, &p->d_reduce_items);
+  if (rc == CLEAVE_OK) rc = make_reduce_table(p);
   if (rc == CLEAVE_OK) rc = allocate_subset_ring(p);
   if (rc != CLEAVE_OK) {
     free_device_tables(p);
@@ -747,7 +765,7 @@ int reduce_impl(cleave_plan* plan, const float* partials, void* C, int64_t ldc, 
           (!epi.adam->w_bf16 || aligned(epi.adam->w_bf16, 8));
   cleave::ReduceArgs args{};
   args.items = plan->d_reduce_items;
-  args.n_items = static_cast<int64_t>(plan->reduce_items.size());
+  args.n_items = plan->reduce_runs;
   args.partials = partials;
   args.C = C;
   args.ldc = ldc;

@@ -116,6 +116,10 @@ static_assert(sizeof(ExpandArgs) <= 4096, "kernel arguments stay within 4 KB");
 // out[dst + sub] = work item `sub` of entries[e].task, for every entry.
 hipError_t launch_expand_subset(const ExpandArgs& args, hipStream_t stream);
 
+// Enqueues the kernel that writes the aggregation's records: one per run of every tile.
+hipError_t launch_expand_reduce(const cleave_task* tasks, const ReduceTile* tiles, int64_t n_tiles, ReduceItem* out,
+                                hipStream_t stream);
+
 struct ReduceArgs {
   const ReduceItem* items;
   int64_t n_items;

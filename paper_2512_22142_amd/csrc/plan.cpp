@@ -153,7 +153,7 @@ void order_work_items(cleave_plan* p) {
 // 28.0 / 26.2 / 24.9; S = 5, 4096 x 4096 80 / - / 74; S = 8, 4096 x 4096
 // 107 / 103 / 113, 8192 x 8192 417 / 419 / 443; S = 1 (a copy), 4096 x 4096
 // 23.2 / 23.7 / 26.2 and 24.6 in runs of 16384, 1024 x 1024 3.3 against 7.2.
-uint64_t reduce_run(uint32_t S) {
+uint32_t reduce_run(uint32_t S) {
   if (S == 1) return 4096;
   return S == 2 || S >= 8 ? 2048 : 1024;
 }
@@ -246,23 +246,13 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
     // and column panels of B, at the same chunk of the inner dimension.
     order_work_items(p);
 
-    for (const cleave_task& t : p->tasks) {
+    p->reduce_tiles.reserve(static_cast<size_t>(p->num_tiles));
+    for (uint32_t i = 0; i < p->tasks.size(); ++i) {
+      const cleave_task& t = p->tasks[i];
       if (t.ksplit_idx != 0) continue;
-      const uint64_t block = static_cast<uint64_t>(t.m_len) * t.n_len;
-      const uint64_t run = reduce_run(t.ksplit_cnt);
-      for (uint64_t e = 0; e < block; e += run) {
-        ReduceItem item{};
-        item.partial_off = t.partial_off + e;
-        item.block = block;
-        item.m0 = t.m0 + static_cast<uint32_t>(e / t.n_len);
-        item.n0 = t.n0;
-        item.col0 = static_cast<uint32_t>(e % t.n_len);
-        item.n_len = t.n_len;
-        item.count = static_cast<uint32_t>(std::min(run, block - e));
-        item.ksplit_cnt = t.ksplit_cnt;
-        item.gemm_id = t.gemm_id;
-        p->reduce_items.push_back(item);
-      }
+      const uint32_t run = reduce_run(t.ksplit_cnt);
+      p->reduce_tiles.push_back(ReduceTile{i, run, static_cast<uint64_t>(p->reduce_runs)});
+      p->reduce_runs += static_cast<int64_t>((static_cast<uint64_t>(t.m_len) * t.n_len + run - 1) / run);
     }
   } catch (const std::bad_alloc&) {
     delete p;

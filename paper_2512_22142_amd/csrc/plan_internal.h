@@ -110,6 +110,32 @@ struct alignas(16) ReduceItem {
   uint32_t pad;
 };
 static_assert(sizeof(ReduceItem) == 48, "ReduceItem is 48 bytes");
+// The run that starts at element e of the tile whose chunk-0 task is t.
+__host__ __device__ inline ReduceItem make_reduce_item(const cleave_task& t, uint64_t e, uint32_t run) {
+  ReduceItem item{};
+  item.partial_off = t.partial_off + e;
+  item.block = static_cast<uint64_t>(t.m_len) * t.n_len;
+  item.m0 = t.m0 + static_cast<uint32_t>(e / t.n_len);
+  item.n0 = t.n0;
+  item.col0 = static_cast<uint32_t>(e % t.n_len);
+  item.n_len = t.n_len;
+  const uint64_t left = item.block - e;
+  item.count = left < run ? static_cast<uint32_t>(left) : run;
+  item.ksplit_cnt = t.ksplit_cnt;
+  item.gemm_id = t.gemm_id;
+  return item;
+}
+// An output tile as the host lists it: the runs' records, one per run, are
+// written on the device when the plan is uploaded.  Written on the host they
+// made a plan up to 1.6 times as long to create and twice as long to upload:
+// creation in us, one 16-byte record per 4096 elements / 48-byte records of all
+// runs on the host / this list, 2048 x 3072 x 768 in 256 x 256 tiles, S = 2
+// 59 / 76 / 57, 4096 x 11008 x 4096 in 512 x 512, S = 4 1920 / 2720 / 1920.
+struct ReduceTile {
+  uint32_t task;    // the tile's chunk-0 task
+  uint32_t run;     // elements per run
+  uint64_t first;   // the first run's place in the table
+};
 
 // Tables of the returned-block check.  A row segment is a distinct (m0, m_len)
 // of the task list, a column segment a distinct (n0, n_len): the projections
@@ -253,7 +279,8 @@ struct cleave_plan {
   size_t items_fine_whole_steps = 0;
   // K steps of the whole-step items of the three lists (large, small, fine), together.
   int64_t items_direct_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};
-  std::vector<cleave::ReduceItem> reduce_items;
+  std::vector<cleave::ReduceTile> reduce_tiles;
+  int64_t reduce_runs = 0;
 
   // Device copies (current device at first use).
   int device = -1;
@@ -264,7 +291,7 @@ struct cleave_plan {
   // the grid sizes of the device the tables were uploaded to; null = equal items.
   uint32_t* d_wg_ranges[cleave::kNumTileClasses + 1] = {nullptr, nullptr, nullptr};
   int wg_ranges_grid[cleave::kNumTileClasses + 1] = {0, 0, 0};
-  cleave::ReduceItem* d_reduce_items = nullptr;
+  cleave::ReduceItem* d_reduce_items = nullptr;   // reduce_runs records, then the tiles they were made from
   // Work-item slices of subset launches (device memory sized once, at upload).
   cleave::SubsetRing subset;
   // Repeat check of a subset's task ids without clearing or allocating: task i

@@ -1,4 +1,5 @@
-// Work-item lists of subset launches, written on the device.
+// Launch tables that are written on the device: the work-item lists of subset
+// launches and the aggregation's records.
 //
 // A re-issued subset (paper Sec. 4.2, churn recovery: the unfinished shards of
 // a departed device are dispatched again) is a list of task indices.  The host
@@ -25,7 +26,29 @@ __global__ __launch_bounds__(64) void expand_subset_kernel(ExpandArgs args) {
     args.out[entry.dst + sub] = make_work_item(t, entry.task, s, sub);
 }
 
+// One workgroup per tile at a time; its threads write one run's record each.
+constexpr int kTileThreads = 256;
+__global__ __launch_bounds__(kTileThreads) void expand_reduce_kernel(const cleave_task* tasks, const ReduceTile* tiles,
+                                                                     int64_t n_tiles, ReduceItem* out) {
+  for (int64_t i = blockIdx.x; i < n_tiles; i += gridDim.x) {
+    const ReduceTile tile = tiles[i];
+    const cleave_task t = tasks[tile.task];
+    const uint64_t block = static_cast<uint64_t>(t.m_len) * t.n_len;
+    const uint64_t runs = (block + tile.run - 1) / tile.run;
+    for (uint64_t r = threadIdx.x; r < runs; r += kTileThreads)
+      out[tile.first + r] = make_reduce_item(t, r * tile.run, tile.run);
+  }
+}
+
 }  // namespace
+
+hipError_t launch_expand_reduce(const cleave_task* tasks, const ReduceTile* tiles, int64_t n_tiles, ReduceItem* out,
+                                hipStream_t stream) {
+  if (n_tiles == 0) return hipSuccess;
+  const int grid = static_cast<int>(n_tiles < (1 << 16) ? n_tiles : 1 << 16);
+  hipLaunchKernelGGL(expand_reduce_kernel, dim3(grid), dim3(kTileThreads), 0, stream, tasks, tiles, n_tiles, out);
+  return hipGetLastError();
+}
 
 hipError_t launch_expand_subset(const ExpandArgs& args, hipStream_t stream) {
   if (args.n_entries == 0) return hipSuccess;

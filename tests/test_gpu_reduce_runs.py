@@ -46,3 +46,18 @@ def test_runs_of_a_batched_plan():
         mine = tasks[tasks["gemm_id"] == g]
         fold = og.reduce_partials(mine, parts.numpy(), M, N)
         assert np.array_equal(C[g * M:(g + 1) * M].cpu().numpy(), fold)
+
+
+@pytest.mark.parametrize("M,N,tm,tn,S", [
+    (600, 1000, 600, 1000, 4),     # one tile, 586 runs: more than the threads that write their records
+    (301, 1003, 301, 1003, 2), (700, 644, 512, 512, 8),
+    (280, 260, 1, 1, 1)])          # 72800 tiles: more than the workgroups
+def test_records_of_large_and_of_many_tiles(M, N, tm, tn, S):
+    K = 64
+    plan = cleave.plan_uniform(M, N, K, tm, tn, S)
+    tasks, elems = planner.plan_uniform(M, N, K, tm, tn, S)
+    parts = torch.randn(elems, generator=torch.Generator().manual_seed(M + N))
+    C = torch.full((M, N), float("nan"), device="cuda")
+    cleave.reduce(plan, parts.cuda(), C)
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().numpy(), og.reduce_partials(tasks, parts.numpy(), M, N))
