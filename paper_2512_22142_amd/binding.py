@@ -59,6 +59,12 @@ class CleaveError(RuntimeError):
         super().__init__("%s: %s" % (where, msg))
 
 
+def _require_native_fit(path):
+    from .build import native_fits, native_tag
+    if not native_fits(path):
+        raise ImportError("_native.so was not built as \"%s\": run `python -m paper_2512_22142_amd.build` again" % native_tag())
+
+
 def _load():
     if not (os.path.exists(LIB_PATH) and os.path.exists(NATIVE_PATH)):
         raise ImportError(
@@ -69,6 +75,7 @@ def _load():
     # order the caller imports things in (two runtimes in one process do not see
     # each other's devices or allocations).
     import torch  # noqa: F401
+    _require_native_fit(NATIVE_PATH)
     lib = ctypes.CDLL(LIB_PATH)
     i64, i32, u32, p = ctypes.c_int64, ctypes.c_int32, ctypes.c_uint32, ctypes.c_void_p
     lib.cleave_plan_uniform.argtypes = [i64, i64, i64, i64, i64, i32, u32, ctypes.POINTER(p)]

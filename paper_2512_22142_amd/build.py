@@ -33,6 +33,20 @@ def _compile(src):
     return src, obj, res
 
 
+def native_tag():
+    """What _native.so is tied to: it is compiled against torch's C++ classes and CPython's."""
+    import torch
+    return "cleave checks for torch %s, Python %d.%d" % (torch.__version__, *sys.version_info[:2])
+
+
+def native_fits(path=NATIVE):
+    """Whether the built file is there and was made for this torch and this Python."""
+    if not os.path.exists(path):
+        return False
+    with open(path, "rb") as f:
+        return native_tag().encode() + b"\0" in f.read()
+
+
 def _compile_native():
     """The binding's argument checks (host code against torch's headers), linked
     to the library beside it; the HIP runtime is the one torch has loaded."""
@@ -43,7 +57,7 @@ def _compile_native():
     inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
     rocm = os.path.dirname(os.path.dirname(HIPCC))
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__",
-           "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-DUSE_ROCM", '-DCLEAVE_NATIVE_TAG="%s"' % native_tag(), "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            os.path.join(CSRC, "native.cpp"), "-o", NATIVE]
     for d in inc + [os.path.join(rocm, "include")]:
         cmd += ["-isystem", d]
@@ -77,9 +91,10 @@ def build(verbose=True, extra=None):
 
 
 def ensure_built(verbose=False):
-    """Builds the library only if none is there (tests, the smoke check and the
-    benchmark use what is built; after a change to a source, build again)."""
-    if not (os.path.exists(LIB) and os.path.exists(NATIVE)):
+    """Builds the library only if none is there that fits this torch and Python
+    (tests, the smoke check and the benchmark use what is built; after a change
+    to a source, build again)."""
+    if not (os.path.exists(LIB) and native_fits()):
         build(verbose=verbose)
     return LIB
 

@@ -20,6 +20,9 @@
 
 #include "cleave.h"
 
+// The torch and Python this file is compiled for, read from the built file before it is loaded.
+extern "C" __attribute__((used)) const char cleave_native_tag[] = CLEAVE_NATIVE_TAG;
+
 namespace {
 
 // The Python exception is set.

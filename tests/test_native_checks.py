@@ -23,6 +23,25 @@ def test_host_tensors_and_non_tensors_are_refused():
         cleave.reduce(plan, P, None)
 
 
+def test_a_build_for_another_torch_is_noticed(tmp_path, monkeypatch):
+    from paper_2512_22142_amd import build
+    with open(build.NATIVE, "rb") as f:
+        mine = f.read()
+    other = tmp_path / "_native.so"
+    other.write_bytes(mine.replace(torch.__version__.encode(), b"0" * len(torch.__version__)))
+    assert build.native_fits(build.NATIVE) and not build.native_fits(str(other))
+    cleave.binding._require_native_fit(build.NATIVE)
+    with pytest.raises(ImportError, match="build"):
+        cleave.binding._require_native_fit(str(other))
+    calls = []
+    monkeypatch.setattr(build, "build", lambda verbose: calls.append(verbose))
+    build.ensure_built()
+    assert calls == []
+    monkeypatch.setattr(build, "native_fits", lambda: False)
+    build.ensure_built()
+    assert calls == [False]
+
+
 class _Stream:
     def __init__(self, address):
         self.cuda_stream = address
