@@ -68,3 +68,24 @@ def test_non_finite_sums_keep_their_class(assembled):
     rest = torch.ones(M, dtype=torch.bool)
     rest[[3, 70, 129, 200]] = False
     assert torch.equal(got[rest][:, cols], ref[rest][:, cols].to(torch.bfloat16).float())
+
+
+def test_rounding_of_all_fp32_values_equals_the_integer_form():
+    """All 2^32 bit patterns (subnormals, ties, infinities, NaN payloads) through
+    the aggregation of a single split, in 64 slices: nearest even by integer
+    arithmetic, NaN stays a quiet NaN with the upper bits of its payload.  Both
+    the four-element stores and, into rows of odd length, the single ones."""
+    M = N = 8192
+    plan = cleave.plan_uniform(M, N, 64, M, N, 1)
+    C = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    wide = torch.empty((M, N + 1), dtype=torch.bfloat16, device="cuda")
+    for first in range(0, 1 << 32, M * N):
+        u = torch.arange(first, first + M * N, dtype=torch.int64, device="cuda")
+        want = torch.where((u & 0x7fffffff) > 0x7f800000, (u >> 16) | 0x40, (u + 0x7fff + ((u >> 16) & 1)) >> 16)
+        want = (want & 0xffff).to(torch.int16).view(M, N)
+        parts = u.to(torch.int32).view(torch.float32)
+        del u
+        cleave.reduce(plan, parts, C)
+        cleave.reduce(plan, parts, wide[:, :N])
+        assert torch.equal(C.view(torch.int16), want), hex(first)
+        assert torch.equal(wide[:, :N].view(torch.int16), want), hex(first)
