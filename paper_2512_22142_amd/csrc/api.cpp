@@ -181,7 +181,8 @@ int ensure_uploaded(cleave_plan* p) {
     const std::vector<cleave::WorkItem>& host = fine ? p->items_fine : p->items[list];
     const size_t n_direct = fine ? p->items_fine_whole_steps : p->items_whole_steps[list];
     cleave::WorkItem** dst = fine ? &p->d_items_fine : &p->d_items[list];
-    const int64_t resident = static_cast<int64_t>(cus) * cleave::direct_workgroups_per_cu(cls == cleave::kTileLarge ? cleave::kDirectLarge : cleave::kDirectSmall);
+    const int64_t resident = static_cast<int64_t>(cus) * cleave::direct_workgroups_per_cu(
+                                                                cls == cleave::kTileLarge ? cleave::kDirectLarge : cleave::kDirectSmall);
     const int grid = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(n_direct), resident));
     std::vector<uint32_t> ranges;
     try {
@@ -506,16 +507,14 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     if (rc != CLEAVE_OK) return rc;
   }
 
-  // 16-byte load path: every chunk and tile edge a multiple of 16 bytes and
+  // The direct kernel: bf16, every chunk and tile edge a multiple of 16 bytes and
   // all rows of both operands starting on 16-byte boundaries.
   const int e = 16 / eb;
-  const bool vec = (e == 8 ? (plan->all_k_mult8 && plan->all_mn_mult8)
-                           : (plan->all_k_mult4 && plan->all_mn_mult4)) &&
-                   lda % e == 0 && ldb % e == 0 && aligned(A, 16) && aligned(B, 16) &&
-                   // in-tile byte offsets are kept in 32 bits
-                   lda * eb < (int64_t{1} << 22) && ldb * eb < (int64_t{1} << 22) &&
-                   offsets_multiple_of(bl.a, bl.shape, e) && offsets_multiple_of(bl.b, bl.shape, e);
-  const bool direct = vec && dtype == CLEAVE_BF16;
+  const bool direct = dtype == CLEAVE_BF16 && plan->all_k_mult8 && plan->all_mn_mult8 &&
+                      lda % e == 0 && ldb % e == 0 && aligned(A, 16) && aligned(B, 16) &&
+                      // in-tile byte offsets are kept in 32 bits
+                      lda * eb < (int64_t{1} << 22) && ldb * eb < (int64_t{1} << 22) &&
+                      offsets_multiple_of(bl.a, bl.shape, e) && offsets_multiple_of(bl.b, bl.shape, e);
   // An operand of the general kernel's 16-byte loads needs that much between the start of a
   // stored row and the end of any chunk (K-contiguous) or row (otherwise), and
   // in-tile byte offsets (up to 128 rows) that fit 32 bits.
@@ -607,13 +606,13 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     args.K = plan->K;
     args.ldc = asm_to.ldc;
     args.c_bf16 = asm_to.out_dtype == CLEAVE_BF16 ? 1 : 0;
-    // block origins and row lengths are multiples of 8 elements whenever `vec` holds
-    args.out_vec = !vec ? 0
+    // block origins and row lengths are multiples of 8 elements whenever `direct` holds
+    args.out_vec = !direct ? 0
                    : !asm_to.C ? aligned(partials, 16)
                                : (asm_to.ldc % 4 == 0 && aligned(asm_to.C, args.c_bf16 ? 8 : 16) &&
                                   offsets_multiple_of(bl.c, bl.shape, 4));
-    // bf16 with 16-byte loads: items made of whole K steps go to the direct
-    // kernel, the others (if any) to the general one.  Which kernel computes a
+    // Of a launch the direct kernel can take, it gets the items made of whole K
+    // steps, and the general one the others (if any).  Which kernel computes a
     // block depends only on the block's own task record.
     const int64_t n_direct = direct ? whole_steps[c] : 0;
     const int64_t n_general = counts[c] - n_direct;
@@ -629,7 +628,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       const int grid = static_cast<int>(std::min<int64_t>(n_direct, resident));
       // items of unequal length: the schedule made for this grid when the tables were uploaded
       const int list = list_of[c];
-      args.wg_ranges = (list >= 0 && shape != cleave::kDirectParts && plan->wg_ranges_grid[list] == grid)
+      args.wg_ranges = (list >= 0 && plan->wg_ranges_grid[list] == grid)
                            ? plan->d_wg_ranges[list] : nullptr;
       const hipError_t he = cleave::launch_execute_direct(args, shape, grid, stream);
       args.wg_ranges = nullptr;

@@ -41,11 +41,11 @@
 // 512 x 512 x 1024 tasks runs at 138-141 TFLOP/s of 157 nominal.  bf16, the LDS
 // (a 64 x 64 wave tile reads 128 bytes per clock and CU at full MFMA rate, and
 // the tile's refill comes on top): the same with an odd leading dimension
-// 613-638 TFLOP/s.  Before, operands that were not 16-byte aligned were loaded
-// one element at a time and fp32 had one workgroup tile with one step in
-// flight.  Execute + reduce, before -> now: forward, dX and dW of 3001 x 1000 x
-// 2500 bf16 in 4 splits 1173 -> 169 us, of 2048 x 768 x 3072 fp32 403 -> 266
-// us, 512^3 fp32 26.7 -> 17.3 us.
+// 613-638 TFLOP/s.  Execute + reduce against unaligned operands loaded by
+// element, and one fp32 tile of 256 x 256 or 128 x 128 with one step in flight:
+// forward, dX and dW of 3001 x 1000 x 2500 bf16 in 4 splits 164 / 1173 us, of
+// 2048 x 768 x 3072 fp32 264 / 403 us, 512^3 fp32 11.9 / 26.7 us (of the last,
+// 4.5 us are host time saved by the native argument checks).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -65,7 +65,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void* lds_void;
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 // 16 bytes at an address that is only a multiple of an element
 typedef uint32_t u32x4_at2 __attribute__((ext_vector_type(4), aligned(2)));
@@ -87,7 +86,7 @@ struct Shape {
   static constexpr int kSub = 4;                // 32-byte sub-steps per step
   static constexpr int kATile = TM * 128, kBTile = TN * 128;   // bytes
   static constexpr int kStage = kATile + kBTile;
-  static_assert(SETS == 1 || SETS == 2 || SETS == 4, "register sets rotate with the two LDS stages");
+  static_assert(SETS == 1 || SETS == 2, "register sets rotate with the two LDS stages");
 };
 
 // All LDS accesses of this wave are done; then the workgroup barrier.  Loads
@@ -428,10 +427,6 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
     // Steps 0 .. SETS-1 into registers, step 0 on into LDS, step SETS behind it.
     fetch(int_c<0>{}, 0);
     if constexpr (SETS > 1) fetch(int_c<1>{}, 1);
-    if constexpr (SETS > 2) {
-      fetch(int_c<2>{}, 2);
-      fetch(int_c<3>{}, 3);
-    }
     if (b != blockIdx.x) CLEAVE_LDS_BARRIER();   // every wave is past the previous item's last fragment reads
     commit(int_c<0>{}, int_c<0>{}, 0);
     fetch(int_c<0>{}, SETS);
@@ -462,13 +457,7 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
       k_step(int_c<0>{}, s);
       if (++s >= steps) break;
       k_step(int_c<1>{}, s);
-      if (++s >= steps) break;
-      if constexpr (SETS == 4) {
-        k_step(int_c<2>{}, s);
-        if (++s >= steps) break;
-        k_step(int_c<3>{}, s);
-        ++s;
-      }
+      if (++s >= steps) break;   // (not left to the loop's condition: the other form spills registers)
     }
 
     const int row0 = wm * S::WTM + lh * 4;

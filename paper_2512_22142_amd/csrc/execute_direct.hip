@@ -1,14 +1,14 @@
 // bf16 sub-GEMM executor, fast path: operand tiles go from global memory
 // straight into LDS (no register staging), through a ring of stages.
 //
-// Same contract as the staged executor (paper Sec. 4.1: a task multiplies its
+// Same contract as the general executor (paper Sec. 4.1: a task multiplies its
 // rows of A with its columns of B over its chunk of the inner dimension and
 // stores an fp32 partial block); used when every chunk length is a multiple of
 // the K step and all tile edges / leading dimensions are multiples of 8.
 //
 // The kernel is a template over its shape (workgroup tile, wave grid, K step,
 // ring depth); a wave always owns 32 x 32 MFMA 32x32x16 blocks with fp32
-// accumulators in registers.  The two instantiations are at the end of the
+// accumulators in registers.  The four instantiations are at the end of the
 // file.
 //
 // A wave-wide direct load writes 64 consecutive 16-byte LDS slots (lane l ->
@@ -59,10 +59,12 @@ typedef __attribute__((address_space(3))) void* lds_void;
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 
 // Shape of the kernel: workgroup tile TM x TN computed by WM x WN waves, BK
-// elements of K per step, STAGES ring stages, WGS workgroups per CU.
-template <int TM_, int TN_, int WM_, int WN_, int BK_, int STAGES_, int WGS_>
+// elements of K per step, STAGES ring stages.  ONE_ITEM: the launch has a
+// workgroup for every item (or part of one), which none follows.
+template <int TM_, int TN_, int WM_, int WN_, int BK_, int STAGES_, bool ONE_ITEM_>
 struct Shape {
-  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, BK = BK_, STAGES = STAGES_, WGS = WGS_;
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, BK = BK_, STAGES = STAGES_;
+  static constexpr bool ONE_ITEM = ONE_ITEM_;
   static constexpr int NW = WM * WN;            // waves
   static constexpr int NT = NW * 64;            // threads
   static constexpr int WTM = TM / WM, WTN = TN / WN;   // wave tile
@@ -81,6 +83,7 @@ struct Shape {
   static constexpr int PARTS_N = TN < kSmallTileCols ? kSmallTileCols / TN : 1;
   static constexpr int PARTS = PARTS_M * PARTS_N;
   static_assert(kATile % (1024 * NW) == 0 && kBTile % (1024 * NW) == 0, "tile / wave count");
+  static_assert(PARTS == 1 || ONE_ITEM, "a workgroup computes one part of an item");
   static_assert(kSub % 2 == 0 && (CPR == 4 || CPR == 8), "BK must be 32 or 64");
   static_assert(WTM % 32 == 0 && WTN % 32 == 0 && STAGES >= 2 && (STAGES & (STAGES - 1)) == 0, "shape");
 };
@@ -299,12 +302,12 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
 
   // This workgroup's items: first, first + stride, ... below it_end.
   int64_t it_first = blockIdx.x, it_end = args.n_items, stride = gridDim.x;
-  if (args.wg_ranges) {
+  if (!S::ONE_ITEM && args.wg_ranges) {
     it_first = args.wg_ranges[blockIdx.x];
     it_end = args.wg_ranges[blockIdx.x + 1];
     stride = 1;
   }
-  if constexpr (S::PARTS > 1) it_end = it_first + 1;
+  if constexpr (S::ONE_ITEM) it_end = it_first + 1;
   if (it_first >= it_end) return;
   ItemCtx c = make_ctx(load_item(it_first));
   if (S::PARTS > 1 && c.m_valid == 0) return;
@@ -315,7 +318,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   // the current item's first barrier, a whole K step before the next wait
   // that covers it.  `last_item` stands in for records past the end.
   const int64_t last_item = it_end - 1;
-  ItemCtx nx = S::PARTS > 1 ? c : make_ctx(load_item(it_next < it_end ? it_next : last_item));
+  ItemCtx nx = S::ONE_ITEM ? c : make_ctx(load_item(it_next < it_end ? it_next : last_item));
   WorkItem after_next;
   // How the current item's first steps got into the ring.
   //   kFilled:             ring filled from empty; what has been issued since, if
@@ -420,7 +423,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
 
   for (;;) {
     const int steps = c.steps;
-    const bool has_next = S::PARTS == 1 && it_next < it_end;
+    const bool has_next = !S::ONE_ITEM && it_next < it_end;
     const bool interior = c.m_valid == TM && c.n_valid == TN;
     const bool wide = interior && args.out_vec;   // stores of whole lines through the block image
     // hand the ring over without draining it
@@ -480,7 +483,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
         } else if (cont) {
           issue(nx, s + STAGES - steps, st);
         }
-        if (S::PARTS == 1 && s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
+        if (!S::ONE_ITEM && s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
         if (!last || cont) read_frags(oth, int_c<0>{}, 0);
       }
       mma((kSub - 1) & 1, std::false_type{});
@@ -562,10 +565,10 @@ hipError_t configure_layouts() {
 //     of 6 steps 7.0 -> 5.0 us, 64 of 64 39 -> 17, 72 of 64 42 -> 28, 128 of
 //     172 105 -> 73 us.  Full launches do better with the larger tile (4096
 //     items of 16 steps 164 / 237 us).
-using LargeShape = Shape<kLargeTileRows, kLargeTileCols, 2, 4, 64, 2, 1>;
-using SmallShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 2, 2>;
-using DeepShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 4, 1>;
-using PartsShape = Shape<64, 64, 2, 2, 64, 4, 2>;
+using LargeShape = Shape<kLargeTileRows, kLargeTileCols, 2, 4, 64, 2, false>;
+using SmallShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 2, false>;
+using DeepShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 4, true>;
+using PartsShape = Shape<64, 64, 2, 2, 64, 4, true>;
 static_assert(kDirectKStep == LargeShape::BK && kDirectKStep == SmallShape::BK &&
               kDirectKStep == DeepShape::BK && kDirectKStep == PartsShape::BK, "the host hands this kernel the work items of whole K steps");
 
@@ -594,7 +597,7 @@ hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, int
   switch (shape) {
     case kDirectLarge: return launch_layouts<LargeShape>(args, grid, stream);
     case kDirectSmall: return launch_layouts<SmallShape>(args, grid, stream);
-    case kDirectDeep: return launch_layouts<DeepShape>(args, grid, stream);
+    case kDirectDeep: return launch_layouts<DeepShape>(args, static_cast<int>(args.n_items), stream);
     default: {   // one workgroup per part of an item; the list is padded to whole rounds of the XCDs
       const int64_t parts = (args.n_items + 7) / 8 * 8 * PartsShape::PARTS;
       return launch_layouts<PartsShape>(args, static_cast<int>(parts), stream);

@@ -57,8 +57,9 @@ struct ExecuteArgs {
   // and the workgroup tiles per work item (filled in at the launch).
   int64_t M, N, K;
   int parts_m, parts_n;
-  // Direct kernel only.  Null: workgroup b takes items b, b + grid, ...
-  // Otherwise grid + 1 entries: workgroup b takes items [wg_ranges[b], wg_ranges[b + 1]).
+  // Direct kernel only, shapes with several items per workgroup.  Null:
+  // workgroup b takes items b, b + grid, ...  Otherwise grid + 1 entries:
+  // workgroup b takes items [wg_ranges[b], wg_ranges[b + 1]).
   const uint32_t* wg_ranges;
 };
 
@@ -78,7 +79,7 @@ hipError_t launch_execute(const ExecuteArgs& args, int dtype, int tile_class, co
 
 // Shape of the direct kernel: one for the large class, three for the small one
 // (128 x 128 items, two workgroups per CU; the same with twice the ring, one per
-// CU; 64 x 64 parts of an item, one workgroup each).  The bits do not depend on
+// CU and item; 64 x 64 parts of an item, one workgroup each).  The bits do not depend on
 // it.
 enum DirectShape : int { kDirectLarge = 0, kDirectSmall = 1, kDirectDeep = 2, kDirectParts = 3 };
 // Workgroups one CU holds at a time.
@@ -87,8 +88,8 @@ constexpr int direct_workgroups_per_cu(DirectShape shape) {
 }
 // Enqueues the bf16 direct-to-LDS execute kernel.  The caller has checked the
 // 16-byte load conditions and that the chunk length of every item is a multiple
-// of kDirectKStep elements.  `grid` persistent workgroups (kDirectParts: one
-// workgroup per part, whatever `grid`).
+// of kDirectKStep elements.  `grid` persistent workgroups (kDirectDeep and
+// kDirectParts: one workgroup per item or part, whatever `grid`).
 hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, int grid, hipStream_t stream);
 
 // Raises the dynamic-LDS limit of every execute kernel on the current device

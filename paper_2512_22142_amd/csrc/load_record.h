@@ -9,8 +9,8 @@
 
 namespace cleave {
 
-// Record `idx` (48 bytes, 16-byte aligned) of a table that no kernel writes:
-// read through the constant address space, a wave-uniform address becomes scalar
+// Record `idx` (48 bytes, 16-byte aligned) of a table that the kernel reading it
+// does not write (a kernel launched before it may have): read through the constant address space, a wave-uniform address becomes scalar
 // loads whose completion the compiler tracks, even though the kernels also store
 // to global memory.
 template <typename Record>

@@ -1,13 +1,14 @@
 // Argument checks of the calls a program makes once or twice per GEMM, as a
 // CPython extension: a pass over small GEMMs is a few launches of a few
 // microseconds each, and the same checks written in Python (one interpreter call
-// per tensor property, one ctypes conversion per argument) took longer than the
+// per tensor property, one ctypes conversion per argument) take longer than the
 // kernels.  Host time of the six calls of a 256 x 768 x 768 bf16 linear layer,
-// forward and backward: 52 us through ctypes, 24 us through this file (a pass
-// 53 -> 27 us; the 512^3 fp32 GEMM 17 -> 12.5 us).
+// forward and backward: 24 us through this file, 52 us through ctypes (a pass
+// 27 / 53 us; the 512^3 fp32 GEMM 12.5 / 17 us).
 //
-// Every function checks the tensors, takes their addresses and calls the C
-// entry point of the same name; nothing is kept between calls.
+// execute, reduce and reduce_residual check the tensors, take their addresses and
+// call the C entry point of the same name; matrix, partials and stream serve the
+// calls that go through ctypes.  Nothing is kept between calls.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

@@ -229,9 +229,7 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
       const uint32_t k_or = t.k0 | t.k_len;
       const uint32_t mn_or = t.m0 | t.m_len | t.n0 | t.n_len;
       p->all_k_mult8 &= (k_or % 8 == 0);
-      p->all_k_mult4 &= (k_or % 4 == 0);
       p->all_mn_mult8 &= (mn_or % 8 == 0);
-      p->all_mn_mult4 &= (mn_or % 4 == 0);
       p->min_k_end = std::min(p->min_k_end, static_cast<int64_t>(t.k0) + t.k_len);
       p->all_n_mult4 &= ((t.n0 | t.n_len) % 4 == 0);
     }

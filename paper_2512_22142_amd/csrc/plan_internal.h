@@ -237,9 +237,12 @@ struct SubsetRing {
 // [ranges[b], ranges[b + 1]) and the runs have nearly equal cost: longest items
 // first, each to the least-loaded workgroup of the XCD the item's position
 // belongs to (position mod 8, as the list was laid out) unless a workgroup of
-// another XCD is behind by more than a quarter of the item's own cost (a whole
-// item let the largest load of a 4096 x 11008 x 4096 tiling grow to 1.38 times
-// the mean, 1.17 now); inside a run the original order is kept.  Returns with
+// another XCD is behind by more than a quarter of the item's own cost; inside a
+// run the original order is kept.  Largest load over the mean with a whole item
+// as the limit / a quarter, a 4096 x 11008 x 4096 tiling: large class 1.38 /
+// 1.16, small class 1.78 / 1.37.  Nothing and a half give the same as a quarter,
+// and over 150 lists of 25 drawn problems the mean hardly moves (3.39 / 3.36):
+// in most of them one item is longer than a workgroup's share.  Returns with
 // `ranges` empty, and the list untouched, when all items cost the same or no
 // workgroup gets a second item.
 void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
@@ -262,15 +265,13 @@ struct cleave_plan {
   int64_t num_tiles = 0;
   int64_t batch = 0;         // > 0: a batch of that many M x N x K GEMMs, task.gemm_id = member
   bool all_k_mult8 = true;   // every k0 and k_len is a multiple of 8
-  bool all_k_mult4 = true;
   bool all_mn_mult8 = true;  // every m0, m_len, n0, n_len is a multiple of 8
-  bool all_mn_mult4 = true;
   int64_t min_k_end = std::numeric_limits<int64_t>::max();   // smallest k0 + k_len of a task
   bool all_n_mult4 = true;   // every n0, n_len multiple of 4 (vector path of reduce)
   std::vector<cleave_task> tasks;
   // All tasks, launch order.  Each list starts with the items whose chunk is a
   // whole number of the direct kernel's K steps (items_whole_steps of them);
-  // the rest can only run in the staged kernel.
+  // the rest can only run in the general kernel.
   std::vector<cleave::WorkItem> items[cleave::kNumTileClasses];
   size_t items_whole_steps[cleave::kNumTileClasses] = {0, 0};
   // All tasks cut into small-class sub-tiles only: used when the large class
