@@ -87,8 +87,26 @@ int upload_vector(const std::vector<T>& v, T** dst) {
 }
 
 // The aggregation's table, from the tasks already on the device and the tile list
-// (which goes behind the records).
+// (which goes behind the records).  The kernel that writes it is on the null
+// stream, and the caller waits for it behind its other uploads, which overlap
+// it (a wait right here added 20-30 us to a small plan's upload).  A short table is
+// written by the host and copied: the wait alone costs 8 us.
+constexpr int64_t kHostRecords = 1024;
 int make_reduce_table(cleave_plan* p) {
+  if (p->reduce_runs <= kHostRecords) {
+    try {
+      std::vector<cleave::ReduceItem> records;
+      records.reserve(static_cast<size_t>(p->reduce_runs));
+      for (const cleave::ReduceTile& tile : p->reduce_tiles) {
+        const cleave_task& t = p->tasks[tile.task];
+        const uint64_t block = static_cast<uint64_t>(t.m_len) * t.n_len;
+        for (uint64_t e = 0; e < block; e += tile.run) records.push_back(cleave::make_reduce_item(t, e, tile.run));
+      }
+      return upload_vector(records, &p->d_reduce_items);
+    } catch (const std::bad_alloc&) {
+      return CLEAVE_ENOMEM;
+    }
+  }
   const int64_t n_tiles = static_cast<int64_t>(p->reduce_tiles.size());
   const size_t records = static_cast<size_t>(p->reduce_runs) * sizeof(cleave::ReduceItem);
   const size_t listed = p->reduce_tiles.size() * sizeof(cleave::ReduceTile);
@@ -100,7 +118,6 @@ int make_reduce_table(cleave_plan* p) {
   cleave::ReduceTile* tiles = reinterpret_cast<cleave::ReduceTile*>(table + records);
   CLEAVE_HIP(hipMemcpy(tiles, p->reduce_tiles.data(), listed, hipMemcpyHostToDevice));
   CLEAVE_HIP(cleave::launch_expand_reduce(p->d_tasks, tiles, n_tiles, p->d_reduce_items, nullptr));
-  CLEAVE_HIP(hipStreamSynchronize(nullptr));   // streams that do not wait for the null stream read it next
   return CLEAVE_OK;
 }
 
@@ -170,6 +187,7 @@ int ensure_uploaded(cleave_plan* p) {
   int rc = ensure_device_ready(dev, nullptr);
   if (rc != CLEAVE_OK) return rc;
   rc = upload_vector(p->tasks, &p->d_tasks);
+  if (rc == CLEAVE_OK) rc = make_reduce_table(p);
   // The three work-item lists; items of unequal length get a balanced workgroup
   // schedule for this device's grid (a copy is reordered: the host lists keep
   // their canonical order for the next device).
@@ -197,8 +215,11 @@ int ensure_uploaded(cleave_plan* p) {
       p->wg_ranges_grid[list] = grid;
     }
   }
-  if (rc == CLEAVE_OK) rc = make_reduce_table(p);
   if (rc == CLEAVE_OK) rc = allocate_subset_ring(p);
+  if (rc == CLEAVE_OK && p->reduce_runs > kHostRecords) {
+    const hipError_t e = hipStreamSynchronize(nullptr);   // streams that do not wait for the null stream read the tables next
+    if (e != hipSuccess) rc = hip_fail(e);
+  }
   if (rc != CLEAVE_OK) {
     free_device_tables(p);
     return rc;

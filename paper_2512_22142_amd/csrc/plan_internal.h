@@ -126,11 +126,11 @@ __host__ __device__ inline ReduceItem make_reduce_item(const cleave_task& t, uin
   return item;
 }
 // An output tile as the host lists it: the runs' records, one per run, are
-// written on the device when the plan is uploaded.  Written on the host they
-// made a plan up to 1.6 times as long to create and twice as long to upload:
-// creation in us, one 16-byte record per 4096 elements / 48-byte records of all
-// runs on the host / this list, 2048 x 3072 x 768 in 256 x 256 tiles, S = 2
-// 59 / 76 / 57, 4096 x 11008 x 4096 in 512 x 512, S = 4 1920 / 2720 / 1920.
+// written when the plan is uploaded, on the device unless the table is short.
+// Making them with the plan took longer; creation + upload in us, one 16-byte
+// record per 4096 elements / 48-byte records of all runs made with the plan /
+// this list, 2048 x 3072 x 768 in 256 x 256 tiles, S = 2 109 / 169 / 105,
+// 4096 x 11008 x 4096 in 512 x 512, S = 4 443 / 658 / 475.
 struct ReduceTile {
   uint32_t task;    // the tile's chunk-0 task
   uint32_t run;     // elements per run
@@ -292,7 +292,7 @@ struct cleave_plan {
   // the grid sizes of the device the tables were uploaded to; null = equal items.
   uint32_t* d_wg_ranges[cleave::kNumTileClasses + 1] = {nullptr, nullptr, nullptr};
   int wg_ranges_grid[cleave::kNumTileClasses + 1] = {0, 0, 0};
-  cleave::ReduceItem* d_reduce_items = nullptr;   // reduce_runs records, then the tiles they were made from
+  cleave::ReduceItem* d_reduce_items = nullptr;   // reduce_runs records (and behind them what they were made from)
   // Work-item slices of subset launches (device memory sized once, at upload).
   cleave::SubsetRing subset;
   // Repeat check of a subset's task ids without clearing or allocating: task i
