@@ -153,6 +153,12 @@ void order_work_items(cleave_plan* p) {
 // 28.0 / 26.2 / 24.9; S = 5, 4096 x 4096 80 / - / 74; S = 8, 4096 x 4096
 // 107 / 103 / 113, 8192 x 8192 417 / 419 / 443; S = 1 (a copy), 4096 x 4096
 // 23.2 / 23.7 / 26.2 and 24.6 in runs of 16384, 1024 x 1024 3.3 against 7.2.
+// Splits without a path of their own, runs of 2048 / 1024: S = 3, 1024 x 1024
+// 5.0 / 4.8, 768 x 3072 7.6 / 8.4, 8192 x 8192 195 / 187; S = 6, 7.1 / 6.5,
+// 13.5 / 15.6, 364 / 346; S = 7, 7.8 / 7.1, 16.1 / 18.0, 417 / 400; S = 9, 9.0 /
+// 8.2, 19.9 / 22.0, 522 / 503; S = 16, 24.7 / 17.6, 40.6 / 38.5, 891 / 841: from
+// nine splits on the run of eight is kept, although 1024 is the better one at
+// most sizes.
 uint32_t reduce_run(uint32_t S) {
   if (S == 1) return 4096;
   return S == 2 || S >= 8 ? 2048 : 1024;
