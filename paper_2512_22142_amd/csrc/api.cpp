@@ -294,14 +294,16 @@ int release_subset_slice(cleave::SubsetRing& r, int64_t begin, int64_t total, hi
 }
 
 const char* kernel_name(int dtype, const cleave::GeneralLoads& how, int transA, int transB) {
-  static const char* names[2][3][4] = {
+  static const char* names[2][4][4] = {
       {{"execute_f32_128x128_nn", "execute_f32_128x128_nt", "execute_f32_128x128_tn", "execute_f32_128x128_tt"},
        {"execute_f32_64x64_nn", "execute_f32_64x64_nt", "execute_f32_64x64_tn", "execute_f32_64x64_tt"},
+       {"none", "none", "none", "none"},
        {"execute_f32_element", "execute_f32_element", "execute_f32_element", "execute_f32_element"}},
       {{"execute_bf16_128x128_nn", "execute_bf16_128x128_nt", "execute_bf16_128x128_tn", "execute_bf16_128x128_tt"},
        {"execute_bf16_64x64_nn", "execute_bf16_64x64_nt", "execute_bf16_64x64_tn", "execute_bf16_64x64_tt"},
+       {"none", "execute_bf16_256x256_nt", "none", "none"},
        {"execute_bf16_element", "execute_bf16_element", "execute_bf16_element", "execute_bf16_element"}}};
-  const int row = how.a_elements || how.b_elements ? 2 : how.tile;
+  const int row = how.a_elements || how.b_elements ? 3 : how.tile;
   return names[dtype == CLEAVE_BF16 ? 1 : 0][row][(transA ? 2 : 0) + (transB ? 1 : 0)];
 }
 
@@ -394,7 +396,7 @@ struct AssembleTarget {
 struct SubsetLayout {
   bool fine = false;                                  // every block cut into small-class sub-tiles
   int64_t counts[cleave::kNumTileClasses][2] = {};    // work items per (class, part)
-  int64_t direct_steps[cleave::kNumTileClasses] = {};   // K steps of the items of part 0, together
+  int64_t steps[cleave::kNumTileClasses][2] = {};     // their whole K steps, together
   int64_t total() const { return counts[0][0] + counts[0][1] + counts[1][0] + counts[1][1]; }
 };
 inline int subset_part(const cleave_task& t) { return t.k_len % cleave::kDirectKStep == 0 ? 0 : 1; }
@@ -425,7 +427,7 @@ int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int
     const cleave_task& t = plan->tasks[task_ids[i]];
     const cleave::SubTiling st = cleave::sub_tiling(t, out->fine);
     out->counts[st.cls][subset_part(t)] += st.count();
-    if (subset_part(t) == 0) out->direct_steps[st.cls] += int64_t{st.count()} * (t.k_len / cleave::kDirectKStep);
+    out->steps[st.cls][subset_part(t)] += int64_t{st.count()} * (t.k_len / cleave::kDirectKStep);
   }
   return CLEAVE_OK;
 }
@@ -469,7 +471,16 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // the wide tile leaves half of the CUs without a workgroup (1000^3, 128 items
 // 13.8 / 11.3; 2001x768x3072, 192 items 27.4 / 29.7; 3001x2999x1001, 1152
 // items 44 / 55).
-cleave::ExecuteTile general_tile(int dtype, int64_t items, int cus) {
+// `whole`: that many 256 x 256 items, with `steps` whole K steps between them,
+// that the kernel could take as they are (bf16, both operands K-contiguous: six
+// fragment reads for eight products instead of eight).  They win when their
+// rounds are nearly full and their chains long enough to cover a start and end
+// alone on a CU (us, 128 / 256: 17 steps, 256 items 57 / 50, 1024 items 230 / 193, 688 items 144 / 132,
+// 576 items, the third round a quarter full, 116 / 127; 5 steps, 1024 items
+// 92.7 / 92.6, 688 items 59 / 66).
+cleave::ExecuteTile general_tile(int dtype, int64_t items, int64_t whole, int64_t steps, int cus) {
+  const int64_t places = (whole + cus - 1) / cus * cus;
+  if (whole > 0 && whole * 8 >= places * 7 && steps >= 16 * whole) return cleave::kTileHuge;
   const int64_t narrow_up_to = dtype == CLEAVE_BF16 ? cus / 2 : int64_t{4} * cus - 1;
   return items <= narrow_up_to ? cleave::kTileNarrow : cleave::kTileWide;
 }
@@ -549,6 +560,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   int64_t whole_steps[cleave::kNumTileClasses] = {static_cast<int64_t>(plan->items_whole_steps[0]),
                                                   static_cast<int64_t>(plan->items_whole_steps[1])};
   int64_t direct_steps[cleave::kNumTileClasses] = {plan->items_direct_steps[0], plan->items_direct_steps[1]};   // of those
+  int64_t other_steps[cleave::kNumTileClasses] = {plan->items_other_steps[0], plan->items_other_steps[1]};      // of the others
   // which of the plan's lists a class runs from (-1: a subset's own list)
   int list_of[cleave::kNumTileClasses] = {task_ids ? -1 : 0, task_ids ? -1 : 1};
   if (!task_ids && (!direct || prefers_fine(plan->items[cleave::kTileLarge].size()))) {
@@ -560,6 +572,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     counts[cleave::kTileSmall] = static_cast<int64_t>(plan->items_fine.size());
     whole_steps[cleave::kTileSmall] = static_cast<int64_t>(plan->items_fine_whole_steps);
     direct_steps[cleave::kTileSmall] = plan->items_direct_steps[cleave::kNumTileClasses];
+    other_steps[cleave::kTileSmall] = plan->items_other_steps[cleave::kNumTileClasses];
   }
   // Subset launches: the work-item lists are written on the device, from the
   // task records, into a slice of memory the plan set aside when its tables
@@ -593,7 +606,8 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     for (int c = 0; c < cleave::kNumTileClasses; ++c) {
       d_lists[c] = slice + pos;
       whole_steps[c] = layout.counts[c][0];
-      direct_steps[c] = layout.direct_steps[c];
+      direct_steps[c] = layout.steps[c][0];
+      other_steps[c] = layout.steps[c][1];
       counts[c] = layout.counts[c][0] + layout.counts[c][1];
       pos += counts[c];
     }
@@ -658,7 +672,12 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     if (n_general > 0) {
       args.items = d_lists[c] + n_direct;
       args.n_items = n_general;
-      how.tile = general_tile(dtype, n_general * (c == cleave::kTileLarge ? 4 : 1), cus);
+      const bool large = c == cleave::kTileLarge;
+      // in-tile byte offsets (256 rows) stay within 32 bits
+      const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
+                        ldb * eb < (int64_t{1} << 24);
+      how.tile = general_tile(dtype, n_general * (large ? 4 : 1), large && dtype == CLEAVE_BF16 && by_k ? n_general : 0,
+                              direct ? other_steps[c] : direct_steps[c] + other_steps[c], cus);
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);
     }

@@ -503,8 +503,9 @@ hipError_t configure_elements() {
 // Grid of a launch over work items of one class, and the workgroup tiles per item.
 template <typename S>
 int cut_items(ExecuteArgs* args, int tile_class) {
-  static_assert(kSmallTileRows % S::TM == 0 && kLargeTileRows % S::TM == 0 && kSmallTileCols % S::TN == 0 &&
-                kLargeTileCols % S::TN == 0, "a work item is cut into whole workgroup tiles");
+  static_assert((kSmallTileRows % S::TM == 0 || S::TM == kLargeTileRows) && kLargeTileRows % S::TM == 0 &&
+                (kSmallTileCols % S::TN == 0 || S::TN == kLargeTileCols) && kLargeTileCols % S::TN == 0,
+                "a work item is cut into whole workgroup tiles");
   args->parts_m = tile_rows(tile_class) / S::TM;
   args->parts_n = tile_cols(tile_class) / S::TN;
   const int64_t blocks = (args->n_items + 7) / 8 * 8 * args->parts_m * args->parts_n;
@@ -537,6 +538,7 @@ hipError_t launch_elements(ExecuteArgs args, int tile_class, bool a_elements, bo
 
 template <int EB>
 using Wide = Shape<EB, 128, 128, 2, 2, 2, 2>;
+using Large = Shape<2, kLargeTileRows, kLargeTileCols, 2, 4, 1, 2>;
 template <int EB>
 using Narrow = Shape<EB, 64, 64, 2, 2, 2, 4>;
 template <int EB>
@@ -547,6 +549,7 @@ hipError_t configure_type() {
   hipError_t e = configure_layouts<Wide<EB>>();
   if (e == hipSuccess) e = configure_layouts<Narrow<EB>>();
   if (e == hipSuccess) e = configure_elements<ByElement<EB>>();
+  if (EB == 2 && e == hipSuccess) e = configure_one<Large, kByK, kByK>();
   return e;
 }
 
@@ -554,6 +557,11 @@ template <int EB>
 hipError_t launch_type(const ExecuteArgs& args, int tile_class, const GeneralLoads& how, hipStream_t stream) {
   if (how.a_elements || how.b_elements)
     return launch_elements<ByElement<EB>>(args, tile_class, how.a_elements, how.b_elements, stream);
+  if (EB == 2 && how.tile == kTileHuge) {   // large items, both operands K-contiguous
+    ExecuteArgs whole = args;
+    const int grid = cut_items<Large>(&whole, tile_class);
+    return launch_one<Large, kByK, kByK>(whole, grid, stream);
+  }
   return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, stream)
                                  : launch_layouts<Wide<EB>>(args, tile_class, stream);
 }

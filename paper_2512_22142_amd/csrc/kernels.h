@@ -63,8 +63,9 @@ struct ExecuteArgs {
   const uint32_t* wg_ranges;
 };
 
-// Workgroup tile of the general execute kernel: 128 x 128 or 64 x 64.
-enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1 };
+// Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, or 256 x 256
+// (only for bf16 work items of the large class with both operands K-contiguous).
+enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2 };
 // An operand with rows shorter than 16 bytes is loaded one element at a time
 // (64 x 64 tile, whatever `tile`); the other one still takes 16-byte loads.
 struct GeneralLoads {

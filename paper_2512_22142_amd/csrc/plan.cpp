@@ -72,10 +72,9 @@ void order_work_items(cleave_plan* p) {
     std::vector<WorkItem> source;
     for (const WorkItem& w : whole_list)
       if ((w.k_len % kDirectKStep == 0) == (part == 0)) source.push_back(w);
-    if (part == 0) {
-      whole_steps = source.size();
-      for (const WorkItem& w : source) p->items_direct_steps[list] += w.k_len / kDirectKStep;
-    }
+    if (part == 0) whole_steps = source.size();
+    int64_t& steps = part == 0 ? p->items_direct_steps[list] : p->items_other_steps[list];
+    for (const WorkItem& w : source) steps += w.k_len / kDirectKStep;
     if (source.empty()) continue;
     const uint32_t tr = static_cast<uint32_t>(tile_rows(cls));
     const uint32_t tc = static_cast<uint32_t>(tile_cols(cls));

@@ -280,6 +280,7 @@ struct cleave_plan {
   size_t items_fine_whole_steps = 0;
   // K steps of the whole-step items of the three lists (large, small, fine), together.
   int64_t items_direct_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};
+  int64_t items_other_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};   // whole ones of the other items
   std::vector<cleave::ReduceTile> reduce_tiles;
   int64_t reduce_runs = 0;
 

@@ -106,6 +106,29 @@ def test_one_operand_by_elements_the_other_in_wide_loads_exact(dtype, transA, tr
     check(70, 9, 9, (64, 64), 1, transA, transB, dtype, pad=(1, far), kernel="element")
 
 
+@pytest.mark.parametrize("M,N,tile,K", [
+    (4096, 4096, (512, 256), 16 * 64 + 8),      # 256 full 256 x 256 items
+    (2120, 2176, (136, 136), 17 * 64 - 8)])     # 256 clipped ones
+def test_large_items_of_two_k_contiguous_operands_exact(M, N, tile, K):
+    check(M, N, K, tile, 1, 0, 1, "bf16", kernel="execute_bf16_256x256_nt")
+
+
+def test_large_items_of_a_subset_with_unaligned_rows():
+    M, N, K = 2120, 2176, 17 * 64 - 8
+    a = make_matrix(31, M, K, "bf16")
+    b = make_matrix(32, K, N, "bf16")
+    plan = cleave.plan_uniform(M, N, K, 136, 136, 1)
+    dA, dB = tight(a, 1), tight(stored(b, 1), 3)
+    parts = [torch.full((plan.partial_elems,), float("nan"), device="cuda") for _ in range(2)]
+    cleave.execute(plan, dA, dB, parts[0], 0, 1)
+    assert "128x128" in plan.last_kernel
+    cleave.execute(plan, dA, dB, parts[1], 0, 1, task_ids=list(range(plan.num_tasks)))
+    assert "256x256" in plan.last_kernel
+    torch.cuda.synchronize()
+    assert torch.equal(parts[0].view(torch.int32), parts[1].view(torch.int32))
+    assert not bool(torch.isnan(parts[0]).any())
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_general_and_fast_kernel_agree_bit_for_bit(dtype):
     """Real-valued inputs, one call with aligned operands and one with the same
