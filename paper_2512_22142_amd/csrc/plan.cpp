@@ -56,6 +56,14 @@ void order_work_items(cleave_plan* p) {
   }
   // three lists: the two classes of the mixed cut, then the all-small cut
   std::vector<WorkItem> all[kNumTileClasses], fine[kNumTileClasses];
+  size_t n_all[kNumTileClasses] = {}, n_fine = 0;
+  for (const cleave_task& t : p->tasks) {
+    const SubTiling mixed = sub_tiling(t, false);
+    n_all[mixed.cls] += mixed.count();
+    n_fine += sub_tiling(t, true).count();
+  }
+  for (int cls = 0; cls < kNumTileClasses; ++cls) all[cls].reserve(n_all[cls]);
+  fine[kTileSmall].reserve(n_fine);
   for (uint32_t i = 0; i < p->tasks.size(); ++i) {
     append_work_items(p->tasks[i], i, all);
     append_work_items(p->tasks[i], i, fine, true);
@@ -70,6 +78,7 @@ void order_work_items(cleave_plan* p) {
     // can take (chunk = whole K steps), then the others.
     for (int part = 0; part < 2; ++part) {
     std::vector<WorkItem> source;
+    source.reserve(whole_list.size());
     for (const WorkItem& w : whole_list)
       if ((w.k_len % kDirectKStep == 0) == (part == 0)) source.push_back(w);
     if (part == 0) whole_steps = source.size();
@@ -83,6 +92,7 @@ void order_work_items(cleave_plan* p) {
       WorkItem item;
     };
     std::vector<Key> lists[kXcds];
+    for (auto& l : lists) l.reserve(source.size() / kXcds + 1);
     // Batch members share no output.  Small members (fewer items than the
     // chip has CUs) stay on one XCD each, member g on XCD g mod 8, one after
     // the other.  Large members (the GEMMs of one DAG level) are spread over
@@ -267,14 +277,18 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
 
 }  // namespace
 
+bool needs_balance(const std::vector<WorkItem>& items, size_t n_direct, int grid) {
+  if (grid < 2 || n_direct <= static_cast<size_t>(grid)) return false;   // one item per workgroup at most
+  for (size_t i = 1; i < n_direct; ++i)
+    if (items[i].k_len != items[0].k_len) return true;
+  return false;
+}
+
 void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
                         std::vector<uint32_t>* ranges) {
   ranges->clear();
-  if (grid < 2 || n_direct <= static_cast<size_t>(grid)) return;   // one item per workgroup at most
+  if (!needs_balance(items, n_direct, grid)) return;
   const auto cost = [&](size_t i) { return work_item_cost(items[i]); };
-  bool equal = true;
-  for (size_t i = 1; i < n_direct && equal; ++i) equal = items[i].k_len == items[0].k_len;
-  if (equal) return;
 
   std::vector<uint32_t> by_cost(n_direct);
   for (size_t i = 0; i < n_direct; ++i) by_cost[i] = static_cast<uint32_t>(i);

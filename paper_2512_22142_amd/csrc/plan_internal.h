@@ -129,8 +129,8 @@ __host__ __device__ inline ReduceItem make_reduce_item(const cleave_task& t, uin
 // written when the plan is uploaded, on the device unless the table is short.
 // Making them with the plan took longer; creation + upload in us, one 16-byte
 // record per 4096 elements / 48-byte records of all runs made with the plan /
-// this list, 2048 x 3072 x 768 in 256 x 256 tiles, S = 2 109 / 169 / 105,
-// 4096 x 11008 x 4096 in 512 x 512, S = 4 443 / 658 / 475.
+// this list, 2048 x 3072 x 768 in 256 x 256 tiles, S = 2 107 / 164 / 154,
+// 4096 x 11008 x 4096 in 512 x 512, S = 4 440 / 661 / 450.
 struct ReduceTile {
   uint32_t task;    // the tile's chunk-0 task
   uint32_t run;     // elements per run
@@ -245,6 +245,7 @@ struct SubsetRing {
 // in most of them one item is longer than a workgroup's share.  Returns with
 // `ranges` empty, and the list untouched, when all items cost the same or no
 // workgroup gets a second item.
+bool needs_balance(const std::vector<WorkItem>& items, size_t n_direct, int grid);
 void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
                         std::vector<uint32_t>* ranges);
 // Cost of a work item in the schedule's unit (one K step of the fast kernel):

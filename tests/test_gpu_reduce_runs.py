@@ -49,8 +49,9 @@ def test_runs_of_a_batched_plan():
 
 
 @pytest.mark.parametrize("M,N,tm,tn,S", [
-    (600, 1000, 600, 1000, 4),     # one tile, 586 runs: more than the threads that write their records
-    (301, 1003, 301, 1003, 2), (700, 644, 512, 512, 8),
+    (600, 1000, 600, 1000, 4), (301, 1003, 301, 1003, 2), (700, 644, 512, 512, 8),   # records written by the host
+    (3001, 3000, 3001, 3000, 4),   # on the device: one tile, 8793 runs, more than a workgroup's threads
+    (3100, 3000, 1000, 900, 4),
     (280, 260, 1, 1, 1)])          # 72800 tiles: more than the workgroups
 def test_records_of_large_and_of_many_tiles(M, N, tm, tn, S):
     K = 64
