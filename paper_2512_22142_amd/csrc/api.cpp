@@ -666,11 +666,6 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     args.K = plan->K;
     args.ldc = asm_to.ldc;
     args.c_bf16 = asm_to.out_dtype == CLEAVE_BF16 ? 1 : 0;
-    // block origins and row lengths are multiples of 8 elements whenever `direct` holds
-    args.out_vec = !direct ? 0
-                   : !asm_to.C ? aligned(partials, 16)
-                               : (asm_to.ldc % 4 == 0 && aligned(asm_to.C, args.c_bf16 ? 8 : 16) &&
-                                  offsets_multiple_of(bl.c, bl.shape, 4));
     // Of a launch the direct kernel can take, it gets the items made of whole K
     // steps, and the general one the others (if any).  Which kernel computes a
     // block depends only on the block's own task record.

@@ -6,41 +6,45 @@
 // stores an fp32 partial block); used when every chunk length is a multiple of
 // the K step and all tile edges / leading dimensions are multiples of 8.
 //
-// The kernel is a template over its shape (workgroup tile, wave grid, K step,
-// ring depth); a wave always owns 32 x 32 MFMA 32x32x16 blocks with fp32
-// accumulators in registers.  The four instantiations are at the end of the
-// file.
+// The kernel is a template over its shape (workgroup tile, wave grid, ring
+// depth); a wave owns a grid of 16 x 16 blocks, computed by MFMA 16x16x32 with
+// fp32 accumulators in registers.  The four instantiations are at the end of the
+// file.  What bounds full launches is the board's power, and this instruction
+// does the same arithmetic for less of it than the 32 x 32 one (half of the
+// accumulator traffic per product): products from registers, random operands,
+// 2.08 against 1.85 PFLOP/s, the same bits.  Together with fewer instructions per
+// K step: 4096 x 4096 x 4096 in 512 x 512 tiles, 4 splits 139 -> 131 us, 4096 x
+// 4096 x 11008 320 -> 292 us, 16384 x 5120 x 13824 in 8 splits 2.06 -> 1.95 ms.
 //
 // A wave-wide direct load writes 64 consecutive 16-byte LDS slots (lane l ->
 // slot l), so the LDS layout is chosen through which global 16 bytes a lane
 // fetches:
-//   * K-contiguous operand (tile row r, CPR chunks of 8 k per step):
-//       slot = r*CPR + (chunk ^ swizzle(r)),  swizzle = (r>>1)&7 for CPR = 8,
-//       (r>>2)&3 for CPR = 4;
-//     16 consecutive rows at one chunk then cover 16 distinct bank groups, so
-//     the 16-byte fragment reads are conflict free.
+//   * K-contiguous operand (tile row r, CPR = 8 chunks of 8 k per step):
+//       slot = r*CPR + (chunk ^ ((r>>1)&7));
+//     16 consecutive rows at one chunk then cover 16 distinct bank groups (and
+//     so do half of them at one chunk and half at its neighbour), so the
+//     16-byte fragment reads are conflict free.
 //   * operand stored with the tile-row index contiguous (read "transposed"):
-//     the tile is kept as BK k rows of R/8 chunks,
-//       slot = k*(R/8) + (chunk ^ (4*(k & 3))),  for R = 64 ^ (4*((k >> 1) & 1));
+//     the tile is kept as 64 k rows of R/8 chunks,
+//       slot = k*(R/8) + (chunk ^ swizzle(k)),
+//       swizzle = 4*(k & 3) ^ 2*((k >> 3) & 1),  for R = 64 4*((k >> 1) & 1) ^ 2*((k >> 3) & 1);
 //     fragments are gathered with the LDS transpose read (ds_read_b64_tr_b16:
 //     within 16 lanes, lane i supplies the address of 4 consecutive elements of
 //     k row i/4 and receives column i of the 4 x 16 block), two reads per
-//     fragment; the XOR spreads the four k rows of a read over the banks.
+//     fragment; the XOR spreads over the banks the eight k rows that 32 lanes
+//     read.
 //
-// Stores: a full sub-tile leaves through a 4 KB row-major image per wave in
-// LDS behind the ring, so that every store instruction writes whole 128-byte
-// lines (a quarter of the store instructions of the accumulator layout, none
-// of them held up by the limit of 63 outstanding operations); outputs that
-// are only element-aligned and clipped sub-tiles take 4-byte stores.
+// Stores: through a row-major image per wave in LDS behind the ring (store_rows).
 //
 // Order of accumulation per output element: ascending K steps, inside a step
-// ascending 16-element sub-steps, one MFMA each -- a function of the task
-// record only (and the same for every shape), hence bitwise reproducible on
-// re-issue.
+// ascending k -- a function of the task record only (and the same for every
+// shape, and for the general kernel's 32x32x16 instruction), hence bitwise
+// reproducible on re-issue.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 #include <type_traits>
+#include <utility>
 
 #include "kernels.h"
 #include "tile_store.h"
@@ -50,7 +54,7 @@ namespace cleave {
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -68,9 +72,9 @@ struct Shape {
   static constexpr int NW = WM * WN;            // waves
   static constexpr int NT = NW * 64;            // threads
   static constexpr int WTM = TM / WM, WTN = TN / WN;   // wave tile
-  static constexpr int MB = WTM / 32, NB = WTN / 32;   // 32 x 32 MFMA blocks per wave tile
+  static constexpr int MB = WTM / 16, NB = WTN / 16;   // 16 x 16 MFMA blocks per wave tile
   static constexpr int CPR = BK / 8;            // 16-byte chunks per K-contiguous row and step
-  static constexpr int kSub = BK / 16;          // MFMA sub-steps per step
+  static constexpr int kSub = BK / 32;          // MFMA sub-steps per step
   static constexpr int kATile = TM * BK * 2;    // bytes
   static constexpr int kBTile = TN * BK * 2;
   static constexpr int kStage = kATile + kBTile;
@@ -84,7 +88,7 @@ struct Shape {
   static constexpr int PARTS = PARTS_M * PARTS_N;
   static_assert(kATile % (1024 * NW) == 0 && kBTile % (1024 * NW) == 0, "tile / wave count");
   static_assert(PARTS == 1 || ONE_ITEM, "a workgroup computes one part of an item");
-  static_assert(kSub % 2 == 0 && (CPR == 4 || CPR == 8), "BK must be 32 or 64");
+  static_assert(BK == 64, "two sub-steps, full lines");
   static_assert(WTM % 32 == 0 && WTN % 32 == 0 && STAGES >= 2 && (STAGES & (STAGES - 1)) == 0, "shape");
 };
 
@@ -102,16 +106,14 @@ using int_c = std::integral_constant<int, V>;
 
 // XOR applied to the chunk index of a K-contiguous row so that 16 consecutive
 // rows at one logical chunk fall into 16 different 16-byte bank groups.
-template <int CPR>
-__device__ __forceinline__ int row_swizzle(int r) {
-  return CPR == 4 ? ((r >> 2) & 3) : ((r >> 1) & 7);
-}
+__device__ __forceinline__ int row_swizzle(int r) { return (r >> 1) & 7; }
 
 // XOR applied to the chunk index of k row `k` of a tile kept as k rows of CH
-// chunks: spreads over the banks the four k rows of a transpose read.
+// chunks: spreads over the banks the eight k rows that half a wave's transpose
+// read touches (four neighbours, and four of the next eight).
 template <int CH>
 __device__ __forceinline__ int k_swizzle(int k) {
-  return CH == 8 ? 4 * ((k >> 1) & 1) : 4 * (k & 3);
+  return (CH == 8 ? 4 * ((k >> 1) & 1) : 4 * (k & 3)) ^ (2 * ((k >> 3) & 1));
 }
 
 template <typename S, bool KCONTIG, int R>
@@ -124,21 +126,21 @@ struct DirectTile {
                                        int lane) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-      const int slot = (wave + S::NW * i) * 64 + lane;
+      const int slot = (wave * kLoads + i) * 64 + lane;
       if constexpr (KCONTIG) {
         const int r = slot / S::CPR;
-        const int c = (slot % S::CPR) ^ row_swizzle<S::CPR>(r);
-        goff[i] = static_cast<uint32_t>((min(r, r_valid - 1) * row_stride + c * 8) * 2);
+        const int c = (slot % S::CPR) ^ row_swizzle(r);
+        goff[i] = static_cast<uint32_t>((min(r, r_valid - 1) * row_stride + c * 8) * 2) + (kLoads - 1 - i) * 1024;
       } else {
         const int k = slot / CH;
         const int c = (slot % CH) ^ k_swizzle<CH>(k);
-        goff[i] = static_cast<uint32_t>((k * k_stride + min(c * 8, r_valid - 8)) * 2);
+        goff[i] = static_cast<uint32_t>((k * k_stride + min(c * 8, r_valid - 8)) * 2) + (kLoads - 1 - i) * 1024;
       }
     }
   }
 
   // gbase: the tile's first row at this step's first k (wave-uniform);
-  // lds_tile: LDS byte address of the tile.  The load is issued through inline
+  // lds_tile: LDS byte address of the tile.  The loads are issued through inline
   // asm (scalar base + per-lane 32-bit offset, LDS base in M0) for two
   // reasons: no VALU address arithmetic in the K loop, and the compiler does
   // not see an LDS-writing vector-memory operation -- it would otherwise wait
@@ -147,22 +149,54 @@ struct DirectTile {
   // written asynchronously; completion is awaited with CLEAVE_WAIT_BARRIER.
   // M0 is on the clobber list so that the compiler keeps no value of its own
   // in M0 across the statement (it is a reserved register, hence the
-  // diagnostic silenced here; nothing needs it preserved).
+  // diagnostic silenced here; nothing needs it preserved).  A wave's loads of a
+  // tile fill neighbouring kilobytes of LDS under one M0: the instruction's
+  // offset counts for both addresses, which the lane offsets and the base make
+  // up for.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-  __device__ __forceinline__ void issue(const unsigned char* gbase, uint32_t lds_tile,
-                                        int wave) const {
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      const uint32_t lds = lds_tile + (wave + S::NW * i) * 1024;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+  // L loads from the FIRST-th.
+  template <int FIRST, int L>
+  __device__ __forceinline__ void issue(const unsigned char* gbase, uint32_t lds_tile, int wave) const {
+    const uint32_t lds = lds_tile + wave * (kLoads * 1024);
+    const unsigned char* base = gbase - (kLoads - 1) * 1024;
+    if constexpr (L == 4) {
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                   "global_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+                   "global_load_lds_dwordx4 %3, %5 offset:2048\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072"
                    :
-                   : "s"(lds), "v"(goff[i]), "s"(gbase)
+                   : "s"(lds), "v"(goff[0]), "v"(goff[1]), "v"(goff[2]), "v"(goff[3]), "s"(base)
+                   : "memory", "m0");
+    } else if constexpr (L == 2) {
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                   "global_load_lds_dwordx4 %1, %3 offset:%4\n\tglobal_load_lds_dwordx4 %2, %3 offset:%5"
+                   :
+                   : "s"(lds), "v"(goff[FIRST]), "v"(goff[FIRST + 1]), "s"(base), "n"(1024 * FIRST), "n"(1024 * FIRST + 1024)
+                   : "memory", "m0");
+    } else {
+      static_assert(L == 1, "the statements above");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+                   :
+                   : "s"(lds), "v"(goff[FIRST]), "s"(base), "n"(1024 * FIRST)
                    : "memory", "m0");
     }
   }
 #pragma clang diagnostic pop
 };
+
+// Order of a run of M MFMAs and READS LDS reads, as a hint to the scheduler: the
+// reads spread evenly behind all but the last eighth of the MFMAs.
+template <int M, int READS, int... I>
+__device__ __forceinline__ void spread_reads_at(std::integer_sequence<int, I...>) {
+  constexpr int kSlots = M > 4 ? M - M / 8 : M > 1 ? M - 1 : 1;
+  constexpr auto done = [](int m) { return m >= kSlots ? READS : (m * READS + kSlots - 1) / kSlots; };
+  ((__builtin_amdgcn_sched_group_barrier(0x008, 1, 0),
+    __builtin_amdgcn_sched_group_barrier(0x100, done(I + 1) - done(I), 0)), ...);
+}
+template <int M, int READS>
+__device__ __forceinline__ void spread_reads() {
+  spread_reads_at<M, READS>(std::make_integer_sequence<int, M>{});
+}
 
 template <typename S, bool A_K, bool B_K>
 __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(ExecuteArgs args) {
@@ -178,42 +212,38 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / S::WN;
   const int wn = wave % S::WN;
-  const int l32 = lane & 31;
-  const int lh = lane >> 5;
+  const int l16 = lane & 15;
+  const int lq = lane >> 4;           // which 8 of a sub-step's 32 k
 
   // Lane-constant fragment addresses (byte offsets inside a stage).
-  // K-contiguous: one per sub-step; blocks are 32 rows apart.  Transposed: one
+  // K-contiguous: one per sub-step; blocks are 16 rows apart.  Transposed: one
   // per block (the XOR touches the block bits); sub-step and half select the k
   // rows through a constant offset.
   const uint32_t smem_off = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_void)smem));
-  const int i16 = lane & 15;
-  const int kq = i16 >> 2;            // k row (mod 4) this lane addresses in a transpose read
-  const int cq = i16 & 3;             // which 4 of the 16 columns
-  const int nsub = (lane >> 4) & 1;   // which 16-column half of the 32-wide block
+  const int kq = l16 >> 2;            // k row (mod 4) this lane addresses in a transpose read
+  const int cq = l16 & 3;             // which 4 of the 16 columns
   uint32_t a_addr[A_K ? kSub : MB];
   uint32_t b_addr[B_K ? kSub : NB];
   if constexpr (A_K) {
-    const int sw = row_swizzle<CPR>(l32);
 #pragma unroll
     for (int ks = 0; ks < kSub; ++ks)
-      a_addr[ks] = (wm * S::WTM + l32) * kRowBytes + (((2 * ks + lh) ^ sw) * 16);
+      a_addr[ks] = (wm * S::WTM + l16) * kRowBytes + (((4 * ks + lq) ^ row_swizzle(l16)) * 16);
   } else {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      const int c = wm * (S::WTM / 8) + i * 4 + 2 * nsub + (cq >> 1);
-      a_addr[i] = ((8 * lh + kq) * CHA + (c ^ k_swizzle<CHA>(kq))) * 16 + (cq & 1) * 8;
+      const int c = wm * (S::WTM / 8) + i * 2 + (cq >> 1);
+      a_addr[i] = ((8 * lq + kq) * CHA + (c ^ k_swizzle<CHA>(8 * lq + kq))) * 16 + (cq & 1) * 8;
     }
   }
   if constexpr (B_K) {
-    const int sw = row_swizzle<CPR>(l32);
 #pragma unroll
     for (int ks = 0; ks < kSub; ++ks)
-      b_addr[ks] = kATile + (wn * S::WTN + l32) * kRowBytes + (((2 * ks + lh) ^ sw) * 16);
+      b_addr[ks] = kATile + (wn * S::WTN + l16) * kRowBytes + (((4 * ks + lq) ^ row_swizzle(l16)) * 16);
   } else {
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int c = wn * (S::WTN / 8) + j * 4 + 2 * nsub + (cq >> 1);
-      b_addr[j] = kATile + ((8 * lh + kq) * CHB + (c ^ k_swizzle<CHB>(kq))) * 16 + (cq & 1) * 8;
+      const int c = wn * (S::WTN / 8) + j * 2 + (cq >> 1);
+      b_addr[j] = kATile + ((8 * lq + kq) * CHB + (c ^ k_swizzle<CHB>(8 * lq + kq))) * 16 + (cq & 1) * 8;
     }
   }
 
@@ -225,7 +255,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
 
   // Everything a work item needs, wave-uniform (scalar registers).
   struct ItemCtx {
-    const unsigned char* a_ptr;   // first row of the A tile at the chunk's first k
+    const unsigned char* a_ptr;   // first row of the A tile at the first k that has not been fetched yet
     const unsigned char* b_ptr;
     TileTarget out;               // where this sub-tile's accumulators go
     int steps, m_valid, n_valid;
@@ -268,19 +298,33 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
 
   DirectTile<S, A_K, TM> ta;
   DirectTile<S, B_K, TN> tb;
-  auto issue = [&](const ItemCtx& c, int s, int st) {
-    const uint32_t stage = smem_off + st * kStage;
-    ta.issue(c.a_ptr + s * a_step, stage, wave);
-    tb.issue(c.b_ptr + s * b_step, stage + kATile, wave);
+  // Fetches the item's next step into ring stage st: A's part and B's, each at
+  // once or in two halves.
+  constexpr int_c<0> whole{};
+  constexpr int_c<1> first_half{};
+  constexpr int_c<2> second_half{};
+  auto issue_a = [&](ItemCtx& c, int st, auto what) {
+    constexpr int W = decltype(what)::value, L = S::kLoadsA / (W ? 2 : 1);
+    ta.template issue<W == 2 ? L : 0, L>(c.a_ptr, smem_off + st * kStage, wave);
+    if (W != 1) c.a_ptr += a_step;
+  };
+  auto issue_b = [&](ItemCtx& c, int st, auto what) {
+    constexpr int W = decltype(what)::value, L = S::kLoadsB / (W ? 2 : 1);
+    tb.template issue<W == 2 ? L : 0, L>(c.b_ptr, smem_off + st * kStage + kATile, wave);
+    if (W != 1) c.b_ptr += b_step;
+  };
+  auto issue = [&](ItemCtx& c, int st) {
+    issue_a(c, st, whole);
+    issue_b(c, st, whole);
   };
   // Start of a work item: lane offsets for its (possibly clipped) tile, then
   // the first STAGES steps into the ring.
-  auto fill_ring = [&](const ItemCtx& c) {
+  auto fill_ring = [&](ItemCtx& c) {
     ta.init(a_rs, a_ks, c.m_valid, wave, lane);
     tb.init(b_rs, b_ks, c.n_valid, wave, lane);
 #pragma unroll
     for (int st = 0; st < STAGES; ++st)
-      if (st < c.steps) issue(c, st, st);
+      if (st < c.steps) issue(c, st);
   };
 
   // A workgroup walks its work items -- every grid-th one, or a run of its own
@@ -293,11 +337,9 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   // other lane offsets) the ring is filled from empty after the item's last
   // step, ahead of its stores.
   //
-  // Store instructions per lane of a full sub-tile whose target takes 16-byte
-  // stores: it goes through the wave's block image in LDS (behind the ring).
-  // bf16 outputs take half as many.
+  // Store instructions per lane of a full sub-tile.
   const bool bf16_out = args.C && args.c_bf16;
-  const int tile_stores = MB * (bf16_out ? staged_stores_per_block_row<NB, true>() : staged_stores_per_block_row<NB, false>());
+  const int tile_stores = bf16_out ? MB * NB / 2 : MB * NB;
   unsigned char* const image = smem + STAGES * kStage + wave * kBlockImageBytes;
 
   // This workgroup's items: first, first + stride, ... below it_end.
@@ -337,7 +379,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   int phase = 0;   // ring stage that holds the current item's step 0
   // Barrier once at most `steps_behind` steps' loads and `stores` stores are
   // outstanding.  (The counts are multiples of four; the counter holds 63.)
-  static_assert(LPS % 4 == 0 && (STAGES - 1) * LPS + MB * NB * 4 <= 40, "the wait counts below");
+  static_assert(LPS % 4 == 0 && (STAGES - 1) * LPS + MB * NB <= 40, "the wait counts below");
   auto wait_behind = [&](int steps_behind, int stores) {
     switch ((steps_behind * LPS + stores) >> 2) {
       case 0: CLEAVE_WAIT_BARRIER(0); break;
@@ -354,8 +396,19 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     }
   };
 
-  f32x16 acc[MB][NB];
-  u32x4 fa[2][MB], fb[2][NB];
+  // A wave holds one sub-step's fragments, in halves of A's and B's that are
+  // replaced as soon as they are done with; small wave tiles hold two sub-steps'.
+  // (Two sub-steps' of the large tile spill; of 64 x 64 they are read in bursts:
+  // 216 items of 64 steps 36.7 us, 34.6 in halves.)
+  constexpr bool kQuarters = MB * NB >= 16;
+  // The refill's loads leave in two groups, or in four where a wave may be alone on
+  // its SIMD and its MFMAs stand behind the queue of the address unit (288 items
+  // of 64 steps: 51.8 us all at once, 49.9 in two groups, 48.5 in four; large
+  // tiles 2.02 / 1.95 / 2.00 ms for 16384 x 5120 x 13824).
+  constexpr bool kPairs = S::NW == 8;
+  constexpr int MH = MB / 2, NH = NB / 2;
+  f32x4 acc[MB][NB];
+  u32x4 fa[kQuarters ? 1 : 2][MB], fb[kQuarters ? 1 : 2][NB];
 
   // Fragment reads are ordinary (compiler-visible) LDS loads: the compiler
   // tracks their completion, and every address is a lane-constant register
@@ -363,131 +416,197 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   auto tr_read = [&](const unsigned char* p) -> u32x2 {
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)p));
   };
-  // Fragments of sub-step KS of the ring stage at byte offset `stage` into
-  // register set `buf`.
-  auto read_frags = [&](uint32_t stage, auto ks_tag, int buf) {
-    constexpr int KS = decltype(ks_tag)::value;
+  // Fragments I0 .. I0 + N - 1 of A (of B) of sub-step KS of the ring stage at
+  // byte offset `stage`.
+  auto read_a = [&](uint32_t stage, auto ks_tag, auto i0_tag, auto n_tag) {
+    constexpr int KS = decltype(ks_tag)::value, I0 = decltype(i0_tag)::value;
+    constexpr int SET = kQuarters ? 0 : KS;
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
+    for (int i = I0; i < I0 + decltype(n_tag)::value; ++i) {
       if constexpr (A_K) {
-        fa[buf][i] = *reinterpret_cast<const u32x4*>(smem + (a_addr[KS] + stage) + i * 32 * kRowBytes);
+        fa[SET][i] = *reinterpret_cast<const u32x4*>(smem + (a_addr[KS] + stage) + i * 16 * kRowBytes);
       } else {
-        const unsigned char* p = smem + (a_addr[i] + stage) + KS * (16 * CHA * 16);
+        const unsigned char* p = smem + (a_addr[i] + stage) + KS * (32 * CHA * 16);
         const u32x2 lo = tr_read(p);
         const u32x2 hi = tr_read(p + 4 * CHA * 16);
-        fa[buf][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        fa[SET][i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
       }
     }
+  };
+  auto read_b = [&](uint32_t stage, auto ks_tag, auto j0_tag, auto n_tag) {
+    constexpr int KS = decltype(ks_tag)::value, J0 = decltype(j0_tag)::value;
+    constexpr int SET = kQuarters ? 0 : KS;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
+    for (int j = J0; j < J0 + decltype(n_tag)::value; ++j) {
       if constexpr (B_K) {
-        fb[buf][j] = *reinterpret_cast<const u32x4*>(smem + (b_addr[KS] + stage) + j * 32 * kRowBytes);
+        fb[SET][j] = *reinterpret_cast<const u32x4*>(smem + (b_addr[KS] + stage) + j * 16 * kRowBytes);
       } else {
-        const unsigned char* p = smem + (b_addr[j] + stage) + KS * (16 * CHB * 16);
+        const unsigned char* p = smem + (b_addr[j] + stage) + KS * (32 * CHB * 16);
         const u32x2 lo = tr_read(p);
         const u32x2 hi = tr_read(p + 4 * CHB * 16);
-        fb[buf][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        fb[SET][j] = u32x4{lo[0], lo[1], hi[0], hi[1]};
       }
     }
   };
-  // `fresh`: the first product of a work item starts from zero (a constant
+  // Rows I0 .. I0 + M - 1 times columns J0 .. J0 + N - 1 of sub-step KS.  B is the
+  // first operand, so that a lane ends up with four neighbouring columns of a
+  // row.  Neighbouring products share a fragment (the columns are walked to and
+  // fro).  `fresh`: the first product of a work item starts from zero (a constant
   // operand of the instruction: no pass over the accumulators to clear them).
-  auto mma = [&](int buf, auto fresh_tag) {
+  auto mma = [&](auto ks_tag, auto i0_tag, auto m_tag, auto j0_tag, auto n_tag, auto fresh_tag) {
+    constexpr int SET = kQuarters ? 0 : decltype(ks_tag)::value;
+    constexpr int I0 = decltype(i0_tag)::value, J0 = decltype(j0_tag)::value, N = decltype(n_tag)::value;
     constexpr bool FRESH = decltype(fresh_tag)::value;
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+    for (int x = 0; x < decltype(m_tag)::value; ++x)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        f32x16 sum = acc[i][j];
-        if constexpr (FRESH) sum = f32x16{};
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            __builtin_bit_cast(bf16x8, fa[buf][i]), __builtin_bit_cast(bf16x8, fb[buf][j]), sum, 0, 0, 0);
+      for (int y = 0; y < N; ++y) {
+        const int i = I0 + x, j = J0 + (i & 1 ? N - 1 - y : y);
+        f32x4 sum = acc[i][j];
+        if constexpr (FRESH) sum = f32x4{};
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, fb[SET][j]), __builtin_bit_cast(bf16x8, fa[SET][i]), sum, 0, 0, 0);
       }
   };
-
-  // Instruction order of one sub-step, as a hint to the scheduler: the MFMAs
-  // of the current fragments with the LDS reads of the next fragments spread
-  // one (or two, for transpose reads) behind each of them, the last two
-  // MFMAs without reads.  Measured +2 % over the compiler's own order.
-  auto interleave = [&]() {
-    constexpr int kReads = (A_K ? MB : 2 * MB) + (B_K ? NB : 2 * NB);
-    constexpr int kMfma = MB * NB;
-    constexpr int kTail = kMfma > 2 ? 2 : kMfma - 1;             // MFMAs without reads behind them
-    constexpr int kPer = (kReads + (kMfma - kTail) - 1) / (kMfma - kTail);
-#pragma unroll
-    for (int i = 0; i < kMfma; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // one MFMA
-      if (i < kMfma - kTail) __builtin_amdgcn_sched_group_barrier(0x100, kPer, 0);   // LDS reads
-    }
-  };
+  constexpr int kReadsA = (A_K ? 1 : 2) * MB, kReadsB = (B_K ? 1 : 2) * NB;
 
   for (;;) {
     const int steps = c.steps;
     const bool has_next = !S::ONE_ITEM && it_next < it_end;
     const bool interior = c.m_valid == TM && c.n_valid == TN;
-    const bool wide = interior && args.out_vec;   // stores of whole lines through the block image
-    // hand the ring over without draining it
-    const bool cont = has_next && wide && nx.m_valid == TM && nx.n_valid == TN && steps >= STAGES && nx.steps >= STAGES;
+        // hand the ring over without draining it
+    const bool cont = has_next && interior && nx.m_valid == TM && nx.n_valid == TN && steps >= STAGES && nx.steps >= STAGES;
     // stores between the steps fetched ahead of the item and its own
     const int stores_behind = entry == kFilled ? 0 : tile_stores;
+
+    // The fragments that a step begins with.
+    auto first_frags = [&](uint32_t stage) {
+      if constexpr (kQuarters) {
+        read_a(stage, int_c<0>{}, int_c<0>{}, int_c<MH>{});
+        read_b(stage, int_c<0>{}, int_c<0>{}, int_c<NH>{});
+      } else {   // in the order in which they are multiplied
+        read_a(stage, int_c<0>{}, int_c<0>{}, int_c<1>{});
+        read_b(stage, int_c<0>{}, int_c<0>{}, int_c<NB>{});
+        read_a(stage, int_c<0>{}, int_c<1>{}, int_c<MB - 1>{});
+      }
+    };
 
     // Step 0 must have landed.  All earlier fragment reads of this workgroup
     // completed before the previous item's final barrier.
     if (entry != kPrefetched) {
       wait_behind(min(STAGES, steps) - 1, stores_behind);
-      read_frags(0u, int_c<0>{}, 0);   // a ring filled from empty starts at stage 0
+      first_frags(0u);   // a ring filled from empty starts at stage 0
     }
 
-    // One K step; step s sits in ring stage (s + phase) % STAGES.  Sub-step j
-    // multiplies register set j & 1 while the fragments of sub-step j+1 are
-    // fetched into the other set.  The barrier sits before the last sub-step's
-    // MFMAs: by then this wave holds all fragments of step s and the step
+    // One K step; step s sits in ring stage (s + phase) % STAGES.  While the
+    // fragments at hand are multiplied, later ones are fetched.  The barrier
+    // sits where this wave holds all that it still needs of step s and the step
     // after it has landed (loads return in order), so the stage is refilled
     // with the step STAGES further on -- this item's, or one of the next item's
-    // first -- and the first fragments of the following step are fetched while
-    // the last sub-step multiplies.  MID: a step with at least STAGES more steps
-    // of this item behind it and none of the steps fetched ahead of the item in
-    // the ring -- no case distinctions, the loop body of long chunks.
+    // first -- and the first fragments of the following step are fetched behind
+    // it, while the rest of the step multiplies.  MID: a step with at least STAGES
+    // more steps of this item behind it and none of the steps fetched ahead of
+    // the item in the ring -- no case distinctions, the loop body of long chunks.
     auto k_step = [&](auto mid_tag, auto first_tag, int s) {
       constexpr bool MID = decltype(mid_tag)::value;
-      constexpr bool FIRST = decltype(first_tag)::value;   // the item's step 0
+      constexpr std::bool_constant<decltype(first_tag)::value> fresh{};   // the item's step 0
+      constexpr std::false_type more{};
       const int st = (s + phase) & (STAGES - 1);
       const uint32_t cur = st * kStage;
       const uint32_t oth = ((st + 1) & (STAGES - 1)) * kStage;
-      auto sub = [&](auto j_tag) {
-        constexpr int J = decltype(j_tag)::value;
-        read_frags(cur, int_c<J + 1>{}, (J + 1) & 1);
-        mma(J & 1, std::bool_constant<FIRST && J == 0>{});
-        interleave();
-      };
-      sub(int_c<0>{});
-      if constexpr (kSub == 4) {
-        sub(int_c<1>{});
-        sub(int_c<2>{});
-      }
-      if constexpr (MID) {
-        CLEAVE_WAIT_BARRIER((STAGES - 2) * LPS);
-        issue(c, s + STAGES, st);
-        read_frags(oth, int_c<0>{}, 0);
-      } else {
-        const bool last = s + 1 >= steps;
-        if (last && !cont) {
-          // no step follows in the ring: nothing to wait for, and no reason to
-          // wait for the previous item's stores either
-          CLEAVE_WAIT_BARRIER(63);
+      const bool last = s + 1 >= steps;
+      const bool go_on = MID || !last || cont;   // a step follows in the ring
+      auto hand_over = [&]() {
+        if constexpr (MID) {
+          CLEAVE_WAIT_BARRIER((STAGES - 2) * LPS);
+          if constexpr (!kQuarters) issue(c, st);
+          else if constexpr (kPairs) issue_a(c, st, whole);
+          else issue_a(c, st, first_half);
         } else {
-          wait_behind(cont ? STAGES - 2 : min(STAGES - 2, steps - 2 - s), s + 1 < STAGES ? stores_behind : 0);
+          if (!go_on) {
+            // nothing to wait for, and no reason to wait for the previous item's stores either
+            CLEAVE_WAIT_BARRIER(63);
+          } else {
+            wait_behind(cont ? STAGES - 2 : min(STAGES - 2, steps - 2 - s), s + 1 < STAGES ? stores_behind : 0);
+          }
+          if (s + STAGES < steps) {
+            issue(c, st);
+          } else if (cont) {
+            issue(nx, st);
+          }
+          if (!S::ONE_ITEM && s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
         }
-        if (s + STAGES < steps) {
-          issue(c, s + STAGES, st);
-        } else if (cont) {
-          issue(nx, s + STAGES - steps, st);
+      };
+      constexpr int_c<0> k0{};
+      constexpr int_c<1> k1{};
+      if constexpr (kQuarters) {
+        // Four quarters per sub-step: (first half of A, one half of B), the other
+        // half of B, then the second half of A with B's halves the other way
+        // round, so that each half of B changes once per sub-step.
+        constexpr int_c<0> lo{};
+        constexpr int_c<MH> a_hi{}, mh{};
+        constexpr int_c<NH> b_hi{}, nh{};
+        read_b(cur, k0, b_hi, nh);
+        mma(k0, lo, mh, lo, nh, fresh);
+        spread_reads<MH * NH, kReadsB / 2>();
+        read_a(cur, k0, a_hi, mh);
+        mma(k0, lo, mh, b_hi, nh, fresh);
+        spread_reads<MH * NH, kReadsA / 2>();
+        read_a(cur, k1, lo, mh);
+        mma(k0, a_hi, mh, b_hi, nh, fresh);
+        spread_reads<MH * NH, kReadsA / 2>();
+        read_b(cur, k1, b_hi, nh);
+        mma(k0, a_hi, mh, lo, nh, fresh);
+        spread_reads<MH * NH, kReadsB / 2>();
+        read_b(cur, k1, lo, nh);
+        mma(k1, lo, mh, b_hi, nh, more);
+        spread_reads<MH * NH, kReadsB / 2>();
+        read_a(cur, k1, a_hi, mh);
+        mma(k1, lo, mh, lo, nh, more);
+        spread_reads<MH * NH, kReadsA / 2>();
+        hand_over();
+        // The refill's loads are spread over the rest of the step.
+        if constexpr (kPairs) {
+          if (go_on) read_a(oth, k0, lo, mh);
+          mma(k1, a_hi, mh, lo, nh, more);
+          spread_reads<MH * NH, kReadsA / 2>();
+          if constexpr (MID) issue_b(c, st, whole);
+          if (go_on) read_b(oth, k0, lo, nh);
+          mma(k1, a_hi, mh, b_hi, nh, more);
+          spread_reads<MH * NH, kReadsB / 2>();
+        } else {
+          constexpr int_c<MH / 2> mq{};
+          constexpr int_c<MH + MH / 2> a_last{};
+          constexpr int_c<NH / 2> nq{};
+          if (go_on) read_a(oth, k0, lo, mq);
+          mma(k1, a_hi, mq, lo, nh, more);
+          spread_reads<MH * NH / 2, kReadsA / 4>();
+          if constexpr (MID) issue_a(c, st, second_half);
+          if (go_on) read_a(oth, k0, mq, mq);
+          mma(k1, a_last, mq, lo, nh, more);
+          spread_reads<MH * NH / 2, kReadsA / 4>();
+          if constexpr (MID) issue_b(c, st, first_half);
+          if (go_on) read_b(oth, k0, lo, nq);
+          mma(k1, a_hi, mq, b_hi, nh, more);
+          spread_reads<MH * NH / 2, kReadsB / 4>();
+          if constexpr (MID) issue_b(c, st, second_half);
+          if (go_on) read_b(oth, k0, nq, nq);
+          mma(k1, a_last, mq, b_hi, nh, more);
+          spread_reads<MH * NH / 2, kReadsB / 4>();
         }
-        if (!S::ONE_ITEM && s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
-        if (!last || cont) read_frags(oth, int_c<0>{}, 0);
+      } else {
+        constexpr int_c<MB> m{};
+        constexpr int_c<NB> n{};
+        read_a(cur, k1, k0, k1);
+        read_b(cur, k1, k0, n);
+        read_a(cur, k1, k1, int_c<MB - 1>{});
+        mma(k0, k0, m, k0, n, fresh);
+        spread_reads<MB * NB, kReadsA + kReadsB>();
+        hand_over();
+        if (go_on) first_frags(oth);
+        mma(k1, k0, m, k0, n, more);
+        spread_reads<MB * NB, kReadsA + kReadsB>();
       }
-      mma((kSub - 1) & 1, std::false_type{});
-      interleave();
     };
     k_step(std::false_type{}, std::true_type{}, 0);
     int s = 1;
@@ -498,21 +617,19 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
 
     // Every wave is past the last step's barrier, hence past all of its
     // fragment reads of this item.
-    const int row0 = wm * S::WTM + lh * 4;
-    const int col0 = wn * S::WTN + l32;
     const TileTarget target = c.out;
     const int m_valid = c.m_valid, n_valid = c.n_valid;
     // The ring is free unless it was handed over: the next item's ring fill is
     // issued before this item's stores so that its latency hides behind them.
     if (!cont && has_next) fill_ring(nx);
-    if (!wide) {
-      store_tile<MB, NB>(acc, target, bf16_out, row0, col0, m_valid, n_valid, interior);
-    } else if (bf16_out) {
-      store_tile_staged_bf16<MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
+    if (!bf16_out) {
+      if (interior) store_rows<false, true, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
+      else store_rows<false, false, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
     } else {
-      store_tile_staged_f32<MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane);
+      if (interior) store_rows<true, true, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
+      else store_rows<true, false, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
     }
-    entry = cont ? kPrefetched : wide ? kFilledBehindStores : kFilled;
+    entry = cont ? kPrefetched : interior ? kFilledBehindStores : kFilled;
     phase = cont ? (phase + steps) & (STAGES - 1) : 0;
     if (!has_next) break;
     c = nx;

@@ -50,9 +50,6 @@ struct ExecuteArgs {
   void* C;
   int64_t ldc;
   int c_bf16;
-  // The output (partials, or C in assemble mode) takes a 16-byte (fp32) or
-  // 8-byte (bf16) store at every fourth column of every sub-tile row.
-  int out_vec;
   // General kernel only: extent of the logical operands (loads stay inside them)
   // and the workgroup tiles per work item (filled in at the launch).
   int64_t M, N, K;

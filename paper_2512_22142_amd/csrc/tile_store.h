@@ -13,6 +13,7 @@
 namespace cleave {
 
 typedef float tile_f32x16 __attribute__((ext_vector_type(16)));
+typedef float tile_f32x4 __attribute__((ext_vector_type(4)));
 
 // Destination of one sub-tile: element (0, 0) of the sub-tile and the row
 // stride in elements (the element type is a property of the launch:
@@ -80,103 +81,68 @@ __device__ __forceinline__ void store_blocks(const tile_f32x16 (&acc)[MB][NB], T
   }
 }
 
-// A full sub-tile, turned through a 4 KB row-major image
-// in LDS that belongs to this wave alone (`image`), so that a lane leaves with
-// 16 consecutive bytes of one row and a store instruction writes eight whole
-// 128-byte lines instead of 64 elements in two rows.  The image holds one
-// 32 x 32 block of fp32 or two neighbouring ones of bf16 (32 rows x 64
-// columns), which therefore take half the LDS traffic and store instructions.
-// The values and their addresses are those of store_blocks.  wave_row0 /
-// wave_col0: first row and column of the wave's part of the sub-tile.  The
-// target must allow 16-byte (fp32) or 8-byte (bf16) stores at every fourth
-// column.  LDS executes a wave's accesses in issue order, and the compiler is
-// kept from reordering them by the asm statements; no other wave touches the
-// image, so no barrier is involved.
+// Stores a wave's MB x NB grid of 16 x 16 blocks of which a lane has row
+// lane % 16 and columns 4 (lane / 16) .. + 3.  One row of blocks at a time is
+// turned through a row-major image in LDS that belongs to this wave alone
+// (`image`), so that neighbouring lanes leave with neighbouring 16 bytes of a
+// row and a store instruction writes whole 128-byte lines in lane order (64-byte
+// rows for bf16 and two blocks).  The order counts: the same lines written by
+// lanes eight apart (the lanes' own 16 bytes, pairs of blocks exchanged across
+// lanes without LDS), or as the 64-byte rows of one block at a time, make every
+// group of sixteen lanes touch eight or sixteen lines: 128 products of 1024 x
+// 1024 x 128 into bf16 88 us through the image, 100 without; 16384 x 13824 x
+// 5120 in 8 splits 2.41 / 2.68 ms.
 //
-// bf16 values are rounded where they are, two rows of a column per
-// instruction; one lane exchange then turns the pairs of two neighbouring
-// columns round, so that a lane writes two neighbouring columns of one row as
-// one dword.  (128 products of 1024 x 1024 x 128 into bf16 followed by 128 of
-// 1024 x 128 x 1024 into fp32: 182 us; 200 us with the rounding on the way out
-// of the image, four values per lane in integer arithmetic, and 8-byte stores,
-// where the store phase is the longer half of a work item of two K steps.)
-constexpr int kBlockImageBytes = 32 * 32 * 4;
-template <int NB, bool BF16>
-__device__ __forceinline__ constexpr int staged_stores_per_block_row() {
-  return NB * (BF16 ? 2 : 4);
-}
-
-template <int MB, int NB>
-__device__ __forceinline__ void store_tile_staged_f32(const tile_f32x16 (&acc)[MB][NB],
-                                                           const TileTarget& t, unsigned char* image,
-                                                           int wave_row0, int wave_col0, int lane) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  float* wr = reinterpret_cast<float*>(image) + (4 * (lane >> 5)) * 32 + (lane & 31);
-  const f32x4* rd = reinterpret_cast<const f32x4*>(image) + lane;   // row lane / 8 (+ 8 k), columns 4 (lane % 8) ..
-  float* gp = reinterpret_cast<float*>(t.base) + static_cast<int64_t>(wave_row0 + (lane >> 3)) * t.ld + wave_col0 +
-              (lane & 7) * 4;
+// wave_row0 / wave_col0: first row and column of the wave's part of the
+// sub-tile, of which m_valid x n_valid elements exist (n_valid a multiple of 8).
+// The target may have any alignment of its elements.  LDS executes a wave's
+// accesses in issue order, and the compiler is kept from reordering them by the
+// asm statements; no other wave touches the image, so no barrier is involved.
+constexpr int kBlockImageBytes = 16 * 64 * 4;
+template <bool BF16, bool INTERIOR, int MB, int NB>
+__device__ __forceinline__ void store_rows(const tile_f32x4 (&acc)[MB][NB], const TileTarget& t, unsigned char* image,
+                                           int wave_row0, int wave_col0, int lane, int m_valid, int n_valid) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  constexpr int EB = BF16 ? 2 : 4;             // bytes per element
+  constexpr int Q = NB * EB;                   // 16-byte pieces of an image row
+  constexpr int R = 16 / Q;                    // image rows in a cycle of the banks
+  constexpr int RR = 64 / Q;                   // rows per read of the whole wave
+  static_assert(16 * Q * 16 <= kBlockImageBytes && Q * R == 16, "image");
+  // piece q of row r sits at r * Q + (q ^ (r / R % Q)): a write's rows and a
+  // read's pieces both fall into different banks
+  const int wrow = lane & 15, wflip = (wrow / R) & (Q - 1);
+  const int rrow = lane / Q, rpiece = lane % Q;
+  const int row = wave_row0 + rrow, col = wave_col0 + rpiece * (16 / EB);
+  unsigned char* gp = t.base + (row * t.ld + col) * EB;
+  const int64_t pitch = t.ld * EB;
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < MB; ++i, gp += 16 * pitch) {
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int r = 0; r < 16; ++r) wr[((r >> 2) * 8 + (r & 3)) * 32] = acc[i][j][r];
-      asm volatile("" ::: "memory");
-      f32x4 v[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = rd[64 * k];
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        *reinterpret_cast<f32x4*>(gp + static_cast<int64_t>(i * 32 + 8 * k) * t.ld + j * 32) = v[k];
+      if constexpr (BF16) {
+        const int piece = (2 * j + (lane >> 5)) ^ wflip;
+        *reinterpret_cast<u32x2*>(image + (wrow * Q + piece) * 16 + 8 * ((lane >> 4) & 1)) =
+            u32x2{pack_bf16(acc[i][j][0], acc[i][j][1]), pack_bf16(acc[i][j][2], acc[i][j][3])};
+      } else {
+        *reinterpret_cast<tile_f32x4*>(image + (wrow * Q + ((4 * j + (lane >> 4)) ^ wflip)) * 16) = acc[i][j];
+      }
     }
-}
-
-template <int MB, int NB>
-__device__ __forceinline__ void store_tile_staged_bf16(const tile_f32x16 (&acc)[MB][NB],
-                                                       const TileTarget& t, unsigned char* image,
-                                                       int wave_row0, int wave_col0, int lane) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  typedef uint32_t u32x4_at8 __attribute__((ext_vector_type(4), aligned(8)));   // rows start on 8 bytes
-  constexpr int W = NB % 2 == 0 ? 2 : 1;      // blocks side by side in the image
-  constexpr int RW = 16 * W;                  // dwords of an image row
-  constexpr int QR = RW / 4;                  // 16-byte pieces of an image row
-  constexpr int RR = 64 / QR;                 // rows per read of the whole wave
-  // An even lane writes columns (l32, l32 + 1) of its rows 8 q + 4 lh + 2 p, an
-  // odd lane columns (l32 - 1, l32) of the rows behind them.  The two halves of
-  // a wave are four rows apart, which is the same banks: with two blocks, rows
-  // with bit 2 set are kept with their 16-dword halves exchanged.
-  const int lh = lane >> 5, odd = lane & 1;
-  const uint32_t select = odd ? 0x03020706u : 0x05040100u;   // (other high, own high) : (own low, other low)
-  uint32_t* wr = reinterpret_cast<uint32_t*>(image) + (4 * lh + odd) * RW + ((lane & 31) >> 1);
-  uint32_t* wr_half[2] = {wr + (W == 2 ? 16 * lh : 0), wr + 16 * (1 - lh)};
-  const int row = lane / QR, quad = (lane % QR) ^ (W == 2 ? 4 * ((row >> 2) & 1) : 0);
-  const u32x4* rd = reinterpret_cast<const u32x4*>(image) + row * QR + quad;
-  uint16_t* gp = reinterpret_cast<uint16_t*>(t.base) + static_cast<int64_t>(wave_row0 + row) * t.ld + wave_col0 +
-                 (lane % QR) * 8;
+    asm volatile("" ::: "memory");
+    u32x4 v[16 / RR];
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; j += W) {
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int h = 0; h < W; ++h)
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {   // rows 8 * (p / 2) + 4 lh + 2 * (p % 2), and the next
-          const uint32_t own = pack_bf16(acc[i][j + h][2 * p], acc[i][j + h][2 * p + 1]);
-          const uint32_t other = __builtin_amdgcn_update_dpp(0u, own, 0xB1, 0xF, 0xF, true);   // lane ^ 1
-          wr_half[h][(8 * (p >> 1) + 2 * (p & 1)) * RW] = __builtin_amdgcn_perm(other, own, select);
-        }
-      asm volatile("" ::: "memory");
-      u32x4 v[32 / RR];
-#pragma unroll
-      for (int k = 0; k < 32 / RR; ++k) v[k] = rd[64 * k];
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int k = 0; k < 32 / RR; ++k)
-        *reinterpret_cast<u32x4_at8*>(gp + static_cast<int64_t>(i * 32 + RR * k) * t.ld + j * 32) = v[k];
+    for (int k = 0; k < 16 / RR; ++k) {
+      const int r = rrow + RR * k;
+      v[k] = *reinterpret_cast<const u32x4*>(image + (r * Q + (rpiece ^ ((r / R) & (Q - 1)))) * 16);
     }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < 16 / RR; ++k)
+      if (INTERIOR || (row + i * 16 + RR * k < m_valid && col < n_valid))
+        *reinterpret_cast<u32x4_any*>(gp + RR * k * pitch) = v[k];
+  }
 }
 
 template <int MB, int NB>
