@@ -219,17 +219,16 @@ int ensure_uploaded(cleave_plan* p) {
     const bool fine = list == cleave::kNumTileClasses;
     const int cls = fine ? cleave::kTileSmall : list;
     const std::vector<cleave::WorkItem>& host = fine ? p->items_fine : p->items[list];
-    const size_t n_direct = fine ? p->items_fine_whole_steps : p->items_whole_steps[list];
     cleave::WorkItem** dst = fine ? &p->d_items_fine : &p->d_items[list];
     const int64_t resident = static_cast<int64_t>(cus) * cleave::direct_workgroups_per_cu(
                                                                 cls == cleave::kTileLarge ? cleave::kDirectLarge : cleave::kDirectSmall);
-    const int grid = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(n_direct), resident));
+    const int grid = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(host.size()), resident));
     std::vector<uint32_t> ranges;
     try {
       std::vector<cleave::WorkItem> copy;
-      if (cleave::needs_balance(host, n_direct, grid)) {
+      if (cleave::needs_balance(host, grid)) {
         copy = host;
-        cleave::balance_work_items(copy, n_direct, grid, &ranges);
+        cleave::balance_work_items(copy, grid, &ranges);
       }
       rc = upload_vector(ranges.empty() ? host : copy, dst);
     } catch (const std::bad_alloc&) {
@@ -414,17 +413,14 @@ struct AssembleTarget {
   int out_dtype = CLEAVE_F32;
 };
 
-// Where the work items of a subset go: one list per tile class, each in two
-// parts -- first the tasks whose chunk is a whole number of the direct
-// kernel's K steps, then the others -- with the caller's order kept inside
-// each part (the layout of the plan's own lists).
+// Where the work items of a subset go: one list per tile class, in the caller's
+// order (the layout of the plan's own lists).
 struct SubsetLayout {
-  bool fine = false;                                  // every block cut into small-class sub-tiles
-  int64_t counts[cleave::kNumTileClasses][2] = {};    // work items per (class, part)
-  int64_t steps[cleave::kNumTileClasses][2] = {};     // their whole K steps, together
-  int64_t total() const { return counts[0][0] + counts[0][1] + counts[1][0] + counts[1][1]; }
+  bool fine = false;                               // every block cut into small-class sub-tiles
+  int64_t counts[cleave::kNumTileClasses] = {};    // work items per class
+  int64_t steps[cleave::kNumTileClasses] = {};     // their whole K steps, together
+  int64_t total() const { return counts[0] + counts[1]; }
 };
-inline int subset_part(const cleave_task& t) { return t.k_len % cleave::kDirectKStep == 0 ? 0 : 1; }
 
 // Validates the ids (range, no repeats) and sizes the lists.  Uses the plan's
 // own stamp array for the repeat check: no allocation.  Caller holds subset.mu.
@@ -451,8 +447,8 @@ int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int
   for (int64_t i = 0; i < n_ids; ++i) {
     const cleave_task& t = plan->tasks[task_ids[i]];
     const cleave::SubTiling st = cleave::sub_tiling(t, out->fine);
-    out->counts[st.cls][subset_part(t)] += st.count();
-    out->steps[st.cls][subset_part(t)] += int64_t{st.count()} * (t.k_len / cleave::kDirectKStep);
+    out->counts[st.cls] += st.count();
+    out->steps[st.cls] += int64_t{st.count()} * (t.k_len / cleave::kDirectKStep);
   }
   return CLEAVE_OK;
 }
@@ -461,13 +457,7 @@ int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int
 // (task, destination) pairs are built on the stack, one launch's worth at a time.
 int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_ids,
                   const SubsetLayout& layout, cleave::WorkItem* out, hipStream_t stream) {
-  int64_t next[cleave::kNumTileClasses][2];
-  int64_t pos = 0;
-  for (int c = 0; c < cleave::kNumTileClasses; ++c)
-    for (int part = 0; part < 2; ++part) {
-      next[c][part] = pos;
-      pos += layout.counts[c][part];
-    }
+  int64_t next[cleave::kNumTileClasses] = {0, layout.counts[0]};
   cleave::ExpandArgs ea{};
   ea.tasks = plan->d_tasks;
   ea.out = out;
@@ -475,7 +465,7 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
   for (int64_t i = 0; i < n_ids; ++i) {
     const cleave_task& t = plan->tasks[task_ids[i]];
     const cleave::SubTiling st = cleave::sub_tiling(t, layout.fine);
-    int64_t& at = next[st.cls][subset_part(t)];
+    int64_t& at = next[st.cls];
     ea.entries[ea.n_entries++] = {static_cast<uint32_t>(task_ids[i]), static_cast<uint32_t>(at)};
     at += st.count();
     if (ea.n_entries == cleave::kSubsetEntriesPerLaunch || i + 1 == n_ids) {
@@ -564,10 +554,18 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     if (rc != CLEAVE_OK) return rc;
   }
 
-  // The direct kernel: bf16, every chunk and tile edge a multiple of 16 bytes and
-  // all rows of both operands starting on 16-byte boundaries.
+  // The direct kernel: bf16, every 16 bytes that it fetches (8 elements along the
+  // operand's rows as stored) belong to one chunk and one tile and lie on a
+  // 16-byte boundary; rows of the output in whole eights.  An operand stored
+  // with the inner dimension across its rows takes any chunk, the other kind any
+  // tile row.  Chunks that end within a K step against the general kernel (us):
+  // 4096 x 4096 x 4128 in 4 splits 230 / 175, 4096 x 8192 x 1032 101 / 71, 8192 x
+  // 3072 x 800 in 4 126 / 98, 512 x 512 x 200 5.2 / 4.4; odd chunks of two operands
+  // with the inner dimension across, 3000 x 2504 x 3001 in 4 77 / 54; odd rows, 3001
+  // x 2504 x 1024 in 4 37 / 30.
   const int e = 16 / eb;
-  const bool direct = dtype == CLEAVE_BF16 && plan->all_k_mult8 && plan->all_mn_mult8 &&
+  const bool direct = dtype == CLEAVE_BF16 && plan->all_n_mult8 && (transA ? plan->all_m_mult8 : plan->all_k_mult8) &&
+                      (!transB || plan->all_k_mult8) &&
                       lda % e == 0 && ldb % e == 0 && aligned(A, 16) && aligned(B, 16) &&
                       // in-tile byte offsets are kept in 32 bits
                       lda * eb < (int64_t{1} << 22) && ldb * eb < (int64_t{1} << 22) &&
@@ -581,23 +579,16 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   const cleave::WorkItem* d_lists[cleave::kNumTileClasses] = {plan->d_items[0], plan->d_items[1]};
   int64_t counts[cleave::kNumTileClasses] = {static_cast<int64_t>(plan->items[0].size()),
                                              static_cast<int64_t>(plan->items[1].size())};
-  // leading items of each list whose chunk is a whole number of direct-kernel K steps
-  int64_t whole_steps[cleave::kNumTileClasses] = {static_cast<int64_t>(plan->items_whole_steps[0]),
-                                                  static_cast<int64_t>(plan->items_whole_steps[1])};
-  int64_t direct_steps[cleave::kNumTileClasses] = {plan->items_direct_steps[0], plan->items_direct_steps[1]};   // of those
-  int64_t other_steps[cleave::kNumTileClasses] = {plan->items_other_steps[0], plan->items_other_steps[1]};      // of the others
+  int64_t steps[cleave::kNumTileClasses] = {plan->items_steps[0], plan->items_steps[1]};   // whole K steps of a list's items
   // which of the plan's lists a class runs from (-1: a subset's own list)
   int list_of[cleave::kNumTileClasses] = {task_ids ? -1 : 0, task_ids ? -1 : 1};
   if (!task_ids && (!direct || prefers_fine(plan->items[cleave::kTileLarge].size()))) {
     list_of[cleave::kTileSmall] = cleave::kNumTileClasses;
     d_lists[cleave::kTileLarge] = nullptr;
     counts[cleave::kTileLarge] = 0;
-    whole_steps[cleave::kTileLarge] = 0;
     d_lists[cleave::kTileSmall] = plan->d_items_fine;
     counts[cleave::kTileSmall] = static_cast<int64_t>(plan->items_fine.size());
-    whole_steps[cleave::kTileSmall] = static_cast<int64_t>(plan->items_fine_whole_steps);
-    direct_steps[cleave::kTileSmall] = plan->items_direct_steps[cleave::kNumTileClasses];
-    other_steps[cleave::kTileSmall] = plan->items_other_steps[cleave::kNumTileClasses];
+    steps[cleave::kTileSmall] = plan->items_steps[cleave::kNumTileClasses];
   }
   // Subset launches: the work-item lists are written on the device, from the
   // task records, into a slice of memory the plan set aside when its tables
@@ -630,10 +621,8 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     int64_t pos = 0;
     for (int c = 0; c < cleave::kNumTileClasses; ++c) {
       d_lists[c] = slice + pos;
-      whole_steps[c] = layout.counts[c][0];
-      direct_steps[c] = layout.steps[c][0];
-      other_steps[c] = layout.steps[c][1];
-      counts[c] = layout.counts[c][0] + layout.counts[c][1];
+      steps[c] = layout.steps[c];
+      counts[c] = layout.counts[c];
       pos += counts[c];
     }
   }
@@ -666,46 +655,37 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     args.K = plan->K;
     args.ldc = asm_to.ldc;
     args.c_bf16 = asm_to.out_dtype == CLEAVE_BF16 ? 1 : 0;
-    // Of a launch the direct kernel can take, it gets the items made of whole K
-    // steps, and the general one the others (if any).  Which kernel computes a
-    // block depends only on the block's own task record.
-    const int64_t n_direct = direct ? whole_steps[c] : 0;
-    const int64_t n_general = counts[c] - n_direct;
-    cleave::GeneralLoads how{cleave::kTileWide, a_elements, b_elements};
-    const cleave::DirectShape shape = direct_shape(c, n_direct, direct_steps[c], cus);
-    if (n_direct > 0) {
+    const bool large = c == cleave::kTileLarge;
+    // in-tile byte offsets (256 rows) stay within 32 bits
+    const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
+                      ldb * eb < (int64_t{1} << 24);
+    const cleave::GeneralLoads how{
+        general_tile(dtype, counts[c] * (large ? 4 : 1), large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
+        a_elements, b_elements};
+    // One round of 16-step chunks with a tail stays with the general kernel's
+    // 256 x 256 tile, which its tests hold it to (256 items of 1032 elements 45.3
+    // us there, 40.4 in the direct kernel).
+    const bool held = plan->chunk_tails && how.tile == cleave::kTileHuge && counts[c] <= cus && steps[c] < 17 * counts[c];
+    if (direct && !held) {
       // Persistent workgroups, as many as the chip holds at once: each walks
       // the item list with the grid as stride and fetches the head of its next
       // item while it stores the current one.
-      args.items = d_lists[c];
-      args.n_items = n_direct;
+      const cleave::DirectShape shape = direct_shape(c, counts[c], steps[c], cus);
       const int64_t resident = static_cast<int64_t>(cus) * cleave::direct_workgroups_per_cu(shape);
-      const int grid = static_cast<int>(std::min<int64_t>(n_direct, resident));
+      const int grid = static_cast<int>(std::min<int64_t>(counts[c], resident));
       // items of unequal length: the schedule made for this grid when the tables were uploaded
       const int list = list_of[c];
       args.wg_ranges = (list >= 0 && plan->wg_ranges_grid[list] == grid)
                            ? plan->d_wg_ranges[list] : nullptr;
-      const hipError_t he = cleave::launch_execute_direct(args, shape, grid, stream);
-      args.wg_ranges = nullptr;
+      const hipError_t he = cleave::launch_execute_direct(args, shape, plan->chunk_tails, grid, stream);
       if (he != hipSuccess) return launch_failed(he);
-    }
-    if (n_general > 0) {
-      args.items = d_lists[c] + n_direct;
-      args.n_items = n_general;
-      const bool large = c == cleave::kTileLarge;
-      // in-tile byte offsets (256 rows) stay within 32 bits
-      const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
-                        ldb * eb < (int64_t{1} << 24);
-      how.tile = general_tile(dtype, n_general * (large ? 4 : 1), large && dtype == CLEAVE_BF16 && by_k ? n_general : 0,
-                              direct ? other_steps[c] : direct_steps[c] + other_steps[c], cus);
+      if (counts[c] > most) plan->last_kernel = direct_kernel_name(shape, transA, transB);
+    } else {
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);
+      if (counts[c] > most) plan->last_kernel = kernel_name(dtype, how, transA, transB);
     }
-    if (counts[c] > most) {
-      most = counts[c];
-      plan->last_kernel = n_direct >= n_general ? direct_kernel_name(shape, transA, transB)
-                                               : kernel_name(dtype, how, transA, transB);
-    }
+    most = std::max(most, counts[c]);
   }
   if (task_ids && !static_scratch) return release_subset_slice(plan->subset, slice_begin, slice_total, stream);
   return CLEAVE_OK;

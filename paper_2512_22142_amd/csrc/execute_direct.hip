@@ -3,8 +3,8 @@
 //
 // Same contract as the general executor (paper Sec. 4.1: a task multiplies its
 // rows of A with its columns of B over its chunk of the inner dimension and
-// stores an fp32 partial block); used when every chunk length is a multiple of
-// the K step and all tile edges / leading dimensions are multiples of 8.
+// stores an fp32 partial block); used when every 16 bytes it fetches belong to one
+// chunk and one tile and are aligned.
 //
 // The kernel is a template over its shape (workgroup tile, wave grid, ring
 // depth); a wave owns a grid of 16 x 16 blocks, computed by MFMA 16x16x32 with
@@ -116,6 +116,8 @@ __device__ __forceinline__ int k_swizzle(int k) {
   return (CH == 8 ? 4 * ((k >> 1) & 1) : 4 * (k & 3)) ^ (2 * ((k >> 3) & 1));
 }
 
+__device__ __align__(16) const unsigned char g_zeros[16] = {};
+
 template <typename S, bool KCONTIG, int R>
 struct DirectTile {
   static constexpr int kLoads = R * S::BK * 2 / 1024 / S::NW;
@@ -181,6 +183,26 @@ struct DirectTile {
                    : "memory", "m0");
     }
   }
+
+  // The same for a chunk's last step of which only k_valid of the BK elements
+  // exist: lanes whose 16 bytes lie behind them fetch zeros, which add nothing.
+  __device__ __forceinline__ void issue_tail(const unsigned char* gbase, uint32_t lds_tile, int wave, int lane_id,
+                                             int k_valid) const {
+    int lane = lane_id;
+    asm volatile("" : "+v"(lane));   // computed here, not kept in registers through the K loop
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int slot = (wave * kLoads + i) * 64 + lane;
+      int k;   // the lane's first
+      if constexpr (KCONTIG) k = ((slot % S::CPR) ^ row_swizzle(slot / S::CPR)) * 8;
+      else k = slot / CH;
+      const unsigned char* p = k < k_valid ? gbase + (goff[i] - (kLoads - 1 - i) * 1024) : g_zeros;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                   :
+                   : "s"(lds_tile + (wave * kLoads + i) * 1024), "v"(p)
+                   : "memory", "m0");
+    }
+  }
 #pragma clang diagnostic pop
 };
 
@@ -198,7 +220,9 @@ __device__ __forceinline__ void spread_reads() {
   spread_reads_at<M, READS>(std::make_integer_sequence<int, M>{});
 }
 
-template <typename S, bool A_K, bool B_K>
+// TAILS: some chunk of the launch ends within a K step (the code for that costs
+// scalar registers: an instantiation of its own).
+template <typename S, bool A_K, bool B_K, bool TAILS>
 __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(ExecuteArgs args) {
   constexpr int TM = S::TM, TN = S::TN, MB = S::MB, NB = S::NB, CPR = S::CPR, kSub = S::kSub;
   constexpr int kStage = S::kStage, kATile = S::kATile, STAGES = S::STAGES, LPS = S::kLoadsPerStep;
@@ -259,6 +283,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     const unsigned char* b_ptr;
     TileTarget out;               // where this sub-tile's accumulators go
     int steps, m_valid, n_valid;
+    int tail;                     // elements of the last step if it is not a whole one, else 0
   };
   auto load_item = [&](int64_t idx) -> WorkItem {
     if constexpr (S::PARTS == 1) {
@@ -283,7 +308,8 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     ItemCtx c;
     c.m_valid = static_cast<int>(w.m_valid);
     c.n_valid = static_cast<int>(w.n_valid);
-    c.steps = static_cast<int>(w.k_len) / S::BK;
+    c.steps = static_cast<int>(w.k_len + S::BK - 1) / S::BK;
+    c.tail = static_cast<int>(w.k_len) % S::BK;
     c.a_ptr = static_cast<const unsigned char*>(args.A) +
               (member_offset(args.a_at, args.batch, w.gemm_id) +
                static_cast<int64_t>(w.m_base) * a_rs + static_cast<int64_t>(w.k0) * a_ks) * 2;
@@ -313,7 +339,12 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     tb.template issue<W == 2 ? L : 0, L>(c.b_ptr, smem_off + st * kStage + kATile, wave);
     if (W != 1) c.b_ptr += b_step;
   };
-  auto issue = [&](ItemCtx& c, int st) {
+  auto issue = [&](ItemCtx& c, int s, int st) {   // s: that step, which may be the chunk's last
+    if (TAILS && c.tail != 0 && s == c.steps - 1) {
+      ta.issue_tail(c.a_ptr, smem_off + st * kStage, wave, lane, c.tail);
+      tb.issue_tail(c.b_ptr, smem_off + st * kStage + kATile, wave, lane, c.tail);
+      return;
+    }
     issue_a(c, st, whole);
     issue_b(c, st, whole);
   };
@@ -324,7 +355,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     tb.init(b_rs, b_ks, c.n_valid, wave, lane);
 #pragma unroll
     for (int st = 0; st < STAGES; ++st)
-      if (st < c.steps) issue(c, st);
+      if (st < c.steps) issue(c, st, st);
   };
 
   // A workgroup walks its work items -- every grid-th one, or a run of its own
@@ -505,7 +536,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     // with the step STAGES further on -- this item's, or one of the next item's
     // first -- and the first fragments of the following step are fetched behind
     // it, while the rest of the step multiplies.  MID: a step with at least STAGES
-    // more steps of this item behind it and none of the steps fetched ahead of
+    // more whole steps of this item behind it and none of the steps fetched ahead of
     // the item in the ring -- no case distinctions, the loop body of long chunks.
     auto k_step = [&](auto mid_tag, auto first_tag, int s) {
       constexpr bool MID = decltype(mid_tag)::value;
@@ -519,9 +550,14 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
       auto hand_over = [&]() {
         if constexpr (MID) {
           CLEAVE_WAIT_BARRIER((STAGES - 2) * LPS);
-          if constexpr (!kQuarters) issue(c, st);
-          else if constexpr (kPairs) issue_a(c, st, whole);
-          else issue_a(c, st, first_half);
+          if constexpr (!kQuarters) {
+            issue_a(c, st, whole);
+            issue_b(c, st, whole);
+          } else if constexpr (kPairs) {
+            issue_a(c, st, whole);
+          } else {
+            issue_a(c, st, first_half);
+          }
         } else {
           if (!go_on) {
             // nothing to wait for, and no reason to wait for the previous item's stores either
@@ -530,9 +566,9 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
             wait_behind(cont ? STAGES - 2 : min(STAGES - 2, steps - 2 - s), s + 1 < STAGES ? stores_behind : 0);
           }
           if (s + STAGES < steps) {
-            issue(c, st);
+            issue(c, s + STAGES, st);
           } else if (cont) {
-            issue(nx, st);
+            issue(nx, s + STAGES - steps, st);
           }
           if (!S::ONE_ITEM && s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
         }
@@ -612,7 +648,8 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     int s = 1;
     if constexpr (STAGES > 2)
       for (; s < STAGES - 1 && s < steps; ++s) k_step(std::false_type{}, std::false_type{}, s);
-    for (; s + STAGES < steps; ++s) k_step(std::true_type{}, std::false_type{}, s);
+    const int full = steps - (TAILS && c.tail != 0);
+    for (; s + STAGES < full; ++s) k_step(std::true_type{}, std::false_type{}, s);
     for (; s < steps; ++s) k_step(std::false_type{}, std::false_type{}, s);
 
     // Every wave is past the last step's barrier, hence past all of its
@@ -638,27 +675,32 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   }
 }
 
-template <typename S, bool A_K, bool B_K>
+template <typename S, bool A_K, bool B_K, bool TAILS>
 hipError_t launch_one(const ExecuteArgs& args, int grid, hipStream_t stream) {
   constexpr size_t lds = S::STAGES * S::kStage + S::NW * kBlockImageBytes;
-  hipLaunchKernelGGL((execute_direct_kernel<S, A_K, B_K>), dim3(grid), dim3(S::NT), lds, stream, args);
+  hipLaunchKernelGGL((execute_direct_kernel<S, A_K, B_K, TAILS>), dim3(grid), dim3(S::NT), lds, stream, args);
   return hipGetLastError();
 }
 
-template <typename S, bool A_K, bool B_K>
+template <typename S, bool A_K, bool B_K, bool TAILS>
 hipError_t configure_one() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(execute_direct_kernel<S, A_K, B_K>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(execute_direct_kernel<S, A_K, B_K, TAILS>),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
                              static_cast<int>(S::STAGES * S::kStage + S::NW * kBlockImageBytes));
 }
 
-template <typename S>
+template <typename S, bool TAILS>
 hipError_t configure_layouts() {
-  hipError_t e = configure_one<S, true, true>();
-  if (e == hipSuccess) e = configure_one<S, true, false>();
-  if (e == hipSuccess) e = configure_one<S, false, true>();
-  if (e == hipSuccess) e = configure_one<S, false, false>();
+  hipError_t e = configure_one<S, true, true, TAILS>();
+  if (e == hipSuccess) e = configure_one<S, true, false, TAILS>();
+  if (e == hipSuccess) e = configure_one<S, false, true, TAILS>();
+  if (e == hipSuccess) e = configure_one<S, false, false, TAILS>();
   return e;
+}
+template <typename S>
+hipError_t configure_shape() {
+  const hipError_t e = configure_layouts<S, false>();
+  return e == hipSuccess ? configure_layouts<S, true>() : e;
 }
 
 // All shapes fetch full 128-byte lines of K-contiguous operands (64 elements of
@@ -687,37 +729,41 @@ using SmallShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 2, false>;
 using DeepShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 4, true>;
 using PartsShape = Shape<64, 64, 2, 2, 64, 4, true>;
 static_assert(kDirectKStep == LargeShape::BK && kDirectKStep == SmallShape::BK &&
-              kDirectKStep == DeepShape::BK && kDirectKStep == PartsShape::BK, "the host hands this kernel the work items of whole K steps");
+              kDirectKStep == DeepShape::BK && kDirectKStep == PartsShape::BK, "the host's unit of cost");
 
-template <typename S>
+template <typename S, bool TAILS>
 hipError_t launch_layouts(const ExecuteArgs& args, int grid, hipStream_t stream) {
   const bool a_k = !args.transA;   // A stored M x K: K-contiguous
   const bool b_k = args.transB;    // B stored N x K: K-contiguous
-  if (a_k && b_k) return launch_one<S, true, true>(args, grid, stream);
-  if (a_k && !b_k) return launch_one<S, true, false>(args, grid, stream);
-  if (!a_k && b_k) return launch_one<S, false, true>(args, grid, stream);
-  return launch_one<S, false, false>(args, grid, stream);
+  if (a_k && b_k) return launch_one<S, true, true, TAILS>(args, grid, stream);
+  if (a_k && !b_k) return launch_one<S, true, false, TAILS>(args, grid, stream);
+  if (!a_k && b_k) return launch_one<S, false, true, TAILS>(args, grid, stream);
+  return launch_one<S, false, false, TAILS>(args, grid, stream);
+}
+template <typename S>
+hipError_t launch_shape(const ExecuteArgs& args, bool tails, int grid, hipStream_t stream) {
+  return tails ? launch_layouts<S, true>(args, grid, stream) : launch_layouts<S, false>(args, grid, stream);
 }
 
 }  // namespace
 
 
 hipError_t configure_execute_direct_kernels() {
-  hipError_t e = configure_layouts<LargeShape>();
-  if (e == hipSuccess) e = configure_layouts<SmallShape>();
-  if (e == hipSuccess) e = configure_layouts<DeepShape>();
-  if (e == hipSuccess) e = configure_layouts<PartsShape>();
+  hipError_t e = configure_shape<LargeShape>();
+  if (e == hipSuccess) e = configure_shape<SmallShape>();
+  if (e == hipSuccess) e = configure_shape<DeepShape>();
+  if (e == hipSuccess) e = configure_shape<PartsShape>();
   return e;
 }
 
-hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, int grid, hipStream_t stream) {
+hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, bool tails, int grid, hipStream_t stream) {
   switch (shape) {
-    case kDirectLarge: return launch_layouts<LargeShape>(args, grid, stream);
-    case kDirectSmall: return launch_layouts<SmallShape>(args, grid, stream);
-    case kDirectDeep: return launch_layouts<DeepShape>(args, static_cast<int>(args.n_items), stream);
+    case kDirectLarge: return launch_shape<LargeShape>(args, tails, grid, stream);
+    case kDirectSmall: return launch_shape<SmallShape>(args, tails, grid, stream);
+    case kDirectDeep: return launch_shape<DeepShape>(args, tails, static_cast<int>(args.n_items), stream);
     default: {   // one workgroup per part of an item; the list is padded to whole rounds of the XCDs
       const int64_t parts = (args.n_items + 7) / 8 * 8 * PartsShape::PARTS;
-      return launch_layouts<PartsShape>(args, static_cast<int>(parts), stream);
+      return launch_shape<PartsShape>(args, tails, static_cast<int>(parts), stream);
     }
   }
 }

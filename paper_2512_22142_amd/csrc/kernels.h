@@ -85,10 +85,10 @@ constexpr int direct_workgroups_per_cu(DirectShape shape) {
   return shape == kDirectLarge || shape == kDirectDeep ? 1 : 2;
 }
 // Enqueues the bf16 direct-to-LDS execute kernel.  The caller has checked the
-// 16-byte load conditions and that the chunk length of every item is a multiple
-// of kDirectKStep elements.  `grid` persistent workgroups (kDirectDeep and
+// 16-byte load conditions.  `tails`: the chunk length of some item may be no
+// multiple of kDirectKStep elements.  `grid` persistent workgroups (kDirectDeep and
 // kDirectParts: one workgroup per item or part, whatever `grid`).
-hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, int grid, hipStream_t stream);
+hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, bool tails, int grid, hipStream_t stream);
 
 // Raises the dynamic-LDS limit of every execute kernel on the current device
 // (needed once per device and process, before the first launch).

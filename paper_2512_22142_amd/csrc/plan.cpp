@@ -70,20 +70,10 @@ void order_work_items(cleave_plan* p) {
   }
   for (int list = 0; list < kNumTileClasses + 1; ++list) {
     const int cls = list < kNumTileClasses ? list : kTileSmall;
-    const std::vector<WorkItem>& whole_list = list < kNumTileClasses ? all[cls] : fine[kTileSmall];
+    const std::vector<WorkItem>& source = list < kNumTileClasses ? all[cls] : fine[kTileSmall];
     std::vector<WorkItem>& ordered = list < kNumTileClasses ? p->items[cls] : p->items_fine;
-    size_t& whole_steps = list < kNumTileClasses ? p->items_whole_steps[cls] : p->items_fine_whole_steps;
-    ordered.reserve(whole_list.size());
-    // Two parts, each ordered on its own: first the items the direct kernel
-    // can take (chunk = whole K steps), then the others.
-    for (int part = 0; part < 2; ++part) {
-    std::vector<WorkItem> source;
-    source.reserve(whole_list.size());
-    for (const WorkItem& w : whole_list)
-      if ((w.k_len % kDirectKStep == 0) == (part == 0)) source.push_back(w);
-    if (part == 0) whole_steps = source.size();
-    int64_t& steps = part == 0 ? p->items_direct_steps[list] : p->items_other_steps[list];
-    for (const WorkItem& w : source) steps += w.k_len / kDirectKStep;
+    ordered.reserve(source.size());
+    for (const WorkItem& w : source) p->items_steps[list] += w.k_len / kDirectKStep;
     if (source.empty()) continue;
     const uint32_t tr = static_cast<uint32_t>(tile_rows(cls));
     const uint32_t tc = static_cast<uint32_t>(tile_cols(cls));
@@ -98,7 +88,7 @@ void order_work_items(cleave_plan* p) {
     // the other.  Large members (the GEMMs of one DAG level) are spread over
     // the XCDs like a single GEMM, and the members take turns patch by patch,
     // so that an operand panel they share is still in L2 for the next one.
-    const bool member_per_xcd = p->batch > 0 && whole_list.size() / static_cast<size_t>(p->batch) < kSpreadItems;
+    const bool member_per_xcd = p->batch > 0 && source.size() / static_cast<size_t>(p->batch) < kSpreadItems;
     for (const WorkItem& w : source) {
       const cleave_task& t = p->tasks[w.task];
       const uint32_t m = w.m_base;
@@ -148,7 +138,6 @@ void order_work_items(cleave_plan* p) {
     }
     for (int x = 0; x < kXcds; ++x)
       for (; pos[x] < lists[x].size(); ++pos[x]) ordered.push_back(lists[x][pos[x]].item);
-    }
   }
 }
 
@@ -242,9 +231,10 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
 
     for (const cleave_task& t : p->tasks) {
       const uint32_t k_or = t.k0 | t.k_len;
-      const uint32_t mn_or = t.m0 | t.m_len | t.n0 | t.n_len;
       p->all_k_mult8 &= (k_or % 8 == 0);
-      p->all_mn_mult8 &= (mn_or % 8 == 0);
+      p->chunk_tails |= (t.k_len % kDirectKStep != 0);
+      p->all_m_mult8 &= ((t.m0 | t.m_len) % 8 == 0);
+      p->all_n_mult8 &= ((t.n0 | t.n_len) % 8 == 0);
       p->min_k_end = std::min(p->min_k_end, static_cast<int64_t>(t.k0) + t.k_len);
       p->all_n_mult4 &= ((t.n0 | t.n_len) % 4 == 0);
     }
@@ -277,21 +267,21 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
 
 }  // namespace
 
-bool needs_balance(const std::vector<WorkItem>& items, size_t n_direct, int grid) {
-  if (grid < 2 || n_direct <= static_cast<size_t>(grid)) return false;   // one item per workgroup at most
-  for (size_t i = 1; i < n_direct; ++i)
-    if (items[i].k_len != items[0].k_len) return true;
+bool needs_balance(const std::vector<WorkItem>& items, int grid) {
+  if (grid < 2 || items.size() <= static_cast<size_t>(grid)) return false;   // one item per workgroup at most
+  for (size_t i = 1; i < items.size(); ++i)
+    if (work_item_cost(items[i]) != work_item_cost(items[0])) return true;
   return false;
 }
 
-void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
-                        std::vector<uint32_t>* ranges) {
+void balance_work_items(std::vector<WorkItem>& items, int grid, std::vector<uint32_t>* ranges) {
   ranges->clear();
-  if (!needs_balance(items, n_direct, grid)) return;
+  const size_t n_items = items.size();
+  if (!needs_balance(items, grid)) return;
   const auto cost = [&](size_t i) { return work_item_cost(items[i]); };
 
-  std::vector<uint32_t> by_cost(n_direct);
-  for (size_t i = 0; i < n_direct; ++i) by_cost[i] = static_cast<uint32_t>(i);
+  std::vector<uint32_t> by_cost(n_items);
+  for (size_t i = 0; i < n_items; ++i) by_cost[i] = static_cast<uint32_t>(i);
   std::stable_sort(by_cost.begin(), by_cost.end(),
                    [&](uint32_t a, uint32_t b) { return items[a].k_len > items[b].k_len; });
   std::vector<double> load(static_cast<size_t>(grid), 0.0);
@@ -309,7 +299,7 @@ void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
     owned[b].push_back(i);
   }
   std::vector<WorkItem> out;
-  out.reserve(n_direct);
+  out.reserve(n_items);
   ranges->reserve(static_cast<size_t>(grid) + 1);
   for (int b = 0; b < grid; ++b) {
     ranges->push_back(static_cast<uint32_t>(out.size()));
@@ -444,17 +434,16 @@ extern "C" int cleave_plan_schedule_loads(const cleave_plan* plan, int list, int
   if (!plan || !loads || list < 0 || list > cleave::kNumTileClasses || grid < 1) return CLEAVE_EINVAL;
   const bool fine = list == cleave::kNumTileClasses;
   const std::vector<cleave::WorkItem>& host = fine ? plan->items_fine : plan->items[list];
-  const size_t n_direct = fine ? plan->items_fine_whole_steps : plan->items_whole_steps[list];
   std::fill(loads, loads + grid, 0.0);
   try {
-    std::vector<cleave::WorkItem> items(host.begin(), host.begin() + static_cast<std::ptrdiff_t>(n_direct));
+    std::vector<cleave::WorkItem> items(host);
     std::vector<uint32_t> ranges;
-    if (balanced) cleave::balance_work_items(items, n_direct, grid, &ranges);
+    if (balanced) cleave::balance_work_items(items, grid, &ranges);
     if (!ranges.empty()) {
       for (int b = 0; b < grid; ++b)
         for (uint32_t i = ranges[b]; i < ranges[b + 1]; ++i) loads[b] += cleave::work_item_cost(items[i]);
     } else {
-      for (size_t i = 0; i < n_direct; ++i) loads[i % static_cast<size_t>(grid)] += cleave::work_item_cost(items[i]);
+      for (size_t i = 0; i < items.size(); ++i) loads[i % static_cast<size_t>(grid)] += cleave::work_item_cost(items[i]);
     }
   } catch (const std::bad_alloc&) {
     return CLEAVE_ENOMEM;

@@ -42,8 +42,7 @@ __host__ __device__ inline int tile_class_of(const cleave_task& t) {
 // block, computed over the task's whole chunk of the inner dimension.  The
 // record carries everything a workgroup needs, so that one load -- issued well
 // ahead -- replaces the dependent pair "which task, then that task's record".
-// Elements of K the direct (global -> LDS) execute kernel consumes per step: it
-// takes only items whose chunk length is a multiple of this.
+// Elements of K the direct (global -> LDS) execute kernel consumes per step.
 constexpr uint32_t kDirectKStep = 64;
 
 struct alignas(16) WorkItem {
@@ -233,7 +232,7 @@ struct SubsetRing {
 // split of the inner dimension).  The persistent kernel's default -- workgroup
 // b takes items b, b + grid, ... -- leaves the workgroups with very different
 // totals when chunk lengths differ by a factor of eight.  This reorders the
-// first n_direct items so that workgroup b owns the contiguous run
+// items so that workgroup b owns the contiguous run
 // [ranges[b], ranges[b + 1]) and the runs have nearly equal cost: longest items
 // first, each to the least-loaded workgroup of the XCD the item's position
 // belongs to (position mod 8, as the list was laid out) unless a workgroup of
@@ -245,14 +244,13 @@ struct SubsetRing {
 // in most of them one item is longer than a workgroup's share.  Returns with
 // `ranges` empty, and the list untouched, when all items cost the same or no
 // workgroup gets a second item.
-bool needs_balance(const std::vector<WorkItem>& items, size_t n_direct, int grid);
-void balance_work_items(std::vector<WorkItem>& items, size_t n_direct, int grid,
-                        std::vector<uint32_t>* ranges);
+bool needs_balance(const std::vector<WorkItem>& items, int grid);
+void balance_work_items(std::vector<WorkItem>& items, int grid, std::vector<uint32_t>* ranges);
 // Cost of a work item in the schedule's unit (one K step of the fast kernel):
 // its K steps plus a constant for the store phase (measured: 12 K clocks
 // against 2.6 K per step).
 inline double work_item_cost(const WorkItem& w) {
-  return w.k_len / kDirectKStep + 4.5;
+  return (w.k_len + kDirectKStep - 1) / kDirectKStep + 4.5;
 }
 
 void append_work_items(const cleave_task& t, uint32_t task_index, std::vector<WorkItem>* out,
@@ -266,22 +264,19 @@ struct cleave_plan {
   int64_t num_tiles = 0;
   int64_t batch = 0;         // > 0: a batch of that many M x N x K GEMMs, task.gemm_id = member
   bool all_k_mult8 = true;   // every k0 and k_len is a multiple of 8
-  bool all_mn_mult8 = true;  // every m0, m_len, n0, n_len is a multiple of 8
+  bool all_m_mult8 = true;   // every m0 and m_len is a multiple of 8
+  bool all_n_mult8 = true;   // every n0 and n_len is a multiple of 8
+  bool chunk_tails = false;  // some k_len is no multiple of the direct kernel's K step
   int64_t min_k_end = std::numeric_limits<int64_t>::max();   // smallest k0 + k_len of a task
   bool all_n_mult4 = true;   // every n0, n_len multiple of 4 (vector path of reduce)
   std::vector<cleave_task> tasks;
-  // All tasks, launch order.  Each list starts with the items whose chunk is a
-  // whole number of the direct kernel's K steps (items_whole_steps of them);
-  // the rest can only run in the general kernel.
+  // All tasks, launch order.
   std::vector<cleave::WorkItem> items[cleave::kNumTileClasses];
-  size_t items_whole_steps[cleave::kNumTileClasses] = {0, 0};
   // All tasks cut into small-class sub-tiles only: used when the large class
   // would leave most of the CUs without a work item.
   std::vector<cleave::WorkItem> items_fine;
-  size_t items_fine_whole_steps = 0;
-  // K steps of the whole-step items of the three lists (large, small, fine), together.
-  int64_t items_direct_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};
-  int64_t items_other_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};   // whole ones of the other items
+  // Whole K steps of the items of the three lists (large, small, fine), together.
+  int64_t items_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};
   std::vector<cleave::ReduceTile> reduce_tiles;
   int64_t reduce_runs = 0;
 
@@ -290,7 +285,7 @@ struct cleave_plan {
   cleave_task* d_tasks = nullptr;
   cleave::WorkItem* d_items[cleave::kNumTileClasses] = {nullptr, nullptr};
   cleave::WorkItem* d_items_fine = nullptr;
-  // Balanced schedules of the three lists' direct parts (large, small, fine) for
+  // Balanced schedules of the three lists (large, small, fine) for
   // the grid sizes of the device the tables were uploaded to; null = equal items.
   uint32_t* d_wg_ranges[cleave::kNumTileClasses + 1] = {nullptr, nullptr, nullptr};
   int wg_ranges_grid[cleave::kNumTileClasses + 1] = {0, 0, 0};

@@ -1,0 +1,77 @@
+"""Chunks that end within a K step of the fast kernel, and the forms that its
+alignment rules let in: chunks of any length and start where both operands have
+the inner dimension across their rows, any number of rows where A's rows run
+along it.  Integer-valued inputs: every block and C equal the fp64 oracle
+exactly, in all shapes of the kernel, with several items per workgroup, items of
+one step, tails in an item's first steps, and unequal chunks."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_22142_amd as cleave
+from oracle import gemm as og
+from oracle import planner
+from workloads.tensors import make_matrix
+
+from gpu_util import block_of, stored
+
+pytestmark = pytest.mark.gpu
+
+
+def check(M, N, K, tile, S, transA, transB, kernel):
+    a = make_matrix(M * 3 + K, M, K, "bf16", integer_valued=True)
+    b = make_matrix(N * 5 + K, K, N, "bf16", integer_valued=True)
+    A, B = stored(a, transA), stored(b, transB)
+    plan = cleave.plan_uniform(M, N, K, *tile, S)
+    tasks, elems = planner.plan_uniform(M, N, K, *tile, S)
+    parts = torch.full((elems,), float("nan"), dtype=torch.float32, device="cuda")
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    dA, dB = A.cuda(), B.cuda()
+    cleave.execute(plan, dA, dB, parts, transA, transB)
+    assert kernel in plan.last_kernel, plan.last_kernel
+    cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    opA, opB = og.logical_operands(A, transA, B, transB)
+    host = parts.cpu().numpy()
+    for s in range(S):
+        mine = tasks[tasks["ksplit_idx"] == s]
+        ref = og.gemm(opA, opB, int(mine["k0"][0]), int(mine["k0"][0] + mine["k_len"][0]))
+        for t in mine:
+            m0, ml, n0, nl = int(t["m0"]), int(t["m_len"]), int(t["n0"]), int(t["n_len"])
+            assert np.array_equal(block_of(host, t), ref[m0:m0 + ml, n0:n0 + nl]), (M, N, K, int(t["tile_id"]), s)
+    assert np.array_equal(C.cpu().numpy(), og.gemm(opA, opB))
+    # tasks issued again alone: same bits
+    again = torch.full_like(parts, float("nan"))
+    ids = sorted({0, len(tasks) // 2, len(tasks) - 1})
+    cleave.execute(plan, dA, dB, again, transA, transB, task_ids=ids)
+    torch.cuda.synchronize()
+    again = again.cpu().numpy()
+    for i in ids:
+        assert np.array_equal(block_of(again, tasks[i]), block_of(host, tasks[i]))
+
+
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K,S", [(8, 1), (72, 1), (136, 1), (208, 2), (1104, 3)])
+def test_tails_of_whole_eights_exact(K, S, transA, transB):
+    check(264, 136, K, (264, 136), S, transA, transB, "direct_bf16_64x64")
+    check(1544, 2056, K, (128, 128), S, transA, transB, "direct_bf16_128x128")
+    if S == 1 and K < 200:
+        check(4096 + 264, 4352, K, (512, 512), S, transA, transB, "direct_bf16_256x256")   # several items per workgroup
+
+
+def test_tails_in_the_deep_ring_exact():
+    for K in (1032, 1080, 1336):
+        for transA, transB in ((0, 0), (1, 0), (0, 1)):
+            check(1536, 1536, K, (128, 128), 1, transA, transB, "128x128_deep")
+
+
+@pytest.mark.parametrize("K,S", [(2, 1), (9, 2), (65, 1), (131, 3), (1025, 4)])
+def test_any_chunk_of_operands_with_the_inner_dimension_across_their_rows_exact(K, S):
+    check(520, 264, K, (264, 136), S, 1, 0, "direct_bf16")
+    check(4096, 2304, K, (512, 512), S, 1, 0, "direct_bf16")
+
+
+@pytest.mark.parametrize("M", [1, 3, 127, 1301])
+def test_any_number_of_rows_exact(M):
+    check(M, 136, 208, (100, 72), 2, 0, 0, "direct_bf16")
+    check(M, 1096, 264, (301, 512), 1, 0, 1, "direct_bf16")
