@@ -520,6 +520,65 @@ cleave::DirectShape direct_shape(int cls, int64_t items, int64_t steps, int cus)
   return items <= cus && steps >= 16 * items ? cleave::kDirectDeep : cleave::kDirectSmall;
 }
 
+// Whether a full launch of the direct kernel cuts every block into small sub-tiles:
+// four times as many items, two workgroups per CU.  They cost more per product
+// (twice the operand traffic into LDS, 1.1-1.25 times the time from four full
+// rounds on), but a round is a quarter as much work, so they win where large items
+// leave much of the last round's CUs idle.  The bits do not depend on the cut.
+// Time of the small cut over the large one's, operands and blocks as the launch
+// before left them in the caches / not in any cache (256 CUs, items of equal
+// length; the three layouts are within 0.06 of each other, the slowest is given):
+//               2 steps      4            8            16           24           64 (48)
+//   136 items   0.88 / 0.90  0.92 / 0.95  0.96 / 0.98  1.01 / 1.04  1.07 / 1.06  1.17 / 1.11
+//   192         0.91 / 0.92  0.91 / 1.00  0.98 / 1.08  1.04 / 1.16  1.09 / 1.21  1.10 / 1.26
+//   224         0.99         0.97         1.05         1.07         1.13         1.17
+//   272         0.84 / 0.85  0.80 / 0.89  0.80 / 0.94  0.83 / 0.93  0.83 / 0.95  0.87 / 0.94
+//   288         0.83 / 0.89  0.77 / 0.94  0.80 / 0.97  0.84 / 1.00  0.85 / 1.00  0.87 / 1.02
+//   320         0.87 / 0.93  0.84 / 0.96  0.83 / 0.99  0.90 / 1.00  0.90 / 1.02  0.91 / 1.03
+//   352         0.97 / 1.00  0.95 / 0.99  0.92 / 1.03  0.98 / 1.03  0.98 / 1.04  0.99 / 1.04
+//   384         0.92 / 0.98  0.94 / 1.03  0.95 / 1.07  1.01 / 1.05  1.04 / 1.07  1.05 / 1.10
+//   544         0.88 / 0.96  0.85 / 0.97  0.92 / 1.00  0.95 / 1.02  0.97 / 1.03  1.06 / 1.02
+//   576         0.90 / 0.98  0.86 / 1.00  0.95 / 1.02  0.96 / 1.03  1.00 / 1.04  1.08 / 1.03
+//   640         0.97         0.83         1.00         1.00         1.07         1.12
+// Where some blocks are small anyway (a rim of the output), cutting all of them
+// also saves the launch for those, and wins further out (a rim of 33 to 51 items,
+// caches as above):
+//               2 steps      4            8            12           16           24
+//   136 items   0.67 / 0.72  0.72 / 0.81  0.75 / 0.89  0.80 / 0.94  0.83 / 0.95  0.88 / 0.98
+//   224         0.77 / 0.80  0.76 / 0.86  0.85 / 0.92  0.88 / 0.95  0.91 / 0.97  0.95 / 1.00
+//   256         0.85 / 0.89  0.73 / 1.01  0.90 / 1.11  0.97 / 1.18  1.04 / 1.23  1.11 / 1.30
+//   272         0.69 / 0.77  0.68 / 0.86  0.69 / 0.90  0.72 / 0.91  0.74 / 0.92  0.77 / 0.93
+//   352         0.81 / 0.89  0.82 / 0.88  0.81 / 0.88  0.85 / 0.90  0.88 / 0.90  0.88 / 0.91
+//   384         0.79 / 0.87  0.85 / 0.91  0.84 / 0.94  0.92 / 0.96  0.93 / 1.01  0.99 / 1.06
+//   448         0.88 / 0.90  0.91 / 0.95  0.96 / 0.98  1.04 / 1.00  1.03 / 1.04  1.05 / 1.04
+//   544         0.78 / 0.87  0.76 / 0.91  0.80 / 0.94  0.83 / 0.96  0.85 / 0.97  0.88 / 0.97
+//   576         0.84 / 0.85  0.82 / 0.89  0.88 / 0.92  0.90 / 0.95  0.94 / 0.95  0.94 / 0.96
+//   640         0.86 / 0.90  0.86 / 0.96  0.92 / 0.98  0.92 / 1.01  0.97 / 1.02  0.98 / 1.05
+// Lists with items of other lengths among them keep the balanced schedule of
+// both classes: rounds say nothing about those.
+bool cut_small(const cleave_plan* plan, int cus) {
+  const int64_t n = static_cast<int64_t>(plan->items[cleave::kTileLarge].size());
+  if (n == 0) return false;
+  if (2 * n <= cus) return true;
+  const int64_t steps = plan->large_steps, over = n % cus;
+  const bool equal = plan->items_steps[cleave::kTileLarge] + 2 * n >= n * steps;   // but for a shorter last chunk
+  const int64_t rim = static_cast<int64_t>(plan->items[cleave::kTileSmall].size());
+  if (!equal || rim > n) return false;
+  switch (n / cus) {
+    case 0: return rim > 0 ? 8 * n <= 7 * cus && steps <= 24 : 4 * n <= 3 * cus && steps <= 4;
+    case 1:
+      if (over == 0) return false;
+      if (8 * over <= cus) return true;
+      if (rim > 0) return (8 * over <= 3 * cus && steps <= 24) || (2 * over <= cus && steps <= 12);
+      return 4 * over <= cus && steps <= 16;
+    case 2:
+      if (over == 0) return false;
+      if (rim > 0) return (4 * over <= cus && steps <= 24) || (2 * over <= cus && steps <= 8);
+      return 8 * over <= cus && steps <= 8;
+    default: return false;
+  }
+}
+
 int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, const void* A,
                  int64_t lda, int transA, const void* B, int64_t ldb, int transB, int dtype,
                  float* partials, const BatchLayout& bl, void* hip_stream,
@@ -536,14 +595,6 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   int cus = 0;
   int rc = compute_units(&cus);
   if (rc != CLEAVE_OK) return rc;
-  // The large class runs one workgroup per CU; when its items would leave
-  // half of the CUs or more idle, every block is cut into small sub-tiles
-  // instead (four times as many items, two workgroups per CU).  The bits do
-  // not depend on the cut.
-  const auto prefers_fine = [cus](size_t large_items) {
-    return large_items > 0 && large_items <= static_cast<size_t>(cus) / 2;
-  };
-
   int dev = 0;
   CLEAVE_HIP(hipGetDevice(&dev));
   if (static_scratch) {
@@ -582,7 +633,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   int64_t steps[cleave::kNumTileClasses] = {plan->items_steps[0], plan->items_steps[1]};   // whole K steps of a list's items
   // which of the plan's lists a class runs from (-1: a subset's own list)
   int list_of[cleave::kNumTileClasses] = {task_ids ? -1 : 0, task_ids ? -1 : 1};
-  if (!task_ids && (!direct || prefers_fine(plan->items[cleave::kTileLarge].size()))) {
+  if (!task_ids && (!direct || cut_small(plan, cus))) {
     list_of[cleave::kTileSmall] = cleave::kNumTileClasses;
     d_lists[cleave::kTileLarge] = nullptr;
     counts[cleave::kTileLarge] = 0;

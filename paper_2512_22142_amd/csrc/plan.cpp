@@ -73,7 +73,10 @@ void order_work_items(cleave_plan* p) {
     const std::vector<WorkItem>& source = list < kNumTileClasses ? all[cls] : fine[kTileSmall];
     std::vector<WorkItem>& ordered = list < kNumTileClasses ? p->items[cls] : p->items_fine;
     ordered.reserve(source.size());
-    for (const WorkItem& w : source) p->items_steps[list] += w.k_len / kDirectKStep;
+    for (const WorkItem& w : source) {
+      p->items_steps[list] += w.k_len / kDirectKStep;
+      if (list == kTileLarge) p->large_steps = std::max<int64_t>(p->large_steps, (w.k_len + kDirectKStep - 1) / kDirectKStep);
+    }
     if (source.empty()) continue;
     const uint32_t tr = static_cast<uint32_t>(tile_rows(cls));
     const uint32_t tc = static_cast<uint32_t>(tile_cols(cls));

@@ -273,10 +273,11 @@ struct cleave_plan {
   // All tasks, launch order.
   std::vector<cleave::WorkItem> items[cleave::kNumTileClasses];
   // All tasks cut into small-class sub-tiles only: used when the large class
-  // would leave most of the CUs without a work item.
+  // would leave too many of the CUs without a work item (cut_small in api.cpp).
   std::vector<cleave::WorkItem> items_fine;
   // Whole K steps of the items of the three lists (large, small, fine), together.
   int64_t items_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};
+  int64_t large_steps = 0;   // K steps of the longest large item
   std::vector<cleave::ReduceTile> reduce_tiles;
   int64_t reduce_runs = 0;
 

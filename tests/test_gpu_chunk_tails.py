@@ -56,7 +56,8 @@ def test_tails_of_whole_eights_exact(K, S, transA, transB):
     check(264, 136, K, (264, 136), S, transA, transB, "direct_bf16_64x64")
     check(1544, 2056, K, (128, 128), S, transA, transB, "direct_bf16_128x128")
     if S == 1 and K < 200:
-        check(4096 + 264, 4352, K, (512, 512), S, transA, transB, "direct_bf16_256x256")   # several items per workgroup
+        check(8192 + 264, 4608, K, (512, 512), S, transA, transB, "direct_bf16_256x256")   # several items per workgroup
+        check(4096 + 264, 4352, K, (512, 512), S, transA, transB, "direct_bf16_128x128")   # a little over a round: cut small
 
 
 def test_tails_in_the_deep_ring_exact():

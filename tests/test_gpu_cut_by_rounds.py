@@ -1,0 +1,69 @@
+"""Which launches cut large blocks small: by their rounds of the chip and the length
+of their chains, at both sides of every line.  Whichever cut is taken, the blocks
+have the bits of the same tasks issued as a subset, which never cuts so many
+blocks, and C equals the fp64 oracle exactly (integer-valued inputs)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_22142_amd as cleave
+from oracle import gemm as og
+from workloads.tensors import make_matrix
+
+from gpu_util import stored
+
+pytestmark = pytest.mark.gpu
+
+LARGE, SMALL = "direct_bf16_256x256", "direct_bf16_128x128"
+
+
+def check(M, N, K, tile, S, transA, transB, kernel):
+    a = make_matrix(M * 3 + K, M, K, "bf16", integer_valued=True)
+    b = make_matrix(N * 5 + K, K, N, "bf16", integer_valued=True)
+    A, B = stored(a, transA), stored(b, transB)
+    plan = cleave.plan_uniform(M, N, K, tile, tile, S)
+    parts, again = (torch.full((plan.partial_elems,), float("nan"), device="cuda") for _ in range(2))
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    dA, dB = A.cuda(), B.cuda()
+    cleave.execute(plan, dA, dB, parts, transA, transB)
+    assert kernel in plan.last_kernel, plan.last_kernel
+    cleave.reduce(plan, parts, C)
+    cleave.execute(plan, dA, dB, again, transA, transB, task_ids=list(range(plan.num_tasks)))
+    assert LARGE in plan.last_kernel, plan.last_kernel
+    torch.cuda.synchronize()
+    assert torch.equal(parts.view(torch.int32), again.view(torch.int32))
+    assert np.array_equal(C.cpu().numpy(), og.gemm(*og.logical_operands(A, transA, B, transB)))
+
+
+# the lines are drawn for 256 CUs; `rows` blocks of 256 rows times `cols` of 256 columns
+@pytest.mark.parametrize("rows,cols,steps,kernel", [
+    (16, 12, 4, SMALL), (16, 12, 5, LARGE), (16, 13, 4, LARGE),     # up to three quarters of a round, short chains
+    (16, 16, 2, LARGE),                                             # a full round
+    (16, 17, 40, SMALL), (16, 18, 20, SMALL),                       # a little over one, any chain
+    (16, 19, 16, SMALL), (16, 20, 17, LARGE), (16, 21, 2, LARGE),   # up to a quarter more
+    (32, 16, 2, LARGE), (32, 17, 8, SMALL), (32, 17, 9, LARGE),     # a little over two, short chains
+    (32, 18, 2, LARGE), (16, 49, 2, LARGE),
+])
+def test_cut_at_the_lines(rows, cols, steps, kernel):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are multiples of 256 CUs")
+    check(rows * 256, cols * 256, steps * 64, 256, 1, 0, 0, kernel)
+
+
+@pytest.mark.parametrize("rows,cols,steps,kernel", [
+    (16, 14, 24, SMALL), (16, 14, 25, LARGE), (16, 15, 2, LARGE), (16, 16, 2, LARGE),
+    (16, 22, 24, SMALL), (16, 24, 12, SMALL), (16, 24, 13, LARGE), (16, 25, 2, LARGE),
+    (32, 16, 2, LARGE), (32, 18, 24, SMALL), (32, 20, 8, SMALL), (32, 20, 9, LARGE), (32, 21, 2, LARGE),
+])
+def test_cut_at_the_lines_with_a_rim_of_small_blocks(rows, cols, steps, kernel):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are multiples of 256 CUs")
+    check(rows * 256 + 72, cols * 256, steps * 64, 256, 1, 0, 0, kernel)
+
+
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_clipped_blocks_members_of_both_classes_and_shorter_last_chunks(transA, transB):
+    check(17 * 256 - 104, 16 * 256, 2 * 72, 256, 1, transA, transB, SMALL)
+    check(8 * 512 + 8, 8 * 512 + 264, 200, 512, 1, transA, transB, SMALL)    # a rim of small blocks
+    if transA and not transB:
+        check(8 * 256, 12 * 256, 770, 256, 3, transA, transB, SMALL)         # chunks of 257, 257 and 256

@@ -33,7 +33,8 @@ def beside(t):
 @pytest.mark.parametrize("special", [False, True])
 @pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("shape,tile,kernel", [
-    ((4352, 2304, 128), 512, "direct_bf16_256x256"),     # several items per workgroup
+    ((8192, 5120, 128), 512, "direct_bf16_256x256"),     # several items per workgroup
+    ((4352, 2304, 128), 512, "direct_bf16_128x128"),     # large blocks that are cut small
     ((2560, 2560, 192), 128, "direct_bf16_128x128"),
     ((1536, 1408, 1088), 128, "direct_bf16_128x128_deep"),
     ((264, 136, 448), 128, "direct_bf16_64x64"),         # clipped parts
