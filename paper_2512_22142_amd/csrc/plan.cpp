@@ -2,8 +2,12 @@
 // the inner dimension (paper Sec. 3.2 "Seamless training", Sec. 4.1 "Search
 // space of GEMM"; coverage and zero-task constraints of Sec. 4.1).
 #include <algorithm>
+#include <cmath>
+#include <functional>
 #include <limits>
 #include <new>
+#include <queue>
+#include <utility>
 
 #include "plan_internal.h"
 
@@ -290,7 +294,7 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
 bool needs_balance(const std::vector<WorkItem>& items, int grid) {
   if (grid < 2 || items.size() <= static_cast<size_t>(grid)) return false;   // one item per workgroup at most
   for (size_t i = 1; i < items.size(); ++i)
-    if (work_item_cost(items[i]) != work_item_cost(items[0])) return true;
+    if (std::abs(work_item_cost(items[i]) - work_item_cost(items[0])) > 1.0) return true;   // one step: a shorter last chunk
   return false;
 }
 
@@ -298,35 +302,34 @@ void balance_work_items(std::vector<WorkItem>& items, int grid, std::vector<uint
   ranges->clear();
   const size_t n_items = items.size();
   if (!needs_balance(items, grid)) return;
-  const auto cost = [&](size_t i) { return work_item_cost(items[i]); };
 
   std::vector<uint32_t> by_cost(n_items);
   for (size_t i = 0; i < n_items; ++i) by_cost[i] = static_cast<uint32_t>(i);
   std::stable_sort(by_cost.begin(), by_cost.end(),
                    [&](uint32_t a, uint32_t b) { return items[a].k_len > items[b].k_len; });
-  std::vector<double> load(static_cast<size_t>(grid), 0.0);
-  std::vector<std::vector<uint32_t>> owned(static_cast<size_t>(grid));
+  // The workgroups of each XCD, least loaded (then lowest) first.  (Looking through
+  // all of them for every item: 150 lists of 30 heterogeneous tilings 87 ms, 37 so.)
+  typedef std::pair<double, uint32_t> Load;
+  std::priority_queue<Load, std::vector<Load>, std::greater<Load>> loads[kXcds];
+  for (int b = 0; b < grid; ++b) loads[b % kXcds].push({0.0, static_cast<uint32_t>(b)});
+  std::vector<uint32_t> owner(n_items), first(static_cast<size_t>(grid) + 1, 0u);
   for (uint32_t i : by_cost) {
     const int home = static_cast<int>(i % kXcds);
-    int best_home = -1, best_any = 0;
-    for (int b = 0; b < grid; ++b) {
-      if (load[b] < load[best_any]) best_any = b;
-      if (b % kXcds == home && (best_home < 0 || load[b] < load[best_home])) best_home = b;
-    }
-    const double c = cost(i);
-    const int b = (best_home >= 0 && load[best_home] <= load[best_any] + 0.25 * c) ? best_home : best_any;
-    load[b] += c;
-    owned[b].push_back(i);
+    int any = -1;
+    for (int x = 0; x < kXcds; ++x)
+      if (!loads[x].empty() && (any < 0 || loads[x].top() < loads[any].top())) any = x;
+    const double c = work_item_cost(items[i]);
+    const int x = !loads[home].empty() && loads[home].top().first <= loads[any].top().first + 0.25 * c ? home : any;
+    const Load least = loads[x].top();
+    loads[x].pop();
+    loads[x].push({least.first + c, least.second});
+    owner[i] = least.second;
+    ++first[least.second + 1];
   }
-  std::vector<WorkItem> out;
-  out.reserve(n_items);
-  ranges->reserve(static_cast<size_t>(grid) + 1);
-  for (int b = 0; b < grid; ++b) {
-    ranges->push_back(static_cast<uint32_t>(out.size()));
-    std::sort(owned[b].begin(), owned[b].end());
-    for (uint32_t i : owned[b]) out.push_back(items[i]);
-  }
-  ranges->push_back(static_cast<uint32_t>(out.size()));
+  for (int b = 0; b < grid; ++b) first[b + 1] += first[b];
+  *ranges = first;
+  std::vector<WorkItem> out(n_items);
+  for (size_t i = 0; i < n_items; ++i) out[first[owner[i]]++] = items[i];
   std::copy(out.begin(), out.end(), items.begin());
 }
 

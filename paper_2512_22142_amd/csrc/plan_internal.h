@@ -242,8 +242,9 @@ struct SubsetRing {
 // 1.16, small class 1.78 / 1.37.  Nothing and a half give the same as a quarter,
 // and over 150 lists of 25 drawn problems the mean hardly moves (3.39 / 3.36):
 // in most of them one item is longer than a workgroup's share.  Returns with
-// `ranges` empty, and the list untouched, when all items cost the same or no
-// workgroup gets a second item.
+// `ranges` empty, and the list untouched, when no two items differ by more than a
+// K step or so (the last chunk of a split that does not divide: every workgroup
+// meets as many of those) or no workgroup gets a second item.
 bool needs_balance(const std::vector<WorkItem>& items, int grid);
 void balance_work_items(std::vector<WorkItem>& items, int grid, std::vector<uint32_t>* ranges);
 // Cost of a work item in the schedule's unit (one K step of the fast kernel):
