@@ -3,9 +3,9 @@
 // dimension, and the fp32 partial block goes to the task's slot in HBM).
 //
 // This is the general executor: fp32 inputs, and every bf16 work item that the
-// direct-to-LDS kernel does not take (chunks that are no whole number of its K
-// steps, operands whose rows do not start on 16-byte boundaries, rows longer
-// than its 32-bit offsets).  One workgroup computes one TM x TN part of a work
+// direct-to-LDS kernel does not take (operands whose rows do not start on
+// 16-byte boundaries, chunks or tile rows that are no whole eights where the
+// operand runs along them, rows longer than its 32-bit offsets).  One workgroup computes one TM x TN part of a work
 // item over the task's whole chunk [k0, k0 + k_len), in ascending steps of 128
 // bytes of K per row (64 bf16 / 32 fp32 elements) and, inside a step, in
 // ascending 32-byte sub-steps; the order of the MFMA accumulation for an
@@ -33,9 +33,9 @@
 //     replaced: us, that tile / both by element / now, bf16 131072 x 1 x 512
 //     161 / 206 / 56, 64 x 1 x 4096 159 / 172 / 51, fp32 1 x 131072 x 512 with
 //     K x M and K x N operands 168 / 201 / 143.
-//   * LDS images and fragment reads are the direct kernel's (swizzled
-//     K-contiguous rows; k rows read through the LDS transpose read for bf16,
-//     one dword per k for fp32), so nothing is transposed in registers.
+//   * LDS images are of the direct kernel's kinds (swizzled K-contiguous rows; k
+//     rows read through the LDS transpose read for bf16, one dword per k for
+//     fp32), so nothing is transposed in registers.
 //
 // What bounds it: fp32, the matrix cores (64 cycles per 32x32x2): 4096^3 as
 // 512 x 512 x 1024 tasks runs at 138-141 TFLOP/s of 157 nominal.  bf16, the LDS

@@ -505,7 +505,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     const int steps = c.steps;
     const bool has_next = !S::ONE_ITEM && it_next < it_end;
     const bool interior = c.m_valid == TM && c.n_valid == TN;
-        // hand the ring over without draining it
+    // hand the ring over without draining it
     const bool cont = has_next && interior && nx.m_valid == TM && nx.n_valid == TN && steps >= STAGES && nx.steps >= STAGES;
     // stores between the steps fetched ahead of the item and its own
     const int stores_behind = entry == kFilled ? 0 : tile_stores;
