@@ -35,9 +35,9 @@ PEAK_HBM_GBPS = 8000.0
 # dropped on a mismatch.
 COUNTER_TRAFFIC = {
     "workload": "c3",
-    "sources_sha256": "ff8180cab31c4ab161b80555ce39918b330bb492191138eb9821767c49c354ab",
-    "execute_bytes_per_launch": (2.0 * 225612 + 388535) * 1024,
-    "reduce_bytes_per_launch": (2.0 * 194743 + 97134) * 1024,
+    "sources_sha256": "08a6037743c3e407cb6bed2a1c3ddaea1e9a4d45f3f175f445b2f49a14e90801",
+    "execute_bytes_per_launch": (2.0 * 225530 + 388535) * 1024,
+    "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
 
 
