@@ -160,7 +160,7 @@ struct OperandTile {
     k_stride = ks * EB;
     r_valid = rv;
     k_len = len;
-    steps = (len + KS - 1) / KS;
+    steps = chunk_steps(len, KS);
     edge_step = len % KS ? steps - 1 : -1;
     if constexpr (KCONTIG) {
       left_to_row_end = 0;
@@ -216,11 +216,11 @@ struct OperandTile {
     for (int i = 0; i < NV; ++i) {
       int r, k;
       where(i, t, &r, &k);
-      k += s * KS;
+      const uint32_t at = static_cast<uint32_t>(k) + static_cast<uint32_t>(s) * KS;   // may pass 2^31
       u32x4 w = {0, 0, 0, 0};
       if (r < r_valid) {
-        const int left = k_len - k;
-        const unsigned char* q = base + r * row_stride + min(k, k_len - 1) * k_stride;
+        const int left = static_cast<int>(static_cast<uint32_t>(k_len) - at);
+        const unsigned char* q = base + r * row_stride + min(at, static_cast<uint32_t>(k_len - 1)) * k_stride;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           uint32_t x;
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
       }
     };
 
-    const int steps = (k_len + S::KS - 1) / S::KS;
+    const int steps = chunk_steps(item.k_len, S::KS);
     // Steps 0 .. SETS-1 into registers, step 0 on into LDS, step SETS behind it.
     fetch(int_c<0>{}, 0);
     if constexpr (SETS > 1) fetch(int_c<1>{}, 1);

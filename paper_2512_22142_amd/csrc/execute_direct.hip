@@ -308,8 +308,8 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     ItemCtx c;
     c.m_valid = static_cast<int>(w.m_valid);
     c.n_valid = static_cast<int>(w.n_valid);
-    c.steps = static_cast<int>(w.k_len + S::BK - 1) / S::BK;
-    c.tail = static_cast<int>(w.k_len) % S::BK;
+    c.steps = chunk_steps(w.k_len, S::BK);
+    c.tail = static_cast<int>(w.k_len % S::BK);
     c.a_ptr = static_cast<const unsigned char*>(args.A) +
               (member_offset(args.a_at, args.batch, w.gemm_id) +
                static_cast<int64_t>(w.m_base) * a_rs + static_cast<int64_t>(w.k0) * a_ks) * 2;

@@ -45,6 +45,13 @@ __host__ __device__ inline int tile_class_of(const cleave_task& t) {
 // Elements of K the direct (global -> LDS) execute kernel consumes per step.
 constexpr uint32_t kDirectKStep = 64;
 
+// Steps of `per_step` elements in a chunk, the last one whole or not.  A chunk has
+// up to 2^31 - 1 elements: rounded up in 32 bits without a sign, or the longest
+// ones come out negative.
+__host__ __device__ constexpr int chunk_steps(uint32_t k_len, uint32_t per_step) {
+  return static_cast<int>((k_len + per_step - 1) / per_step);
+}
+
 struct alignas(16) WorkItem {
   uint32_t m_base, n_base;    // first row / column of the sub-tile in the logical output
   uint32_t k0, k_len;         // the task's chunk
@@ -251,7 +258,7 @@ void balance_work_items(std::vector<WorkItem>& items, int grid, std::vector<uint
 // its K steps plus a constant for the store phase (measured: 12 K clocks
 // against 2.6 K per step).
 inline double work_item_cost(const WorkItem& w) {
-  return (w.k_len + kDirectKStep - 1) / kDirectKStep + 4.5;
+  return chunk_steps(w.k_len, kDirectKStep) + 4.5;
 }
 
 void append_work_items(const cleave_task& t, uint32_t task_index, std::vector<WorkItem>* out,
