@@ -707,17 +707,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     args.ldc = asm_to.ldc;
     args.c_bf16 = asm_to.out_dtype == CLEAVE_BF16 ? 1 : 0;
     const bool large = c == cleave::kTileLarge;
-    // in-tile byte offsets (256 rows) stay within 32 bits
-    const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
-                      ldb * eb < (int64_t{1} << 24);
-    const cleave::GeneralLoads how{
-        general_tile(dtype, counts[c] * (large ? 4 : 1), large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
-        a_elements, b_elements};
-    // One round of 16-step chunks with a tail stays with the general kernel's
-    // 256 x 256 tile, which its tests hold it to (256 items of 1032 elements 45.3
-    // us there, 40.4 in the direct kernel).
-    const bool held = plan->chunk_tails && how.tile == cleave::kTileHuge && counts[c] <= cus && steps[c] < 17 * counts[c];
-    if (direct && !held) {
+    if (direct) {
       // Persistent workgroups, as many as the chip holds at once: each walks
       // the item list with the grid as stride and fetches the head of its next
       // item while it stores the current one.
@@ -732,6 +722,12 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       if (he != hipSuccess) return launch_failed(he);
       if (counts[c] > most) plan->last_kernel = direct_kernel_name(shape, transA, transB);
     } else {
+      // in-tile byte offsets (256 rows) stay within 32 bits
+      const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
+                        ldb * eb < (int64_t{1} << 24);
+      const cleave::GeneralLoads how{
+          general_tile(dtype, counts[c] * (large ? 4 : 1), large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
+          a_elements, b_elements};
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);
       if (counts[c] > most) plan->last_kernel = kernel_name(dtype, how, transA, transB);

@@ -60,6 +60,32 @@ def test_tails_of_whole_eights_exact(K, S, transA, transB):
         check(4096 + 264, 4352, K, (512, 512), S, transA, transB, "direct_bf16_128x128")   # a little over a round: cut small
 
 
+@pytest.mark.parametrize("rows", [15, 16])
+def test_a_round_of_large_items_stays_in_the_fast_kernel_beside_tails(rows):
+    """About one round of 16-step items of two K-contiguous operands, whole steps,
+    in a plan some of whose other chunks end within a step: every launch of it is
+    the fast kernel's, the full one and the subset without those."""
+    M, N, K = rows * 256, 16 * 256 + 72, 1024
+    band_h, col_w, ks = [256] * rows, [[256] * 16 + [72]] * rows, ([1] * 16 + [26]) * rows     # 26 chunks of 40, the last 24
+    plan = cleave.plan_explicit(M, N, K, band_h, col_w, ks)
+    a = make_matrix(rows, M, K, "bf16", integer_valued=True)
+    b = make_matrix(rows + 1, K, N, "bf16", integer_valued=True)
+    dA, dB = a.cuda(), stored(b, 1).cuda()
+    parts, again = (torch.full((plan.partial_elems,), float("nan"), device="cuda") for _ in range(2))
+    C = torch.full((M, N), float("nan"), device="cuda")
+    cleave.execute(plan, dA, dB, parts, 0, 1)
+    assert "direct" in plan.last_kernel
+    cleave.reduce(plan, parts, C)
+    ids = [i for i, t in enumerate(plan.tasks) if t["k_len"] == K]
+    cleave.execute(plan, dA, dB, again, 0, 1, task_ids=ids)
+    assert plan.last_kernel == "execute_direct_bf16_256x256_nt"
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().numpy(), og.gemm(*og.logical_operands(a, 0, stored(b, 1), 1)))
+    host, again = parts.cpu().numpy(), again.cpu().numpy()
+    for i in ids:
+        assert np.array_equal(block_of(again, plan.tasks[i]), block_of(host, plan.tasks[i]))
+
+
 def test_tails_in_the_deep_ring_exact():
     for K in (1032, 1080, 1336):
         for transA, transB in ((0, 0), (1, 0), (0, 1)):

@@ -110,7 +110,19 @@ def test_one_operand_by_elements_the_other_in_wide_loads_exact(dtype, transA, tr
     (4096, 4096, (512, 256), 16 * 64 + 8),      # 256 full 256 x 256 items
     (2120, 2176, (136, 136), 17 * 64 - 8)])     # 256 clipped ones
 def test_large_items_of_two_k_contiguous_operands_exact(M, N, tile, K):
-    check(M, N, K, tile, 1, 0, 1, "bf16", kernel="execute_bf16_256x256_nt")
+    """Aligned, the fast kernel's; with rows that are not, the general kernel's 256 x
+    256 tile where they are issued as a subset (a full launch cuts them small)."""
+    check(M, N, K, tile, 1, 0, 1, "bf16", kernel="direct_bf16_256x256")
+    a = make_matrix(M * 7 + K, M, K, "bf16", integer_valued=True)
+    b = make_matrix(N * 5 + K, K, N, "bf16", integer_valued=True)
+    plan = cleave.plan_uniform(M, N, K, *tile, 1)
+    parts = torch.full((plan.partial_elems,), float("nan"), dtype=torch.float32, device="cuda")
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    cleave.execute(plan, tight(a, 1), tight(stored(b, 1), 3), parts, 0, 1, task_ids=list(range(plan.num_tasks)))
+    assert plan.last_kernel == "execute_bf16_256x256_nt"
+    cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().numpy(), og.gemm(*og.logical_operands(a, 0, stored(b, 1), 1)))
 
 
 def test_large_items_of_a_subset_with_unaligned_rows():
