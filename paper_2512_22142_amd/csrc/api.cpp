@@ -200,6 +200,8 @@ int allocate_subset_ring(cleave_plan* p) {
   return CLEAVE_OK;
 }
 
+bool cut_small(const cleave_plan* plan, int cus);
+
 int ensure_uploaded(cleave_plan* p) {
   int dev = 0;
   CLEAVE_HIP(hipGetDevice(&dev));
@@ -211,8 +213,9 @@ int ensure_uploaded(cleave_plan* p) {
   hipStream_t writing = nullptr;
   if (rc == CLEAVE_OK) rc = make_reduce_table(p, &writing);
   // The three work-item lists; items of unequal length get a balanced workgroup
-  // schedule for this device's grid (a copy is reordered: the host lists keep
-  // their canonical order for the next device).
+  // schedule for this device's grid (the host lists keep their canonical order for
+  // the next device).  Full launches of the general kernel run the third list, the
+  // fast kernel's only where it cuts large blocks small.
   int cus = 0;
   if (rc == CLEAVE_OK) rc = ensure_device_ready(dev, &cus);
   for (int list = 0; rc == CLEAVE_OK && list < cleave::kNumTileClasses + 1; ++list) {
@@ -225,12 +228,9 @@ int ensure_uploaded(cleave_plan* p) {
     const int grid = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(host.size()), resident));
     std::vector<uint32_t> ranges;
     try {
-      std::vector<cleave::WorkItem> copy;
-      if (cleave::needs_balance(host, grid)) {
-        copy = host;
-        cleave::balance_work_items(copy, grid, &ranges);
-      }
-      rc = upload_vector(ranges.empty() ? host : copy, dst);
+      std::vector<cleave::WorkItem> scheduled;
+      if (!fine || cut_small(p, cus)) scheduled = cleave::scheduled_list(host, grid, fine, &ranges);
+      rc = upload_vector(ranges.empty() ? host : scheduled, dst);
     } catch (const std::bad_alloc&) {
       rc = CLEAVE_ENOMEM;
     }
@@ -718,6 +718,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       const int list = list_of[c];
       args.wg_ranges = (list >= 0 && plan->wg_ranges_grid[list] == grid)
                            ? plan->d_wg_ranges[list] : nullptr;
+      if (args.wg_ranges && list == cleave::kNumTileClasses) args.items += counts[c];   // behind the list as laid out
       const hipError_t he = cleave::launch_execute_direct(args, shape, plan->chunk_tails, grid, stream);
       if (he != hipSuccess) return launch_failed(he);
       if (counts[c] > most) plan->last_kernel = direct_kernel_name(shape, transA, transB);

@@ -333,6 +333,20 @@ void balance_work_items(std::vector<WorkItem>& items, int grid, std::vector<uint
   std::copy(out.begin(), out.end(), items.begin());
 }
 
+std::vector<WorkItem> scheduled_list(const std::vector<WorkItem>& items, int grid, bool both,
+                                     std::vector<uint32_t>* ranges) {
+  ranges->clear();
+  if (!needs_balance(items, grid)) return {};
+  std::vector<WorkItem> balanced(items);
+  balance_work_items(balanced, grid, ranges);
+  if (!both) return balanced;
+  std::vector<WorkItem> list;
+  list.reserve(2 * items.size());
+  list = items;
+  list.insert(list.end(), balanced.begin(), balanced.end());
+  return list;
+}
+
 void append_work_items(const cleave_task& t, uint32_t task_index, std::vector<WorkItem>* out,
                        bool fine) {
   const SubTiling s = sub_tiling(t, fine);

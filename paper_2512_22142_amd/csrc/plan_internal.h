@@ -254,6 +254,18 @@ struct SubsetRing {
 // meets as many of those) or no workgroup gets a second item.
 bool needs_balance(const std::vector<WorkItem>& items, int grid);
 void balance_work_items(std::vector<WorkItem>& items, int grid, std::vector<uint32_t>* ranges);
+// The balanced schedule as it is uploaded.  The runs are the persistent kernel's
+// alone; the general kernel takes position i of a list on XCD i % 8, where the
+// items as they were laid out share operands.  A list that both kernels run
+// (`both`) therefore keeps its order, and the balanced one follows it.  us, the
+// general kernel on heterogeneous tilings in the order of the runs / as laid out:
+// bf16 with unaligned rows, 4096 x 11008 x 4096 1024 / 739, 5064 x 3080 x 6472
+// 528 / 440, 1096 x 2312 x 7304 114 / 115; fp32, 4096^3 1306 / 1157, 2056 x 4104 x
+// 4104 720 / 631; the other way round where few items are far longer than the
+// rest: bf16 1224 x 4872 x 5384 178 / 193, fp32 2048 x 2048 x 8192 619 / 648.
+// Empty, with no ranges, where the list needs no balance.
+std::vector<WorkItem> scheduled_list(const std::vector<WorkItem>& items, int grid, bool both,
+                                     std::vector<uint32_t>* ranges);
 // Cost of a work item in the schedule's unit (one K step of the fast kernel):
 // its K steps plus a constant for the store phase (measured: 12 K clocks
 // against 2.6 K per step).
@@ -295,7 +307,9 @@ struct cleave_plan {
   cleave::WorkItem* d_items[cleave::kNumTileClasses] = {nullptr, nullptr};
   cleave::WorkItem* d_items_fine = nullptr;
   // Balanced schedules of the three lists (large, small, fine) for
-  // the grid sizes of the device the tables were uploaded to; null = equal items.
+  // the grid sizes of the device the tables were uploaded to; null = equal items,
+  // or a list that the persistent kernel does not run.  The items in balanced order
+  // replace those of the first two lists, and stand behind those of the third.
   uint32_t* d_wg_ranges[cleave::kNumTileClasses + 1] = {nullptr, nullptr, nullptr};
   int wg_ranges_grid[cleave::kNumTileClasses + 1] = {0, 0, 0};
   cleave::ReduceItem* d_reduce_items = nullptr;   // reduce_runs records (and behind them what they were made from)

@@ -67,3 +67,28 @@ def test_clipped_blocks_members_of_both_classes_and_shorter_last_chunks(transA, 
     check(8 * 512 + 8, 8 * 512 + 264, 200, 512, 1, transA, transB, SMALL)    # a rim of small blocks
     if transA and not transB:
         check(8 * 256, 12 * 256, 770, 256, 3, transA, transB, SMALL)         # chunks of 257, 257 and 256
+
+
+@pytest.mark.parametrize("dtype,K", [("bf16", 512), ("bf16", 1088), ("f32", 512), ("f32", 520)])
+def test_cut_small_lists_of_unequal_items(dtype, K):
+    """Few large blocks among many small ones whose chunks differ by a factor of
+    eight: the all-small list in its balanced order (bf16) and as it was laid out
+    (fp32, the general kernel's)."""
+    M, N = 4096, 2048
+    band_h, col_w = [256] * 16, [[256] + [128] * 14] * 16
+    ks = [(1, 2, 4, 8)[(3 * i + j) % 4] for i in range(16) for j in range(15)]
+    plan = cleave.plan_explicit(M, N, K, band_h, col_w, ks)
+    strided, used = cleave.schedule_loads(plan, 2, 512, False), cleave.schedule_loads(plan, 2, 512, True)
+    assert used.max() < strided.max()
+    a = make_matrix(K, M, K, dtype, integer_valued=True)
+    b = make_matrix(K + 1, K, N, dtype, integer_valued=True)
+    dA, dB = a.cuda(), b.cuda()
+    parts, again = (torch.full((plan.partial_elems,), float("nan"), device="cuda") for _ in range(2))
+    C = torch.full((M, N), float("nan"), device="cuda")
+    cleave.execute(plan, dA, dB, parts)
+    assert (SMALL if dtype == "bf16" else "execute_f32") in plan.last_kernel, plan.last_kernel
+    cleave.reduce(plan, parts, C)
+    cleave.execute(plan, dA, dB, again, task_ids=list(range(plan.num_tasks)))
+    torch.cuda.synchronize()
+    assert torch.equal(parts.view(torch.int32), again.view(torch.int32))
+    assert np.array_equal(C.cpu().numpy(), og.gemm(*og.logical_operands(a, 0, b, 0)))
