@@ -79,7 +79,9 @@ void order_work_items(cleave_plan* p) {
     ordered.reserve(source.size());
     for (const WorkItem& w : source) {
       p->items_steps[list] += w.k_len / kDirectKStep;
-      if (list == kTileLarge) p->large_steps = std::max<int64_t>(p->large_steps, chunk_steps(w.k_len, kDirectKStep));
+      if (list != kTileLarge) continue;
+      p->large_steps = std::max(p->large_steps, chunk_steps(w.k_len, kDirectKStep));
+      p->large_steps_least = std::min(p->large_steps_least, chunk_steps(w.k_len, kDirectKStep));
     }
     if (source.empty()) continue;
     const uint32_t tr = static_cast<uint32_t>(tile_rows(cls));

@@ -297,7 +297,8 @@ struct cleave_plan {
   std::vector<cleave::WorkItem> items_fine;
   // Whole K steps of the items of the three lists (large, small, fine), together.
   int64_t items_steps[cleave::kNumTileClasses + 1] = {0, 0, 0};
-  int64_t large_steps = 0;   // K steps of the longest large item
+  // K steps of the longest and of the shortest large item, the last one whole or not.
+  int large_steps = 0, large_steps_least = std::numeric_limits<int>::max();
   std::vector<cleave::ReduceTile> reduce_tiles;
   int64_t reduce_runs = 0;
 

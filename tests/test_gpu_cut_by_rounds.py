@@ -69,6 +69,35 @@ def test_clipped_blocks_members_of_both_classes_and_shorter_last_chunks(transA, 
         check(8 * 256, 12 * 256, 770, 256, 3, transA, transB, SMALL)         # chunks of 257, 257 and 256
 
 
+@pytest.mark.parametrize("K,S,every,kernel", [
+    (128, 2, 2, SMALL),       # chunks of two steps and of one: no more apart than a shorter last chunk
+    (192, 3, 2, LARGE),       # of three steps and of one
+    (320, 5, 10, LARGE), (1024, 2, 20, LARGE),
+])
+def test_only_lists_of_equal_items_are_cut_by_rounds(K, S, every, kernel):
+    """A little over a round of large items, some of them shorter: every `every`-th
+    tile of the first rows is split in S."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are multiples of 256 CUs")
+    ks, items = [], 0
+    while len(ks) % 16 or items < 264:       # whole rows of 16 tiles
+        ks.append(S if len(ks) % every == 0 and items + S <= 272 else 1)
+        items += ks[-1]
+    rows = len(ks) // 16
+    assert 256 < items <= 288
+    M, N = rows * 256, 4096
+    plan = cleave.plan_explicit(M, N, K, [256] * rows, [[256] * 16] * rows, ks)
+    a = make_matrix(K, M, K, "bf16", integer_valued=True)
+    b = make_matrix(K + 1, K, N, "bf16", integer_valued=True)
+    parts = torch.full((plan.partial_elems,), float("nan"), device="cuda")
+    C = torch.full((M, N), float("nan"), device="cuda")
+    cleave.execute(plan, a.cuda(), b.cuda(), parts)
+    assert kernel in plan.last_kernel, plan.last_kernel
+    cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().numpy(), og.gemm(*og.logical_operands(a, 0, b, 0)))
+
+
 @pytest.mark.parametrize("dtype,K", [("bf16", 512), ("bf16", 1088), ("f32", 512), ("f32", 520)])
 def test_cut_small_lists_of_unequal_items(dtype, K):
     """Few large blocks among many small ones whose chunks differ by a factor of
