@@ -527,33 +527,49 @@ cleave::DirectShape direct_shape(int cls, int64_t items, int64_t steps, int cus)
 // leave much of the last round's CUs idle.  The bits do not depend on the cut.
 // Time of the small cut over the large one's, operands and blocks as the launch
 // before left them in the caches / not in any cache (256 CUs, items of equal
-// length; the three layouts are within 0.06 of each other, the slowest is given):
-//               2 steps      4            8            16           24           64 (48)
-//   136 items   0.88 / 0.90  0.92 / 0.95  0.96 / 0.98  1.01 / 1.04  1.07 / 1.06  1.17 / 1.11
-//   192         0.91 / 0.92  0.91 / 1.00  0.98 / 1.08  1.04 / 1.16  1.09 / 1.21  1.10 / 1.26
-//   224         0.99         0.97         1.05         1.07         1.13         1.17
-//   272         0.84 / 0.85  0.80 / 0.89  0.80 / 0.94  0.83 / 0.93  0.83 / 0.95  0.87 / 0.94
-//   288         0.83 / 0.89  0.77 / 0.94  0.80 / 0.97  0.84 / 1.00  0.85 / 1.00  0.87 / 1.02
-//   320         0.87 / 0.93  0.84 / 0.96  0.83 / 0.99  0.90 / 1.00  0.90 / 1.02  0.91 / 1.03
-//   352         0.97 / 1.00  0.95 / 0.99  0.92 / 1.03  0.98 / 1.03  0.98 / 1.04  0.99 / 1.04
-//   384         0.92 / 0.98  0.94 / 1.03  0.95 / 1.07  1.01 / 1.05  1.04 / 1.07  1.05 / 1.10
-//   544         0.88 / 0.96  0.85 / 0.97  0.92 / 1.00  0.95 / 1.02  0.97 / 1.03  1.06 / 1.02
-//   576         0.90 / 0.98  0.86 / 1.00  0.95 / 1.02  0.96 / 1.03  1.00 / 1.04  1.08 / 1.03
-//   640         0.97         0.83         1.00         1.00         1.07         1.12
-// Where some blocks are small anyway (a rim of the output), cutting all of them
-// also saves the launch for those, and wins further out (a rim of 33 to 51 items,
-// caches as above):
-//               2 steps      4            8            12           16           24
-//   136 items   0.67 / 0.72  0.72 / 0.81  0.75 / 0.89  0.80 / 0.94  0.83 / 0.95  0.88 / 0.98
-//   224         0.77 / 0.80  0.76 / 0.86  0.85 / 0.92  0.88 / 0.95  0.91 / 0.97  0.95 / 1.00
-//   256         0.85 / 0.89  0.73 / 1.01  0.90 / 1.11  0.97 / 1.18  1.04 / 1.23  1.11 / 1.30
-//   272         0.69 / 0.77  0.68 / 0.86  0.69 / 0.90  0.72 / 0.91  0.74 / 0.92  0.77 / 0.93
-//   352         0.81 / 0.89  0.82 / 0.88  0.81 / 0.88  0.85 / 0.90  0.88 / 0.90  0.88 / 0.91
-//   384         0.79 / 0.87  0.85 / 0.91  0.84 / 0.94  0.92 / 0.96  0.93 / 1.01  0.99 / 1.06
-//   448         0.88 / 0.90  0.91 / 0.95  0.96 / 0.98  1.04 / 1.00  1.03 / 1.04  1.05 / 1.04
-//   544         0.78 / 0.87  0.76 / 0.91  0.80 / 0.94  0.83 / 0.96  0.85 / 0.97  0.88 / 0.97
-//   576         0.84 / 0.85  0.82 / 0.89  0.88 / 0.92  0.90 / 0.95  0.94 / 0.95  0.94 / 0.96
-//   640         0.86 / 0.90  0.86 / 0.96  0.92 / 0.98  0.92 / 1.01  0.97 / 1.02  0.98 / 1.05
+// length; of three layouts and of square outputs and ones 1024 wide, where cold
+// operands cost the small cut most, the one with the largest product of the two):
+//            2 steps      4            8            12           16           24
+//   136      0.88 / 0.89  0.94 / 1.00  0.98 / 1.08  1.01 / 1.14  1.02 / 1.19  1.07 / 1.25
+//   192      0.91 / 0.92  0.89 / 0.98  0.95 / 1.07  0.96 / 1.18  0.96 / 1.20  0.97 / 1.33
+//   224      0.98 / 0.97  0.93 / 1.12  0.97 / 1.33  1.01 / 1.45  1.04 / 1.48  1.05 / 1.51
+//   272      0.81 / 0.94  0.74 / 1.06  0.75 / 1.10  0.78 / 1.11  0.78 / 1.12  0.80 / 1.13
+//   288      0.81 / 0.94  0.75 / 1.09  0.76 / 1.11  0.78 / 1.15  0.80 / 1.13  0.82 / 1.16
+//   320      0.86 / 0.97  0.84 / 1.02  0.81 / 1.04  0.79 / 1.12  0.81 / 1.13  0.81 / 1.15
+//   352      0.92 / 1.09  0.90 / 1.19  0.87 / 1.21  0.88 / 1.25  0.90 / 1.21  0.90 / 1.23
+//   384      0.89 / 1.05  0.93 / 1.16  0.89 / 1.25  0.90 / 1.24  0.92 / 1.23  0.91 / 1.25
+//   544      0.89 / 1.01  0.83 / 1.13  0.88 / 1.12  0.86 / 1.21  0.86 / 1.18  0.85 / 1.21
+//   576      0.89 / 1.05  0.84 / 1.14  0.88 / 1.22  0.91 / 1.24  0.89 / 1.23  1.04 / 1.30
+//   640      0.92 / 1.18  0.93 / 1.22  0.94 / 1.32  0.96 / 1.33  0.95 / 1.25  1.23 / 1.33
+// Chains of 64 steps: 272 items 0.87 / 0.94, 288 0.87 / 1.02.  Where some blocks are
+// small anyway (a rim of the output), cutting all of them also saves the launch for
+// those, and wins further out (few: 4 to 40 small items; many: as many as large ones):
+//            2 steps      4            8            12           16           24
+//   136 few  0.69 / 0.71  0.73 / 0.81  0.77 / 0.88  0.83 / 0.98  0.86 / 1.00  0.92 / 1.04
+//   136 many 0.64 / 0.66  0.64 / 0.74  0.66 / 0.79  0.70 / 0.80  0.75 / 0.86  0.80 / 0.87
+//   192 few  0.82 / 0.86  0.81 / 0.95  0.86 / 0.98  0.89 / 1.02  0.91 / 1.06  0.94 / 1.11
+//   192 many 0.70 / 0.79  0.71 / 0.84  0.74 / 0.90  0.76 / 0.91  0.80 / 0.96  0.84 / 0.99
+//   224 few  0.78 / 0.82  0.75 / 0.93  0.81 / 1.08  0.86 / 1.11  0.88 / 1.16  0.92 / 1.24
+//   224 many 0.72 / 0.83  0.74 / 0.90  0.79 / 1.02  0.86 / 1.07  0.96 / 1.16  1.02 / 1.21
+//   272 few  0.70 / 0.78  0.65 / 0.84  0.67 / 0.92  0.71 / 0.97  0.74 / 0.99  0.78 / 0.99
+//   272 many 0.67 / 0.79  0.66 / 0.86  0.67 / 0.86  0.70 / 0.86  0.71 / 0.83  0.71 / 0.84
+//   288 few  0.68 / 0.79  0.65 / 0.88  0.68 / 0.94  0.72 / 0.96  0.75 / 0.97  0.79 / 1.01
+//   288 many 0.69 / 0.77  0.67 / 0.85  0.68 / 0.91  0.71 / 0.87  0.72 / 0.84  0.73 / 0.84
+//   320 few  0.79 / 0.90  0.78 / 0.96  0.80 / 1.01  0.82 / 0.98  0.83 / 1.01  0.84 / 1.05
+//   320 many 0.72 / 0.84  0.71 / 0.90  0.77 / 0.90  0.79 / 0.93  0.81 / 0.94  0.83 / 0.97
+//   352 few  0.79 / 0.94  0.79 / 1.05  0.78 / 1.04  0.80 / 1.08  0.83 / 1.10  0.84 / 1.14
+//   352 many 0.75 / 0.86  0.74 / 0.92  0.74 / 0.97  0.85 / 0.93  0.80 / 1.00  0.85 / 1.00
+//   384 few  0.77 / 0.92  0.82 / 1.03  0.82 / 1.12  0.89 / 1.19  0.93 / 1.21  0.97 / 1.26
+//   384 many 0.77 / 0.93  0.81 / 1.04  0.84 / 1.04  0.88 / 1.04  0.89 / 1.04  0.89 / 1.07
+//   544 few  0.79 / 0.91  0.74 / 1.06  0.80 / 1.13  0.82 / 1.16  0.84 / 1.17  0.88 / 1.21
+//   544 many 0.76 / 0.83  0.72 / 0.94  0.80 / 0.96  0.79 / 0.97  0.79 / 0.98  0.94 / 0.98
+//   576 few  0.84 / 0.98  0.83 / 1.09  0.91 / 1.18  0.91 / 1.20  0.93 / 1.21  0.96 / 1.27
+//   576 many 0.79 / 0.91  0.78 / 1.00  0.88 / 1.02  0.86 / 1.05  0.97 / 1.04  1.01 / 1.05
+//   640 few  0.85 / 1.03  0.83 / 1.13  0.92 / 1.23  0.92 / 1.25  0.95 / 1.33  1.25 / 1.37
+//   640 many 0.82 / 0.96  0.81 / 1.04  0.88 / 1.10  0.98 / 1.11  1.05 / 1.11  1.12 / 1.07
+// Each line lies where, over layouts, shapes and rims, a launch with its operands in
+// the caches still gains more than one with cold operands loses (576 few of 8 steps
+// and 192 few of 24 lose 1.07 and 1.04 of the two together, the others less).
 // Lists with items of other lengths among them keep the balanced schedule of
 // both classes: rounds say nothing about those (caches as above: 320 items of 3
 // and 1 steps 1.12 / 1.06; 16 steps and a few of 8, 269 items 1.04 / 1.15, 286
@@ -567,15 +583,17 @@ bool cut_small(const cleave_plan* plan, int cus) {
   const int64_t rim = static_cast<int64_t>(plan->items[cleave::kTileSmall].size());
   if (!equal || rim > n) return false;
   switch (n / cus) {
-    case 0: return rim > 0 ? 8 * n <= 7 * cus && steps <= 24 : 4 * n <= 3 * cus && steps <= 4;
+    case 0:
+      if (rim > 0) return (4 * n <= 3 * cus && steps <= 24) || (8 * n <= 7 * cus && steps <= 12);
+      return 4 * n <= 3 * cus && steps <= 4;
     case 1:
       if (over == 0) return false;
       if (8 * over <= cus) return true;
-      if (rim > 0) return (8 * over <= 3 * cus && steps <= 24) || (2 * over <= cus && steps <= 12);
+      if (rim > 0) return (8 * over <= 3 * cus && steps <= 24) || (2 * over <= cus && steps <= 8);
       return 4 * over <= cus && steps <= 16;
     case 2:
       if (over == 0) return false;
-      if (rim > 0) return (4 * over <= cus && steps <= 24) || (2 * over <= cus && steps <= 8);
+      if (rim > 0) return (8 * over <= cus && steps <= 16) || (4 * over <= cus && steps <= 8) || (2 * over <= cus && steps <= 4);
       return 8 * over <= cus && steps <= 8;
     default: return false;
   }
