@@ -92,6 +92,36 @@ def test_tails_in_the_deep_ring_exact():
             check(1536, 1536, K, (128, 128), 1, transA, transB, "128x128_deep")
 
 
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,tile,S,kernel", [
+    (8192 + 264, 4608, 136, 512, 1, "direct_bf16_256x256"),
+    (4096, 4352, 1032, 512, 1, "direct_bf16_128x128"),     # large blocks cut small
+    (1536, 1536, 1080, 128, 1, "128x128_deep"),
+    (1544, 2056, 1104, 128, 3, "direct_bf16_128x128"),
+])
+def test_tasks_issued_again_have_the_same_bits(M, N, K, tile, S, kernel, transA, transB):
+    """Real-valued inputs, whose sums depend on their order: the parts shape, a subset
+    with operands one element further on (the general kernel), and the launch of all."""
+    a, b = stored(make_matrix(M + K, M, K, "bf16"), transA), stored(make_matrix(N + K, K, N, "bf16"), transB)
+    plan = cleave.plan_uniform(M, N, K, tile, tile, S)
+    dA, dB = a.cuda(), b.cuda()
+    beside = torch.zeros(dA.numel() + 8, dtype=dA.dtype, device="cuda")[1:1 + dA.numel()].view(dA.shape).copy_(dA)
+    parts, again, general = (torch.full((plan.partial_elems,), float("nan"), device="cuda") for _ in range(3))
+    cleave.execute(plan, dA, dB, parts, transA, transB)
+    assert kernel in plan.last_kernel, plan.last_kernel
+    ids = sorted({0, plan.num_tasks // 3, plan.num_tasks // 2, plan.num_tasks - 1})
+    cleave.execute(plan, dA, dB, again, transA, transB, task_ids=ids)
+    assert "direct_bf16_64x64" in plan.last_kernel, plan.last_kernel
+    cleave.execute(plan, beside, dB, general, transA, transB, task_ids=ids)
+    assert "direct" not in plan.last_kernel
+    torch.cuda.synchronize()
+    host, again, general = (x.cpu().numpy().view(np.int32) for x in (parts, again, general))
+    for i in ids:
+        block = block_of(host, plan.tasks[i])
+        assert np.array_equal(block_of(again, plan.tasks[i]), block)
+        assert np.array_equal(block_of(general, plan.tasks[i]), block)
+
+
 @pytest.mark.parametrize("K,S", [(2, 1), (9, 2), (65, 1), (131, 3), (1025, 4)])
 def test_any_chunk_of_operands_with_the_inner_dimension_across_their_rows_exact(K, S):
     check(520, 264, K, (264, 136), S, 1, 0, "direct_bf16")

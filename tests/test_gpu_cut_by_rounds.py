@@ -1,7 +1,8 @@
 """Which launches cut large blocks small: by their rounds of the chip and the length
-of their chains, at both sides of every line.  Whichever cut is taken, the blocks
-have the bits of the same tasks issued as a subset, which never cuts so many
-blocks, and C equals the fp64 oracle exactly (integer-valued inputs)."""
+of their chains, at both sides of every line.  Whichever cut is taken, every block
+is where the same tasks issued as a subset, which never cuts so many blocks, put
+it, and C equals the fp64 oracle exactly (integer-valued inputs); with real-valued
+ones, whose sums depend on their order, the two launches' bits are the same."""
 import numpy as np
 import pytest
 import torch
@@ -60,6 +61,28 @@ def test_cut_at_the_lines_with_a_rim_of_small_blocks(rows, cols, steps, kernel):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the sizes are multiples of 256 CUs")
     check(rows * 256 + 72, cols * 256, steps * 64, 256, 1, 0, 0, kernel)
+
+
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("cols,K,kernel", [(17, 1024, SMALL), (17, 1032, SMALL), (21, 1032, LARGE)])
+def test_bits_do_not_depend_on_the_cut(cols, K, kernel, transA, transB):
+    M, N = 4096, cols * 256
+    a, b = stored(make_matrix(cols, M, K, "bf16"), transA), stored(make_matrix(cols + 1, K, N, "bf16"), transB)
+    plan = cleave.plan_uniform(M, N, K, 256, 256, 1)
+    parts, again = (torch.full((plan.partial_elems,), float("nan"), device="cuda") for _ in range(2))
+    dA, dB = a.cuda(), b.cuda()
+    cleave.execute(plan, dA, dB, parts, transA, transB)
+    assert kernel in plan.last_kernel, plan.last_kernel
+    cleave.execute(plan, dA, dB, again, transA, transB, task_ids=list(range(plan.num_tasks)))
+    assert LARGE in plan.last_kernel, plan.last_kernel
+    few = torch.full_like(parts, float("nan"))
+    cleave.execute(plan, dA, dB, few, transA, transB, task_ids=list(range(100)))     # cut small
+    assert SMALL in plan.last_kernel, plan.last_kernel
+    torch.cuda.synchronize()
+    assert not bool(torch.isnan(parts).any())
+    assert torch.equal(parts.view(torch.int32), again.view(torch.int32))
+    n = 100 * 256 * 256
+    assert torch.equal(parts[:n].view(torch.int32), few[:n].view(torch.int32))
 
 
 @pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])

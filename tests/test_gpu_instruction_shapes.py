@@ -2,7 +2,8 @@
 with 32 x 32 x 16: an element's bits must not depend on that, whatever the inputs --
 exponents over most of bf16's range with subnormals among them (sums of every
 order of magnitude, cancellation, underflow), infinities and NaN -- nor on the
-shape of the fast kernel.  The general kernel runs the same values one element
+shape of the fast kernel, nor on whether the chunk ends within a step (which the
+fast kernel fills with zeros to 32 elements, the general one to 16).  The general kernel runs the same values one element
 further on in memory, where the fast one does not go."""
 import pytest
 import torch
@@ -30,16 +31,7 @@ def beside(t):
     return view
 
 
-@pytest.mark.parametrize("special", [False, True])
-@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0)])
-@pytest.mark.parametrize("shape,tile,kernel", [
-    ((8192, 5120, 128), 512, "direct_bf16_256x256"),     # several items per workgroup
-    ((4352, 2304, 128), 512, "direct_bf16_128x128"),     # large blocks that are cut small
-    ((2560, 2560, 192), 128, "direct_bf16_128x128"),
-    ((1536, 1408, 1088), 128, "direct_bf16_128x128_deep"),
-    ((264, 136, 448), 128, "direct_bf16_64x64"),         # clipped parts
-])
-def test_same_bits_from_both_matrix_instructions(shape, tile, kernel, transA, transB, special):
+def compare(shape, tile, kernel, transA, transB, special):
     M, N, K = shape
     A = wide_range(*((K, M) if transA else (M, K)), 1, special).cuda()
     B = wide_range(*((N, K) if transB else (K, N)), 2, special).cuda()
@@ -52,3 +44,35 @@ def test_same_bits_from_both_matrix_instructions(shape, tile, kernel, transA, tr
     nan = torch.isnan(fast)
     assert torch.equal(nan, torch.isnan(slow)) and bool(nan.any()) == special
     assert torch.equal(fast.view(torch.int32)[~nan], slow.view(torch.int32)[~nan])
+
+
+@pytest.mark.parametrize("special", [False, True])
+@pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape,tile,kernel", [
+    ((8192, 5120, 128), 512, "direct_bf16_256x256"),     # several items per workgroup
+    ((4352, 2304, 128), 512, "direct_bf16_128x128"),     # large blocks that are cut small
+    ((2560, 2560, 192), 128, "direct_bf16_128x128"),
+    ((1536, 1408, 1088), 128, "direct_bf16_128x128_deep"),
+    ((264, 136, 448), 128, "direct_bf16_64x64"),         # clipped parts
+    # chunks that end within a step: 8, 16, 24, 40 and 56 elements of it
+    ((8192, 5120, 72), 512, "direct_bf16_256x256"),
+    ((8192, 5120, 80), 512, "direct_bf16_256x256"),
+    ((4352, 2304, 104), 512, "direct_bf16_128x128"),
+    ((2560, 2560, 216), 128, "direct_bf16_128x128"),
+    ((1536, 1408, 1080), 128, "direct_bf16_128x128_deep"),
+    ((264, 136, 424), 128, "direct_bf16_64x64"),
+])
+def test_same_bits_from_both_matrix_instructions(shape, tile, kernel, transA, transB, special):
+    compare(shape, tile, kernel, transA, transB, special)
+
+
+@pytest.mark.parametrize("special", [False, True])
+@pytest.mark.parametrize("shape,tile,kernel", [
+    ((8192, 5120, 65), 512, "direct_bf16_256x256"),
+    ((4352, 2304, 131), 512, "direct_bf16_128x128"),
+    ((2560, 2560, 177), 128, "direct_bf16_128x128"),
+    ((1536, 1408, 1025), 128, "direct_bf16_128x128_deep"),
+    ((264, 136, 415), 128, "direct_bf16_64x64"),
+])
+def test_same_bits_of_odd_chunks(shape, tile, kernel, special):
+    compare(shape, tile, kernel, 1, 0, special)
