@@ -486,8 +486,9 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // the wide tile leaves half of the CUs without a workgroup (1000^3, 128 items
 // 13.8 / 11.3; 2001x768x3072, 192 items 27.4 / 29.7; 3001x2999x1001, 1152
 // items 44 / 55).
-// `whole`: that many 256 x 256 items, with `steps` whole K steps between them,
-// that the kernel could take as they are (bf16, both operands K-contiguous: six
+// `whole`: that many 256 x 256 items of a subset (full launches of this kernel run
+// the all-small list), with `steps` whole K steps between them, that the kernel
+// could take as they are (bf16, both operands K-contiguous: six
 // fragment reads for eight products instead of eight).  They win when their
 // rounds are nearly full and their chains long enough to cover a start and end
 // alone on a CU (us, 128 / 256: 17 steps, 256 items 57 / 50, 1024 items 230 / 193, 688 items 144 / 132,

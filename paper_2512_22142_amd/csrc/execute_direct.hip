@@ -8,13 +8,15 @@
 //
 // The kernel is a template over its shape (workgroup tile, wave grid, ring
 // depth); a wave owns a grid of 16 x 16 blocks, computed by MFMA 16x16x32 with
-// fp32 accumulators in registers.  The four instantiations are at the end of the
-// file.  What bounds full launches is the board's power, and this instruction
-// does the same arithmetic for less of it than the 32 x 32 one (half of the
-// accumulator traffic per product): products from registers, random operands,
-// 2.08 against 1.85 PFLOP/s, the same bits.  Together with fewer instructions per
-// K step: 4096 x 4096 x 4096 in 512 x 512 tiles, 4 splits 139 -> 131 us, 4096 x
-// 4096 x 11008 320 -> 292 us, 16384 x 5120 x 13824 in 8 splits 2.06 -> 1.95 ms.
+// fp32 accumulators in registers.  Its four shapes are at the end of the file,
+// each for the four layouts of the operands, with and without chunks that end
+// within a step.  What bounds full launches is the board's power, and this
+// instruction does the same arithmetic for less of it than the 32 x 32 one (half
+// of the accumulator traffic per product): products from registers, random
+// operands, 2.05 against 1.82 PFLOP/s, the same bits.  Together with fewer
+// instructions per K step: 4096 x 4096 x 4096 in 512 x 512 tiles, 4 splits 139 ->
+// 131 us, 4096 x 4096 x 11008 320 -> 292 us, 16384 x 5120 x 13824 in 8 splits 2.06
+// -> 1.95 ms.
 //
 // A wave-wide direct load writes 64 consecutive 16-byte LDS slots (lane l ->
 // slot l), so the LDS layout is chosen through which global 16 bytes a lane

@@ -86,7 +86,7 @@ constexpr int direct_workgroups_per_cu(DirectShape shape) {
 }
 // Enqueues the bf16 direct-to-LDS execute kernel.  The caller has checked the
 // 16-byte load conditions.  `tails`: the chunk length of some item may be no
-// multiple of kDirectKStep elements.  `grid` persistent workgroups (kDirectDeep and
+// multiple of kDirectKStep elements (false where one is: its last step reads too far).  `grid` persistent workgroups (kDirectDeep and
 // kDirectParts: one workgroup per item or part, whatever `grid`).
 hipError_t launch_execute_direct(const ExecuteArgs& args, DirectShape shape, bool tails, int grid, hipStream_t stream);
 

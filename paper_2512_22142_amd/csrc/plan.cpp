@@ -271,9 +271,12 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
     // A long table lists the last tiles first: what wrote or read the blocks before
     // (the executor, the returned-block check) went through them from the start, so
     // the end is what the Infinity Cache still holds, and going towards the start
-    // keeps ahead of what it evicts.  us behind execute, tiles in order / the other
-    // way round: 8192 x 3072, S = 2 50.8 / 48.2, 4096 x 11008, S = 4 136.5 / 134.5,
-    // 5120 x 13824, S = 8 475 / 457; no difference where all blocks fit.
+    // keeps ahead of what it evicts.  Aggregation behind execute, and both, us, tiles in
+    // order / the other way round: 8192 x 3072, S = 2 54.9 / 53.6 and 102.2 / 101.4; 5120^2,
+    // S = 4 79.2 / 77.6 and 173.7 / 172.6; 4096 x 11008, S = 4 135.6 / 132.9 and 267.5 /
+    // 262.5; 8192^2, S = 4 211.5 / 205.6 and 469 / 462.  With less than some 200 MB of
+    // blocks, on both sides of the line, no difference: 2048 x 1024, S = 2 (1024 runs)
+    // both 21.1 / 21.1, 2048^2, S = 4 (4096) 30.7 / 30.8, 4096^2, S = 2 (8192) 63.9 / 63.9.
     if (p->reduce_runs >= kLongTable) {
       std::reverse(p->reduce_tiles.begin(), p->reduce_tiles.end());
       uint64_t first = 0;

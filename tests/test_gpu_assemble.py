@@ -48,7 +48,7 @@ def test_assemble_equals_execute_plus_reduce_and_the_oracle(dtype, M, N, K, tm, 
 @pytest.mark.parametrize("pad,shift", [(24, 0), (25, 0), (24, 1), (25, 1)])
 def test_assemble_bf16_output_alignment_cases(pad, shift):
     """bf16 C with an even / odd leading dimension and a 4-byte / 2-byte aligned
-    origin: the two-element and the one-element store paths give the same bits."""
+    origin: the 16-byte pieces of the rows land there with the same bits."""
     M, N, K = 384, 320, 128
     A, B = make_matrix(311, M, K, "bf16"), make_matrix(312, K, N, "bf16", std=0.02)
     plan = cleave.plan_uniform(M, N, K, 256, 256, 1)

@@ -17,8 +17,8 @@ def _rounded(ref):
     return torch.from_numpy(ref).to(torch.bfloat16).view(torch.int16).numpy()
 
 
-# ld pad / origin in elements: rows on 16 bytes, on 8 bytes only (both the widest store the
-# sub-tile takes), and an origin that only takes element stores
+# ld pad / origin in elements: rows on 16 bytes, on 8 bytes only, and an origin on 4; the
+# sub-tile leaves in 16-byte pieces at all of them
 @pytest.mark.parametrize("pad,origin", [(8, 0), (4, 4), (12, 0), (8, 4), (4, 2)])
 @pytest.mark.parametrize("tile,steps", [(256, 1), (256, 2), (512, 3), (128, 1), (128, 2), (128, 5)])
 def test_assembled_bf16_rounds_and_stays_inside(tile, steps, pad, origin):

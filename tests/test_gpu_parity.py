@@ -118,9 +118,10 @@ def test_heterogeneous_plan_small():
 
 def test_mixed_chunk_lengths_reissue_bitwise():
     """Tiles whose chunks are whole K steps of the fast kernel next to tiles whose
-    chunks are not (K = 768: S = 1, 2, 4 give 768, 384, 192; S = 8 gives 96): a
-    block's bits depend on its own task record only, whichever other tasks run
-    in the same call and in whatever order they are listed."""
+    chunks end within one (K = 768: S = 1, 2, 4 give 768, 384, 192; S = 8 gives 96),
+    all of them the fast kernel's: a block's bits depend on its own task record
+    only, whichever other tasks run in the same call, in whatever order they are
+    listed, and in whichever shape of the kernel they run."""
     M, N, K = 768, 768, 768
     band_h = [512, 256]
     col_w = [[256, 512], [256, 256, 256]]

@@ -68,11 +68,11 @@ def test_many_short_items_per_workgroup_exact(cls, steps, transA, transB):
 
 @pytest.mark.parametrize("out", ["partials", "assembled_f32", "assembled_bf16"])
 def test_outputs_that_only_take_element_stores_exact(out):
-    """The fast kernel writes full sub-tiles with 16-byte stores when the output
-    allows them.  Here it does not: the partial workspace starts one element
-    into its allocation, the assembled output has an odd row pitch and starts
-    one element in.  Same kernel, element stores, several items per workgroup,
-    every value equal to the oracle's."""
+    """Outputs that are aligned to an element only: the partial workspace starts one
+    element into its allocation, the assembled output has an odd row pitch and
+    starts one element in.  The fast kernel writes its 16-byte pieces there all the
+    same, several items per workgroup; every value equals the oracle's, and nothing
+    is written beside the view."""
     M, N, tile = 8192, 4096, 256
     S = 4 if out == "partials" else 1
     K = 2 * K_STEP * S
