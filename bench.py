@@ -35,8 +35,8 @@ PEAK_HBM_GBPS = 8000.0
 # dropped on a mismatch.
 COUNTER_TRAFFIC = {
     "workload": "c3",
-    "sources_sha256": "08a6037743c3e407cb6bed2a1c3ddaea1e9a4d45f3f175f445b2f49a14e90801",
-    "execute_bytes_per_launch": (2.0 * 225530 + 388535) * 1024,
+    "sources_sha256": "4db04d67603f54d9443e154a21c4e42fcb54417ce097c68d1f43eedb10988d0f",
+    "execute_bytes_per_launch": (2.0 * 225658 + 388535) * 1024,
     "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
 
