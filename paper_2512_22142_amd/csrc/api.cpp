@@ -568,9 +568,14 @@ cleave::DirectShape direct_shape(int cls, int64_t items, int64_t steps, int cus)
 //   576 many 0.79 / 0.91  0.78 / 1.00  0.88 / 1.02  0.86 / 1.05  0.97 / 1.04  1.01 / 1.05
 //   640 few  0.85 / 1.03  0.83 / 1.13  0.92 / 1.23  0.92 / 1.25  0.95 / 1.33  1.25 / 1.37
 //   640 many 0.82 / 0.96  0.81 / 1.04  0.88 / 1.10  0.98 / 1.11  1.05 / 1.11  1.12 / 1.07
-// Each line lies where, over layouts, shapes and rims, a launch with its operands in
-// the caches still gains more than one with cold operands loses (576 few of 8 steps
-// and 192 few of 24 lose 1.07 and 1.04 of the two together, the others less).
+// Operands are rarely as cold as that in a layer's pass: beside a rim of an eighth to
+// a half of the large items its launches gain to the further lines (passes of layers
+// and linears whose launches lie between the two, small / large cut: 208 items and 52
+// small of 17 steps 1908 / 1960, 224 and 108 of 24 2468 / 2513, 522 and 154 of 20 1992
+// / 2034, 528 and 96 of 18 1226 / 1244, 576 and 196 of 18 490 / 508 us).  Beside fewer
+// they do not (one product, three sets of operands in turn: 224 and 8 of 20 steps 83 /
+// 69, 384 and 8 of 12 104 / 93, 544 and 8 of 24 211 / 187, 576 and 8 of 10 142 / 127,
+// 640 and 8 of 5 123 / 110 with an output 1024 wide; square 0.94 to 1.07).
 // Lists with items of other lengths among them keep the balanced schedule of
 // both classes: rounds say nothing about those (caches as above: 320 items of 3
 // and 1 steps 1.12 / 1.06; 16 steps and a few of 8, 269 items 1.04 / 1.15, 286
@@ -583,18 +588,21 @@ bool cut_small(const cleave_plan* plan, int cus) {
   const bool equal = steps - plan->large_steps_least <= 1;   // but for a shorter last chunk
   const int64_t rim = static_cast<int64_t>(plan->items[cleave::kTileSmall].size());
   if (!equal || rim > n) return false;
+  const bool few = 8 * rim < n, many = 2 * rim > n;
   switch (n / cus) {
     case 0:
-      if (rim > 0) return (4 * n <= 3 * cus && steps <= 24) || (8 * n <= 7 * cus && steps <= 12);
+      if (rim > 0) return (4 * n <= 3 * cus && steps <= 24) || (8 * n <= 7 * cus && steps <= (few || many ? 12 : 24));
       return 4 * n <= 3 * cus && steps <= 4;
     case 1:
       if (over == 0) return false;
       if (8 * over <= cus) return true;
-      if (rim > 0) return (8 * over <= 3 * cus && steps <= 24) || (2 * over <= cus && steps <= 8);
+      if (rim > 0) return (8 * over <= 3 * cus && steps <= 24) || (2 * over <= cus && steps <= (few ? 8 : 12));
       return 4 * over <= cus && steps <= 16;
     case 2:
       if (over == 0) return false;
-      if (rim > 0) return (8 * over <= cus && steps <= 16) || (4 * over <= cus && steps <= 8) || (2 * over <= cus && steps <= 4);
+      if (rim > 0 && few)
+        return (8 * over <= cus && steps <= 16) || (4 * over <= cus && steps <= 8) || (2 * over <= cus && steps <= 4);
+      if (rim > 0) return (4 * over <= cus && steps <= 24) || (2 * over <= cus && steps <= 8);
       return 8 * over <= cus && steps <= 8;
     default: return false;
   }

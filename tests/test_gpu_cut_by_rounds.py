@@ -52,10 +52,15 @@ def test_cut_at_the_lines(rows, cols, steps, kernel):
 
 
 @pytest.mark.parametrize("rows,cols,steps,kernel", [
-    (16, 12, 24, SMALL), (16, 12, 25, LARGE), (16, 14, 12, SMALL), (16, 14, 13, LARGE), (16, 15, 2, LARGE), (16, 16, 2, LARGE),
-    (16, 22, 24, SMALL), (16, 22, 25, LARGE), (16, 24, 8, SMALL), (16, 24, 9, LARGE), (16, 25, 2, LARGE),
+    (16, 14, 24, SMALL), (16, 14, 25, LARGE), (16, 15, 2, LARGE), (16, 16, 2, LARGE),
+    (16, 22, 24, SMALL), (16, 24, 12, SMALL), (16, 24, 13, LARGE), (16, 25, 2, LARGE),
+    (16, 36, 24, SMALL), (16, 36, 25, LARGE), (16, 40, 8, SMALL), (16, 40, 9, LARGE), (16, 41, 2, LARGE),
+    # less than one small block to eight large ones
+    (28, 8, 12, SMALL), (28, 8, 13, LARGE), (24, 8, 24, SMALL), (24, 8, 25, LARGE), (32, 12, 8, SMALL), (32, 12, 9, LARGE),
     (32, 16, 2, LARGE), (32, 17, 16, SMALL), (32, 17, 17, LARGE), (32, 18, 8, SMALL), (32, 18, 9, LARGE),
     (32, 20, 4, SMALL), (32, 20, 5, LARGE), (32, 21, 2, LARGE),
+    # more than one to two
+    (2, 112, 12, SMALL), (2, 112, 13, LARGE),
 ])
 def test_cut_at_the_lines_with_a_rim_of_small_blocks(rows, cols, steps, kernel):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
