@@ -413,6 +413,46 @@ struct AssembleTarget {
   int out_dtype = CLEAVE_F32;
 };
 
+// Bytes of the Infinity Cache: what is written last, up to that much, is still
+// there when the next launch reads it.
+constexpr int64_t kCacheBytes = int64_t{256} << 20;
+
+// The work items of a full launch whose chunk starts below the returned k leave
+// through non-temporal stores.  An output that the cache cannot hold pushes its own
+// first part (and the operands) out of it, and the next launch waits for those
+// write-backs; a streamed one goes to memory without them.  One that it can hold is
+// read from there by whoever comes next.
+//   Assembled outputs: streamed from the cache's size on.  Scores of 1024 x 1024 x
+// 128 members into bf16, us, plain / streamed: the launch alone 33.4 / 33.0 for 134
+// MB, 72 / 51 for 235 MB, 86 / 57 for 268 MB; with a softmax that reads them 136 /
+// 148, 267 / 257, 302 / 289; with an update in place 71 / 76, 137 / 136, 160 / 160.
+//   Partial blocks of uniform plans (their items run chunk by chunk): execute +
+// reduce over plain, all chunks but the last streamed / all of them streamed:
+//   blocks of a chunk x chunks
+//    67 MB x 4   1.031, 0.998 / 1.043, 1.005      67 MB x 8   0.893, 0.894 / 0.907, 0.901
+//   134 MB x 2   1.034, 0.992 / 1.033, 0.991     134 MB x 4   0.884, 0.927 / 0.904, 0.920
+//   134 MB x 8   0.911, 0.975 / 0.862, 0.992     180 MB x 2   0.969, 0.955 / 0.979, 0.954
+//   180 MB x 4   0.945, 0.980 / 0.925, 0.965     180 MB x 8   0.984, 0.978 / 0.922, 0.988
+//   268 MB x 4   1.001, 0.986 / 0.921, 1.005     268 MB x 8   0.968, 0.984 / 0.988, 0.981
+//   336 MB x 2   0.976, 0.985 / 1.029, 1.002     336 MB x 8   0.955, 0.974 / 0.959, 0.967
+//   453 MB x 2   0.989, 0.991 / 1.012, 0.996     453 MB x 4   0.967, 0.980 / 0.971, 0.980
+//   453 MB x 8   0.981 / 0.971                   537 MB x 2   1.011, 1.007 / 1.025, 1.015
+//   537 MB x 4   0.977, 0.989 / 0.974, 0.982     537 MB x 8   0.972 / 0.958
+//   906 MB x 2   0.985, 0.991 / 0.970, 0.981     906 MB x 8   0.891 / 0.879
+// (chunks of 512 and of 1024 elements, 1024 alone where one figure is given).
+uint32_t streamed_below(const cleave_plan* plan, const AssembleTarget& asm_to) {
+  const int64_t members = std::max<int64_t>(plan->batch, 1);
+  const int64_t outputs = plan->M * plan->N * members;
+  if (asm_to.C) {
+    const int64_t bytes = outputs * (asm_to.out_dtype == CLEAVE_BF16 ? 2 : 4);
+    return bytes >= kCacheBytes ? static_cast<uint32_t>(plan->K) : 0;
+  }
+  const int64_t splits = plan->uniform_splits;
+  if (splits < 2 || 4 * plan->partial_elems < kCacheBytes / 4 * 5) return 0;
+  const bool all = 4 * outputs >= 3 * kCacheBytes || (4 * outputs >= kCacheBytes / 2 * 3 && splits >= 4);
+  return static_cast<uint32_t>(all ? plan->K : (splits - 1) * ((plan->K + splits - 1) / splits));
+}
+
 // Where the work items of a subset go: one list per tile class, in the caller's
 // order (the layout of the plan's own lists).
 struct SubsetLayout {
@@ -734,6 +774,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     args.N = plan->N;
     args.K = plan->K;
     args.ldc = asm_to.ldc;
+    args.stream_below_k = task_ids ? 0 : streamed_below(plan, asm_to);
     args.c_bf16 = asm_to.out_dtype == CLEAVE_BF16 ? 1 : 0;
     const bool large = c == cleave::kTileLarge;
     if (direct) {
@@ -1157,6 +1198,18 @@ struct AggregateTarget {
   int out_dtype = CLEAVE_F32;
 };
 
+// Whether the check writes the sum with non-temporal stores: an fp32 sum that takes up
+// much of the cache.  us, plain / streamed, blocks not in any cache, the pass alone and
+// with a launch behind it that reads the sum and writes another matrix, or updates
+// it in place: 67 MB in 4 splits 67 / 70, 87 / 94, 87 / 93; 134 MB in 4 125 / 129,
+// 182 / 180, 164 / 171; 180 MB in 2 110 / 103, 174 / 170, 166 / 163, in 4 177 /
+// 164, 240 / 230, 231 / 222, in 8 321 / 309, 386 / 374, 375 / 367; 268 MB in 4 262 /
+// 255, 349 / 348, 345 / 352.  The linear layer's three GEMMs one behind the other
+// (180, 67 and 180 MB in 4 splits) 524 / 470 with all three streamed.
+bool streamed_sum(const cleave_plan* plan, const AggregateTarget& agg) {
+  return agg.out_dtype == CLEAVE_F32 && 4 * plan->M * plan->N >= (int64_t{160} << 20);
+}
+
 int verify_impl(cleave_plan* plan, const void* A, int64_t lda, int transA, const void* B, int64_t ldb,
                 int transB, int dtype, const float* partials, const float* r, const float* s, double tol,
                 double* lhs, double* rhs, double* scale, int32_t* accept, const BatchLayout& bl,
@@ -1226,7 +1279,8 @@ int verify_impl(cleave_plan* plan, const void* A, int64_t lda, int transA, const
     fused.B = pass.B;
     fused.bil = pass.bil;
     fused.bil.item_sums = v->d_agg_item_sums;
-    fused.agg = cleave::AggregateArgs{v->d_agg_items, static_cast<int64_t>(v->agg_items.size()), agg.C, agg.ldc, agg.out_dtype == CLEAVE_BF16 ? 1 : 0};
+    fused.agg = cleave::AggregateArgs{v->d_agg_items, static_cast<int64_t>(v->agg_items.size()), agg.C, agg.ldc, agg.out_dtype == CLEAVE_BF16 ? 1 : 0,
+                                      streamed_sum(plan, agg) ? 1 : 0};
     CLEAVE_HIP(cleave::launch_verify_reduce_pass(fused, dtype, a_contig, b_contig,
                                                  a_vec && b_vec && p_vec && c_vec, stream));
   } else {

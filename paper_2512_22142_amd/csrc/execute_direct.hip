@@ -661,12 +661,20 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     // The ring is free unless it was handed over: the next item's ring fill is
     // issued before this item's stores so that its latency hides behind them.
     if (!cont && has_next) fill_ring(nx);
+    const auto leave = [&](auto bf16_tag, auto interior_tag, auto stream_tag) {
+      store_rows<decltype(bf16_tag)::value, decltype(interior_tag)::value, decltype(stream_tag)::value, MB, NB>(
+          acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
     if (!bf16_out) {
-      if (interior) store_rows<false, true, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
-      else store_rows<false, false, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
+      if (!interior) leave(no, no, no);
+      else if (!S::ONE_ITEM && target.stream) leave(no, yes, yes);
+      else leave(no, yes, no);
     } else {
-      if (interior) store_rows<true, true, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
-      else store_rows<true, false, MB, NB>(acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
+      if (!interior) leave(yes, no, no);
+      else if (!S::ONE_ITEM && target.stream) leave(yes, yes, yes);
+      else leave(yes, yes, no);
     }
     entry = cont ? kPrefetched : interior ? kFilledBehindStores : kFilled;
     phase = cont ? (phase + steps) & (STAGES - 1) : 0;

@@ -50,6 +50,9 @@ struct ExecuteArgs {
   void* C;
   int64_t ldc;
   int c_bf16;
+  // Direct kernel only: work items whose chunk starts below this k leave through
+  // non-temporal stores (streamed_below in api.cpp).
+  uint32_t stream_below_k;
   // General kernel only: extent of the logical operands (loads stay inside them)
   // and the workgroup tiles per work item (filled in at the launch).
   int64_t M, N, K;
@@ -225,6 +228,7 @@ struct AggregateArgs {
   void* C;
   int64_t ldc;                    // elements
   int out_bf16;
+  int stream;                     // fp32 sums leave through non-temporal stores
 };
 struct VerifyReducePassArgs {
   ProjectArgs A, B;

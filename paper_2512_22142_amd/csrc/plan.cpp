@@ -377,7 +377,9 @@ extern "C" int cleave_plan_uniform(int64_t M, int64_t N, int64_t K, int64_t tile
   } catch (const std::bad_alloc&) {
     return CLEAVE_ENOMEM;
   }
-  return cleave::finish_plan(M, N, K, tiles, gemm_id, out);
+  const int rc = cleave::finish_plan(M, N, K, tiles, gemm_id, out);
+  if (rc == CLEAVE_OK) (*out)->uniform_splits = ksplit;
+  return rc;
 }
 
 extern "C" int cleave_plan_batched(int64_t M, int64_t N, int64_t K, int64_t tile_m, int64_t tile_n,

@@ -283,6 +283,7 @@ struct cleave_plan {
   int64_t partial_elems = 0;
   int64_t num_tiles = 0;
   int64_t batch = 0;         // > 0: a batch of that many M x N x K GEMMs, task.gemm_id = member
+  int64_t uniform_splits = 0;   // plain plans whose tiles all have that many splits (0: others)
   bool all_k_mult8 = true;   // every k0 and k_len is a multiple of 8
   bool all_m_mult8 = true;   // every m0 and m_len is a multiple of 8
   bool all_n_mult8 = true;   // every n0 and n_len is a multiple of 8

@@ -21,6 +21,7 @@ typedef float tile_f32x4 __attribute__((ext_vector_type(4)));
 struct TileTarget {
   unsigned char* base;
   int64_t ld;
+  bool stream;
 };
 
 // Partial mode (args.C == nullptr): the benchmark's fp32 block, row-major
@@ -30,6 +31,7 @@ struct TileTarget {
 // for tasks that cover the whole inner dimension.
 __device__ __forceinline__ TileTarget tile_target(const ExecuteArgs& args, const WorkItem& w) {
   TileTarget t;
+  t.stream = w.k0 < args.stream_below_k;
   if (args.C == nullptr) {
     t.ld = w.out_ld;
     t.base = reinterpret_cast<unsigned char*>(args.partials + w.out_off);
@@ -99,7 +101,11 @@ __device__ __forceinline__ void store_blocks(const tile_f32x16 (&acc)[MB][NB], T
 // accesses in issue order, and the compiler is kept from reordering them by the
 // asm statements; no other wave touches the image, so no barrier is involved.
 constexpr int kBlockImageBytes = 16 * 64 * 4;
-template <bool BF16, bool INTERIOR, int MB, int NB>
+//
+// STREAM: non-temporal stores, for outputs that the caches cannot hold until they
+// are read (ExecuteArgs::stream_below_k).  The differing asm statements keep the
+// compiler from merging this form with the other one, which would drop the hint.
+template <bool BF16, bool INTERIOR, bool STREAM, int MB, int NB>
 __device__ __forceinline__ void store_rows(const tile_f32x4 (&acc)[MB][NB], const TileTarget& t, unsigned char* image,
                                            int wave_row0, int wave_col0, int lane, int m_valid, int n_valid) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -119,7 +125,8 @@ __device__ __forceinline__ void store_rows(const tile_f32x4 (&acc)[MB][NB], cons
   const int64_t pitch = t.ld * EB;
 #pragma unroll
   for (int i = 0; i < MB; ++i, gp += 16 * pitch) {
-    asm volatile("" ::: "memory");
+    if constexpr (STREAM) asm volatile("; streamed" ::: "memory");
+    else asm volatile("" ::: "memory");
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       if constexpr (BF16) {
@@ -140,9 +147,13 @@ __device__ __forceinline__ void store_rows(const tile_f32x4 (&acc)[MB][NB], cons
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int k = 0; k < 16 / RR; ++k)
-      if (INTERIOR || (row + i * 16 + RR * k < m_valid && col < n_valid))
-        *reinterpret_cast<u32x4_any*>(gp + RR * k * pitch) = v[k];
+      if (INTERIOR || (row + i * 16 + RR * k < m_valid && col < n_valid)) {
+        u32x4_any* const to = reinterpret_cast<u32x4_any*>(gp + RR * k * pitch);
+        if constexpr (STREAM) __builtin_nontemporal_store(v[k], to);
+        else *to = v[k];
+      }
   }
+  if constexpr (STREAM) asm volatile("; end of streamed stores" ::: "memory");
 }
 
 template <int MB, int NB>

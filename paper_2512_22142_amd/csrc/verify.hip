@@ -435,6 +435,11 @@ __device__ __forceinline__ void aggregate_item(const BilinearArgs& a, const Aggr
             w[0] = pack_bf16(sum[0], sum[1]);
             w[1] = pack_bf16(sum[2], sum[3]);
             *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(g.C) + off) = w;
+          } else if (g.stream) {
+            // (the asm statements keep the compiler from merging this with the plain store, hint lost)
+            asm volatile("; streamed" ::: "memory");
+            __builtin_nontemporal_store(sum, reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + off));
+            asm volatile("; streamed" ::: "memory");
           } else {
             *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + off) = sum;
           }
