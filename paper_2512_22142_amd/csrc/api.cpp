@@ -773,6 +773,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     args.M = plan->M;
     args.N = plan->N;
     args.K = plan->K;
+    args.cus = cus;
     args.ldc = asm_to.ldc;
     args.stream_below_k = task_ids ? 0 : streamed_below(plan, asm_to);
     args.c_bf16 = asm_to.out_dtype == CLEAVE_BF16 ? 1 : 0;

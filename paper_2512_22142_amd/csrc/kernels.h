@@ -57,6 +57,7 @@ struct ExecuteArgs {
   // and the workgroup tiles per work item (filled in at the launch).
   int64_t M, N, K;
   int parts_m, parts_n;
+  int cus;   // of the device
   // Direct kernel only, shapes with several items per workgroup.  Null:
   // workgroup b takes items b, b + grid, ...  Otherwise grid + 1 entries:
   // workgroup b takes items [wg_ranges[b], wg_ranges[b + 1]).
