@@ -318,16 +318,19 @@ int release_subset_slice(cleave::SubsetRing& r, int64_t begin, int64_t total, hi
 }
 
 const char* kernel_name(int dtype, const cleave::GeneralLoads& how, int transA, int transB) {
-  static const char* names[2][4][4] = {
+  static const char* names[2][5][4] = {
       {{"execute_f32_128x128_nn", "execute_f32_128x128_nt", "execute_f32_128x128_tn", "execute_f32_128x128_tt"},
        {"execute_f32_64x64_nn", "execute_f32_64x64_nt", "execute_f32_64x64_tn", "execute_f32_64x64_tt"},
        {"none", "none", "none", "none"},
+       {"execute_f32_64x64_quarters_nn", "execute_f32_64x64_quarters_nt", "execute_f32_64x64_quarters_tn",
+        "execute_f32_64x64_quarters_tt"},
        {"execute_f32_element", "execute_f32_element", "execute_f32_element", "execute_f32_element"}},
       {{"execute_bf16_128x128_nn", "execute_bf16_128x128_nt", "execute_bf16_128x128_tn", "execute_bf16_128x128_tt"},
        {"execute_bf16_64x64_nn", "execute_bf16_64x64_nt", "execute_bf16_64x64_tn", "execute_bf16_64x64_tt"},
        {"none", "execute_bf16_256x256_nt", "none", "none"},
+       {"none", "none", "none", "none"},
        {"execute_bf16_element", "execute_bf16_element", "execute_bf16_element", "execute_bf16_element"}}};
-  const int row = how.a_elements || how.b_elements ? 3 : how.tile;
+  const int row = how.a_elements || how.b_elements ? 4 : how.tile;
   return names[dtype == CLEAVE_BF16 ? 1 : 0][row][(transA ? 2 : 0) + (transB ? 1 : 0)];
 }
 
@@ -526,6 +529,14 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // the wide tile leaves half of the CUs without a workgroup (1000^3, 128 items
 // 13.8 / 11.3; 2001x768x3072, 192 items 27.4 / 29.7; 3001x2999x1001, 1152
 // items 44 / 55).
+// Few fp32 items run as quarters of the 64 x 64 tile, up to two on each CU: a wave's
+// chain of matrix instructions is what such a launch takes, and a quarter's is a
+// quarter as long (with four times the waves, half as many products per load).
+// Execute + reduce, us, 64 x 64 / quarters, layouts NN, NT, TN: 16 items of 256 of K
+// 12.4 / 10.5, 12.0 / 10.9, 12.4 / 10.2; 32 items of 128 10.3 / 10.1, 10.1 / 10.6,
+// 10.5 / 9.7, of 256 12.7 / 11.5, 12.4 / 12.5, 12.8 / 11.0, of 1024 28.4 / 21.1, 28.1 /
+// 24.7, 28.6 / 19.7; 40 items of 256 12.8 / 13.1, 12.6 / 14.0, 12.9 / 12.1; 64 of 512
+// 19.3 / 21.3, 18.8 / 22.7, 19.3 / 19.1.
 // `whole`: that many 256 x 256 items of a subset (full launches of this kernel run
 // the all-small list), with `steps` whole K steps between them, that the kernel
 // could take as they are (bf16, both operands K-contiguous: six
@@ -538,6 +549,7 @@ cleave::ExecuteTile general_tile(int dtype, int64_t items, int64_t whole, int64_
   const int64_t places = (whole + cus - 1) / cus * cus;
   if (whole > 0 && whole * 8 >= places * 7 && steps >= 16 * whole) return cleave::kTileHuge;
   const int64_t narrow_up_to = dtype == CLEAVE_BF16 ? cus / 2 : int64_t{4} * cus - 1;
+  if (dtype == CLEAVE_F32 && 8 * items <= cus) return cleave::kTileQuarter;
   return items <= narrow_up_to ? cleave::kTileNarrow : cleave::kTileWide;
 }
 

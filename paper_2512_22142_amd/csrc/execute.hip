@@ -13,7 +13,8 @@
 // kernel's), which is what makes a re-issued task bitwise reproducible.
 //
 // Data path per K step: global -> VGPR in 16-byte loads -> LDS -> fragments ->
-// MFMA 32x32x16 bf16 (or 32x32x2 fp32) into fp32 accumulators.
+// MFMA 32x32x16 bf16 (or 32x32x2 fp32, 16x16x4 in the smallest tile) into fp32
+// accumulators.
 //   * The loads need only the alignment of an element (global memory takes
 //     16-byte loads at any address), so an odd leading dimension or chunk
 //     start costs a second cache line per row, not sixteen-fold instructions.
@@ -82,10 +83,13 @@ struct Shape {
   static constexpr int E = 16 / EB;             // elements per 16-byte chunk
   static constexpr int KS = 128 / EB;           // elements of K per step
   static constexpr int WTM = TM / WM, WTN = TN / WN;
-  static constexpr int MB = WTM / 32, NB = WTN / 32;
+  // MFMA block: 32 x 32 (x 2, or 16 for bf16), or, fp32 wave tiles of one, 16 x 16 (x 4)
+  static constexpr int BLK = WTM < 32 ? 16 : 32;
+  static constexpr int MB = WTM / BLK, NB = WTN / BLK;
   static constexpr int kSub = 4;                // 32-byte sub-steps per step
   static constexpr int kATile = TM * 128, kBTile = TN * 128;   // bytes
   static constexpr int kStage = kATile + kBTile;
+  static_assert(BLK == 32 || (EB == 4 && MB == 1 && NB == 1), "16 x 16: one block per wave, fp32");
   static_assert(SETS == 1 || SETS == 2, "register sets rotate with the two LDS stages");
 };
 
@@ -128,7 +132,7 @@ struct OperandTile {
   static_assert(R * 8 % NT == 0, "tile / thread count");
 
   static __device__ __forceinline__ int k_swizzle(int k) {
-    if constexpr (EB == 4) return 8 * ((k >> 2) & 1);
+    if constexpr (EB == 4) return (CH == 8 ? 4 : 8) * ((k >> 2) & 1);
     else if constexpr (CH == 8) return 4 * ((k >> 1) & 1);
     else return 4 * (k & 3);
   }
@@ -296,14 +300,16 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / S::WN;
   const int wn = wave % S::WN;
-  const int l32 = lane & 31;
-  const int lh = lane >> 5;
+  const int l32 = lane & (S::BLK - 1);   // row (column) of an MFMA block
+  const int lh = S::BLK == 32 ? lane >> 5 : (lane >> 4) & 1;
+  const int l4 = lane >> 5;              // 16 x 16 blocks: which of two neighbouring k
 
   // Lane-constant fragment addresses inside a stage: K-contiguous operands one
   // per sub-step (blocks are 32 rows apart), others one per block.
   const int i16 = lane & 15, kq = i16 >> 2, cq = i16 & 3, nsub = (lane >> 4) & 1;
   const auto frag_addr = [&](int row0, int x, int r_tile, bool kcontig) -> uint32_t {
-    if (kcontig) return (row0 + l32) * 128 + (((2 * x + lh) ^ ((l32 >> 1) & 7)) * 16);
+    if (kcontig) return (row0 + l32) * 128 + (((2 * x + lh) ^ ((l32 >> 1) & 7)) * 16) + (S::BLK == 16 ? 4 * l4 + 8 * lh : 0);
+    if (S::BLK == 16) return ((4 * lh + l4) * r_tile + ((row0 + l32) ^ (16 * lh))) * 4;
     if (EB == 4) return (4 * lh * r_tile + ((row0 + x * 32 + l32) ^ (32 * lh))) * 4;
     const int ch = r_tile / 8;
     const int k = 8 * lh + kq;
@@ -352,11 +358,12 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
                  static_cast<int64_t>(item.k0) * b_ks) * EB,
             b_rs, b_ks, n_valid, n_base, args.N, item.k0, k_len, args.K, t);
 
-    f32x16 acc[MB][NB];
+    typedef typename std::conditional<S::BLK == 32, f32x16, f32x4>::type block_t;
+    block_t acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int jn = 0; jn < NB; ++jn) acc[i][jn] = f32x16{};
+      for (int jn = 0; jn < NB; ++jn) acc[i][jn] = block_t{};
 
     u32x4 va[SETS][ta.NV], vb[SETS][tb.NV];
     auto fetch = [&](auto set_tag, int s) {
@@ -380,7 +387,16 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
                          auto ks_tag, int x) -> u32x4 {
       constexpr bool KC = decltype(kcontig_tag)::value;
       constexpr int R = decltype(rows_tag)::value, KSUB = decltype(ks_tag)::value;
-      if constexpr (KC) {
+      if constexpr (S::BLK == 16 && KC) {
+        // k of the sub-step: 4 lh + l4, and two further on; half of the lanes read them
+        // the other way round, so that the 64 words are in different banks
+        const uint32_t one = *reinterpret_cast<const uint32_t*>(stage + addr[KSUB]);
+        const uint32_t two = *reinterpret_cast<const uint32_t*>(stage + (addr[KSUB] ^ 8));
+        return lh ? u32x4{two, one, 0, 0} : u32x4{one, two, 0, 0};
+      } else if constexpr (S::BLK == 16) {
+        const uint32_t* q = reinterpret_cast<const uint32_t*>(stage + addr[x] + KSUB * (8 * R * 4));
+        return u32x4{q[0], q[2 * R], 0, 0};
+      } else if constexpr (KC) {
         return *reinterpret_cast<const u32x4*>(stage + addr[KSUB] + x * 32 * 128);
       } else if constexpr (EB == 2) {
         const unsigned char* q = stage + addr[x] + KSUB * (16 * R * 2);
@@ -400,7 +416,14 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
         fb[buf][i] = read_frag(smem + stage * S::kStage, b_addr, std::bool_constant<B_K>{}, int_c<TN>{}, ks_tag, i);
     };
     auto mma = [&](int buf) {
-      if constexpr (EB == 2) {
+      if constexpr (S::BLK == 16) {
+        // One instruction multiplies k, k + 4, k + 1, k + 5 of a sub-step, in this order
+        // (lanes 0-15, 16-31, ...): the chain of two 32 x 32 x 2 ones, bit for bit.
+        const f32x4 a4 = __builtin_bit_cast(f32x4, fa[buf][0]);
+        const f32x4 b4 = __builtin_bit_cast(f32x4, fb[buf][0]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[e], b4[e], acc[0][0], 0, 0, 0);
+      } else if constexpr (EB == 2) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -464,8 +487,12 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
     const int col0 = wn * S::WTN + l32;
     TileTarget target = tile_target(args, item);
     target.base += (m_off * target.ld + n_off) * (args.C && args.c_bf16 ? 2 : 4);
-    store_tile<MB, NB>(acc, target, args.C && args.c_bf16, row0, col0, m_valid, n_valid,
-                       m_valid == TM && n_valid == TN);
+    if constexpr (S::BLK == 16) {
+      store_block(acc[0][0], target, args.C && args.c_bf16, wm * S::WTM + 4 * (lane >> 4), col0, m_valid, n_valid);
+    } else {
+      store_tile<MB, NB>(acc, target, args.C && args.c_bf16, row0, col0, m_valid, n_valid,
+                         m_valid == TM && n_valid == TN);
+    }
   }
 }
 
@@ -546,6 +573,9 @@ hipError_t launch_elements(ExecuteArgs args, int tile_class, bool a_elements, bo
                      : launch_one<S, kByK, kElements>(args, grid, stream);
 }
 
+// Quarters of the 64 x 64 tile, a 16 x 16 block per wave, for launches of few fp32
+// items (general_tile in api.cpp).
+using Quarter = Shape<4, 32, 32, 2, 2, 2, 8>;
 template <int EB>
 using Wide = Shape<EB, 128, 128, 2, 2, 2, 2>;
 using Large = Shape<2, kLargeTileRows, kLargeTileCols, 2, 4, 1, 2>;
@@ -559,6 +589,7 @@ hipError_t configure_type() {
   hipError_t e = configure_layouts<Wide<EB>>();
   if (e == hipSuccess) e = configure_layouts<Narrow<EB>>();
   if (e == hipSuccess) e = configure_elements<ByElement<EB>>();
+  if (EB == 4 && e == hipSuccess) e = configure_layouts<Quarter>();
   if (EB == 2 && e == hipSuccess) e = configure_one<Large, kByK, kByK>();
   return e;
 }
@@ -572,6 +603,7 @@ hipError_t launch_type(const ExecuteArgs& args, int tile_class, const GeneralLoa
     const int grid = cut_items<Large>(&whole, tile_class);
     return launch_one<Large, kByK, kByK>(whole, grid, stream);
   }
+  if (EB == 4 && how.tile == kTileQuarter) return launch_layouts<Quarter>(args, tile_class, stream);
   return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, stream)
                                  : launch_layouts<Wide<EB>>(args, tile_class, stream);
 }

@@ -64,9 +64,10 @@ struct ExecuteArgs {
   const uint32_t* wg_ranges;
 };
 
-// Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, or 256 x 256
-// (only for bf16 work items of the large class with both operands K-contiguous).
-enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2 };
+// Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, 256 x 256
+// (only for bf16 work items of the large class with both operands K-contiguous), or
+// the quarters of the 64 x 64 one (32 x 32, only fp32).
+enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2, kTileQuarter = 3 };
 // An operand with rows shorter than 16 bytes is loaded one element at a time
 // (64 x 64 tile, whatever `tile`); the other one still takes 16-byte loads.
 struct GeneralLoads {

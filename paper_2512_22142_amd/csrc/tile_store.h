@@ -156,6 +156,19 @@ __device__ __forceinline__ void store_rows(const tile_f32x4 (&acc)[MB][NB], cons
   if constexpr (STREAM) asm volatile("; end of streamed stores" ::: "memory");
 }
 
+// One 16 x 16 block: lane l has column l % 16 and rows 4 (l / 16) .. + 3.
+__device__ __forceinline__ void store_block(tile_f32x4 acc, const TileTarget& t, bool bf16, int row0, int col0,
+                                            int m_valid, int n_valid) {
+  if (col0 >= n_valid) return;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (row0 + r >= m_valid) break;
+    const int64_t at = (row0 + r) * t.ld + col0;
+    if (bf16) reinterpret_cast<uint16_t*>(t.base)[at] = to_bf16_bits(acc[r]);
+    else reinterpret_cast<float*>(t.base)[at] = acc[r];
+  }
+}
+
 template <int MB, int NB>
 __device__ __forceinline__ void store_tile(const tile_f32x16 (&acc)[MB][NB], const TileTarget& t,
                                            bool bf16, int row0, int col0, int m_valid,

@@ -1,0 +1,81 @@
+"""Few fp32 work items run as 32 x 32 quarters of the 64 x 64 tile (16 x 16 matrix
+blocks): the bits of the same tasks in a launch of many, and the oracle's values at the
+edges of the tile, of the K step and of the chip's rounds of workgroups."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_22142_amd as cleave
+from oracle import gemm as og
+from workloads.tensors import make_matrix
+
+from gpu_util import TOL, block_of, stored
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = [(0, 0), (0, 1), (1, 0), (1, 1)]
+
+
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+@pytest.mark.parametrize("K", [8, 31, 32, 33, 96, 301])
+def test_a_few_tasks_have_the_bits_of_the_full_launch(K, transA, transB):
+    M, N = 1309, 505                                   # 11 x 4 tiles, the last ones clipped
+    A = stored(make_matrix(21, M, K, "f32"), transA)
+    B = stored(make_matrix(22, K, N, "f32"), transB)
+    plan = cleave.plan_uniform(M, N, K, 128, 128, 1)
+    dA, dB = A.cuda(), B.cuda()
+    full = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
+    cleave.execute(plan, dA, dB, full, transA, transB)
+    assert plan.num_tasks == 44 and "f32_64x64" in plan.last_kernel and "quarters" not in plan.last_kernel
+    ids = [0, 3, 17, 40, 43]
+    few = torch.full_like(full, float("nan"))
+    cleave.execute(plan, dA, dB, few, transA, transB, task_ids=ids)
+    assert "quarters" in plan.last_kernel
+    torch.cuda.synchronize()
+    full, few = full.cpu().numpy(), few.cpu().numpy()
+    opA, opB = og.logical_operands(A, transA, B, transB)
+    exact = og.gemm(opA, opB)
+    for i, t in enumerate(plan.tasks):
+        got = block_of(few, t)
+        if i not in ids:
+            assert np.isnan(got).all()
+            continue
+        assert np.array_equal(got, block_of(full, t))
+        m0, n0 = int(t["m0"]), int(t["n0"])
+        ref = exact[m0:m0 + got.shape[0], n0:n0 + got.shape[1]]
+        assert og.rel_frobenius(got, ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M,N", [(1, 7), (15, 17), (16, 16), (31, 33), (32, 32), (65, 63)])
+def test_assembled_edges_of_the_quarter(M, N, out_dtype):
+    K = 40
+    A, B = make_matrix(23, M, K, "f32"), make_matrix(24, K, N, "f32")
+    plan = cleave.plan_uniform(M, N, K, 128, 128, 1)
+    wide = torch.full((M, N + 3), float("nan"), dtype=out_dtype, device="cuda")
+    cleave.execute_assemble(plan, A.cuda(), B.cuda(), wide[:, :N])
+    parts = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
+    cleave.execute(plan, A.cuda(), B.cuda(), parts)
+    C = torch.empty((M, N), dtype=out_dtype, device="cuda")
+    cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    assert torch.equal(wide[:, :N], C) and bool(torch.isnan(wide[:, N:].float()).all())
+    # bf16 output: one rounding of a value within the fp32 bar
+    assert og.rel_frobenius(C.float().cpu().numpy(), og.gemm(*og.logical_operands(A, 0, B, 0))) <= (TOL["f32"] if out_dtype == torch.float32 else 2.0 ** -8)
+
+
+@pytest.mark.parametrize("dtype,M,N,K,S", [("bf16", 1025, 1999, 131, 4), ("bf16", 1151, 2175, 67, 2), ("f32", 2100, 2000, 40, 1),
+                                           ("f32", 2177, 1921, 33, 1)])
+def test_between_one_and_two_rounds_of_workgroups(dtype, M, N, K, S):
+    """Integer-valued inputs: every block exact, whoever computes it."""
+    g = torch.Generator().manual_seed(5)
+    A = torch.randint(-3, 4, (M, K), generator=g).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    B = torch.randint(-3, 4, (K, N), generator=g).to(A.dtype)
+    plan = cleave.plan_uniform(M, N, K, 128, 128, S)
+    parts = torch.full((plan.partial_elems,), float("nan"), dtype=torch.float32, device="cuda")
+    C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        cleave.execute(plan, A.cuda(), B.cuda(), parts)
+        cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    assert torch.equal(C.cpu(), (A.double() @ B.double()).float())
