@@ -522,13 +522,15 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // Workgroup tile of the general kernel for `items` 128 x 128 work items.  The
 // 64 x 64 tile gives four times as many workgroups, four of them per CU
 // instead of two, at twice the LDS traffic per flop.  fp32 MFMAs leave the LDS
-// mostly idle, so there the narrow tile wins until the wide one has several
-// rounds of workgroups (us, wide / narrow: 512^3 with 32 items 22 / 10,
-// 768x3072x2048 with 288 items 128 / 89, 2048x3072x768 with 768 items 90 / 92,
-// 4096^3 with 4096 items 999 / 1046).  bf16 MFMAs do not: narrow only while
-// the wide tile leaves half of the CUs without a workgroup (1000^3, 128 items
-// 13.8 / 11.3; 2001x768x3072, 192 items 27.4 / 29.7; 3001x2999x1001, 1152
-// items 44 / 55).
+// mostly idle, so there the narrow tile wins unless the wide one's workgroups fill
+// their rounds of the CUs to 15/16 (from four rounds on it always runs).  us, wide /
+// narrow, layouts NN, NT, TN: 32 steps, 256 items 71 / 68, 70 / 67, 72 / 69, 480 items
+// 125 / 129, 123 / 127, 127 / 129, 704 items 183 / 182, 184 / 177, 183 / 183, 768 items 184 /
+// 196, 185 / 191, 184 / 195, 896 items 246 / 227, 242 / 226, 249 / 229; 12 steps, 480 items
+// 52.7 / 54.1, 52.3 / 54.0, 53.5 / 55.1, 768 items 76.4 / 81.2, 76.3 / 81.9, 77.4 / 80.9.
+// bf16 MFMAs do not: narrow only while the wide tile leaves half of the CUs without a
+// workgroup (11 steps, 128 items 14.6 / 12.6, 13.7 / 12.4, 14.5 / 12.4, 192 items 15.2 /
+// 17.4, 15.1 / 17.7, 15.5 / 17.4; 3 to 6 steps, 64 items 9.6 / 7.1, 192 items 9.5 / 10.0).
 // Few fp32 items run as quarters of the 64 x 64 tile, up to two on each CU: a wave's
 // chain of matrix instructions is what such a launch takes, and a quarter's is a
 // quarter as long (with four times the waves, half as many products per load).
@@ -548,9 +550,11 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 cleave::ExecuteTile general_tile(int dtype, int64_t items, int64_t whole, int64_t steps, int cus) {
   const int64_t places = (whole + cus - 1) / cus * cus;
   if (whole > 0 && whole * 8 >= places * 7 && steps >= 16 * whole) return cleave::kTileHuge;
-  const int64_t narrow_up_to = dtype == CLEAVE_BF16 ? cus / 2 : int64_t{4} * cus - 1;
   if (dtype == CLEAVE_F32 && 8 * items <= cus) return cleave::kTileQuarter;
-  return items <= narrow_up_to ? cleave::kTileNarrow : cleave::kTileWide;
+  if (dtype == CLEAVE_BF16) return 2 * items <= cus ? cleave::kTileNarrow : cleave::kTileWide;
+  const int64_t places_wide = (items + cus - 1) / cus * cus;
+  const bool wide = items >= int64_t{4} * cus || (items > cus && 16 * items >= 15 * places_wide);
+  return wide ? cleave::kTileWide : cleave::kTileNarrow;
 }
 
 // Shape of the direct kernel for `items` work items of a class with `steps` K

@@ -576,8 +576,14 @@ hipError_t launch_elements(ExecuteArgs args, int tile_class, bool a_elements, bo
 // Quarters of the 64 x 64 tile, a 16 x 16 block per wave, for launches of few fp32
 // items (general_tile in api.cpp).
 using Quarter = Shape<4, 32, 32, 2, 2, 2, 8>;
+// Eight waves of 32 x 64: two on each SIMD where a launch leaves a CU one workgroup,
+// four where it has two.  us, four waves of 64 x 64 / eight, layouts NN, NT, TN: bf16, 192
+// items of 11 steps 17.3 / 15.2, 16.9 / 15.1, 17.7 / 15.5, 320 of 21 37.5 / 33.0, 36.2 /
+// 33.6, 35.6 / 33.1, 1152 of 11 54.7 / 50.9, 54.8 / 53.6, 52.6 / 51.5, 768 of 3 18.9 / 18.3,
+// 18.7 / 19.3, 18.6 / 18.3; fp32, 768 items of 32 steps 195 / 184, 187 / 185, 186 / 184,
+// 4096^3 1012 / 967.
 template <int EB>
-using Wide = Shape<EB, 128, 128, 2, 2, 2, 2>;
+using Wide = Shape<EB, 128, 128, 4, 2, 2, 4>;
 using Large = Shape<2, kLargeTileRows, kLargeTileCols, 2, 4, 1, 2>;
 template <int EB>
 using Narrow = Shape<EB, 64, 64, 2, 2, 2, 4>;
