@@ -1091,10 +1091,12 @@ int ensure_verify_tables_host(cleave_plan* p) {
     if (!v) return CLEAVE_ENOMEM;
     try {
       std::map<std::pair<uint32_t, uint32_t>, uint32_t> rows, cols;
-      // Elements of a partial block per bilinear item: long runs stream best
-      // (measured +11 % with 8 splits of 4 MiB blocks), as long as the launch
-      // still has a few thousand items to spread over the chip.
-      const uint32_t kElemsPerItem = p->partial_elems >= (int64_t{2048} << 15) ? 32768u : 16384u;
+      // Elements of a partial block per bilinear item: runs long enough to stream, as
+      // short as the last round of workgroups needs.  us, runs of 8 K / 16 K / 32 K: 17 M
+      // elements in all 23.4 / 20.1 / 21.8, 67 M 71.8 / 64.4 / 67.4, behind the launch that
+      // wrote them 189.4 / 187.9 / 191.4, 134 M 113 / 101 / 104, 180 M 174 / 139 / 144, 268 M
+      // 208 / 185 / 188; 451 M in 8 splits of 4 MiB blocks 421 / 336 / 330.
+      const uint32_t kElemsPerItem = p->partial_elems >= (int64_t{384} << 20) ? 32768u : 16384u;
       v->task_first_item.push_back(0);
       for (const cleave_task& t : p->tasks) {
         auto ri = rows.emplace(std::make_pair(t.m0, t.m_len), static_cast<uint32_t>(rows.size()));
