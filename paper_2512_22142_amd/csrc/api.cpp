@@ -442,7 +442,10 @@ constexpr int64_t kCacheBytes = int64_t{256} << 20;
 //   453 MB x 8   0.981 / 0.971                   537 MB x 2   1.011, 1.007 / 1.025, 1.015
 //   537 MB x 4   0.977, 0.989 / 0.974, 0.982     537 MB x 8   0.972 / 0.958
 //   906 MB x 2   0.985, 0.991 / 0.970, 0.981     906 MB x 8   0.891 / 0.879
-// (chunks of 512 and of 1024 elements, 1024 alone where one figure is given).
+// (chunks of 512 and of 1024 elements, 1024 alone where one figure is given).  Short
+// chains, whose launches are bound by the stores themselves, lose: linear layers, us,
+// plain / streamed, chunks of 48 elements 292 / 302, of 63 494 / 512, of 82 525 / 531, of
+// 200 639 / 651; of 476 1703 / 1612.
 uint32_t streamed_below(const cleave_plan* plan, const AssembleTarget& asm_to) {
   const int64_t members = std::max<int64_t>(plan->batch, 1);
   const int64_t outputs = plan->M * plan->N * members;
@@ -452,8 +455,10 @@ uint32_t streamed_below(const cleave_plan* plan, const AssembleTarget& asm_to) {
   }
   const int64_t splits = plan->uniform_splits;
   if (splits < 2 || 4 * plan->partial_elems < kCacheBytes / 4 * 5) return 0;
+  const int64_t chunk = (plan->K + splits - 1) / splits;
+  if (chunk < 6 * int64_t{cleave::kDirectKStep}) return 0;
   const bool all = 4 * outputs >= 3 * kCacheBytes || (4 * outputs >= kCacheBytes / 2 * 3 && splits >= 4);
-  return static_cast<uint32_t>(all ? plan->K : (splits - 1) * ((plan->K + splits - 1) / splits));
+  return static_cast<uint32_t>(all ? plan->K : (splits - 1) * chunk);
 }
 
 // Where the work items of a subset go: one list per tile class, in the caller's

@@ -661,6 +661,9 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     // The ring is free unless it was handed over: the next item's ring fill is
     // issued before this item's stores so that its latency hides behind them.
     if (!cont && has_next) fill_ring(nx);
+    // (only the large shape has both forms: the second one's code alone cost launches of few
+    // K steps of the others 1-2 %)
+    constexpr bool kStreams = S::NW == 8;
     const auto leave = [&](auto bf16_tag, auto interior_tag, auto stream_tag) {
       store_rows<decltype(bf16_tag)::value, decltype(interior_tag)::value, decltype(stream_tag)::value, MB, NB>(
           acc, target, image, wm * S::WTM, wn * S::WTN, lane, m_valid, n_valid);
@@ -669,11 +672,11 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     constexpr std::false_type no{};
     if (!bf16_out) {
       if (!interior) leave(no, no, no);
-      else if (!S::ONE_ITEM && target.stream) leave(no, yes, yes);
+      else if (kStreams && target.stream) leave(no, yes, yes);
       else leave(no, yes, no);
     } else {
       if (!interior) leave(yes, no, no);
-      else if (!S::ONE_ITEM && target.stream) leave(yes, yes, yes);
+      else if (kStreams && target.stream) leave(yes, yes, yes);
       else leave(yes, yes, no);
     }
     entry = cont ? kPrefetched : interior ? kFilledBehindStores : kFilled;

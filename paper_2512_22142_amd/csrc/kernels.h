@@ -50,7 +50,7 @@ struct ExecuteArgs {
   void* C;
   int64_t ldc;
   int c_bf16;
-  // Direct kernel only: work items whose chunk starts below this k leave through
+  // Direct kernel's large shape only: items whose chunk starts below this k leave through
   // non-temporal stores (streamed_below in api.cpp).
   uint32_t stream_below_k;
   // General kernel only: extent of the logical operands (loads stay inside them)
