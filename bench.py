@@ -35,8 +35,8 @@ PEAK_HBM_GBPS = 8000.0
 # dropped on a mismatch.
 COUNTER_TRAFFIC = {
     "workload": "c3",
-    "sources_sha256": "4db04d67603f54d9443e154a21c4e42fcb54417ce097c68d1f43eedb10988d0f",
-    "execute_bytes_per_launch": (2.0 * 225658 + 388535) * 1024,
+    "sources_sha256": "5a6cd599c9251d57f1ec4f2d0875929634a4c1e572554dbfedb1f2181de56c68",
+    "execute_bytes_per_launch": (2.0 * 218007 + 388631) * 1024,
     "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
 

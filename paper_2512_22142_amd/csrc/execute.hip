@@ -39,14 +39,14 @@
 //     fp32), so nothing is transposed in registers.
 //
 // What bounds it: fp32, the matrix cores (64 cycles per 32x32x2): 4096^3 as
-// 512 x 512 x 1024 tasks runs at 138-141 TFLOP/s of 157 nominal.  bf16, the LDS
-// (a 64 x 64 wave tile reads 128 bytes per clock and CU at full MFMA rate, and
-// the tile's refill comes on top): the same with an odd leading dimension
-// 613-638 TFLOP/s.  Execute + reduce against unaligned operands loaded by
-// element, and one fp32 tile of 256 x 256 or 128 x 128 with one step in flight:
-// forward, dX and dW of 3001 x 1000 x 2500 bf16 in 4 splits 164 / 1173 us, of
-// 2048 x 768 x 3072 fp32 264 / 403 us, 512^3 fp32 11.9 / 26.7 us (of the last,
-// 4.5 us are host time saved by the native argument checks).
+// 512 x 512 x 1024 tasks runs at 142 TFLOP/s of 157 nominal.  bf16, the LDS (32 x 64
+// wave tiles read 192 bytes per clock and CU at full MFMA rate, and the tile's
+// refill comes on top): the same with an odd leading dimension 620-640 TFLOP/s.
+// Execute + reduce against unaligned operands loaded by element, and one fp32 tile
+// of 256 x 256 or 128 x 128 with one step in flight: forward, dX and dW of 3001 x 1000
+// x 2500 bf16 in 4 splits 155 / 1173 us, of 2048 x 768 x 3072 fp32 254 / 403 us, 512^3
+// fp32 10.7 / 26.7 us (of the last, 4.5 us are host time saved by the native argument
+// checks).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
