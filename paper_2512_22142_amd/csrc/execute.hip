@@ -529,30 +529,22 @@ hipError_t configure_elements() {
 
 // Grid of a launch over work items of one class, and the workgroup tiles per item.
 template <typename S>
-int cut_items(ExecuteArgs* args, int tile_class) {
+int cut_items(ExecuteArgs* args, int tile_class, const GeneralLoads& how) {
   static_assert((kSmallTileRows % S::TM == 0 || S::TM == kLargeTileRows) && kLargeTileRows % S::TM == 0 &&
                 (kSmallTileCols % S::TN == 0 || S::TN == kLargeTileCols) && kLargeTileCols % S::TN == 0,
                 "a work item is cut into whole workgroup tiles");
   args->parts_m = tile_rows(tile_class) / S::TM;
   args->parts_n = tile_cols(tile_class) / S::TN;
   const int64_t blocks = (args->n_items + 7) / 8 * 8 * args->parts_m * args->parts_n;
-  // Between one round of the chip and two, the workgroups that fit take their second
-  // part themselves: number b's is on the CU of number b - resident, so a second round
-  // of half as many is spread over all CUs (workgroups are dealt to the CUs in turn).
-  // Left to the dispatcher, the first CUs to finish get a full second round and the
-  // others none.  us, dispatcher / taken: bf16, 128 x 128, 768 parts of 10 steps 44 /
-  // 37, 640 of 12 30.8 / 29.9; fp32, 64 x 64, 1152 parts of 32 steps 83.5 / 80.6.
-  // Behind two rounds the finish times are spread anyway: 1920 parts of 4 steps 45.6 /
-  // 46.2, fp32 4096^3 1007 / 1016, bf16 4095^3 219 / 226.
-  const int64_t resident = static_cast<int64_t>(args->cus) * (S::WPE * 4 / (S::NT / 64));
-  if (blocks > resident && blocks <= 2 * resident) return static_cast<int>(resident);
-  constexpr int64_t kMaxGrid = int64_t{1} << 20;   // the kernel loops beyond that
-  return static_cast<int>(blocks < kMaxGrid ? blocks : kMaxGrid);
+  // (only for the two shapes that the figures beside general_workgroups are of)
+  constexpr bool kTakesSecond = S::SETS == 2 && (S::TM == 128 || S::TM == 64);
+  const int64_t resident = static_cast<int64_t>(how.cus) * (S::WPE * 4 / (S::NT / 64));
+  return general_workgroups(blocks, resident, kTakesSecond && how.equal);
 }
 
 template <typename S>
-hipError_t launch_layouts(ExecuteArgs args, int tile_class, hipStream_t stream) {
-  const int grid = cut_items<S>(&args, tile_class);
+hipError_t launch_layouts(ExecuteArgs args, int tile_class, const GeneralLoads& how, hipStream_t stream) {
+  const int grid = cut_items<S>(&args, tile_class, how);
   const bool a_k = !args.transA;   // A stored M x K: K-contiguous
   const bool b_k = args.transB;    // B stored N x K: K-contiguous
   if (a_k && b_k) return launch_one<S, kByK, kByK>(args, grid, stream);
@@ -561,12 +553,12 @@ hipError_t launch_layouts(ExecuteArgs args, int tile_class, hipStream_t stream) 
   return launch_one<S, kByRow, kByRow>(args, grid, stream);
 }
 
-// a_elements / b_elements: at least one of them.
+// how.a_elements / how.b_elements: at least one of them.
 template <typename S>
-hipError_t launch_elements(ExecuteArgs args, int tile_class, bool a_elements, bool b_elements, hipStream_t stream) {
-  const int grid = cut_items<S>(&args, tile_class);
-  if (a_elements && b_elements) return launch_one<S, kElements, kElements>(args, grid, stream);
-  if (a_elements)
+hipError_t launch_elements(ExecuteArgs args, int tile_class, const GeneralLoads& how, hipStream_t stream) {
+  const int grid = cut_items<S>(&args, tile_class, how);
+  if (how.a_elements && how.b_elements) return launch_one<S, kElements, kElements>(args, grid, stream);
+  if (how.a_elements)
     return args.transB ? launch_one<S, kElements, kByK>(args, grid, stream)
                        : launch_one<S, kElements, kByRow>(args, grid, stream);
   return args.transA ? launch_one<S, kByRow, kElements>(args, grid, stream)
@@ -603,15 +595,15 @@ hipError_t configure_type() {
 template <int EB>
 hipError_t launch_type(const ExecuteArgs& args, int tile_class, const GeneralLoads& how, hipStream_t stream) {
   if (how.a_elements || how.b_elements)
-    return launch_elements<ByElement<EB>>(args, tile_class, how.a_elements, how.b_elements, stream);
+    return launch_elements<ByElement<EB>>(args, tile_class, how, stream);
   if (EB == 2 && how.tile == kTileHuge) {   // large items, both operands K-contiguous
     ExecuteArgs whole = args;
-    const int grid = cut_items<Large>(&whole, tile_class);
+    const int grid = cut_items<Large>(&whole, tile_class, how);
     return launch_one<Large, kByK, kByK>(whole, grid, stream);
   }
-  if (EB == 4 && how.tile == kTileQuarter) return launch_layouts<Quarter>(args, tile_class, stream);
-  return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, stream)
-                                 : launch_layouts<Wide<EB>>(args, tile_class, stream);
+  if (EB == 4 && how.tile == kTileQuarter) return launch_layouts<Quarter>(args, tile_class, how, stream);
+  return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, how, stream)
+                                 : launch_layouts<Wide<EB>>(args, tile_class, how, stream);
 }
 
 }  // namespace

@@ -57,7 +57,6 @@ struct ExecuteArgs {
   // and the workgroup tiles per work item (filled in at the launch).
   int64_t M, N, K;
   int parts_m, parts_n;
-  int cus;   // of the device
   // Direct kernel only, shapes with several items per workgroup.  Null:
   // workgroup b takes items b, b + grid, ...  Otherwise grid + 1 entries:
   // workgroup b takes items [wg_ranges[b], wg_ranges[b + 1]).
@@ -73,7 +72,33 @@ enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2, kTileQua
 struct GeneralLoads {
   ExecuteTile tile;
   bool a_elements, b_elements;
+  bool equal;   // no chunk of the list is shorter than 15/16 of its longest one
+  int cus;      // of the device
 };
+
+// Workgroups of a general launch over `blocks` workgroup tiles, of which the chip holds
+// `resident` at a time.  Between one round and two, the workgroups that fit take their
+// second tile themselves: number b's is on the CU of number b - resident, so a second
+// round of half as many is spread over all CUs (workgroups are dealt to the CUs in
+// turn).  Left to the dispatcher, the first CUs to finish get a full second round and
+// the others none.  us, dispatcher / taken, layouts NN, NT, TN: bf16, 128 x 128, 768 tiles
+// of 10 steps 36.1 / 35.1, 33.2 / 33.3, 32.2 / 32.2, of 3 17.9 / 17.2, 17.6 / 16.3, 19.2 / 17.4,
+// 544 of 16 34.3 / 32.6, 32.5 / 31.3, 40.1 / 39.1; fp32, 128 x 128, 768 of 32 188 / 184, 187 /
+// 184, 190 / 184, 480 of 32 the same; 64 x 64, 1152 of 32 84.3 / 81.1, 83.0 / 80.3, 84.5 / 81.4,
+// of 8 27.8 / 26.5, 29.0 / 26.1, 29.0 / 26.7, 1536 of 32 the same.  Behind two rounds the
+// finish times are spread anyway: bf16, 1920 tiles of 4 steps 45.6 / 46.2, 4095^3 219 /
+// 226, fp32 4096^3 1007 / 1016.
+//   Only with `equal` chunks: a fixed pairing can put two long ones on one workgroup,
+// where the dispatcher hands the next tile to whoever is done.  Tiles of 128 with one,
+// two or four splits at random, dispatcher / taken: fp32, 1536 x 1536 x 2048 94.2 / 115, 91.9 /
+// 114, 93.0 / 115, 1536 x 1024 x 4096 (up to eight) 142 / 161, 140 / 160, 142 / 161; bf16 with
+// unaligned rows, 2048 x 2048 x 2048 36.2 / 43.6, 37.5 / 43.8, 35.9 / 43.7, one or two, 3072 x
+// 3072 x 512 25.7 / 28.2, 26.1 / 28.4, 26.6 / 28.9.
+inline int general_workgroups(int64_t blocks, int64_t resident, bool equal) {
+  if (equal && blocks > resident && blocks <= 2 * resident) return static_cast<int>(resident);
+  constexpr int64_t kMaxGrid = int64_t{1} << 20;   // the kernel loops beyond that
+  return static_cast<int>(blocks < kMaxGrid ? blocks : kMaxGrid);
+}
 
 // Enqueues the general execute kernel over work items of one tile class: any
 // element type, size and alignment.

@@ -1,0 +1,73 @@
+"""How a launch of the general kernel is laid out (host logic): between one round of the
+chip and two, the resident workgroups take the second tiles only where the chunks are of
+equal length."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2512_22142_amd import build
+
+SOURCE = r"""
+#include <cstdio>
+#include "kernels.h"
+
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+
+using cleave::general_workgroups;
+
+// a band of 12 tiles of 128 x 128, tile j with splits[j % n]
+cleave_plan* band(int64_t K, const std::vector<int32_t>& splits) {
+  const int64_t height = 128;
+  const int32_t columns = 12;
+  const std::vector<int64_t> widths(12, 128);
+  std::vector<int32_t> all;
+  for (int j = 0; j < 12; ++j) all.push_back(splits[j % splits.size()]);
+  cleave_plan* plan = nullptr;
+  return cleave_plan_explicit(128, 1536, K, 1, &height, &columns, widths.data(), all.data(), 0, &plan) == CLEAVE_OK ? plan : nullptr;
+}
+
+int main() {
+BODY
+  return 0;
+}
+"""
+
+CASES = {
+    "unequal_chunks_are_left_to_the_dispatcher": """
+  CHECK(!band(1024, {1, 2, 4})->lengths.equal() && !band(128, {1, 2})->lengths.equal());
+  CHECK(general_workgroups(600, 512, false) == 600 && general_workgroups(1024, 512, false) == 1024);
+""",
+    "equal_ones_and_a_shorter_last_chunk_are_not": """
+  CHECK(band(1024, {1})->lengths.equal() && band(1024, {4})->lengths.equal() && band(3001, {4})->lengths.equal());
+  CHECK(band(1501, {2})->lengths.equal() && !band(10, {4})->lengths.equal());
+  CHECK(general_workgroups(513, 512, true) == 512 && general_workgroups(1024, 512, true) == 512);
+""",
+    "one_round_and_more_than_two": """
+  CHECK(general_workgroups(512, 512, true) == 512 && general_workgroups(8, 512, true) == 8);
+  CHECK(general_workgroups(1025, 512, true) == 1025 && general_workgroups(int64_t{1} << 40, 512, true) == 1 << 20);
+""",
+    "the_longest_chunks": """
+  cleave::ChunkLengths l;
+  l.add(2147483647u);
+  l.add(2013265919u);
+  CHECK(!l.equal());
+  cleave::ChunkLengths m;
+  m.add(2147483647u);
+  m.add(2013265920u);
+  CHECK(m.equal());
+""",
+}
+
+
+@pytest.mark.parametrize("case", list(CASES))
+def test_grid_of_the_general_kernel(tmp_path, case):
+    src, exe = tmp_path / "launch.cpp", tmp_path / "launch"
+    src.write_text(SOURCE.replace("BODY", CASES[case]))
+    rocm = os.path.dirname(os.path.dirname(build.HIPCC))
+    res = subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-isystem", os.path.join(rocm, "include"),
+                          "-I" + os.path.join(build.ROOT, "include"), "-I" + build.CSRC, str(src),
+                          os.path.join(build.CSRC, "plan.cpp"), "-o", str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout
