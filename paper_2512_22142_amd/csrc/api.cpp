@@ -467,7 +467,7 @@ struct SubsetLayout {
   bool fine = false;                               // every block cut into small-class sub-tiles
   int64_t counts[cleave::kNumTileClasses] = {};    // work items per class
   int64_t steps[cleave::kNumTileClasses] = {};     // their whole K steps, together
-  cleave::ChunkLengths lengths[cleave::kNumTileClasses];
+  cleave::ListShape shapes[cleave::kNumTileClasses];
   int64_t total() const { return counts[0] + counts[1]; }
 };
 
@@ -498,7 +498,7 @@ int layout_subset(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, int
     const cleave::SubTiling st = cleave::sub_tiling(t, out->fine);
     out->counts[st.cls] += st.count();
     out->steps[st.cls] += int64_t{st.count()} * (t.k_len / cleave::kDirectKStep);
-    out->lengths[st.cls].add(t.k_len);
+    out->shapes[st.cls].add(t);
   }
   return CLEAVE_OK;
 }
@@ -723,7 +723,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
   int64_t counts[cleave::kNumTileClasses] = {static_cast<int64_t>(plan->items[0].size()),
                                              static_cast<int64_t>(plan->items[1].size())};
   int64_t steps[cleave::kNumTileClasses] = {plan->items_steps[0], plan->items_steps[1]};   // whole K steps of a list's items
-  cleave::ChunkLengths lengths[cleave::kNumTileClasses] = {plan->lengths, plan->lengths};   // (the general kernel runs all tasks, or a subset)
+  cleave::ListShape shapes[cleave::kNumTileClasses] = {plan->shape, plan->shape};   // (the general kernel runs all tasks, or a subset)
   // which of the plan's lists a class runs from (-1: a subset's own list)
   int list_of[cleave::kNumTileClasses] = {task_ids ? -1 : 0, task_ids ? -1 : 1};
   if (!task_ids && (!direct || cut_small(plan, cus))) {
@@ -766,7 +766,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
     for (int c = 0; c < cleave::kNumTileClasses; ++c) {
       d_lists[c] = slice + pos;
       steps[c] = layout.steps[c];
-      lengths[c] = layout.lengths[c];
+      shapes[c] = layout.shapes[c];
       counts[c] = layout.counts[c];
       pos += counts[c];
     }
@@ -823,7 +823,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
                         ldb * eb < (int64_t{1} << 24);
       const cleave::GeneralLoads how{
           general_tile(dtype, counts[c] * (large ? 4 : 1), large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
-          a_elements, b_elements, lengths[c].equal(), cus};
+          a_elements, b_elements, shapes[c], cus};
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);
       if (counts[c] > most) plan->last_kernel = kernel_name(dtype, how, transA, transB);

@@ -533,13 +533,13 @@ int cut_items(ExecuteArgs* args, int tile_class, const GeneralLoads& how) {
   static_assert((kSmallTileRows % S::TM == 0 || S::TM == kLargeTileRows) && kLargeTileRows % S::TM == 0 &&
                 (kSmallTileCols % S::TN == 0 || S::TN == kLargeTileCols) && kLargeTileCols % S::TN == 0,
                 "a work item is cut into whole workgroup tiles");
-  args->parts_m = tile_rows(tile_class) / S::TM;
-  args->parts_n = tile_cols(tile_class) / S::TN;
+  args->parts_m = parts_along(how.list.rows, tile_rows(tile_class), S::TM);
+  args->parts_n = parts_along(how.list.cols, tile_cols(tile_class), S::TN);
   const int64_t blocks = (args->n_items + 7) / 8 * 8 * args->parts_m * args->parts_n;
   // (only for the two shapes that the figures beside general_workgroups are of)
   constexpr bool kTakesSecond = S::SETS == 2 && (S::TM == 128 || S::TM == 64);
   const int64_t resident = static_cast<int64_t>(how.cus) * (S::WPE * 4 / (S::NT / 64));
-  return general_workgroups(blocks, resident, kTakesSecond && how.equal);
+  return general_workgroups(blocks, resident, kTakesSecond && how.list.equal());
 }
 
 template <typename S>

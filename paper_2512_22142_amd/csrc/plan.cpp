@@ -247,7 +247,7 @@ int finish_plan(int64_t M, int64_t N, int64_t K, const std::vector<Tile>& tiles,
       p->all_m_mult8 &= ((t.m0 | t.m_len) % 8 == 0);
       p->all_n_mult8 &= ((t.n0 | t.n_len) % 8 == 0);
       p->min_k_end = std::min(p->min_k_end, static_cast<int64_t>(t.k0) + t.k_len);
-      p->lengths.add(t.k_len);
+      p->shape.add(t);
       p->all_n_mult4 &= ((t.n0 | t.n_len) % 4 == 0);
     }
 

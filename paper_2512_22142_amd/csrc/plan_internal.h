@@ -52,15 +52,18 @@ __host__ __device__ constexpr int chunk_steps(uint32_t k_len, uint32_t per_step)
   return static_cast<int>((k_len + per_step - 1) / per_step);
 }
 
-// Longest and shortest chunk of a list of tasks.
-struct ChunkLengths {
-  uint32_t most = 0, least = std::numeric_limits<uint32_t>::max();
-  void add(uint32_t k_len) {
-    most = k_len > most ? k_len : most;
-    least = k_len < least ? k_len : least;
+// What the general kernel's launch over a list of tasks is chosen by.
+struct ListShape {
+  uint32_t longest = 0, shortest = std::numeric_limits<uint32_t>::max();   // chunks
+  uint32_t rows = 0, cols = 0;   // most of a block
+  void add(const cleave_task& t) {
+    longest = t.k_len > longest ? t.k_len : longest;
+    shortest = t.k_len < shortest ? t.k_len : shortest;
+    rows = t.m_len > rows ? t.m_len : rows;
+    cols = t.n_len > cols ? t.n_len : cols;
   }
   // a sixteenth shorter at most: the last chunk of a split that does not divide
-  bool equal() const { return uint64_t{16} * least >= uint64_t{15} * most; }
+  bool equal() const { return uint64_t{16} * shortest >= uint64_t{15} * longest; }
 };
 
 struct alignas(16) WorkItem {
@@ -300,7 +303,7 @@ struct cleave_plan {
   bool all_n_mult8 = true;   // every n0 and n_len is a multiple of 8
   bool chunk_tails = false;  // some k_len is no multiple of the direct kernel's K step
   int64_t min_k_end = std::numeric_limits<int64_t>::max();   // smallest k0 + k_len of a task
-  cleave::ChunkLengths lengths;   // of all tasks
+  cleave::ListShape shape;   // of all tasks
   bool all_n_mult4 = true;   // every n0, n_len multiple of 4 (vector path of reduce)
   std::vector<cleave_task> tasks;
   // All tasks, launch order.

@@ -1,6 +1,6 @@
 """How a launch of the general kernel is laid out (host logic): between one round of the
 chip and two, the resident workgroups take the second tiles only where the chunks are of
-equal length."""
+equal length, and an item is cut into the tiles that its list's blocks fill."""
 import os
 import subprocess
 
@@ -15,6 +15,7 @@ SOURCE = r"""
 #define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
 
 using cleave::general_workgroups;
+using cleave::parts_along;
 
 // a band of 12 tiles of 128 x 128, tile j with splits[j % n]
 cleave_plan* band(int64_t K, const std::vector<int32_t>& splits) {
@@ -35,27 +36,39 @@ BODY
 
 CASES = {
     "unequal_chunks_are_left_to_the_dispatcher": """
-  CHECK(!band(1024, {1, 2, 4})->lengths.equal() && !band(128, {1, 2})->lengths.equal());
+  CHECK(!band(1024, {1, 2, 4})->shape.equal() && !band(128, {1, 2})->shape.equal());
   CHECK(general_workgroups(600, 512, false) == 600 && general_workgroups(1024, 512, false) == 1024);
 """,
     "equal_ones_and_a_shorter_last_chunk_are_not": """
-  CHECK(band(1024, {1})->lengths.equal() && band(1024, {4})->lengths.equal() && band(3001, {4})->lengths.equal());
-  CHECK(band(1501, {2})->lengths.equal() && !band(10, {4})->lengths.equal());
+  CHECK(band(1024, {1})->shape.equal() && band(1024, {4})->shape.equal() && band(3001, {4})->shape.equal());
+  CHECK(band(1501, {2})->shape.equal() && !band(10, {4})->shape.equal());
   CHECK(general_workgroups(513, 512, true) == 512 && general_workgroups(1024, 512, true) == 512);
 """,
     "one_round_and_more_than_two": """
   CHECK(general_workgroups(512, 512, true) == 512 && general_workgroups(8, 512, true) == 8);
   CHECK(general_workgroups(1025, 512, true) == 1025 && general_workgroups(int64_t{1} << 40, 512, true) == 1 << 20);
 """,
+    "no_tiles_that_hold_nothing": """
+  cleave_plan* plan = nullptr;
+  CHECK(cleave_plan_uniform(1000, 700, 64, 64, 100, 1, 0, &plan) == CLEAVE_OK);
+  CHECK(plan->shape.rows == 64 && plan->shape.cols == 100);
+  CHECK(parts_along(64, 128, 64) == 1 && parts_along(65, 128, 64) == 2 && parts_along(100, 128, 128) == 1);
+  CHECK(parts_along(1, 128, 32) == 1 && parts_along(33, 128, 32) == 2 && parts_along(128, 128, 32) == 4);
+  CHECK(parts_along(129, 128, 64) == 2 && parts_along(2147483647u, 256, 128) == 2 && parts_along(4294967295u, 256, 256) == 1);
+  CHECK(parts_along(129, 256, 128) == 2 && parts_along(129, 256, 64) == 3 && parts_along(256, 256, 64) == 4);
+""",
     "the_longest_chunks": """
-  cleave::ChunkLengths l;
-  l.add(2147483647u);
-  l.add(2013265919u);
+  cleave::ListShape l;
+  cleave_task t{};
+  t.m_len = t.n_len = 2147483647u;
+  t.k_len = 2147483647u;
+  l.add(t);
+  t.k_len = 2013265920u;
+  l.add(t);
+  CHECK(l.equal());
+  t.k_len = 2013265919u;
+  l.add(t);
   CHECK(!l.equal());
-  cleave::ChunkLengths m;
-  m.add(2147483647u);
-  m.add(2013265920u);
-  CHECK(m.equal());
 """,
 }
 
