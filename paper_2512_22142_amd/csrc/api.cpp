@@ -530,11 +530,19 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // 64 x 64 tile gives four times as many workgroups, four of them per CU
 // instead of two, at twice the LDS traffic per flop.  fp32 MFMAs leave the LDS
 // mostly idle, so there the narrow tile wins unless the wide one's workgroups fill
-// their rounds of the CUs to 15/16 (from four rounds on it always runs).  us, wide /
+// their rounds of the CUs to 15/16 (from four rounds on it runs whether or not).  us, wide /
 // narrow, layouts NN, NT, TN: 32 steps, 256 items 71 / 68, 70 / 67, 72 / 69, 480 items
 // 125 / 129, 123 / 127, 127 / 129, 704 items 183 / 182, 184 / 177, 183 / 183, 768 items 184 /
 // 196, 185 / 191, 184 / 195, 896 items 246 / 227, 242 / 226, 249 / 229; 12 steps, 480 items
 // 52.7 / 54.1, 52.3 / 54.0, 53.5 / 55.1, 768 items 76.4 / 81.2, 76.3 / 81.9, 77.4 / 80.9.
+// The wide tile multiplies all of an item, the narrow one the 64 x 64 parts that hold
+// something (`parts64` in all): with small blocks there is less to win.  Below four
+// rounds it runs from four fifths on, from there on from a half.  fp32, 1024 of K, by what
+// the items hold: 960 items 0.56 246 / 230, 242 / 225, 248 / 231; 720 items 0.88 183 / 186,
+// 184 / 183, 183 / 187; 512 items of 64 x 64 blocks (0.25, 512 of K) 64 / 22, 64 / 21, 66 / 22;
+// 1024 items 0.25 244 / 68, 241 / 67, 248 / 68, 0.52 246 / 246, 242 / 241, 248 / 246; 2048 items
+// 0.5 252 / 136, 251 / 134, 255 / 135; 2560 items 0.56 314 / 316, 314 / 308, 318 / 318, with 256
+// of K 97 / 102, 97 / 102, 100 / 106.
 // bf16 MFMAs do not: narrow only while the wide tile leaves half of the CUs without a
 // workgroup (11 steps, 128 items 14.6 / 12.6, 13.7 / 12.4, 14.5 / 12.4, 192 items 15.2 /
 // 17.4, 15.1 / 17.7, 15.5 / 17.4; 3 to 6 steps, 64 items 9.6 / 7.1, 192 items 9.5 / 10.0).
@@ -554,13 +562,14 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // alone on a CU (us, 128 / 256: 17 steps, 256 items 57 / 50, 1024 items 230 / 193, 688 items 144 / 132,
 // 576 items, the third round a quarter full, 116 / 127; 5 steps, 1024 items
 // 92.7 / 92.6, 688 items 59 / 66).
-cleave::ExecuteTile general_tile(int dtype, int64_t items, int64_t whole, int64_t steps, int cus) {
+cleave::ExecuteTile general_tile(int dtype, int64_t items, int64_t parts64, int64_t whole, int64_t steps, int cus) {
   const int64_t places = (whole + cus - 1) / cus * cus;
   if (whole > 0 && whole * 8 >= places * 7 && steps >= 16 * whole) return cleave::kTileHuge;
   if (dtype == CLEAVE_F32 && 8 * items <= cus) return cleave::kTileQuarter;
   if (dtype == CLEAVE_BF16) return 2 * items <= cus ? cleave::kTileNarrow : cleave::kTileWide;
   const int64_t places_wide = (items + cus - 1) / cus * cus;
-  const bool wide = items >= int64_t{4} * cus || (items > cus && 16 * items >= 15 * places_wide);
+  const bool wide = items >= int64_t{4} * cus ? parts64 > 2 * items
+                                              : items > cus && 16 * items >= 15 * places_wide && 5 * parts64 >= 16 * items;
   return wide ? cleave::kTileWide : cleave::kTileNarrow;
 }
 
@@ -822,7 +831,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
                         ldb * eb < (int64_t{1} << 24);
       const cleave::GeneralLoads how{
-          general_tile(dtype, counts[c] * (large ? 4 : 1), large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
+          general_tile(dtype, counts[c] * (large ? 4 : 1), shapes[c].parts64, large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
           a_elements, b_elements, shapes[c], cus};
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);

@@ -56,11 +56,13 @@ __host__ __device__ constexpr int chunk_steps(uint32_t k_len, uint32_t per_step)
 struct ListShape {
   uint32_t longest = 0, shortest = std::numeric_limits<uint32_t>::max();   // chunks
   uint32_t rows = 0, cols = 0;   // most of a block
+  int64_t parts64 = 0;           // 64 x 64 parts that the blocks fill or reach into
   void add(const cleave_task& t) {
     longest = t.k_len > longest ? t.k_len : longest;
     shortest = t.k_len < shortest ? t.k_len : shortest;
     rows = t.m_len > rows ? t.m_len : rows;
     cols = t.n_len > cols ? t.n_len : cols;
+    parts64 += int64_t{t.m_len / 64 + (t.m_len % 64 != 0)} * (t.n_len / 64 + (t.n_len % 64 != 0));
   }
   // a sixteenth shorter at most: the last chunk of a split that does not divide
   bool equal() const { return uint64_t{16} * shortest >= uint64_t{15} * longest; }

@@ -49,3 +49,23 @@ def test_blocks_smaller_than_an_item_exact(tiling, dtype, transA, transB):
             m0, n0, k0 = int(t["m0"]), int(t["n0"]), int(t["k0"])
             ref = og.gemm(opA[m0:m0 + block.shape[0]], opB[:, n0:n0 + block.shape[1]], k0, k0 + int(t["k_len"]))
             assert np.array_equal(block, ref), (i, ids)
+
+
+@pytest.mark.parametrize("M,N,tile,S,tile_name", [
+    (1024, 1024, (64, 64), 2, "64x64"), (2048, 1920, (64, 64), 1, "64x64"), (2048, 1536, (128, 64), 1, "64x64"),   # 512, 960, 384 items
+    (2048, 2048, (64, 64), 1, "64x64"), (4096, 2048, (64, 128), 1, "64x64"), (1024, 1024, (32, 32), 1, "64x64"),   # 1024 and more
+    (1920, 4096, (128, 128), 1, "128x128"), (3008, 3776, (128, 128), 1, "128x128"), (3072, 3840, (256, 256), 1, "128x128"), (4096, 4096, (128, 128), 1, "128x128")])
+def test_items_at_most_half_full_run_in_small_tiles(M, N, tile, S, tile_name):
+    """fp32: what counts is the work of the items, not their number (720 items, nearly full
+    ones among them: the large tile)."""
+    K = 33 * S
+    plan = cleave.plan_uniform(M, N, K, *tile, S)
+    A = make_matrix(43, M, K, "f32", integer_valued=True).cuda()
+    B = make_matrix(44, K, N, "f32", integer_valued=True).cuda()
+    parts = torch.full((plan.partial_elems,), float("nan"), dtype=torch.float32, device="cuda")
+    C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    cleave.execute(plan, A, B, parts)
+    assert plan.last_kernel == "execute_f32_%s_nn" % tile_name
+    cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    assert torch.equal(C.cpu(), (A.cpu().double() @ B.cpu().double()).float())
