@@ -1234,18 +1234,6 @@ struct AggregateTarget {
   int out_dtype = CLEAVE_F32;
 };
 
-// Whether the check writes the sum with non-temporal stores: an fp32 sum that takes up
-// much of the cache.  us, plain / streamed, blocks not in any cache, the pass alone and
-// with a launch behind it that reads the sum and writes another matrix, or updates
-// it in place: 67 MB in 4 splits 67 / 70, 87 / 94, 87 / 93; 134 MB in 4 125 / 129,
-// 182 / 180, 164 / 171; 180 MB in 2 110 / 103, 174 / 170, 166 / 163, in 4 177 /
-// 164, 240 / 230, 231 / 222, in 8 321 / 309, 386 / 374, 375 / 367; 268 MB in 4 262 /
-// 255, 349 / 348, 345 / 352.  The linear layer's three GEMMs one behind the other
-// (180, 67 and 180 MB in 4 splits) 524 / 470 with all three streamed.
-bool streamed_sum(const cleave_plan* plan, const AggregateTarget& agg) {
-  return agg.out_dtype == CLEAVE_F32 && 4 * plan->M * plan->N >= (int64_t{160} << 20);
-}
-
 int verify_impl(cleave_plan* plan, const void* A, int64_t lda, int transA, const void* B, int64_t ldb,
                 int transB, int dtype, const float* partials, const float* r, const float* s, double tol,
                 double* lhs, double* rhs, double* scale, int32_t* accept, const BatchLayout& bl,
@@ -1316,7 +1304,7 @@ int verify_impl(cleave_plan* plan, const void* A, int64_t lda, int transA, const
     fused.bil = pass.bil;
     fused.bil.item_sums = v->d_agg_item_sums;
     fused.agg = cleave::AggregateArgs{v->d_agg_items, static_cast<int64_t>(v->agg_items.size()), agg.C, agg.ldc, agg.out_dtype == CLEAVE_BF16 ? 1 : 0,
-                                      streamed_sum(plan, agg) ? 1 : 0};
+                                      agg.out_dtype == CLEAVE_F32 && cleave::streamed_sum(plan->M * plan->N, plan->partial_elems)};
     CLEAVE_HIP(cleave::launch_verify_reduce_pass(fused, dtype, a_contig, b_contig,
                                                  a_vec && b_vec && p_vec && c_vec, stream));
   } else {

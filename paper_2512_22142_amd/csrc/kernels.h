@@ -269,6 +269,36 @@ struct AggregateArgs {
   int out_bf16;
   int stream;                     // fp32 sums leave through non-temporal stores
 };
+// Whether a check of `partials` elements writes its fp32 sum of `outputs` elements
+// with non-temporal stores: where the pass alone gains and nobody who reads the sum next
+// loses.  A sum that fits the Infinity Cache is still there for its reader, unless it was
+// streamed; one that does not pushes its own first part out again.  us, plain / streamed,
+// blocks not in any cache: the pass alone, with a product into another matrix, an
+// update in place, a sum over all of it behind it:
+//   67 MB in 4 splits    67 / 70     87 / 94     87 / 93     87 / 97
+//  134 MB in 4          124 / 129   181 / 180   165 / 171   157 / 172
+//  168 MB in 2          105 / 98    166 / 162   157 / 151   152 / 149     in 4 166 / 155   227 / 217   215 / 209   206 / 205
+//         in 5          202 / 191   267 / 257   259 / 247   248 / 243     in 8 299 / 290   362 / 352   346 / 343   331 / 341
+//  180 MB in 2          111 / 104   177 / 172   168 / 163   160 / 158     in 4 178 / 165   242 / 231   234 / 224   220 / 218
+//         in 5          213 / 202   284 / 273   276 / 266   262 / 259     in 8 322 / 309   386 / 376   376 / 367   357 / 363
+//  189 MB in 2          116 / 111   197 / 188   187 / 177   177 / 169     in 4 192 / 181   260 / 255   250 / 249   235 / 241
+//  201 MB in 2          122 / 116   199 / 193   186 / 187   174 / 175     in 4 195 / 186   268 / 260   260 / 256   243 / 244
+//  235 MB in 2          143 / 135   227 / 222   209 / 219   193 / 201     in 4 230 / 217   305 / 301   296 / 300   272 / 284
+//  268 MB in 2          169 / 158   263 / 255   249 / 259   244 / 239     in 4 259 / 253   348 / 347   343 / 351   327 / 331
+//         in 8          461 / 465   547 / 560   551 / 565   528 / 542
+//  302 MB in 1          137 / 118   242 / 227   241 / 230   222 / 209     in 4 295 / 272   391 / 383   405 / 388   369 / 361
+//         in 5          351 / 329   451 / 439   464 / 445   432 / 419     in 8 540 / 517   632 / 636   655 / 643   600 / 612
+//  336 MB in 2          211 / 185   322 / 308   332 / 315   301 / 285     in 4 326 / 298   433 / 419   454 / 427   409 / 396
+//  361 MB in 5          425 / 398   538 / 530   563 / 539   506 / 505     in 7 577 / 544   686 / 680   711 / 691   647 / 655
+//  453 MB in 5          536 / 504   679 / 668   703 / 677   640 / 636     in 8 816 / 782   952 / 954   986 / 964   902 / 920
+//  537 MB in 4          529 / 472   693 / 662   723 / 676   651 / 624     in 8 972 / 911  1135 /1119  1171 /1135  1075 /1075
+// The linear layer's three GEMMs one behind the other (180, 67 and 180 MB in 4 splits; the
+// 67 MB stay plain) 523 / 485.
+inline bool streamed_sum(int64_t outputs, int64_t partials) {
+  const int64_t mib = outputs >> 18;   // whole MiB of fp32
+  return partials <= 5 * outputs && ((mib >= 160 && mib < 176) || mib >= 288);
+}
+
 struct VerifyReducePassArgs {
   ProjectArgs A, B;
   BilinearArgs bil;
