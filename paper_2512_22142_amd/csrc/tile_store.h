@@ -49,9 +49,10 @@ __device__ __forceinline__ TileTarget tile_target(const ExecuteArgs& args, const
 // wave writes one aligned run of 32 elements per store.  row0 / col0: this
 // lane's first row and column inside the sub-tile; one per-thread base pointer
 // plus wave-uniform row offsets keeps the stores free of address arithmetic.
-// `interior`: the sub-tile is full, no bounds checks.  Plain stores:
-// non-temporal ones make execute ~1 % faster but the reducer that follows
-// ~10 % slower.
+// `interior`: the sub-tile is full, no bounds checks.  Plain stores, whatever the
+// output's size: with outputs that the caches hold, non-temporal ones made execute ~1 %
+// faster and the reducer that follows ~10 % slower; with larger ones, where store_rows
+// streams, they were not measured for the kernel that uses this.
 template <int MB, int NB, typename T, typename Cvt>
 __device__ __forceinline__ void store_blocks(const tile_f32x16 (&acc)[MB][NB], T* tp, int64_t ld,
                                              int row0, int col0, int m_valid, int n_valid,

@@ -78,6 +78,16 @@ def test_edges_of_loads_steps_and_tiles_exact(dtype, transA, transB):
 
 
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
+def test_edges_of_the_fp32_tile_of_64_exact(transA, transB):
+    """As above with more items than run in quarters of the tile."""
+    name = "f32_64x64_" + "nt"[transA] + "nt"[transB]
+    for K in (31, 33, 64, 71, 151):
+        check(770, 701, K, (128, 128), 1, transA, transB, "f32", pad=1, kernel=name)
+    check(1089, 1025, 101, (128, 256), 2, transA, transB, "f32", pad=3, kernel=name)
+    check(513, 575, 97, (96, 100), 3, transA, transB, "f32", pad=0, kernel=name)
+
+
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_wide_tiles_exact(dtype, transA, transB):
     # more 128 x 128 work items than the narrow tile is used for, full and clipped ones

@@ -64,10 +64,14 @@ def test_assembled_edges_of_the_quarter(M, N, out_dtype):
     assert og.rel_frobenius(C.float().cpu().numpy(), og.gemm(*og.logical_operands(A, 0, B, 0))) <= (TOL["f32"] if out_dtype == torch.float32 else 2.0 ** -8)
 
 
-@pytest.mark.parametrize("dtype,M,N,K,S", [("bf16", 1025, 1999, 131, 4), ("bf16", 1151, 2175, 67, 2), ("f32", 2100, 2000, 40, 1),
-                                           ("f32", 2177, 1921, 33, 1)])
-def test_between_one_and_two_rounds_of_workgroups(dtype, M, N, K, S):
+@pytest.mark.parametrize("dtype,M,N,K,S,tile", [("bf16", 1025, 1999, 131, 4, 128), ("bf16", 1151, 2175, 67, 4, 128), ("f32", 2100, 2000, 40, 1, 64),
+                                                ("f32", 2177, 1921, 33, 1, 64), ("f32", 3000, 4000, 40, 1, 128), ("f32", 3968, 4096, 65, 1, 128),
+                                                ("f32", 1270, 3070, 99, 3, 128)])
+def test_between_one_and_two_rounds_of_workgroups(dtype, M, N, K, S, tile):
     """Integer-valued inputs: every block exact, whoever computes it."""
+    # workgroups against those that the chip holds: two 128 x 128 ones on a CU, four 64 x 64 ones
+    rounds = -(-M // 128) * -(-N // 128) * S / (2 * torch.cuda.get_device_properties(0).multi_processor_count)
+    assert 1 < rounds * (1 if tile == 128 else 2) <= 2
     g = torch.Generator().manual_seed(5)
     A = torch.randint(-3, 4, (M, K), generator=g).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
     B = torch.randint(-3, 4, (K, N), generator=g).to(A.dtype)
@@ -77,5 +81,6 @@ def test_between_one_and_two_rounds_of_workgroups(dtype, M, N, K, S):
     for _ in range(2):
         cleave.execute(plan, A.cuda(), B.cuda(), parts)
         cleave.reduce(plan, parts, C)
+    assert plan.last_kernel == "execute_%s_%dx%d_nn" % (dtype, tile, tile)
     torch.cuda.synchronize()
     assert torch.equal(C.cpu(), (A.double() @ B.double()).float())

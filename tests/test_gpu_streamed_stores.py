@@ -26,7 +26,32 @@ def test_assembled_output_around_the_size_of_the_cache(M, N, out_dtype):
     plan = cleave.plan_uniform(M, N, 64, 512, 512, 1)
     C = torch.full((M, N), float("nan"), dtype=out_dtype, device="cuda")
     cleave.execute_assemble(plan, A, B, C)
+    assert plan.last_kernel == "execute_direct_bf16_256x256_nn"
     assert torch.equal(C.float(), exact(A, B))
+
+
+@pytest.mark.parametrize("shift,gap,out_dtype", [(0, 8, torch.bfloat16), (1, 1, torch.bfloat16), (3, 5, torch.float32), (0, 0, torch.float32)])
+def test_assembled_members_with_gaps_at_any_alignment(shift, gap, out_dtype):
+    """257 MiB and more: members `gap` elements further apart than they are long, in rows `gap`
+    elements longer than N, from `shift` elements behind an allocation's start."""
+    members, inner, L, d = 132, 4, 1024 if out_dtype == torch.bfloat16 else 720, 64
+    ld = L + gap
+    member = L * ld + gap
+    A = ints((members * L, d), 9) * (torch.arange(d, device="cuda") < 16)
+    B = ints((members * L, d), 10)
+    plan = cleave.plan_batched(L, L, d, 512, 512, 1, members)
+    flat = torch.full((shift + members * member + ld,), float("nan"), dtype=out_dtype, device="cuda")
+    C = flat[shift:].as_strided((L, L), (ld, 1))
+    cleave.execute_assemble(plan, A, B, C, 0, 1, (inner * L * d, L * d), (inner * L * d, L * d), (inner * member, member), inner)
+    assert plan.last_kernel == "execute_direct_bf16_256x256_nt"
+    assert members * L * L * flat.element_size() >= 256 << 20
+    for g in range(members):
+        rows = flat[shift + g * member:shift + (g + 1) * member]
+        got = rows[:L * ld].view(L, ld)
+        a, b = A[g * L:(g + 1) * L], B[g * L:(g + 1) * L]
+        assert torch.equal(got[:, :L].float(), exact(a, b.t())), g
+        assert bool(torch.isnan(got[:, L:].float()).all()) and bool(torch.isnan(rows[L * ld:].float()).all())
+    assert bool(torch.isnan(flat[:shift].float()).all()) and bool(torch.isnan(flat[shift + members * member:].float()).all())
 
 
 @pytest.mark.parametrize("M,N,K,S", [(4096, 5376, 1536, 4), (4096, 4864, 1536, 4), (8192, 6144, 832, 2), (4096, 10752, 3072, 8),
@@ -37,6 +62,7 @@ def test_partial_blocks_around_the_lines(M, N, K, S):
     plan = cleave.plan_uniform(M, N, K, 512, 512, S)
     parts = torch.full((plan.partial_elems,), float("nan"), dtype=torch.float32, device="cuda")
     cleave.execute(plan, A, B, parts)
+    assert plan.last_kernel == "execute_direct_bf16_256x256_nn"
     C = torch.empty((M, N), dtype=torch.float32, device="cuda")
     cleave.reduce(plan, parts, C)
     assert torch.equal(C, exact(A, B))
@@ -49,8 +75,8 @@ def test_partial_blocks_around_the_lines(M, N, K, S):
         assert torch.equal(again[a:a + n], parts[a:a + n])
 
 
-@pytest.mark.parametrize("N", [10232, 10240])
-def test_checked_sum_around_the_line(N):
+@pytest.mark.parametrize("N", [10232, 10240, 11256, 11264, 18424, 18432])
+def test_checked_sum_around_the_lines(N):
     M, K = 4096, 128
     A, B = ints((M, K), 5), ints((K, N), 6)
     plan = cleave.plan_uniform(M, N, K, 512, 512, 2)
