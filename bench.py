@@ -30,12 +30,12 @@ PEAK_HBM_GBPS = 8000.0
 # FETCH_SIZE and WRITE_SIZE counter runs summarised under profiles/ (FETCH_SIZE
 # scaled by 2.0, WRITE_SIZE by 1.0: what the same counters read for a plain copy
 # of known size).  Valid only for the kernel sources they were taken with: the
-# digest below (over the files that define the execute and reduce kernels, their
-# arguments and the work-item order) is checked at run time and the figures are
+# digest below (over the files that define the execute and reduce kernels, what they are
+# launched with and the work-item order) is checked at run time and the figures are
 # dropped on a mismatch.
 COUNTER_TRAFFIC = {
     "workload": "c3",
-    "sources_sha256": "5a6cd599c9251d57f1ec4f2d0875929634a4c1e572554dbfedb1f2181de56c68",
+    "sources_sha256": "3772f9066c4bd9a8c9d70b22d3bf8223cffebbdc950ecfc0e6f1045464be396a",
     "execute_bytes_per_launch": (2.0 * 218007 + 388631) * 1024,
     "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
@@ -45,7 +45,7 @@ def kernel_sources_digest():
     import hashlib
     csrc = os.path.join(ROOT, "paper_2512_22142_amd", "csrc")
     h = hashlib.sha256()
-    for name in ("execute.hip", "execute_direct.hip", "kernels.h", "plan.cpp", "plan_internal.h", "reduce.hip", "tile_store.h"):
+    for name in ("api.cpp", "execute.hip", "execute_direct.hip", "kernels.h", "plan.cpp", "plan_internal.h", "reduce.hip", "tile_store.h"):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(name.encode() + b"\0" + f.read())
     return h.hexdigest()

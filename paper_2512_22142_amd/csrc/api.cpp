@@ -426,9 +426,16 @@ constexpr int64_t kCacheBytes = int64_t{256} << 20;
 // write-backs; a streamed one goes to memory without them.  One that it can hold is
 // read from there by whoever comes next.
 //   Assembled outputs: streamed from the cache's size on.  Scores of 1024 x 1024 x
-// 128 members into bf16, us, plain / streamed: the launch alone 33.4 / 33.0 for 134
-// MB, 72 / 51 for 235 MB, 86 / 57 for 268 MB; with a softmax that reads them 136 /
-// 148, 267 / 257, 302 / 289; with an update in place 71 / 76, 137 / 136, 160 / 160.
+// members into bf16, us, plain / streamed: the launch alone, with a softmax, an update in
+// place, the largest value of all behind it:
+//   134 MB    33 / 33     136 / 148    71 / 76     89 / 110
+//   168 MB    39 / 39     158 / 191    84 / 89    104 / 131
+//   201 MB    43 / 44     216 / 224    98 / 104   121 / 154
+//   235 MB    72 / 51     267 / 257   137 / 136   164 / 176
+//   268 MB    83 / 61     301 / 287   158 / 158   209 / 198
+//   336 MB   102 / 73     371 / 357   216 / 196   294 / 254
+//   537 MB   157 / 112    580 / 564   338 / 316   453 / 425
+// A reader that does little else still loses 7 % just below the cache's size.
 //   Partial blocks of uniform plans (their items run chunk by chunk): execute +
 // reduce over plain, all chunks but the last streamed / all of them streamed:
 //   blocks of a chunk x chunks
@@ -442,7 +449,10 @@ constexpr int64_t kCacheBytes = int64_t{256} << 20;
 //   453 MB x 8   0.981 / 0.971                   537 MB x 2   1.011, 1.007 / 1.025, 1.015
 //   537 MB x 4   0.977, 0.989 / 0.974, 0.982     537 MB x 8   0.972 / 0.958
 //   906 MB x 2   0.985, 0.991 / 0.970, 0.981     906 MB x 8   0.891 / 0.879
-// (chunks of 512 and of 1024 elements, 1024 alone where one figure is given).  Short
+// (chunks of 512 and of 1024 elements, 1024 alone where one figure is given).  537 MB x 2
+// (8192 x 16384) loses 1 % in every form, again in a second run (1.016, 1.010); beside it
+// 528 MB x 2 0.998, 1.011, 604 MB x 2 0.985, 0.993, so no line by size leaves it out.
+// Batched, grouped and explicit plans have not been measured and keep plain stores.  Short
 // chains, whose launches are bound by the stores themselves, lose: linear layers, us,
 // plain / streamed, chunks of 48 elements 292 / 302, of 63 494 / 512, of 82 525 / 531, of
 // 200 639 / 651; of 476 1703 / 1612.

@@ -44,7 +44,7 @@
 // refill comes on top): the same with an odd leading dimension 620-640 TFLOP/s.
 // Execute + reduce against unaligned operands loaded by element, and one fp32 tile
 // of 256 x 256 or 128 x 128 with one step in flight: forward, dX and dW of 3001 x 1000
-// x 2500 bf16 in 4 splits 155 / 1173 us, of 2048 x 768 x 3072 fp32 254 / 403 us, 512^3
+// x 2500 bf16 in 4 splits 158 / 1173 us, of 2048 x 768 x 3072 fp32 257 / 403 us, 512^3
 // fp32 10.7 / 26.7 us (of the last, 4.5 us are host time saved by the native argument
 // checks).
 #include <hip/hip_runtime.h>
