@@ -36,7 +36,7 @@ PEAK_HBM_GBPS = 8000.0
 COUNTER_TRAFFIC = {
     "workload": "c3",
     "sources_sha256": "3772f9066c4bd9a8c9d70b22d3bf8223cffebbdc950ecfc0e6f1045464be396a",
-    "execute_bytes_per_launch": (2.0 * 218007 + 388631) * 1024,
+    "execute_bytes_per_launch": (2.0 * 217594 + 388667) * 1024,
     "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
 
