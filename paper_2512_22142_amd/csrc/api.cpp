@@ -416,26 +416,12 @@ struct AssembleTarget {
   int out_dtype = CLEAVE_F32;
 };
 
-// Bytes of the Infinity Cache: what is written last, up to that much, is still
-// there when the next launch reads it.
-constexpr int64_t kCacheBytes = int64_t{256} << 20;
-
 // The work items of a full launch whose chunk starts below the returned k leave
 // through non-temporal stores.  An output that the cache cannot hold pushes its own
 // first part (and the operands) out of it, and the next launch waits for those
 // write-backs; a streamed one goes to memory without them.  One that it can hold is
 // read from there by whoever comes next.
-//   Assembled outputs: streamed from the cache's size on.  Scores of 1024 x 1024 x
-// members into bf16, us, plain / streamed: the launch alone, with a softmax, an update in
-// place, the largest value of all behind it:
-//   134 MB    33 / 33     136 / 148    71 / 76     89 / 110
-//   168 MB    39 / 39     158 / 191    84 / 89    104 / 131
-//   201 MB    43 / 44     216 / 224    98 / 104   121 / 154
-//   235 MB    72 / 51     267 / 257   137 / 136   164 / 176
-//   268 MB    83 / 61     301 / 287   158 / 158   209 / 198
-//   336 MB   102 / 73     371 / 357   216 / 196   294 / 254
-//   537 MB   157 / 112    580 / 564   338 / 316   453 / 425
-// A reader that does little else still loses 7 % just below the cache's size.
+//   Assembled outputs: see streamed_output.
 //   Partial blocks of uniform plans (their items run chunk by chunk): execute +
 // reduce over plain, all chunks but the last streamed / all of them streamed:
 //   blocks of a chunk x chunks
@@ -461,13 +447,13 @@ uint32_t streamed_below(const cleave_plan* plan, const AssembleTarget& asm_to) {
   const int64_t outputs = plan->M * plan->N * members;
   if (asm_to.C) {
     const int64_t bytes = outputs * (asm_to.out_dtype == CLEAVE_BF16 ? 2 : 4);
-    return bytes >= kCacheBytes ? static_cast<uint32_t>(plan->K) : 0;
+    return cleave::streamed_output(bytes, plan->batch > 0) ? static_cast<uint32_t>(plan->K) : 0;
   }
   const int64_t splits = plan->uniform_splits;
-  if (splits < 2 || 4 * plan->partial_elems < kCacheBytes / 4 * 5) return 0;
+  if (splits < 2 || 4 * plan->partial_elems < cleave::kCacheBytes / 4 * 5) return 0;
   const int64_t chunk = (plan->K + splits - 1) / splits;
   if (chunk < 6 * int64_t{cleave::kDirectKStep}) return 0;
-  const bool all = 4 * outputs >= 3 * kCacheBytes || (4 * outputs >= kCacheBytes / 2 * 3 && splits >= 4);
+  const bool all = 4 * outputs >= 3 * cleave::kCacheBytes || (4 * outputs >= cleave::kCacheBytes / 2 * 3 && splits >= 4);
   return static_cast<uint32_t>(all ? plan->K : (splits - 1) * chunk);
 }
 

@@ -63,6 +63,34 @@ struct ExecuteArgs {
   const uint32_t* wg_ranges;
 };
 
+// Bytes of the Infinity Cache: what is written last, up to that much, is still
+// there when the next launch reads it.
+constexpr int64_t kCacheBytes = int64_t{256} << 20;
+
+// Whether the direct kernel streams an assembled output of `bytes` (streamed_below in
+// api.cpp).  A batch from the cache's size on: scores of 1024 x 1024 x members into bf16, us,
+// plain / streamed, the launch alone, with a softmax, an update in place, the largest value
+// of all behind it:
+//   134 MB    33 / 33     136 / 148    71 / 76     89 / 110
+//   168 MB    39 / 39     158 / 191    84 / 89    104 / 131
+//   201 MB    43 / 44     216 / 224    98 / 104   121 / 154
+//   235 MB    72 / 51     267 / 257   137 / 136   164 / 176
+//   268 MB    83 / 61     301 / 287   158 / 158   209 / 198
+//   336 MB   102 / 73     371 / 357   216 / 196   294 / 254
+//   537 MB   157 / 112    580 / 564   338 / 316   453 / 425
+// A reader that does little else still loses 7 % just below the cache's size.  A single
+// output, all of it in one order, is held a little longer: alone, with a product into
+// another matrix, in place, the largest value, K = 128 and 512, 268 MB of fp32 50 / 54,
+// 155 / 149, 131 / 133, 119 / 135 and 83 / 85, 180 / 178, 161 / 164, 161 / 164, of bf16 60 / 55,
+// 164 / 157, 139 / 134, 170 / 198 and 127 / 124, 221 / 220, 201 / 198, 239 / 260; 302 MB of fp32
+// 57 / 64, 175 / 167, 147 / 149, 162 / 151 and 95 / 94, 212 / 203, 186 / 181, 198 / 182, of bf16
+// 64 / 65, 186 / 170, 159 / 152, 230 / 222 and 146 / 144, 250 / 244, 227 / 225, 295 / 289; 361 MB
+// of bf16 79 / 75, 216 / 202, 189 / 182, 288 / 261.  So those from an eighth more on.  (A launch
+// of K up to 128 that only overwrites its own output again loses 11 to 19 % at 302 MB.)
+inline bool streamed_output(int64_t bytes, bool batched) {
+  return bytes >= (batched ? kCacheBytes : kCacheBytes / 8 * 9);
+}
+
 // Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, 256 x 256
 // (only for bf16 work items of the large class with both operands K-contiguous), or
 // the quarters of the 64 x 64 one (32 x 32, only fp32).

@@ -18,9 +18,10 @@ def exact(A, B):
 
 
 @pytest.mark.parametrize("M,N,out_dtype", [(16384, 8192, torch.bfloat16), (16384, 8184, torch.bfloat16),
-                                           (8192, 8192, torch.float32), (8456, 8192, torch.float32)])
+                                           (8192, 8192, torch.float32), (8456, 8192, torch.float32), (9216, 8192, torch.float32),
+                                           (9208, 8192, torch.float32), (18504, 8192, torch.bfloat16)])
 def test_assembled_output_around_the_size_of_the_cache(M, N, out_dtype):
-    """256 MiB and a little below or above it, full and clipped sub-tiles; sums below 2^8 in
+    """256 and 288 MiB and a little below or above, full and clipped sub-tiles; sums below 2^8 in
     magnitude are exact in bf16 too."""
     A, B = ints((M, 64), 1) * (torch.arange(64, device="cuda") < 16), ints((64, N), 2)
     plan = cleave.plan_uniform(M, N, 64, 512, 512, 1)

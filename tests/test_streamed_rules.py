@@ -1,5 +1,5 @@
-"""Which checked sums leave through non-temporal stores (host logic): those that lose
-nothing, whether or not the next launch reads them."""
+"""Which checked sums and assembled outputs leave through non-temporal stores (host
+logic): those that lose nothing, whether or not the next launch reads them."""
 import os
 import subprocess
 
@@ -12,8 +12,9 @@ SOURCE = r"""
 #include <cstdlib>
 #include "kernels.h"
 int main(int, char** v) {
-  const int64_t outputs = std::atoll(v[1]) * std::atoll(v[2]);
-  std::printf("%d", cleave::streamed_sum(outputs, outputs * std::atoll(v[3])));
+  const int64_t outputs = std::atoll(v[2]) * std::atoll(v[3]), x = std::atoll(v[4]);
+  if (v[1][0] == 's') std::printf("%d", cleave::streamed_sum(outputs, outputs * x));
+  else std::printf("%d", cleave::streamed_output(outputs * x, v[1][0] == 'b'));
   return 0;
 }
 """
@@ -39,4 +40,11 @@ def rule(tmp_path_factory):
     (8192, 9216, 1, True), (8192, 10240, 4, True), (8192, 10240, 6, False), (16384, 16384, 4, True),
     (2**29, 2**30, 1, True)])
 def test_sums_that_a_reader_would_miss_stay_in_the_cache(rule, M, N, S, streams):
-    assert rule(M, N, S) == streams
+    assert rule("sum", M, N, S) == streams
+
+
+@pytest.mark.parametrize("M,N,element,single,batch", [
+    (16384, 4096, 2, False, False), (16384, 8184, 2, False, False), (16384, 8192, 2, False, True), (8192, 8192, 4, False, True),
+    (8192, 9208, 4, False, True), (8192, 9216, 4, True, True), (16384, 16384, 2, True, True)])
+def test_a_single_output_is_streamed_later_than_a_batch(rule, M, N, element, single, batch):
+    assert rule("output", M, N, element) == single and rule("batch", M, N, element) == batch
