@@ -532,7 +532,7 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // 196, 185 / 191, 184 / 195, 896 items 246 / 227, 242 / 226, 249 / 229; 12 steps, 480 items
 // 52.7 / 54.1, 52.3 / 54.0, 53.5 / 55.1, 768 items 76.4 / 81.2, 76.3 / 81.9, 77.4 / 80.9.
 // The wide tile multiplies all of an item, the narrow one the 64 x 64 parts that hold
-// something (`parts64` in all): with small blocks there is less to win.  Below four
+// something (`list.parts64` in all): with small blocks there is less to win.  Below four
 // rounds it runs from four fifths on, from there on from a half.  fp32, 1024 of K, by what
 // the items hold: 960 items 0.56 246 / 230, 242 / 225, 248 / 231; 720 items 0.88 183 / 186,
 // 184 / 183, 183 / 187; 512 items of 64 x 64 blocks (0.25, 512 of K) 64 / 22, 64 / 21, 66 / 22;
@@ -549,7 +549,14 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // 12.4 / 10.5, 12.0 / 10.9, 12.4 / 10.2; 32 items of 128 10.3 / 10.1, 10.1 / 10.6,
 // 10.5 / 9.7, of 256 12.7 / 11.5, 12.4 / 12.5, 12.8 / 11.0, of 1024 28.4 / 21.1, 28.1 /
 // 24.7, 28.6 / 19.7; 40 items of 256 12.8 / 13.1, 12.6 / 14.0, 12.9 / 12.1; 64 of 512
-// 19.3 / 21.3, 18.8 / 22.7, 19.3 / 19.1.
+// 19.3 / 21.3, 18.8 / 22.7, 19.3 / 19.1.  With two on a CU, beyond 16 items, only chunks from
+// 128 elements on, of two K-contiguous operands (whose fragments take twice the reads) from
+// 256; execute alone, layouts NN, NT, TN, TT: 16 items of 32 4.4 / 4.4, 4.4 / 4.5, 4.6 / 4.5,
+// 4.6 / 4.4, of 128 6.3 / 5.3, 6.1 / 5.7, 6.4 / 4.9, 6.3 / 5.2; 21 items of 32 4.5 / 4.8, 4.5 / 5.0,
+// 4.6 / 4.6, 4.6 / 4.8, of 64 5.1 / 5.3, 4.9 / 5.5, 5.2 / 4.9, 5.1 / 5.3, of 128 6.4 / 6.1, 6.1 / 6.5,
+// 6.4 / 5.5, 6.3 / 6.1; 32 items of 64 5.5 / 5.7, 5.5 / 5.9, 5.5 / 5.6, 5.6 / 5.6, of 128 6.4 / 6.3,
+// 6.3 / 6.7, 6.5 / 5.7, 6.5 / 6.4, of 200 8.5 / 7.7, 8.3 / 8.4, 8.6 / 6.8, 8.5 / 7.7, of 384
+// 11.6 / 9.8, 11.5 / 11.1, 11.8 / 8.7, 11.7 / 10.0.
 // `whole`: that many 256 x 256 items of a subset (full launches of this kernel run
 // the all-small list), with `steps` whole K steps between them, that the kernel
 // could take as they are (bf16, both operands K-contiguous: six
@@ -558,14 +565,17 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // alone on a CU (us, 128 / 256: 17 steps, 256 items 57 / 50, 1024 items 230 / 193, 688 items 144 / 132,
 // 576 items, the third round a quarter full, 116 / 127; 5 steps, 1024 items
 // 92.7 / 92.6, 688 items 59 / 66).
-cleave::ExecuteTile general_tile(int dtype, int64_t items, int64_t parts64, int64_t whole, int64_t steps, int cus) {
+cleave::ExecuteTile general_tile(int dtype, bool both_k, int64_t items, const cleave::ListShape& list, int64_t whole,
+                                 int64_t steps, int cus) {
   const int64_t places = (whole + cus - 1) / cus * cus;
   if (whole > 0 && whole * 8 >= places * 7 && steps >= 16 * whole) return cleave::kTileHuge;
-  if (dtype == CLEAVE_F32 && 8 * items <= cus) return cleave::kTileQuarter;
+  if (dtype == CLEAVE_F32 && 8 * items <= cus && (16 * items <= cus || list.longest >= (both_k ? 256u : 128u)))
+    return cleave::kTileQuarter;
   if (dtype == CLEAVE_BF16) return 2 * items <= cus ? cleave::kTileNarrow : cleave::kTileWide;
   const int64_t places_wide = (items + cus - 1) / cus * cus;
-  const bool wide = items >= int64_t{4} * cus ? parts64 > 2 * items
-                                              : items > cus && 16 * items >= 15 * places_wide && 5 * parts64 >= 16 * items;
+  const bool wide = items >= int64_t{4} * cus
+                        ? list.parts64 > 2 * items
+                        : items > cus && 16 * items >= 15 * places_wide && 5 * list.parts64 >= 16 * items;
   return wide ? cleave::kTileWide : cleave::kTileNarrow;
 }
 
@@ -827,7 +837,8 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
                         ldb * eb < (int64_t{1} << 24);
       const cleave::GeneralLoads how{
-          general_tile(dtype, counts[c] * (large ? 4 : 1), shapes[c].parts64, large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
+          general_tile(dtype, !transA && transB, counts[c] * (large ? 4 : 1), shapes[c],
+                       large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
           a_elements, b_elements, shapes[c], cus};
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);

@@ -46,6 +46,25 @@ def test_a_few_tasks_have_the_bits_of_the_full_launch(K, transA, transB):
         assert og.rel_frobenius(got, ref) <= TOL["f32"]
 
 
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+@pytest.mark.parametrize("K", [127, 128, 255, 256])
+def test_two_quarters_on_a_cu_only_with_longer_chunks(K, transA, transB):
+    """Up to 16 items in quarters at any length; beyond, where their fewer products per load
+    do not cost more than the shorter chains give."""
+    least = 256 if (transA, transB) == (0, 1) else 128
+    for N, quarters in ((512, True), (640, K >= least), (1024, K >= least)):    # 16, 20 and 32 items
+        A = stored(make_matrix(25, 512, K, "f32", integer_valued=True), transA)
+        B = stored(make_matrix(26, K, N, "f32", integer_valued=True), transB)
+        plan = cleave.plan_uniform(512, N, K, 256, 256, 1)
+        parts = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
+        C = torch.empty((512, N), dtype=torch.float32, device="cuda")
+        cleave.execute(plan, A.cuda(), B.cuda(), parts, transA, transB)
+        assert ("quarters" in plan.last_kernel) == quarters, (N, plan.last_kernel)
+        cleave.reduce(plan, parts, C)
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy(), og.gemm(*og.logical_operands(A, transA, B, transB)))
+
+
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("M,N", [(1, 7), (15, 17), (16, 16), (31, 33), (32, 32), (65, 63)])
 def test_assembled_edges_of_the_quarter(M, N, out_dtype):
