@@ -539,7 +539,7 @@ int cut_items(ExecuteArgs* args, int tile_class, const GeneralLoads& how) {
   // (only for the two shapes that the figures beside general_workgroups are of)
   constexpr bool kTakesSecond = S::SETS == 2 && (S::TM == 128 || S::TM == 64);
   const int64_t resident = static_cast<int64_t>(how.cus) * (S::WPE * 4 / (S::NT / 64));
-  return general_workgroups(blocks, resident, kTakesSecond && how.list.equal());
+  return general_workgroups(blocks, resident, kTakesSecond ? second_tiles_taken_up_to(resident, S::TM, how.list) : 0);
 }
 
 template <typename S>

@@ -123,21 +123,30 @@ inline int parts_along(uint32_t extent, int item, int tile) {
 // turn).  Left to the dispatcher, the first CUs to finish get a full second round and
 // the others none.  us, dispatcher / taken, layouts NN, NT, TN: bf16, 128 x 128, 768 tiles
 // of 10 steps 36.1 / 35.1, 33.2 / 33.3, 32.2 / 32.2, of 3 17.9 / 17.2, 17.6 / 16.3, 19.2 / 17.4,
-// 544 of 16 34.3 / 32.6, 32.5 / 31.3, 40.1 / 39.1; fp32, 128 x 128, 768 of 32 188 / 184, 187 /
-// 184, 190 / 184, 480 of 32 the same; 64 x 64, 1152 of 32 84.3 / 81.1, 83.0 / 80.3, 84.5 / 81.4,
-// of 8 27.8 / 26.5, 29.0 / 26.1, 29.0 / 26.7, 1536 of 32 the same.  Behind two rounds the
-// finish times are spread anyway: bf16, 1920 tiles of 4 steps 45.6 / 46.2, 4095^3 219 /
-// 226, fp32 4096^3 1007 / 1016.
-//   Only with `equal` chunks: a fixed pairing can put two long ones on one workgroup,
+// 544 of 16 34.3 / 32.6, 32.5 / 31.3, 40.1 / 39.1; fp32, 128 x 128, 768 of 32 187 / 183, 186 /
+// 184, 188 / 185; 64 x 64, 1152 of 32 84.3 / 81.1, 83.0 / 80.3, 84.5 / 81.4, of 8 27.8 / 26.5,
+// 29.0 / 26.1, 29.0 / 26.7, 1536 of 32 the same, 1792 of 32 116 / 116, 125 / 114, 118 / 117.
+//   `taken_up_to` (second_tiles_taken_up_to): two rounds for 64 x 64; for 128 x 128 one and a
+// half, two with short chunks, up to 256 elements: longer ones lose there.  bf16, 832 tiles of 8
+// steps 32.8 / 34.7, 35.7 / 37.5, 33.4 / 34.5, of 32 81 / 84, 76 / 79, 89 / 93, 1024 of 32 87 / 90,
+// 82 / 84, 94 / 99, of 3 22.1 / 21.4, 21.9 / 20.8, 23.6 / 22.1; fp32, 1024 of 32 246 / 247, 243 /
+// 243, 248 / 250, of 8 72.5 / 70.7, 72.6 / 70.9, 74.2 / 72.3.  Behind two rounds the finish
+// times are spread anyway: bf16, 1920 tiles of 4 steps 45.6 / 46.2, 4095^3 219 / 226, fp32
+// 4096^3 1007 / 1016.
+//   Nothing (0) without equal chunks: a fixed pairing can put two long ones on one workgroup,
 // where the dispatcher hands the next tile to whoever is done.  Tiles of 128 with one,
 // two or four splits at random, dispatcher / taken: fp32, 1536 x 1536 x 2048 94.2 / 115, 91.9 /
 // 114, 93.0 / 115, 1536 x 1024 x 4096 (up to eight) 142 / 161, 140 / 160, 142 / 161; bf16 with
 // unaligned rows, 2048 x 2048 x 2048 36.2 / 43.6, 37.5 / 43.8, 35.9 / 43.7, one or two, 3072 x
 // 3072 x 512 25.7 / 28.2, 26.1 / 28.4, 26.6 / 28.9.
-inline int general_workgroups(int64_t blocks, int64_t resident, bool equal) {
-  if (equal && blocks > resident && blocks <= 2 * resident) return static_cast<int>(resident);
+inline int general_workgroups(int64_t blocks, int64_t resident, int64_t taken_up_to) {
+  if (blocks > resident && blocks <= taken_up_to) return static_cast<int>(resident);
   constexpr int64_t kMaxGrid = int64_t{1} << 20;   // the kernel loops beyond that
   return static_cast<int>(blocks < kMaxGrid ? blocks : kMaxGrid);
+}
+inline int64_t second_tiles_taken_up_to(int64_t resident, int tile, const ListShape& list) {
+  if (!list.equal()) return 0;
+  return tile == 64 || list.longest <= 256 ? 2 * resident : resident / 2 * 3;
 }
 
 // Enqueues the general execute kernel over work items of one tile class: any

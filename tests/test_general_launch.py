@@ -16,6 +16,7 @@ SOURCE = r"""
 
 using cleave::general_workgroups;
 using cleave::parts_along;
+using cleave::second_tiles_taken_up_to;
 
 // a band of 12 tiles of 128 x 128, tile j with splits[j % n]
 cleave_plan* band(int64_t K, const std::vector<int32_t>& splits) {
@@ -37,16 +38,22 @@ BODY
 CASES = {
     "unequal_chunks_are_left_to_the_dispatcher": """
   CHECK(!band(1024, {1, 2, 4})->shape.equal() && !band(128, {1, 2})->shape.equal());
-  CHECK(general_workgroups(600, 512, false) == 600 && general_workgroups(1024, 512, false) == 1024);
+  CHECK(second_tiles_taken_up_to(512, 128, band(1024, {1, 2, 4})->shape) == 0 && second_tiles_taken_up_to(1024, 64, band(128, {1, 2})->shape) == 0);
+  CHECK(general_workgroups(600, 512, 0) == 600 && general_workgroups(1024, 512, 0) == 1024);
 """,
     "equal_ones_and_a_shorter_last_chunk_are_not": """
   CHECK(band(1024, {1})->shape.equal() && band(1024, {4})->shape.equal() && band(3001, {4})->shape.equal());
   CHECK(band(1501, {2})->shape.equal() && !band(10, {4})->shape.equal());
-  CHECK(general_workgroups(513, 512, true) == 512 && general_workgroups(1024, 512, true) == 512);
+  CHECK(general_workgroups(513, 512, 768) == 512 && general_workgroups(768, 512, 768) == 512 && general_workgroups(1024, 512, 1024) == 512);
 """,
     "one_round_and_more_than_two": """
-  CHECK(general_workgroups(512, 512, true) == 512 && general_workgroups(8, 512, true) == 8);
-  CHECK(general_workgroups(1025, 512, true) == 1025 && general_workgroups(int64_t{1} << 40, 512, true) == 1 << 20);
+  CHECK(general_workgroups(512, 512, 1024) == 512 && general_workgroups(8, 512, 1024) == 8 && general_workgroups(769, 512, 768) == 769);
+  CHECK(general_workgroups(1025, 512, 1024) == 1025 && general_workgroups(int64_t{1} << 40, 512, 1024) == 1 << 20);
+""",
+    "the_large_tile_to_half_of_the_second_round": """
+  CHECK(second_tiles_taken_up_to(512, 128, band(257, {1})->shape) == 768 && second_tiles_taken_up_to(512, 128, band(4096, {1})->shape) == 768);
+  CHECK(second_tiles_taken_up_to(512, 128, band(256, {1})->shape) == 1024 && second_tiles_taken_up_to(512, 128, band(1024, {4})->shape) == 1024);
+  CHECK(second_tiles_taken_up_to(1024, 64, band(4096, {1})->shape) == 2048);
 """,
     "no_tiles_that_hold_nothing": """
   cleave_plan* plan = nullptr;
