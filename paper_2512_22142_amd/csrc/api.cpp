@@ -330,7 +330,7 @@ const char* kernel_name(int dtype, const cleave::GeneralLoads& how, int transA, 
        {"none", "execute_bf16_256x256_nt", "none", "none"},
        {"none", "none", "none", "none"},
        {"execute_bf16_element", "execute_bf16_element", "execute_bf16_element", "execute_bf16_element"}}};
-  const int row = how.a_elements || how.b_elements ? 4 : how.tile;
+  const int row = how.a_elements || how.b_elements ? 4 : how.tile == cleave::kTileWide4 ? cleave::kTileWide : how.tile;
   return names[dtype == CLEAVE_BF16 ? 1 : 0][row][(transA ? 2 : 0) + (transB ? 1 : 0)];
 }
 
@@ -836,10 +836,13 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       // in-tile byte offsets (256 rows) stay within 32 bits
       const bool by_k = !transA && transB && !a_elements && !b_elements && lda * eb < (int64_t{1} << 24) &&
                         ldb * eb < (int64_t{1} << 24);
-      const cleave::GeneralLoads how{
-          general_tile(dtype, !transA && transB, counts[c] * (large ? 4 : 1), shapes[c],
-                       large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0, steps[c], cus),
+      const int64_t items = counts[c] * (large ? 4 : 1);
+      cleave::GeneralLoads how{
+          general_tile(dtype, !transA && transB, items, shapes[c], large && dtype == CLEAVE_BF16 && by_k ? counts[c] : 0,
+                       steps[c], cus),
           a_elements, b_elements, shapes[c], cus};
+      if (how.tile == cleave::kTileWide && cleave::four_waves(dtype, transA, transB, items, shapes[c], cus))
+        how.tile = cleave::kTileWide4;
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);
       if (counts[c] > most) plan->last_kernel = kernel_name(dtype, how, transA, transB);

@@ -537,7 +537,7 @@ int cut_items(ExecuteArgs* args, int tile_class, const GeneralLoads& how) {
   args->parts_n = parts_along(how.list.cols, tile_cols(tile_class), S::TN);
   const int64_t blocks = (args->n_items + 7) / 8 * 8 * args->parts_m * args->parts_n;
   // (only for the two shapes that the figures beside general_workgroups are of)
-  constexpr bool kTakesSecond = S::SETS == 2 && (S::TM == 128 || S::TM == 64);
+  constexpr bool kTakesSecond = S::SETS == 2 && S::WPE == 4;
   const int64_t resident = static_cast<int64_t>(how.cus) * (S::WPE * 4 / (S::NT / 64));
   return general_workgroups(blocks, resident, kTakesSecond ? second_tiles_taken_up_to(resident, S::TM, how.list) : 0);
 }
@@ -576,6 +576,9 @@ using Quarter = Shape<4, 32, 32, 2, 2, 2, 8>;
 // 4096^3 1012 / 967.
 template <int EB>
 using Wide = Shape<EB, 128, 128, 4, 2, 2, 4>;
+// (which launches run it: four_waves in kernels.h)
+template <int EB>
+using Wide4 = Shape<EB, 128, 128, 2, 2, 2, 2>;
 using Large = Shape<2, kLargeTileRows, kLargeTileCols, 2, 4, 1, 2>;
 template <int EB>
 using Narrow = Shape<EB, 64, 64, 2, 2, 2, 4>;
@@ -589,6 +592,9 @@ hipError_t configure_type() {
   if (e == hipSuccess) e = configure_elements<ByElement<EB>>();
   if (EB == 4 && e == hipSuccess) e = configure_layouts<Quarter>();
   if (EB == 2 && e == hipSuccess) e = configure_one<Large, kByK, kByK>();
+  if (e == hipSuccess) e = configure_one<Wide4<EB>, kByK, kByK>();
+  if (e == hipSuccess) e = configure_one<Wide4<EB>, kByRow, kByRow>();
+  if (EB == 4 && e == hipSuccess) e = configure_one<Wide4<4>, kByRow, kByK>();
   return e;
 }
 
@@ -600,6 +606,13 @@ hipError_t launch_type(const ExecuteArgs& args, int tile_class, const GeneralLoa
     ExecuteArgs whole = args;
     const int grid = cut_items<Large>(&whole, tile_class, how);
     return launch_one<Large, kByK, kByK>(whole, grid, stream);
+  }
+  if (how.tile == kTileWide4) {   // NT, TN and, fp32 only, TT
+    ExecuteArgs cut = args;
+    const int grid = cut_items<Wide4<EB>>(&cut, tile_class, how);
+    if (!args.transA) return launch_one<Wide4<EB>, kByK, kByK>(cut, grid, stream);
+    if (EB == 4 && args.transB) return launch_one<Wide4<4>, kByRow, kByK>(cut, grid, stream);
+    return launch_one<Wide4<EB>, kByRow, kByRow>(cut, grid, stream);
   }
   if (EB == 4 && how.tile == kTileQuarter) return launch_layouts<Quarter>(args, tile_class, how, stream);
   return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, how, stream)

@@ -93,8 +93,35 @@ inline bool streamed_output(int64_t bytes, bool batched) {
 
 // Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, 256 x 256
 // (only for bf16 work items of the large class with both operands K-contiguous), or
-// the quarters of the 64 x 64 one (32 x 32, only fp32).
-enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2, kTileQuarter = 3 };
+// the quarters of the 64 x 64 one (32 x 32, only fp32).  kTileWide4: 128 x 128 in four waves.
+enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2, kTileQuarter = 3, kTileWide4 = 4 };
+
+// Whether a list of `items` 128 x 128 tiles runs in four waves of 64 x 64 each instead of eight
+// of 32 x 64.  Eight read half as much again from LDS per product and hide a workgroup's start
+// and end, a wait for operands and a round that is not full; over several rounds the chip is
+// full anyway.  bf16 with two K-contiguous operands (whose wave tiles of 64 x 64 read the
+// least), from three rounds of the CUs on; TN, whose transpose reads are the dearest, from
+// seven on with chunks beyond 256.  us, four waves / eight, each running by itself:
+//   elements         33            515            1023           2047           4095
+//   NT  1024     17.9 / 18.8    37.8 / 38.3    46.7 / 47.6    81.7 / 83.5   153 / 154
+//       1155                    44.3 / 45.0    55.2 / 56.8    97.0 / 97.4   182 / 184
+//       2048     29.1 / 31.4    70.0 / 74.0    90.0 / 91.0    160 / 161     299 / 302
+//       4096     51.4 / 55.7    134 / 144      178 / 180      316 / 320     595 / 609
+//   TN  1024     16.9 / 16.4    36.5 / 35.1    55.0 / 55.6    97.0 / 98.8   181 / 192
+//       1155                    43.0 / 41.5    66.0 / 66.0    119 / 118     223 / 220
+//       2048     28.5 / 28.4    67.1 / 67.8    107 / 111      192 / 198     361 / 369
+//       4096     51.3 / 50.1    134 / 135      216 / 221      383 / 394     739 / 755
+// NN and TT are 1 % slower to 6 % faster in eight but for 4096 items of 515 (134 / 136, 133 /
+// 136).  Between launches of other kernels eight gain up to 4 % more with long chunks.
+// fp32 from four rounds on with up to 128 elements, but for NN, which changes side at every
+// length (.962 to 1.021); time of eight over four's, NT, TN, TT: 1280 items of 64 1.045,
+// 1.053, 1.043, of 128 1.020, 1.012, 1.020, of 192 1.002, 1.012, 1.002; 4096 items of 64 1.036,
+// 1.036, 1.029, of 128 1.005, 1.011, 1.001, of 512 .992, .990, .963; 1024 of 64 .997, 1.018, .985.
+inline bool four_waves(int dtype, int transA, int transB, int64_t items, const ListShape& list, int cus) {
+  if (dtype == CLEAVE_BF16)
+    return transA != transB && (transB ? items > int64_t{3} * cus : items > int64_t{7} * cus && list.longest > 256);
+  return (transA || transB) && items > int64_t{4} * cus && list.longest <= 128;
+}
 // An operand with rows shorter than 16 bytes is loaded one element at a time
 // (64 x 64 tile, whatever `tile`); the other one still takes 16-byte loads.
 struct GeneralLoads {

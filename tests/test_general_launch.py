@@ -64,6 +64,24 @@ CASES = {
   CHECK(parts_along(129, 128, 64) == 2 && parts_along(2147483647u, 256, 128) == 2 && parts_along(4294967295u, 256, 256) == 1);
   CHECK(parts_along(129, 256, 128) == 2 && parts_along(129, 256, 64) == 3 && parts_along(256, 256, 64) == 4);
 """,
+    "waves_of_the_large_tile": """
+  cleave::ListShape l;
+  cleave_task t{};
+  t.m_len = t.n_len = t.k_len = 128;
+  l.add(t);
+  const auto four = [&](int dtype, int ta, int tb, int64_t items) { return cleave::four_waves(dtype, ta, tb, items, l, 256); };
+  CHECK(four(CLEAVE_BF16, 0, 1, 769) && !four(CLEAVE_BF16, 0, 1, 768));
+  CHECK(!four(CLEAVE_BF16, 0, 0, 4096) && !four(CLEAVE_BF16, 1, 0, 4096) && !four(CLEAVE_BF16, 1, 1, 4096));
+  CHECK(four(CLEAVE_F32, 0, 1, 1025) && four(CLEAVE_F32, 1, 0, 1025) && four(CLEAVE_F32, 1, 1, 1025));
+  CHECK(!four(CLEAVE_F32, 0, 0, 4096) && !four(CLEAVE_F32, 0, 1, 1024));
+  t.k_len = 129;
+  l.add(t);
+  CHECK(!four(CLEAVE_F32, 0, 1, 4096) && four(CLEAVE_BF16, 0, 1, 4096));
+  t.k_len = 257;
+  l.add(t);
+  CHECK(four(CLEAVE_BF16, 1, 0, 1793) && !four(CLEAVE_BF16, 1, 0, 1792) && four(CLEAVE_BF16, 0, 1, 4096));
+  CHECK(!four(CLEAVE_BF16, 0, 0, 4096) && !four(CLEAVE_BF16, 1, 1, 4096));
+""",
     "the_longest_chunks": """
   cleave::ListShape l;
   cleave_task t{};

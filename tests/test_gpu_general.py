@@ -97,6 +97,28 @@ def test_wide_tiles_exact(dtype, transA, transB):
 
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_wide_tiles_of_several_rounds_exact(dtype, transA, transB):
+    # beyond three (bf16, NT), seven (TN) and four (fp32) rounds of the CUs: the tile in four waves
+    M, N, K, S = (1400, 1303, 8 * 70 - 3, 8) if dtype == "bf16" else (2049, 2055, 4 * 65 - 1, 4)
+    check(M, N, K, (256, 250), S, transA, transB, dtype, pad=1, kernel="128x128")
+
+
+def test_four_waves_of_two_operands_across_exact():
+    """bf16, TN: 1815 items of 261 elements, full and clipped ones."""
+    M, N, K = 1400, 1900, 11 * 261 - 5
+    a, b = make_matrix(51, M, K, "bf16", integer_valued=True), make_matrix(52, K, N, "bf16", integer_valued=True)
+    plan = cleave.plan_uniform(M, N, K, 128, 128, 11)
+    parts = torch.full((plan.partial_elems,), float("nan"), dtype=torch.float32, device="cuda")
+    C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    cleave.execute(plan, tight(stored(a, 1), 1), tight(b, 3), parts, 1, 0)
+    assert plan.num_tasks == 1815 and plan.last_kernel == "execute_bf16_128x128_tn"
+    cleave.reduce(plan, parts, C)
+    torch.cuda.synchronize()
+    assert torch.equal(C.cpu(), (a.double() @ b.double()).float())
+
+
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_rows_shorter_than_a_load_exact(dtype, transA, transB):
     for M, N, K, S in ((1, 1, 1, 1), (3, 2, 5, 5), (2, 300, 70, 2), (130, 3, 65, 1), (40, 50, 6, 2), (5, 7, 100, 3)):
         check(M, N, K, (64, 64), S, transA, transB, dtype)
