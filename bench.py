@@ -35,8 +35,8 @@ PEAK_HBM_GBPS = 8000.0
 # dropped on a mismatch.
 COUNTER_TRAFFIC = {
     "workload": "c3",
-    "sources_sha256": "3772f9066c4bd9a8c9d70b22d3bf8223cffebbdc950ecfc0e6f1045464be396a",
-    "execute_bytes_per_launch": (2.0 * 217594 + 388667) * 1024,
+    "sources_sha256": "9283fe1123acbbc002f7125430b1b7f7e24ca21b7ebe5c1122aae6c728b1cdf2",
+    "execute_bytes_per_launch": (2.0 * 217814 + 388644) * 1024,
     "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
 
