@@ -579,24 +579,22 @@ cleave::ExecuteTile general_tile(int dtype, bool both_k, int64_t items, const cl
   return wide ? cleave::kTileWide : cleave::kTileNarrow;
 }
 
-// Shape of the direct kernel for `items` work items of a class with `steps` K
-// steps between them.  Small items run as 64 x 64 parts while a part has a
-// place of its own, two on each CU (an item is four of them): there parts win
-// at every chain length.  From there to one item per CU the deep ring wins when
-// chains are long and the operands come from HBM.  Time against 128 x 128 items
-// with two stages, operands in L2 / from HBM, by K steps per item (256 CUs, all
-// layouts):
-//                    4 steps      8            16           24           48
-//   128 items parts  0.83 / 0.84  0.85 / 0.89  0.80 / 0.73  0.80 / 0.70  0.73 / 0.66
-//   130 items parts  1.04 / 1.00  1.15 / 1.06  1.07 / 0.88  0.93 / 0.82  0.86 / 0.78
-//             deep   1.10 / 1.12  1.14 / 1.08  1.09 / 0.88  0.92 / 0.83  0.78 / 0.76
-//   160 items parts  1.06 / 1.03  1.15 / 1.06  1.08 / 0.91  1.01 / 0.90  0.93 / 0.88
-//             deep   1.09 / 1.12  1.12 / 1.03  1.09 / 0.89  1.02 / 0.84  0.84 / 0.77
-//   256 items deep   1.09 / 1.09  1.10 / 0.99  1.05 / 0.87  0.91 / 0.84  0.86 / 0.78
-cleave::DirectShape direct_shape(int cls, int64_t items, int64_t steps, int cus) {
+// Shape of the direct kernel for `items` work items of a class.  Small items run as 64 x 64
+// parts while a part has a place of its own, two on each CU (an item is four of them): there
+// parts win at every chain length.  From there to one item per CU the deep ring does.  Time
+// against 128 x 128 items with two stages, operands in L2 / from HBM, the largest of three
+// layouts, by K steps per item (256 CUs):
+//                    2 steps      4            8            16           24           48
+//   130 items parts  0.92 / 0.95  0.94 / 0.94  0.98 / 0.93  1.01 / 0.88  0.88 / 0.89  0.86 / 0.81
+//             deep   0.88 / 0.87  0.91 / 0.91  0.92 / 0.86  0.93 / 0.80  0.78 / 0.78  0.72 / 0.72
+//   160 items parts  0.97 / 0.98  0.98 / 0.98  1.02 / 0.98  0.98 / 0.91  0.96 / 0.92  0.95 / 0.93
+//             deep   0.88 / 0.88  0.91 / 0.90  0.92 / 0.87  0.93 / 0.83  0.90 / 0.76  0.78 / 0.73
+//   224 items deep   0.89 / 0.89  0.92 / 0.91  0.92 / 0.88  0.93 / 0.82  0.83 / 0.76  0.83 / 0.74
+//   256 items deep   0.90 / 0.90  0.92 / 0.92  0.93 / 0.87  0.91 / 0.80  0.83 / 0.76  0.85 / 0.73
+cleave::DirectShape direct_shape(int cls, int64_t items, int cus) {
   if (cls == cleave::kTileLarge) return cleave::kDirectLarge;
   if (items * 2 <= cus) return cleave::kDirectParts;
-  return items <= cus && steps >= 16 * items ? cleave::kDirectDeep : cleave::kDirectSmall;
+  return items <= cus ? cleave::kDirectDeep : cleave::kDirectSmall;
 }
 
 // Whether a full launch of the direct kernel cuts every block into small sub-tiles:
@@ -821,7 +819,7 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
       // Persistent workgroups, as many as the chip holds at once: each walks
       // the item list with the grid as stride and fetches the head of its next
       // item while it stores the current one.
-      const cleave::DirectShape shape = direct_shape(c, counts[c], steps[c], cus);
+      const cleave::DirectShape shape = direct_shape(c, counts[c], cus);
       const int64_t resident = static_cast<int64_t>(cus) * cleave::direct_workgroups_per_cu(shape);
       const int grid = static_cast<int>(std::min<int64_t>(counts[c], resident));
       // items of unequal length: the schedule made for this grid when the tables were uploaded

@@ -503,6 +503,15 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   };
   constexpr int kReadsA = (A_K ? 1 : 2) * MB, kReadsB = (B_K ? 1 : 2) * NB;
 
+  // How a step hands its ring stage on.
+  //   kRefilled: at least STAGES more whole steps follow it and only the ring's own loads are
+  //     outstanding: the stage is refilled, no case distinctions.
+  //   kRefilledLast (ONE_ITEM): the same, but the step it is refilled with is the chunk's last
+  //     and no whole one.
+  //   1 .. STAGES (ONE_ITEM): that many steps are left, this one among them, all in the ring.
+  //   kAnyStep: whatever applies.
+  constexpr int kAnyStep = 100, kRefilled = 101, kRefilledLast = 102;
+
   for (;;) {
     const int steps = c.steps;
     const bool has_next = !S::ONE_ITEM && it_next < it_end;
@@ -537,18 +546,17 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
     // after it has landed (loads return in order), so the stage is refilled
     // with the step STAGES further on -- this item's, or one of the next item's
     // first -- and the first fragments of the following step are fetched behind
-    // it, while the rest of the step multiplies.  MID: a step with at least STAGES
-    // more whole steps of this item behind it and none of the steps fetched ahead of
-    // the item in the ring -- no case distinctions, the loop body of long chunks.
-    auto k_step = [&](auto mid_tag, auto first_tag, int s) {
-      constexpr bool MID = decltype(mid_tag)::value;
+    // it, while the rest of the step multiplies.
+    auto k_step = [&](auto how_tag, auto first_tag, int s) {
+      constexpr int HOW = decltype(how_tag)::value;
+      constexpr bool MID = HOW == kRefilled;
       constexpr std::bool_constant<decltype(first_tag)::value> fresh{};   // the item's step 0
       constexpr std::false_type more{};
       const int st = (s + phase) & (STAGES - 1);
       const uint32_t cur = st * kStage;
       const uint32_t oth = ((st + 1) & (STAGES - 1)) * kStage;
       const bool last = s + 1 >= steps;
-      const bool go_on = MID || !last || cont;   // a step follows in the ring
+      const bool go_on = HOW == kAnyStep ? !last || cont : HOW != 1;   // a step follows in the ring
       auto hand_over = [&]() {
         if constexpr (MID) {
           CLEAVE_WAIT_BARRIER((STAGES - 2) * LPS);
@@ -560,6 +568,12 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
           } else {
             issue_a(c, st, first_half);
           }
+        } else if constexpr (HOW == kRefilledLast) {
+          CLEAVE_WAIT_BARRIER((STAGES - 2) * LPS);
+          ta.issue_tail(c.a_ptr, smem_off + st * kStage, wave, lane, c.tail);
+          tb.issue_tail(c.b_ptr, smem_off + st * kStage + kATile, wave, lane, c.tail);
+        } else if constexpr (HOW != kAnyStep) {
+          if constexpr (HOW > 1) CLEAVE_WAIT_BARRIER((HOW - 2) * LPS);
         } else {
           if (!go_on) {
             // nothing to wait for, and no reason to wait for the previous item's stores either
@@ -646,13 +660,35 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
         spread_reads<MB * NB, kReadsA + kReadsB>();
       }
     };
-    k_step(std::false_type{}, std::true_type{}, 0);
-    int s = 1;
-    if constexpr (STAGES > 2)
-      for (; s < STAGES - 1 && s < steps; ++s) k_step(std::false_type{}, std::false_type{}, s);
     const int full = steps - (TAILS && c.tail != 0);
-    for (; s + STAGES < full; ++s) k_step(std::true_type{}, std::false_type{}, s);
-    for (; s < steps; ++s) k_step(std::false_type{}, std::false_type{}, s);
+    if constexpr (S::ONE_ITEM) {
+      // The ring drains once: a copy of the step for each number of steps left, whose waits
+      // are constants.  What bounds a lone workgroup is the time of a step, and through the
+      // general form, with its branches between the matrix instructions, each of the first three
+      // and last four steps of a chunk took 0.1 us longer.  us, that form / this: parts, 16 items
+      // of 6 steps 4.7 / 4.1, of 16 6.5 / 5.7, 64 items of 8 5.8 / 4.9, 128 items of 16 9.9 / 9.1,
+      // deep, 192 items of 16 13.9 / 12.9, of 32 20.5 / 19.1.
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{};
+      int s = 0;
+      for (; s + STAGES < full; ++s) k_step(int_c<kRefilled>{}, std::false_type{}, s);
+      if (TAILS && s + STAGES < steps) k_step(int_c<kRefilledLast>{}, std::false_type{}, s++);
+      const int left = steps - s;
+      static_assert(!S::ONE_ITEM || STAGES == 4, "the copies below");
+      if (left > 3) k_step(int_c<4>{}, std::false_type{}, s++);
+      if (left > 2) k_step(int_c<3>{}, std::false_type{}, s++);
+      if (left > 1) k_step(int_c<2>{}, std::false_type{}, s++);
+      k_step(int_c<1>{}, std::false_type{}, s);
+    } else {
+      k_step(int_c<kAnyStep>{}, std::true_type{}, 0);
+      int s = 1;
+      if constexpr (STAGES > 2)
+        for (; s < STAGES - 1 && s < steps; ++s) k_step(int_c<kAnyStep>{}, std::false_type{}, s);
+      for (; s + STAGES < full; ++s) k_step(int_c<kRefilled>{}, std::false_type{}, s);
+      for (; s < steps; ++s) k_step(int_c<kAnyStep>{}, std::false_type{}, s);
+    }
 
     // Every wave is past the last step's barrier, hence past all of its
     // fragment reads of this item.
@@ -723,10 +759,10 @@ hipError_t configure_shape() {
 //   small class: 128 x 128 tile, 4 waves (each 64 x 64), two 32 KB stages, two
 //     workgroups per CU;
 //   deep: a launch with at most one small item per CU leaves half of the LDS
-//     unused and a lone workgroup waiting for its loads, one step ahead, when
-//     the operands come from HBM.  Four stages, three steps ahead, one workgroup
-//     per CU: 216 items of 64 steps 55 -> 42 us, 192 of 24 25.7 -> 21.6 us (inputs
-//     not in any cache); 256 of 12 steps 14.3 / 14.6 us, full launches lose the
+//     unused and a lone workgroup waiting for its loads, one step ahead.  Four
+//     stages, three steps ahead, one workgroup per CU: 192 items of 24 steps
+//     24.7 -> 18.5 us, of 12 12.9 -> 10.8, of 2 7.5 -> 6.6 (inputs not in any
+//     cache; the other lengths are beside direct_shape); full launches lose the
 //     second workgroup (4096 items of 16 steps 187 / 221 us);
 //   parts: a launch of few small items has one short-lived workgroup per CU, or
 //     none, and what bounds it is the time one K step takes a lone workgroup:
