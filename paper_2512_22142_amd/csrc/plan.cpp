@@ -33,18 +33,19 @@ constexpr int kXcds = 8;
 // spread over all XCDs instead of being kept on one.
 constexpr size_t kSpreadItems = 256;
 
-// The work items that run on an XCD at the same time (one per CU, 32 CUs) are
-// taken from a patch of kPatchRows x kPatchCols sub-tiles at one chunk of the
-// inner dimension: they share that many row panels of A and column panels of
-// B in the XCD's L2.
-#ifndef CLEAVE_PATCH_ROWS
-#define CLEAVE_PATCH_ROWS 4
-#endif
-#ifndef CLEAVE_PATCH_COLS
-#define CLEAVE_PATCH_COLS 8
-#endif
-constexpr uint32_t kPatchRows = CLEAVE_PATCH_ROWS;
-constexpr uint32_t kPatchCols = CLEAVE_PATCH_COLS;
+// The work items that run on an XCD at the same time (32 CUs, one large item or two small
+// ones on each) are taken from a patch of 4 x 8 (8 x 8) sub-tiles at one chunk of the
+// inner dimension: they share that many row panels of A and column panels of B in the XCD's L2.
+// Small items in patches of 4 x 8 / 8 x 8, bf16 in 128 x 128 blocks, the time of the second
+// over the first's, operands as the launch before left them / in no cache, layouts NN, NT, TN: 8192^2
+// with 128 of K 0.914 / 0.930, 0.918 / 0.931, 0.943 / 0.933, with 1024 0.984 / 0.924, 0.990 / 0.937, 0.960
+// / 0.920; 16384 x 4096 x 4096 in 4 splits 0.944 / 0.943, 0.951 / 0.945, 0.959 / 0.961; 6144^2 with 2048
+// 0.989 / 0.988, 0.976 / 0.984, 0.966 / 0.972.  Fewer items cover their regions in a few patches
+// and gain less or lose: 2048 with 1024 of K 1.002 / 0.955, 0.997 / 0.980, 1.003 / 0.972, with 512 up to
+// 1.035 / 1.011, 1024 with 2048 1.003 / 1.001, 1.026 / 1.002, 1.034 / 0.997.
+constexpr uint32_t kPatchCols = 8;
+constexpr size_t kManySmallItems = 2048;
+constexpr uint32_t patch_rows(int cls, size_t items) { return cls == kTileLarge || items <= kManySmallItems ? 4 : 8; }
 
 void order_work_items(cleave_plan* p) {
   // Region grid: minimise M/gm + N/gn over gm * gn = 8.
@@ -90,6 +91,7 @@ void order_work_items(cleave_plan* p) {
       uint32_t outer_member, split, pm, pn, inner_member, m, n;
       WorkItem item;
     };
+    const uint32_t rows = patch_rows(cls, source.size());
     std::vector<Key> lists[kXcds];
     for (auto& l : lists) l.reserve(source.size() / kXcds + 1);
     // Batch members share no output.  Small members (fewer items than the
@@ -108,7 +110,7 @@ void order_work_items(cleave_plan* p) {
       // split counts still line up by where in K they work
       const uint32_t split = static_cast<uint32_t>(static_cast<uint64_t>(t.k0) * 64 / static_cast<uint64_t>(p->K));
       const int region = member_per_xcd ? static_cast<int>(t.gemm_id % kXcds) : rm * gn + rn;
-      lists[region].push_back(Key{member_per_xcd ? t.gemm_id : 0u, split, m / (kPatchRows * tr),
+      lists[region].push_back(Key{member_per_xcd ? t.gemm_id : 0u, split, m / (rows * tr),
                                   n / (kPatchCols * tc), member_per_xcd ? 0u : t.gemm_id, m, n, w});
     }
     size_t longest = 0;
