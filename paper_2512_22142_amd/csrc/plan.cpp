@@ -34,8 +34,12 @@ constexpr int kXcds = 8;
 constexpr size_t kSpreadItems = 256;
 
 // The work items that run on an XCD at the same time (32 CUs, one large item or two small
-// ones on each) are taken from a patch of 4 x 8 (8 x 8) sub-tiles at one chunk of the
+// ones on each) are taken from a patch of 4 x 8 (long lists 8 x 8) sub-tiles at one chunk of the
 // inner dimension: they share that many row panels of A and column panels of B in the XCD's L2.
+// A long list's large items are two rounds then that share the column panels: 16384 x 5120 x
+// 13824 in 8 splits, three layouts with their sums, 8645 -> 8580 us, a layer of width 4096 6190 ->
+// 6160.  (Taller patches, 12 or 16 rows, the rows of patches to and fro, columns of patches
+// first: less, and up to 1.5 % slower on layers of width 768.)
 // Small items in patches of 4 x 8 / 8 x 8, bf16 in 128 x 128 blocks, the time of the second
 // over the first's, operands as the launch before left them / in no cache, layouts NN, NT, TN: 8192^2
 // with 128 of K 0.914 / 0.930, 0.918 / 0.931, 0.943 / 0.933, with 1024 0.984 / 0.924, 0.990 / 0.937, 0.960
@@ -44,8 +48,7 @@ constexpr size_t kSpreadItems = 256;
 // and gain less or lose: 2048 with 1024 of K 1.002 / 0.955, 0.997 / 0.980, 1.003 / 0.972, with 512 up to
 // 1.035 / 1.011, 1024 with 2048 1.003 / 1.001, 1.026 / 1.002, 1.034 / 0.997.
 constexpr uint32_t kPatchCols = 8;
-constexpr size_t kManySmallItems = 2048;
-constexpr uint32_t patch_rows(int cls, size_t items) { return cls == kTileLarge || items <= kManySmallItems ? 4 : 8; }
+constexpr uint32_t patch_rows(size_t items) { return items <= 2048 ? 4 : 8; }
 
 void order_work_items(cleave_plan* p) {
   // Region grid: minimise M/gm + N/gn over gm * gn = 8.
@@ -91,7 +94,7 @@ void order_work_items(cleave_plan* p) {
       uint32_t outer_member, split, pm, pn, inner_member, m, n;
       WorkItem item;
     };
-    const uint32_t rows = patch_rows(cls, source.size());
+    const uint32_t rows = patch_rows(source.size());
     std::vector<Key> lists[kXcds];
     for (auto& l : lists) l.reserve(source.size() / kXcds + 1);
     // Batch members share no output.  Small members (fewer items than the
