@@ -556,7 +556,8 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // 4.6 / 4.6, 4.6 / 4.8, of 64 5.1 / 5.3, 4.9 / 5.5, 5.2 / 4.9, 5.1 / 5.3, of 128 6.4 / 6.1, 6.1 / 6.5,
 // 6.4 / 5.5, 6.3 / 6.1; 32 items of 64 5.5 / 5.7, 5.5 / 5.9, 5.5 / 5.6, 5.6 / 5.6, of 128 6.4 / 6.3,
 // 6.3 / 6.7, 6.5 / 5.7, 6.5 / 6.4, of 200 8.5 / 7.7, 8.3 / 8.4, 8.6 / 6.8, 8.5 / 7.7, of 384
-// 11.6 / 9.8, 11.5 / 11.1, 11.8 / 8.7, 11.7 / 10.0.
+// 11.6 / 9.8, 11.5 / 11.1, 11.8 / 8.7, 11.7 / 10.0.  (The quarters' times are those of their
+// first form; since they read a step ahead they take 0.73-1.0 of them.)
 // `whole`: that many 256 x 256 items of a subset (full launches of this kernel run
 // the all-small list), with `steps` whole K steps between them, that the kernel
 // could take as they are (bf16, both operands K-contiguous: six

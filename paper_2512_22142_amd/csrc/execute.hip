@@ -264,6 +264,14 @@ struct OperandTile {
     if (s + 1 < steps) next += k_stride * KS;
   }
 
+  // A step before the last one: nothing to keep inside the operand.
+  __device__ __forceinline__ void load_inner(u32x4 (&v)[NV]) {
+    typedef typename std::conditional<EB == 2, u32x4_at2, u32x4_at4>::type chunk_t;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = *reinterpret_cast<const chunk_t*>(next + off[i]);
+    next += k_stride * KS;
+  }
+
   // Before the edge step is written to LDS: the wanted elements into place.
   __device__ __forceinline__ void settle(u32x4 (&v)[NV], int s, int t) const {
     if (!ELEMENTWISE && s == edge_step) {
@@ -389,10 +397,11 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
       constexpr int R = decltype(rows_tag)::value, KSUB = decltype(ks_tag)::value;
       if constexpr (S::BLK == 16 && KC) {
         // k of the sub-step: 4 lh + l4, and two further on; half of the lanes read them
-        // the other way round, so that the 64 words are in different banks
+        // the other way round (and swap them back before use), so that the 64 words are in
+        // different banks
         const uint32_t one = *reinterpret_cast<const uint32_t*>(stage + addr[KSUB]);
         const uint32_t two = *reinterpret_cast<const uint32_t*>(stage + (addr[KSUB] ^ 8));
-        return lh ? u32x4{two, one, 0, 0} : u32x4{one, two, 0, 0};
+        return u32x4{one, two, 0, 0};
       } else if constexpr (S::BLK == 16) {
         const uint32_t* q = reinterpret_cast<const uint32_t*>(stage + addr[x] + KSUB * (8 * R * 4));
         return u32x4{q[0], q[2 * R], 0, 0};
@@ -447,40 +456,114 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
     };
 
     const int steps = chunk_steps(item.k_len, S::KS);
-    // Steps 0 .. SETS-1 into registers, step 0 on into LDS, step SETS behind it.
-    fetch(int_c<0>{}, 0);
-    if constexpr (SETS > 1) fetch(int_c<1>{}, 1);
-    if (b != blockIdx.x) CLEAVE_LDS_BARRIER();   // every wave is past the previous item's last fragment reads
-    commit(int_c<0>{}, int_c<0>{}, 0);
-    fetch(int_c<0>{}, SETS);
-    CLEAVE_LDS_BARRIER();
-    read_frags(0, int_c<0>{}, 0);
-
-    // Step s sits in LDS stage s % 2; register set s % SETS holds step s until
-    // it is written to LDS at the end of step s - 1 (the stage's readers, step
-    // s - 2's, are past the barrier between), and then takes step s + SETS.
-    auto k_step = [&](auto phase_tag, int s) {
-      constexpr int P = decltype(phase_tag)::value;
-      constexpr int cur = P & 1, oth = cur ^ 1, next_set = (P + 1) % SETS;
-      read_frags(cur, int_c<1>{}, 1);
-      mma(0);
-      read_frags(cur, int_c<2>{}, 0);
-      mma(1);
-      read_frags(cur, int_c<3>{}, 1);
-      mma(0);
-      if (s + 1 < steps) {
-        commit(int_c<next_set>{}, int_c<oth>{}, s + 1);
-        fetch(int_c<next_set>{}, s + 1 + SETS);
+    if constexpr (S::BLK == 16) {
+      // A quarter is what a wave has alone on its SIMD, or with one other: a K step took 0.35
+      // us of which the matrix instructions are 0.11, the rest being waits for fragments read
+      // just before their use and the checks of the edge step.  So the fragments of step
+      // s + 1 are read, step s + 2 is written to LDS and step s + 4 loaded while step s is
+      // multiplied, and steps that are not near the last one check nothing.  Stage s % 2 is
+      // free then: step s's fragments were read before the barrier that ended step s - 1.
+      // Execute alone, us, before / after, layouts NN, NT, TN, operands in L2: 16 items of 128
+      // 5.3 / 5.0, 5.6 / 5.0, 4.7 / 4.6, of 512 9.5 / 8.2, 10.6 / 8.6, 8.2 / 6.9, of 2048
+      // 25.8 / 19.9, 30.5 / 22.2, 22.1 / 16.2; 32 items (two workgroups on a CU) of 256 8.0 / 7.5,
+      // 8.7 / 7.9, 6.9 / 6.7, of 1000 17.5 / 16.6, 21.2 / 19.0, 15.8 / 14.5.  (Four register sets
+      // instead of two: equal.)
+      u32x4 ga[2][S::kSub], gb[2][S::kSub];
+      auto read_sub = [&](auto stage_tag, auto ks_tag) {
+        constexpr int P = decltype(stage_tag)::value, KSUB = decltype(ks_tag)::value;
+        const unsigned char* stage = smem + P * S::kStage;
+        ga[P][KSUB] = read_frag(stage, a_addr, std::bool_constant<A_K>{}, int_c<TM>{}, ks_tag, 0);
+        gb[P][KSUB] = read_frag(stage, b_addr, std::bool_constant<B_K>{}, int_c<TN>{}, ks_tag, 0);
+      };
+      // (barriers to the scheduler: left alone it moves the reads down to their use)
+      auto mma_sub = [&](int p, int x) {
+        fa[0][0] = A_K && lh ? u32x4{ga[p][x][1], ga[p][x][0], 0, 0} : ga[p][x];
+        fb[0][0] = B_K && lh ? u32x4{gb[p][x][1], gb[p][x][0], 0, 0} : gb[p][x];
+        mma(0);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      fetch(int_c<0>{}, 0);
+      fetch(int_c<1>{}, 1);
+      if (b != blockIdx.x) CLEAVE_LDS_BARRIER();   // every wave is past the previous item's last fragment reads
+      commit(int_c<0>{}, int_c<0>{}, 0);
+      fetch(int_c<0>{}, 2);
+      CLEAVE_LDS_BARRIER();
+      read_sub(int_c<0>{}, int_c<0>{});
+      read_sub(int_c<0>{}, int_c<1>{});
+      read_sub(int_c<0>{}, int_c<2>{});
+      read_sub(int_c<0>{}, int_c<3>{});
+      if (steps > 1) commit(int_c<1>{}, int_c<1>{}, 1);
+      fetch(int_c<1>{}, 3);
+      CLEAVE_LDS_BARRIER();
+      auto k_step = [&](auto phase_tag, auto inner_tag, int s) {
+        constexpr int P = decltype(phase_tag)::value, O = P ^ 1;
+        constexpr bool INNER = decltype(inner_tag)::value;
+        read_sub(int_c<O>{}, int_c<0>{});
+        read_sub(int_c<O>{}, int_c<1>{});
+        mma_sub(P, 0);
+        read_sub(int_c<O>{}, int_c<2>{});
+        read_sub(int_c<O>{}, int_c<3>{});
+        mma_sub(P, 1);
+        if constexpr (INNER) {
+          ta.store(va[P], smem + P * S::kStage, t);
+          tb.store(vb[P], smem + P * S::kStage + S::kATile, t);
+          ta.load_inner(va[P]);
+          tb.load_inner(vb[P]);
+        } else if (s + 2 < steps) {
+          commit(int_c<P>{}, int_c<P>{}, s + 2);
+          fetch(int_c<P>{}, s + 4);
+        }
+        mma_sub(P, 2);
+        mma_sub(P, 3);
         CLEAVE_LDS_BARRIER();
-        read_frags(oth, int_c<0>{}, 0);
+      };
+      int s = 0;
+      for (; s + 6 < steps; s += 2) {   // the turn's last load is of step s + 5, not of the last step (the edge step)
+        k_step(int_c<0>{}, std::true_type{}, s);
+        k_step(int_c<1>{}, std::true_type{}, s + 1);
       }
-      mma(1);
-    };
-    for (int s = 0; s < steps;) {
-      k_step(int_c<0>{}, s);
-      if (++s >= steps) break;
-      k_step(int_c<1>{}, s);
-      if (++s >= steps) break;   // (not left to the loop's condition: the other form spills registers)
+      while (s < steps) {
+        k_step(int_c<0>{}, std::false_type{}, s);
+        if (++s >= steps) break;
+        k_step(int_c<1>{}, std::false_type{}, s);
+        ++s;
+      }
+    } else {
+      // Steps 0 .. SETS-1 into registers, step 0 on into LDS, step SETS behind it.
+      fetch(int_c<0>{}, 0);
+      if constexpr (SETS > 1) fetch(int_c<1>{}, 1);
+      if (b != blockIdx.x) CLEAVE_LDS_BARRIER();   // every wave is past the previous item's last fragment reads
+      commit(int_c<0>{}, int_c<0>{}, 0);
+      fetch(int_c<0>{}, SETS);
+      CLEAVE_LDS_BARRIER();
+      read_frags(0, int_c<0>{}, 0);
+
+      // Step s sits in LDS stage s % 2; register set s % SETS holds step s until
+      // it is written to LDS at the end of step s - 1 (the stage's readers, step
+      // s - 2's, are past the barrier between), and then takes step s + SETS.
+      auto k_step = [&](auto phase_tag, int s) {
+        constexpr int P = decltype(phase_tag)::value;
+        constexpr int cur = P & 1, oth = cur ^ 1, next_set = (P + 1) % SETS;
+        read_frags(cur, int_c<1>{}, 1);
+        mma(0);
+        read_frags(cur, int_c<2>{}, 0);
+        mma(1);
+        read_frags(cur, int_c<3>{}, 1);
+        mma(0);
+        if (s + 1 < steps) {
+          commit(int_c<next_set>{}, int_c<oth>{}, s + 1);
+          fetch(int_c<next_set>{}, s + 1 + SETS);
+          CLEAVE_LDS_BARRIER();
+          read_frags(oth, int_c<0>{}, 0);
+        }
+        mma(1);
+      };
+      for (int s = 0; s < steps;) {
+        k_step(int_c<0>{}, s);
+        if (++s >= steps) break;
+        k_step(int_c<1>{}, s);
+        if (++s >= steps) break;   // (not left to the loop's condition: the other form spills registers)
+      }
     }
 
     const int row0 = wm * S::WTM + lh * 4;
@@ -537,7 +620,7 @@ int cut_items(ExecuteArgs* args, int tile_class, const GeneralLoads& how) {
   args->parts_n = parts_along(how.list.cols, tile_cols(tile_class), S::TN);
   const int64_t blocks = (args->n_items + 7) / 8 * 8 * args->parts_m * args->parts_n;
   // (only for the two shapes that the figures beside general_workgroups are of)
-  constexpr bool kTakesSecond = S::SETS == 2 && S::WPE == 4;
+  constexpr bool kTakesSecond = S::BLK == 32 && S::SETS == 2 && S::WPE == 4;
   const int64_t resident = static_cast<int64_t>(how.cus) * (S::WPE * 4 / (S::NT / 64));
   return general_workgroups(blocks, resident, kTakesSecond ? second_tiles_taken_up_to(resident, S::TM, how.list) : 0);
 }
@@ -567,7 +650,7 @@ hipError_t launch_elements(ExecuteArgs args, int tile_class, const GeneralLoads&
 
 // Quarters of the 64 x 64 tile, a 16 x 16 block per wave, for launches of few fp32
 // items (general_tile in api.cpp).
-using Quarter = Shape<4, 32, 32, 2, 2, 2, 8>;
+using Quarter = Shape<4, 32, 32, 2, 2, 2, 4>;
 // Eight waves of 32 x 64: two on each SIMD where a launch leaves a CU one workgroup,
 // four where it has two.  us, four waves of 64 x 64 / eight, layouts NN, NT, TN: bf16, 192
 // items of 11 steps 17.3 / 15.2, 16.9 / 15.1, 17.7 / 15.5, 320 of 21 37.5 / 33.0, 36.2 /

@@ -65,6 +65,32 @@ def test_two_quarters_on_a_cu_only_with_longer_chunks(K, transA, transB):
         assert np.array_equal(C.cpu().numpy(), og.gemm(*og.logical_operands(A, transA, B, transB)))
 
 
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+@pytest.mark.parametrize("K", [33, 64, 65, 97, 161, 192, 193, 224, 225, 257, 289, 544])   # 2 to 17 steps of 32
+def test_steps_that_check_no_edge_and_the_last_ones(K, transA, transB):
+    """From seven steps on the quarters run pairs of steps without edge checks: the bits of the
+    64 x 64 tile, and nothing read behind the operands (NaN there)."""
+    M, N = 640, 512
+    def placed(x):
+        rows, cols = x.shape
+        room = torch.full((rows * cols + 4096,), float("nan"))
+        room[:rows * cols] = x.reshape(-1)
+        return room.cuda()[:rows * cols].view(rows, cols)
+    A, B = placed(stored(make_matrix(31, M, K, "f32"), transA)), placed(stored(make_matrix(32, K, N, "f32"), transB))
+    plan = cleave.plan_uniform(M, N, K, 64, 64, 1)     # 80 tiles
+    full = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
+    cleave.execute(plan, A, B, full, transA, transB)
+    assert "f32_64x64" in plan.last_kernel and "quarters" not in plan.last_kernel
+    ids = [0, 7, 41, 79]
+    few = torch.full_like(full, float("nan"))
+    cleave.execute(plan, A, B, few, transA, transB, task_ids=ids)
+    assert "quarters" in plan.last_kernel
+    torch.cuda.synchronize()
+    full, few = full.cpu().numpy(), few.cpu().numpy()
+    for i in ids:
+        assert np.array_equal(block_of(few, plan.tasks[i]), block_of(full, plan.tasks[i]))
+
+
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("M,N", [(1, 7), (15, 17), (16, 16), (31, 33), (32, 32), (65, 63)])
 def test_assembled_edges_of_the_quarter(M, N, out_dtype):
