@@ -89,6 +89,8 @@ struct Shape {
   static constexpr int kSub = 4;                // 32-byte sub-steps per step
   static constexpr int kATile = TM * 128, kBTile = TN * 128;   // bytes
   static constexpr int kStage = kATile + kBTile;
+  // the fragments of the next K step are read while a step is multiplied
+  static constexpr bool kAhead = SETS == 2 && MB == 1 && NB == 1 && (BLK == 16 || WPE == 2);
   static_assert(BLK == 32 || (EB == 4 && MB == 1 && NB == 1), "16 x 16: one block per wave, fp32");
   static_assert(SETS == 1 || SETS == 2, "register sets rotate with the two LDS stages");
 };
@@ -456,14 +458,14 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
     };
 
     const int steps = chunk_steps(item.k_len, S::KS);
-    if constexpr (S::BLK == 16) {
-      // A quarter is what a wave has alone on its SIMD, or with one other: a K step took 0.35
-      // us of which the matrix instructions are 0.11, the rest being waits for fragments read
+    if constexpr (S::kAhead) {
+      // A wave is alone on its SIMD here, or a quarter's with one other: a quarter's K step took
+      // 0.35 us of which the matrix instructions are 0.11, the rest being waits for fragments read
       // just before their use and the checks of the edge step.  So the fragments of step
       // s + 1 are read, step s + 2 is written to LDS and step s + 4 loaded while step s is
       // multiplied, and steps that are not near the last one check nothing.  Stage s % 2 is
       // free then: step s's fragments were read before the barrier that ended step s - 1.
-      // Execute alone, us, before / after, layouts NN, NT, TN, operands in L2: 16 items of 128
+      // Quarters, execute alone, us, before / after, layouts NN, NT, TN, operands in L2: 16 items of 128
       // 5.3 / 5.0, 5.6 / 5.0, 4.7 / 4.6, of 512 9.5 / 8.2, 10.6 / 8.6, 8.2 / 6.9, of 2048
       // 25.8 / 19.9, 30.5 / 22.2, 22.1 / 16.2; 32 items (two workgroups on a CU) of 256 8.0 / 7.5,
       // 8.7 / 7.9, 6.9 / 6.7, of 1000 17.5 / 16.6, 21.2 / 19.0, 15.8 / 14.5.  (Four register sets
@@ -477,8 +479,8 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
       };
       // (barriers to the scheduler: left alone it moves the reads down to their use)
       auto mma_sub = [&](int p, int x) {
-        fa[0][0] = A_K && lh ? u32x4{ga[p][x][1], ga[p][x][0], 0, 0} : ga[p][x];
-        fb[0][0] = B_K && lh ? u32x4{gb[p][x][1], gb[p][x][0], 0, 0} : gb[p][x];
+        fa[0][0] = S::BLK == 16 && A_K && lh ? u32x4{ga[p][x][1], ga[p][x][0], 0, 0} : ga[p][x];
+        fb[0][0] = S::BLK == 16 && B_K && lh ? u32x4{gb[p][x][1], gb[p][x][0], 0, 0} : gb[p][x];
         mma(0);
         __builtin_amdgcn_sched_barrier(0);
       };
@@ -665,6 +667,16 @@ using Wide4 = Shape<EB, 128, 128, 2, 2, 2, 2>;
 using Large = Shape<2, kLargeTileRows, kLargeTileCols, 2, 4, 1, 2>;
 template <int EB>
 using Narrow = Shape<EB, 64, 64, 2, 2, 2, 4>;
+// Read ahead as the quarters do, 180 registers instead of 126, for launches of at most one
+// 64 x 64 workgroup per CU whose longest chunk has eight steps or more.  us, Narrow / Lone,
+// layouts NN, NT, TN: fp32, 64 items, 4 steps 6.8 / 6.9, 6.4 / 6.6, 6.8 / 6.9, 8 steps 9.4 / 9.3,
+// 9.1 / 8.9, 9.5 / 9.2, 24 steps 20.1 / 17.5, 19.9 / 17.5, 20.3 / 17.6, 64 steps 47.2 / 38.9,
+// 47.4 / 38.9, 47.9 / 39.1; bf16, rows not 16-byte aligned, operands from HBM, 16 items, 4 steps
+// 5.3 / 5.5, 5.3 / 5.3, 5.5 / 5.7, 8 steps 8.0 / 7.7, 7.2 / 7.0, 8.3 / 7.8, 40 steps 22.3 / 17.5,
+// 22.5 / 17.4, 22.8 / 17.7, 64 items of 40 22.9 / 18.1, 22.9 / 18.3, 23.4 / 18.3.  With two
+// workgroups on a CU steps without edge checks were 1-8 % slower (128 and 384 items of 24).
+template <int EB>
+using Lone = Shape<EB, 64, 64, 2, 2, 2, 2>;
 template <int EB>
 using ByElement = Shape<EB, 64, 64, 2, 2, 1, 4>;
 
@@ -672,6 +684,7 @@ template <int EB>
 hipError_t configure_type() {
   hipError_t e = configure_layouts<Wide<EB>>();
   if (e == hipSuccess) e = configure_layouts<Narrow<EB>>();
+  if (e == hipSuccess) e = configure_layouts<Lone<EB>>();
   if (e == hipSuccess) e = configure_elements<ByElement<EB>>();
   if (EB == 4 && e == hipSuccess) e = configure_layouts<Quarter>();
   if (EB == 2 && e == hipSuccess) e = configure_one<Large, kByK, kByK>();
@@ -698,8 +711,11 @@ hipError_t launch_type(const ExecuteArgs& args, int tile_class, const GeneralLoa
     return launch_one<Wide4<EB>, kByRow, kByRow>(cut, grid, stream);
   }
   if (EB == 4 && how.tile == kTileQuarter) return launch_layouts<Quarter>(args, tile_class, how, stream);
-  return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, how, stream)
-                                 : launch_layouts<Wide<EB>>(args, tile_class, how, stream);
+  if (how.tile != kTileNarrow) return launch_layouts<Wide<EB>>(args, tile_class, how, stream);
+  ExecuteArgs cut = args;
+  return cut_items<Narrow<EB>>(&cut, tile_class, how) <= how.cus && how.list.longest > 7 * Narrow<EB>::KS
+             ? launch_layouts<Lone<EB>>(args, tile_class, how, stream)
+             : launch_layouts<Narrow<EB>>(args, tile_class, how, stream);
 }
 
 }  // namespace

@@ -91,6 +91,33 @@ def test_steps_that_check_no_edge_and_the_last_ones(K, transA, transB):
         assert np.array_equal(block_of(few, plan.tasks[i]), block_of(full, plan.tasks[i]))
 
 
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+@pytest.mark.parametrize("dtype,K", [("f32", 224), ("f32", 225), ("f32", 256), ("f32", 289), ("f32", 352), ("bf16", 448), ("bf16", 449),
+                                     ("bf16", 512), ("bf16", 577), ("bf16", 713)])
+def test_one_tile_per_cu_has_the_bits_of_the_full_launch(dtype, K, transA, transB):
+    """7 to 12 K steps; launches that leave a CU one 64 x 64 workgroup read ahead from 8 on."""
+    M, N = 1309, 1299                                  # 11 x 11 tiles, the last ones clipped
+    def placed(x):                                     # odd row stride, NaN behind the rows
+        x = stored(x, 0)
+        room = torch.full((x.shape[0], x.shape[1] + 1 + x.shape[1] % 2 * 2), float("nan"), dtype=x.dtype)
+        room[:, :x.shape[1]] = x
+        return room.cuda()[:, :x.shape[1]]
+    A = placed(stored(make_matrix(33, M, K, dtype), transA))
+    B = placed(stored(make_matrix(34, K, N, dtype), transB))
+    plan = cleave.plan_uniform(M, N, K, 128, 128, 1)
+    full = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
+    cleave.execute(plan, A, B, full, transA, transB)
+    assert "64x64" in plan.last_kernel and "direct" not in plan.last_kernel
+    ids = list(range(81, 121))
+    few = torch.full_like(full, float("nan"))
+    cleave.execute(plan, A, B, few, transA, transB, task_ids=ids)
+    assert "64x64" in plan.last_kernel and "direct" not in plan.last_kernel and "quarters" not in plan.last_kernel
+    torch.cuda.synchronize()
+    full, few = full.cpu().numpy(), few.cpu().numpy()
+    for i in ids:
+        assert np.array_equal(block_of(few, plan.tasks[i]), block_of(full, plan.tasks[i]))
+
+
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("M,N", [(1, 7), (15, 17), (16, 16), (31, 33), (32, 32), (65, 63)])
 def test_assembled_edges_of_the_quarter(M, N, out_dtype):
