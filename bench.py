@@ -35,8 +35,8 @@ PEAK_HBM_GBPS = 8000.0
 # dropped on a mismatch.
 COUNTER_TRAFFIC = {
     "workload": "c3",
-    "sources_sha256": "9283fe1123acbbc002f7125430b1b7f7e24ca21b7ebe5c1122aae6c728b1cdf2",
-    "execute_bytes_per_launch": (2.0 * 217814 + 388644) * 1024,
+    "sources_sha256": "2c1344d81797e57fb68841947b06dc774ebc01d79b772e49b5f6e2fc2f3abf58",
+    "execute_bytes_per_launch": (2.0 * 206335 + 388642) * 1024,
     "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
 
