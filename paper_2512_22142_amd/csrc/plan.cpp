@@ -34,21 +34,30 @@ constexpr int kXcds = 8;
 constexpr size_t kSpreadItems = 256;
 
 // The work items that run on an XCD at the same time (32 CUs, one large item or two small
-// ones on each) are taken from a patch of 4 x 8 (long lists 8 x 8) sub-tiles at one chunk of the
+// ones on each) are taken from a patch of 4 x 8 (8 x 8) sub-tiles at one chunk of the
 // inner dimension: they share that many row panels of A and column panels of B in the XCD's L2.
-// A long list's large items are two rounds then that share the column panels: 16384 x 5120 x
-// 13824 in 8 splits, three layouts with their sums, 8645 -> 8580 us, a layer of width 4096 6190 ->
-// 6160.  (Taller patches, 12 or 16 rows, the rows of patches to and fro, columns of patches
-// first: less, and up to 1.5 % slower on layers of width 768.)
 // Small items in patches of 4 x 8 / 8 x 8, bf16 in 128 x 128 blocks, the time of the second
 // over the first's, operands as the launch before left them / in no cache, layouts NN, NT, TN: 8192^2
 // with 128 of K 0.914 / 0.930, 0.918 / 0.931, 0.943 / 0.933, with 1024 0.984 / 0.924, 0.990 / 0.937, 0.960
 // / 0.920; 16384 x 4096 x 4096 in 4 splits 0.944 / 0.943, 0.951 / 0.945, 0.959 / 0.961; 6144^2 with 2048
 // 0.989 / 0.988, 0.976 / 0.984, 0.966 / 0.972.  Fewer items cover their regions in a few patches
 // and gain less or lose: 2048 with 1024 of K 1.002 / 0.955, 0.997 / 0.980, 1.003 / 0.972, with 512 up to
-// 1.035 / 1.011, 1024 with 2048 1.003 / 1.001, 1.026 / 1.002, 1.034 / 0.997.
+// 1.035 / 1.011, 1024 with 2048 1.003 / 1.001, 1.026 / 1.002, 1.034 / 0.997.  The general kernel,
+// which runs this list too: 4096 items, fp32, 8192^2 with 128 of K 0.993 / 0.971, 0.996 / 0.978, 1.002 /
+// 0.997, bf16 with unaligned rows 16384 x 4096 with 256 0.981 / 0.974, 0.955 / 0.978, 0.964 / 0.968; both
+// 0.98 to 1.01 from 2304 items on with 512 of K and more.
+// Large items stay with 4 x 8, which is all that an XCD runs at a time: the second round that 8 x 8
+// adds wins or loses with how the patches divide the regions, on both sides of any length of the
+// list.  8192 x 12288 with 512 of K (1536 items) 0.993 / 1.038, 1.002 / 1.047, 0.983 / 1.026; 16384 x 8192 with
+// 1024 (2048) 1.020 / 1.022, 1.022 / 1.004, 1.024 / 1.014; 9216 x 8448 in 2 splits of 1024 (2376) 0.999 /
+// 0.978, 0.974 / 0.980, 0.971 / 0.985; 16384 x 12288 with 512 (3072) 1.049 / 1.026, 1.029 / 1.021, 1.040 / 1.030;
+// 8192 x 3072 in 8 splits of 512 (3072) 1.004 / 1.063, 1.007 / 1.001, 1.005 / 1.073; 16384 x 5120 in 8 of 1728
+// (10240) 0.984 / 0.988, 0.977 / 0.973, 0.986 / 0.991; three products in a launch, 8192 x 3072 in 2 splits
+// of 512 (2304) 1.089 / 1.103, 1.023 / 1.034, 1.094 / 1.089, 4096 x 4096 in 4 of 1024 (3072) 1.047 / 1.047, 1.045 /
+// 1.050, 1.102 / 1.051.
 constexpr uint32_t kPatchCols = 8;
-constexpr uint32_t patch_rows(size_t items) { return items <= 2048 ? 4 : 8; }
+constexpr size_t kManySmallItems = 2048;
+constexpr uint32_t patch_rows(int cls, size_t items) { return cls == kTileLarge || items <= kManySmallItems ? 4 : 8; }
 
 void order_work_items(cleave_plan* p) {
   // Region grid: minimise M/gm + N/gn over gm * gn = 8.
@@ -94,7 +103,7 @@ void order_work_items(cleave_plan* p) {
       uint32_t outer_member, split, pm, pn, inner_member, m, n;
       WorkItem item;
     };
-    const uint32_t rows = patch_rows(source.size());
+    const uint32_t rows = patch_rows(cls, source.size());
     std::vector<Key> lists[kXcds];
     for (auto& l : lists) l.reserve(source.size() / kXcds + 1);
     // Batch members share no output.  Small members (fewer items than the
