@@ -34,7 +34,7 @@ constexpr int kXcds = 8;
 constexpr size_t kSpreadItems = 256;
 
 // The work items that run on an XCD at the same time (32 CUs, one large item or two small
-// ones on each) are taken from a patch of 4 x 8 (8 x 8) sub-tiles at one chunk of the
+// ones on each) are taken from a patch of 4 x 8 (long lists of small items of one GEMM 8 x 8) sub-tiles at one chunk of the
 // inner dimension: they share that many row panels of A and column panels of B in the XCD's L2.
 // Small items in patches of 4 x 8 / 8 x 8, bf16 in 128 x 128 blocks, the time of the second
 // over the first's, operands as the launch before left them / in no cache, layouts NN, NT, TN: 8192^2
@@ -45,7 +45,7 @@ constexpr size_t kSpreadItems = 256;
 // 1.035 / 1.011, 1024 with 2048 1.003 / 1.001, 1.026 / 1.002, 1.034 / 0.997.  The general kernel,
 // which runs this list too: 4096 items, fp32, 8192^2 with 128 of K 0.993 / 0.971, 0.996 / 0.978, 1.002 /
 // 0.997, bf16 with unaligned rows 16384 x 4096 with 256 0.981 / 0.974, 0.955 / 0.978, 0.964 / 0.968; both
-// 0.98 to 1.01 from 2304 items on with 512 of K and more.
+// 0.97 to 1.03 from 2304 items on with 512 of K and more.
 // Large items stay with 4 x 8, which is all that an XCD runs at a time: the second round that 8 x 8
 // adds wins or loses with how the patches divide the regions, on both sides of any length of the
 // list.  8192 x 12288 with 512 of K (1536 items) 0.993 / 1.038, 1.002 / 1.047, 0.983 / 1.026; 16384 x 8192 with
@@ -57,7 +57,15 @@ constexpr size_t kSpreadItems = 256;
 // 1.050, 1.102 / 1.051.
 constexpr uint32_t kPatchCols = 8;
 constexpr size_t kManySmallItems = 2048;
-constexpr uint32_t patch_rows(int cls, size_t items) { return cls == kTileLarge || items <= kManySmallItems ? 4 : 8; }
+// So do those of several members: where they take turns patch by patch, a larger patch is longer on its way
+// to the member that reads the same panels next.  Three products of one A in a launch, 2048 x 2048 in 4 splits
+// of 128 0.979 / 1.074, 0.983 / 1.048, 0.980 / 1.085, 1024 x 4096 in 4 of 256 0.986 / 1.142, 0.997 / 1.141,
+// 0.993 / 1.125, 4096 x 4096 with 512 of K 1.005 / 0.992, 0.997 / 0.991, 1.019 / 0.974, bf16 with unaligned
+// rows 2048 x 2048 in 3 of 171 0.985 / 1.024, 0.987 / 1.040, 0.978 / 1.035; 32 members of 2048 x 2048 x 128
+// 1.109 / 1.051, 1.074 / 1.038, 1.081 / 1.035, 64 of 1024 x 1024 x 128 0.997 / 1.003, 0.991 / 0.999, 1.003 / 0.992.
+constexpr uint32_t patch_rows(int cls, size_t items, bool members) {
+  return cls == kTileLarge || members || items <= kManySmallItems ? 4 : 8;
+}
 
 void order_work_items(cleave_plan* p) {
   // Region grid: minimise M/gm + N/gn over gm * gn = 8.
@@ -103,7 +111,7 @@ void order_work_items(cleave_plan* p) {
       uint32_t outer_member, split, pm, pn, inner_member, m, n;
       WorkItem item;
     };
-    const uint32_t rows = patch_rows(cls, source.size());
+    const uint32_t rows = patch_rows(cls, source.size(), p->batch > 0);
     std::vector<Key> lists[kXcds];
     for (auto& l : lists) l.reserve(source.size() / kXcds + 1);
     // Batch members share no output.  Small members (fewer items than the

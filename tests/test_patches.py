@@ -65,3 +65,10 @@ def test_large_items_are_listed_in_patches_of_four_rows(program, M, N, items):
 def test_more_than_2048_small_items_are_listed_in_patches_of_eight_rows(program, M, N, rows):
     first = {4: ["4x8", "4x16", "2048"], 8: ["4x8", "8x8", "4096"]}[rows]
     assert listed(program, M, N, 64, 128, 1, 0, False) == first
+
+
+@pytest.mark.parametrize("M,N,members,then", [(1024, 2048, 24, "4x16"), (4096, 4096, 3, "4x8")])
+def test_small_items_of_several_members_are_listed_in_patches_of_four_rows(program, M, N, members, then):
+    """More than 2048 items: members on an XCD each, the patch beside it next; members spread over
+    the XCDs, the same patch of the next member next."""
+    assert listed(program, M, N, 64, 128, 1, members, False) == ["4x8", then, str(members * M * N // 16384)]
