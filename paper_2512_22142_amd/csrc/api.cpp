@@ -318,18 +318,21 @@ int release_subset_slice(cleave::SubsetRing& r, int64_t begin, int64_t total, hi
 }
 
 const char* kernel_name(int dtype, const cleave::GeneralLoads& how, int transA, int transB) {
-  static const char* names[2][5][4] = {
+  static const char* names[2][6][4] = {
       {{"execute_f32_128x128_nn", "execute_f32_128x128_nt", "execute_f32_128x128_tn", "execute_f32_128x128_tt"},
        {"execute_f32_64x64_nn", "execute_f32_64x64_nt", "execute_f32_64x64_tn", "execute_f32_64x64_tt"},
        {"none", "none", "none", "none"},
        {"execute_f32_64x64_quarters_nn", "execute_f32_64x64_quarters_nt", "execute_f32_64x64_quarters_tn",
         "execute_f32_64x64_quarters_tt"},
-       {"execute_f32_element", "execute_f32_element", "execute_f32_element", "execute_f32_element"}},
+       {"execute_f32_element", "execute_f32_element", "execute_f32_element", "execute_f32_element"},
+       {"execute_f32_64x64_lone_nn", "execute_f32_64x64_lone_nt", "execute_f32_64x64_lone_tn", "execute_f32_64x64_lone_tt"}},
       {{"execute_bf16_128x128_nn", "execute_bf16_128x128_nt", "execute_bf16_128x128_tn", "execute_bf16_128x128_tt"},
        {"execute_bf16_64x64_nn", "execute_bf16_64x64_nt", "execute_bf16_64x64_tn", "execute_bf16_64x64_tt"},
        {"none", "execute_bf16_256x256_nt", "none", "none"},
        {"none", "none", "none", "none"},
-       {"execute_bf16_element", "execute_bf16_element", "execute_bf16_element", "execute_bf16_element"}}};
+       {"execute_bf16_element", "execute_bf16_element", "execute_bf16_element", "execute_bf16_element"},
+       {"execute_bf16_64x64_lone_nn", "execute_bf16_64x64_lone_nt", "execute_bf16_64x64_lone_tn",
+        "execute_bf16_64x64_lone_tt"}}};
   const int row = how.a_elements || how.b_elements ? 4 : how.tile == cleave::kTileWide4 ? cleave::kTileWide : how.tile;
   return names[dtype == CLEAVE_BF16 ? 1 : 0][row][(transA ? 2 : 0) + (transB ? 1 : 0)];
 }
@@ -842,6 +845,8 @@ int execute_impl(cleave_plan* plan, const int64_t* task_ids, int64_t n_ids, cons
           a_elements, b_elements, shapes[c], cus};
       if (how.tile == cleave::kTileWide && cleave::four_waves(dtype, transA, transB, items, shapes[c], cus))
         how.tile = cleave::kTileWide4;
+      if (how.tile == cleave::kTileNarrow && cleave::runs_lone(dtype, c, counts[c], shapes[c], cus))
+        how.tile = cleave::kTileLone;
       const hipError_t he = cleave::launch_execute(args, dtype, c, how, stream);
       if (he != hipSuccess) return launch_failed(he);
       if (counts[c] > most) plan->last_kernel = kernel_name(dtype, how, transA, transB);

@@ -668,7 +668,7 @@ using Large = Shape<2, kLargeTileRows, kLargeTileCols, 2, 4, 1, 2>;
 template <int EB>
 using Narrow = Shape<EB, 64, 64, 2, 2, 2, 4>;
 // Read ahead as the quarters do, 180 registers instead of 126, for launches of at most one
-// 64 x 64 workgroup per CU whose longest chunk has eight steps or more.  us, Narrow / Lone,
+// 64 x 64 workgroup per CU whose longest chunk has eight steps or more (runs_lone).  us, Narrow / Lone,
 // layouts NN, NT, TN: fp32, 64 items, 4 steps 6.8 / 6.9, 6.4 / 6.6, 6.8 / 6.9, 8 steps 9.4 / 9.3,
 // 9.1 / 8.9, 9.5 / 9.2, 24 steps 20.1 / 17.5, 19.9 / 17.5, 20.3 / 17.6, 64 steps 47.2 / 38.9,
 // 47.4 / 38.9, 47.9 / 39.1; bf16, rows not 16-byte aligned, operands from HBM, 16 items, 4 steps
@@ -711,11 +711,9 @@ hipError_t launch_type(const ExecuteArgs& args, int tile_class, const GeneralLoa
     return launch_one<Wide4<EB>, kByRow, kByRow>(cut, grid, stream);
   }
   if (EB == 4 && how.tile == kTileQuarter) return launch_layouts<Quarter>(args, tile_class, how, stream);
-  if (how.tile != kTileNarrow) return launch_layouts<Wide<EB>>(args, tile_class, how, stream);
-  ExecuteArgs cut = args;
-  return cut_items<Narrow<EB>>(&cut, tile_class, how) <= how.cus && how.list.longest > 7 * Narrow<EB>::KS
-             ? launch_layouts<Lone<EB>>(args, tile_class, how, stream)
-             : launch_layouts<Narrow<EB>>(args, tile_class, how, stream);
+  if (how.tile == kTileLone) return launch_layouts<Lone<EB>>(args, tile_class, how, stream);
+  return how.tile == kTileNarrow ? launch_layouts<Narrow<EB>>(args, tile_class, how, stream)
+                                 : launch_layouts<Wide<EB>>(args, tile_class, how, stream);
 }
 
 }  // namespace

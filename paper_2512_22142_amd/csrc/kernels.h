@@ -94,7 +94,8 @@ inline bool streamed_output(int64_t bytes, bool batched) {
 // Workgroup tile of the general execute kernel: 128 x 128, 64 x 64, 256 x 256
 // (only for bf16 work items of the large class with both operands K-contiguous), or
 // the quarters of the 64 x 64 one (32 x 32, only fp32).  kTileWide4: 128 x 128 in four waves.
-enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2, kTileQuarter = 3, kTileWide4 = 4 };
+// kTileLone: 64 x 64, reading a K step ahead.
+enum ExecuteTile : int { kTileWide = 0, kTileNarrow = 1, kTileHuge = 2, kTileQuarter = 3, kTileWide4 = 4, kTileLone = 5 };
 
 // Whether a list of `items` 128 x 128 tiles runs in four waves of 64 x 64 each instead of eight
 // of 32 x 64.  Eight read half as much again from LDS per product and hide a workgroup's start
@@ -170,6 +171,14 @@ inline int general_workgroups(int64_t blocks, int64_t resident, int64_t taken_up
   if (blocks > resident && blocks <= taken_up_to) return static_cast<int>(resident);
   constexpr int64_t kMaxGrid = int64_t{1} << 20;   // the kernel loops beyond that
   return static_cast<int>(blocks < kMaxGrid ? blocks : kMaxGrid);
+}
+// Whether a list of `items` work items that runs in 64 x 64 tiles runs in the form that reads a K step
+// ahead: at most one workgroup per CU, and eight steps or more in the longest chunk (both
+// sides beside the form, Lone in execute.hip).
+inline bool runs_lone(int dtype, int tile_class, int64_t items, const ListShape& list, int cus) {
+  const int64_t workgroups = (items + 7) / 8 * 8 * parts_along(list.rows, tile_rows(tile_class), 64) *
+                             parts_along(list.cols, tile_cols(tile_class), 64);
+  return workgroups <= cus && list.longest > (dtype == CLEAVE_BF16 ? 7u * 64 : 7u * 32);
 }
 inline int64_t second_tiles_taken_up_to(int64_t resident, int tile, const ListShape& list) {
   if (!list.equal()) return 0;

@@ -82,6 +82,31 @@ CASES = {
   CHECK(four(CLEAVE_BF16, 1, 0, 1793) && !four(CLEAVE_BF16, 1, 0, 1792) && four(CLEAVE_BF16, 0, 1, 4096));
   CHECK(!four(CLEAVE_BF16, 0, 0, 4096) && !four(CLEAVE_BF16, 1, 1, 4096));
 """,
+    "one_workgroup_of_64_per_cu_reads_ahead": """
+  cleave::ListShape l;
+  cleave_task t{};
+  t.m_len = t.n_len = 128;
+  t.k_len = 224;
+  l.add(t);
+  const auto lone = [&](int dtype, int cls, int64_t items) { return cleave::runs_lone(dtype, cls, items, l, 256); };
+  CHECK(!lone(CLEAVE_F32, cleave::kTileSmall, 8));
+  t.k_len = 225;
+  l.add(t);
+  CHECK(lone(CLEAVE_F32, cleave::kTileSmall, 64) && lone(CLEAVE_F32, cleave::kTileSmall, 57) && !lone(CLEAVE_F32, cleave::kTileSmall, 65) && !lone(CLEAVE_BF16, cleave::kTileSmall, 64));
+  t.k_len = 448;
+  l.add(t);
+  CHECK(!lone(CLEAVE_BF16, cleave::kTileSmall, 64));
+  t.k_len = 449;
+  l.add(t);
+  CHECK(lone(CLEAVE_BF16, cleave::kTileSmall, 64) && !lone(CLEAVE_BF16, cleave::kTileSmall, 65));
+  t.m_len = t.n_len = 256;
+  l.add(t);
+  CHECK(lone(CLEAVE_F32, cleave::kTileLarge, 16) && !lone(CLEAVE_F32, cleave::kTileLarge, 17));
+  cleave::ListShape small;
+  t.m_len = t.n_len = 64;
+  small.add(t);
+  CHECK(cleave::runs_lone(CLEAVE_F32, cleave::kTileSmall, 256, small, 256) && !cleave::runs_lone(CLEAVE_F32, cleave::kTileSmall, 257, small, 256));
+""",
     "the_longest_chunks": """
   cleave::ListShape l;
   cleave_task t{};

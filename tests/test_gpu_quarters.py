@@ -107,11 +107,12 @@ def test_one_tile_per_cu_has_the_bits_of_the_full_launch(dtype, K, transA, trans
     plan = cleave.plan_uniform(M, N, K, 128, 128, 1)
     full = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
     cleave.execute(plan, A, B, full, transA, transB)
-    assert "64x64" in plan.last_kernel and "direct" not in plan.last_kernel
+    layout = "%s_64x64%%s_%s%s" % (dtype, "nt"[transA], "nt"[transB])
+    assert plan.last_kernel == "execute_" + layout % ""
     ids = list(range(81, 121))
     few = torch.full_like(full, float("nan"))
     cleave.execute(plan, A, B, few, transA, transB, task_ids=ids)
-    assert "64x64" in plan.last_kernel and "direct" not in plan.last_kernel and "quarters" not in plan.last_kernel
+    assert plan.last_kernel == "execute_" + layout % ("_lone" if K > 7 * (32 if dtype == "f32" else 64) else "")
     torch.cuda.synchronize()
     full, few = full.cpu().numpy(), few.cpu().numpy()
     for i in ids:
