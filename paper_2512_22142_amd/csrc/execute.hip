@@ -399,8 +399,7 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
       constexpr int R = decltype(rows_tag)::value, KSUB = decltype(ks_tag)::value;
       if constexpr (S::BLK == 16 && KC) {
         // k of the sub-step: 4 lh + l4, and two further on; half of the lanes read them
-        // the other way round (and swap them back before use), so that the 64 words are in
-        // different banks
+        // the other way round (mma puts them back), so that the 64 words are in different banks
         const uint32_t one = *reinterpret_cast<const uint32_t*>(stage + addr[KSUB]);
         const uint32_t two = *reinterpret_cast<const uint32_t*>(stage + (addr[KSUB] ^ 8));
         return u32x4{one, two, 0, 0};
@@ -430,8 +429,8 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
       if constexpr (S::BLK == 16) {
         // One instruction multiplies k, k + 4, k + 1, k + 5 of a sub-step, in this order
         // (lanes 0-15, 16-31, ...): the chain of two 32 x 32 x 2 ones, bit for bit.
-        const f32x4 a4 = __builtin_bit_cast(f32x4, fa[buf][0]);
-        const f32x4 b4 = __builtin_bit_cast(f32x4, fb[buf][0]);
+        const f32x4 a4 = __builtin_bit_cast(f32x4, A_K && lh ? u32x4{fa[buf][0][1], fa[buf][0][0], 0, 0} : fa[buf][0]);
+        const f32x4 b4 = __builtin_bit_cast(f32x4, B_K && lh ? u32x4{fb[buf][0][1], fb[buf][0][0], 0, 0} : fb[buf][0]);
 #pragma unroll
         for (int e = 0; e < 2; ++e) acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[e], b4[e], acc[0][0], 0, 0, 0);
       } else if constexpr (EB == 2) {
@@ -479,8 +478,8 @@ __global__ __launch_bounds__(S::NT, S::WPE) void execute_kernel(ExecuteArgs args
       };
       // (barriers to the scheduler: left alone it moves the reads down to their use)
       auto mma_sub = [&](int p, int x) {
-        fa[0][0] = S::BLK == 16 && A_K && lh ? u32x4{ga[p][x][1], ga[p][x][0], 0, 0} : ga[p][x];
-        fb[0][0] = S::BLK == 16 && B_K && lh ? u32x4{gb[p][x][1], gb[p][x][0], 0, 0} : gb[p][x];
+        fa[0][0] = ga[p][x];
+        fb[0][0] = gb[p][x];
         mma(0);
         __builtin_amdgcn_sched_barrier(0);
       };
