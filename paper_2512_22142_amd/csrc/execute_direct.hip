@@ -509,7 +509,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
   //   kRefilledLast (ONE_ITEM): the same, but the step it is refilled with is the chunk's last
   //     and no whole one.
   //   1 .. STAGES (ONE_ITEM): that many steps are left, this one among them, all in the ring.
-  //   kAnyStep: whatever applies.
+  //   kAnyStep (several items per workgroup): whatever applies.
   constexpr int kAnyStep = 100, kRefilled = 101, kRefilledLast = 102;
 
   for (;;) {
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
           } else if (cont) {
             issue(nx, s + STAGES - steps, st);
           }
-          if (!S::ONE_ITEM && s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
+          if (s == 0) after_next = load_item(it_next + stride < it_end ? it_next + stride : last_item);
         }
       };
       constexpr int_c<0> k0{};
@@ -676,22 +676,22 @@ __global__ __launch_bounds__(S::NT, 512 / S::NT) void execute_direct_kernel(Exec
       for (; s + STAGES < full; ++s) k_step(int_c<kRefilled>{}, std::false_type{}, s);
       if (TAILS && s + STAGES < steps) k_step(int_c<kRefilledLast>{}, std::false_type{}, s++);
       const int left = steps - s;
-      static_assert(!S::ONE_ITEM || STAGES == 4, "the copies below");
+      static_assert(STAGES == 4, "the copies below");
       if (left > 3) k_step(int_c<4>{}, std::false_type{}, s++);
       if (left > 2) k_step(int_c<3>{}, std::false_type{}, s++);
       if (left > 1) k_step(int_c<2>{}, std::false_type{}, s++);
       k_step(int_c<1>{}, std::false_type{}, s);
     } else {
+      static_assert(STAGES == 2, "a step behind step 0 has only the ring's own loads outstanding");
       k_step(int_c<kAnyStep>{}, std::true_type{}, 0);
       int s = 1;
-      if constexpr (STAGES > 2)
-        for (; s < STAGES - 1 && s < steps; ++s) k_step(int_c<kAnyStep>{}, std::false_type{}, s);
       for (; s + STAGES < full; ++s) k_step(int_c<kRefilled>{}, std::false_type{}, s);
       for (; s < steps; ++s) k_step(int_c<kAnyStep>{}, std::false_type{}, s);
     }
 
-    // Every wave is past the last step's barrier, hence past all of its
-    // fragment reads of this item.
+    // With items to follow, every wave is past the last step's barrier, hence past all of its
+    // fragment reads of this item.  A lone item's last step has none: nothing refills the ring,
+    // and the stores' image lies behind it and is the wave's own.
     const TileTarget target = c.out;
     const int m_valid = c.m_valid, n_valid = c.n_valid;
     // The ring is free unless it was handed over: the next item's ring fill is
