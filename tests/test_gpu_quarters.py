@@ -19,15 +19,16 @@ LAYOUTS = [(0, 0), (0, 1), (1, 0), (1, 1)]
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
 @pytest.mark.parametrize("K", [8, 31, 32, 33, 96, 301])
 def test_a_few_tasks_have_the_bits_of_the_full_launch(K, transA, transB):
-    M, N = 1309, 505                                   # 11 x 4 tiles, the last ones clipped
+    M, N = 1309, 761                                   # 11 x 6 tiles, the last ones clipped
     A = stored(make_matrix(21, M, K, "f32"), transA)
     B = stored(make_matrix(22, K, N, "f32"), transB)
     plan = cleave.plan_uniform(M, N, K, 128, 128, 1)
     dA, dB = A.cuda(), B.cuda()
     full = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
     cleave.execute(plan, dA, dB, full, transA, transB)
-    assert plan.num_tasks == 44 and "f32_64x64" in plan.last_kernel and "quarters" not in plan.last_kernel
-    ids = [0, 3, 17, 40, 43]
+    # more than one workgroup per CU: not the form that reads ahead, as the quarters do
+    assert plan.num_tasks == 66 and plan.last_kernel == "execute_f32_64x64_" + "nt"[transA] + "nt"[transB]
+    ids = [0, 5, 17, 60, 65]
     few = torch.full_like(full, float("nan"))
     cleave.execute(plan, dA, dB, few, transA, transB, task_ids=ids)
     assert "quarters" in plan.last_kernel
@@ -69,19 +70,19 @@ def test_two_quarters_on_a_cu_only_with_longer_chunks(K, transA, transB):
 @pytest.mark.parametrize("K", [33, 64, 65, 97, 161, 192, 193, 224, 225, 257, 289, 544])   # 2 to 17 steps of 32
 def test_steps_that_check_no_edge_and_the_last_ones(K, transA, transB):
     """From seven steps on the quarters run pairs of steps without edge checks: the bits of the
-    64 x 64 tile, and nothing read behind the operands (NaN there)."""
-    M, N = 640, 512
+    64 x 64 tile that reads nothing ahead, and nothing read behind the operands (NaN there)."""
+    M, N = 1088, 1024
     def placed(x):
         rows, cols = x.shape
         room = torch.full((rows * cols + 4096,), float("nan"))
         room[:rows * cols] = x.reshape(-1)
         return room.cuda()[:rows * cols].view(rows, cols)
     A, B = placed(stored(make_matrix(31, M, K, "f32"), transA)), placed(stored(make_matrix(32, K, N, "f32"), transB))
-    plan = cleave.plan_uniform(M, N, K, 64, 64, 1)     # 80 tiles
+    plan = cleave.plan_uniform(M, N, K, 64, 64, 1)     # 272 tiles, more than one per CU
     full = torch.empty(plan.partial_elems, dtype=torch.float32, device="cuda")
     cleave.execute(plan, A, B, full, transA, transB)
-    assert "f32_64x64" in plan.last_kernel and "quarters" not in plan.last_kernel
-    ids = [0, 7, 41, 79]
+    assert plan.last_kernel == "execute_f32_64x64_" + "nt"[transA] + "nt"[transB]
+    ids = [0, 7, 141, 271]
     few = torch.full_like(full, float("nan"))
     cleave.execute(plan, A, B, few, transA, transB, task_ids=ids)
     assert "quarters" in plan.last_kernel
