@@ -18,7 +18,11 @@ from gpu_util import block_of, stored
 pytestmark = pytest.mark.gpu
 
 
-def check(M, N, K, tile, S, transA, transB, kernel):
+def layout(transA, transB):
+    return "_" + "nt"[transA] + "nt"[transB]
+
+
+def check(M, N, K, tile, S, transA, transB, kernel=None):
     a = make_matrix(M * 3 + K, M, K, "bf16", integer_valued=True)
     b = make_matrix(N * 5 + K, K, N, "bf16", integer_valued=True)
     A, B = stored(a, transA), stored(b, transB)
@@ -28,7 +32,10 @@ def check(M, N, K, tile, S, transA, transB, kernel):
     C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
     dA, dB = A.cuda(), B.cuda()
     cleave.execute(plan, dA, dB, parts, transA, transB)
-    assert kernel in plan.last_kernel, plan.last_kernel
+    if kernel is None:
+        assert "direct_bf16" in plan.last_kernel, plan.last_kernel
+    else:
+        assert plan.last_kernel == "execute_" + kernel + layout(transA, transB)
     cleave.reduce(plan, parts, C)
     torch.cuda.synchronize()
     opA, opB = og.logical_operands(A, transA, B, transB)
@@ -54,7 +61,10 @@ def check(M, N, K, tile, S, transA, transB, kernel):
 @pytest.mark.parametrize("K,S", [(8, 1), (72, 1), (136, 1), (208, 2), (1104, 3)])
 def test_tails_of_whole_eights_exact(K, S, transA, transB):
     check(264, 136, K, (264, 136), S, transA, transB, "direct_bf16_64x64")
-    check(1544, 2056, K, (128, 128), S, transA, transB, "direct_bf16_128x128")
+    # 221 blocks, then 323: from more than one item per CU on two stages and several items per workgroup
+    check(1544, 2056, K, (128, 128), S, transA, transB, "direct_bf16_128x128_deep" if S == 1 else "direct_bf16_128x128")
+    if S == 1:
+        check(2312, 2056, K, (128, 128), S, transA, transB, "direct_bf16_128x128")
     if S == 1 and K < 200:
         check(8192 + 264, 4608, K, (512, 512), S, transA, transB, "direct_bf16_256x256")   # several items per workgroup
         check(4096 + 264, 4352, K, (512, 512), S, transA, transB, "direct_bf16_128x128")   # a little over a round: cut small
@@ -89,14 +99,14 @@ def test_a_round_of_large_items_stays_in_the_fast_kernel_beside_tails(rows):
 def test_tails_in_the_deep_ring_exact():
     for K in (1032, 1080, 1336):
         for transA, transB in ((0, 0), (1, 0), (0, 1)):
-            check(1536, 1536, K, (128, 128), 1, transA, transB, "128x128_deep")
+            check(1536, 1536, K, (128, 128), 1, transA, transB, "direct_bf16_128x128_deep")
 
 
 @pytest.mark.parametrize("transA,transB", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K,tile,S,kernel", [
     (8192 + 264, 4608, 136, 512, 1, "direct_bf16_256x256"),
     (4096, 4352, 1032, 512, 1, "direct_bf16_128x128"),     # large blocks cut small
-    (1536, 1536, 1080, 128, 1, "128x128_deep"),
+    (1536, 1536, 1080, 128, 1, "direct_bf16_128x128_deep"),
     (1544, 2056, 1104, 128, 3, "direct_bf16_128x128"),
 ])
 def test_tasks_issued_again_have_the_same_bits(M, N, K, tile, S, kernel, transA, transB):
@@ -108,7 +118,7 @@ def test_tasks_issued_again_have_the_same_bits(M, N, K, tile, S, kernel, transA,
     beside = torch.zeros(dA.numel() + 8, dtype=dA.dtype, device="cuda")[1:1 + dA.numel()].view(dA.shape).copy_(dA)
     parts, again, general = (torch.full((plan.partial_elems,), float("nan"), device="cuda") for _ in range(3))
     cleave.execute(plan, dA, dB, parts, transA, transB)
-    assert kernel in plan.last_kernel, plan.last_kernel
+    assert plan.last_kernel == "execute_" + kernel + layout(transA, transB)
     ids = sorted({0, plan.num_tasks // 3, plan.num_tasks // 2, plan.num_tasks - 1})
     cleave.execute(plan, dA, dB, again, transA, transB, task_ids=ids)
     assert "direct_bf16_64x64" in plan.last_kernel, plan.last_kernel
@@ -124,11 +134,11 @@ def test_tasks_issued_again_have_the_same_bits(M, N, K, tile, S, kernel, transA,
 
 @pytest.mark.parametrize("K,S", [(2, 1), (9, 2), (65, 1), (131, 3), (1025, 4)])
 def test_any_chunk_of_operands_with_the_inner_dimension_across_their_rows_exact(K, S):
-    check(520, 264, K, (264, 136), S, 1, 0, "direct_bf16")
-    check(4096, 2304, K, (512, 512), S, 1, 0, "direct_bf16")
+    check(520, 264, K, (264, 136), S, 1, 0)
+    check(4096, 2304, K, (512, 512), S, 1, 0)
 
 
 @pytest.mark.parametrize("M", [1, 3, 127, 1301])
 def test_any_number_of_rows_exact(M):
-    check(M, 136, 208, (100, 72), 2, 0, 0, "direct_bf16")
-    check(M, 1096, 264, (301, 512), 1, 0, 1, "direct_bf16")
+    check(M, 136, 208, (100, 72), 2, 0, 0)
+    check(M, 1096, 264, (301, 512), 1, 0, 1)

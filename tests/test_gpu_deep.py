@@ -1,5 +1,5 @@
-"""Launches of at most one small work item per CU with long chains run with a
-ring of four stages: every partial block exact (integer-valued inputs) in all
+"""Launches of more than half a small work item per CU and at most one run with a
+ring of four stages (long chains here): every partial block exact (integer-valued inputs) in all
 layouts, for full and clipped items, and C with it."""
 import numpy as np
 import pytest
