@@ -548,19 +548,19 @@ int expand_subset(const cleave_plan* plan, const int64_t* task_ids, int64_t n_id
 // Few fp32 items run as quarters of the 64 x 64 tile, up to two on each CU: a wave's
 // chain of matrix instructions is what such a launch takes, and a quarter's is a
 // quarter as long (with four times the waves, half as many products per load).
-// Execute + reduce, us, 64 x 64 / quarters, layouts NN, NT, TN: 16 items of 256 of K
-// 12.4 / 10.5, 12.0 / 10.9, 12.4 / 10.2; 32 items of 128 10.3 / 10.1, 10.1 / 10.6,
-// 10.5 / 9.7, of 256 12.7 / 11.5, 12.4 / 12.5, 12.8 / 11.0, of 1024 28.4 / 21.1, 28.1 /
-// 24.7, 28.6 / 19.7; 40 items of 256 12.8 / 13.1, 12.6 / 14.0, 12.9 / 12.1; 64 of 512
-// 19.3 / 21.3, 18.8 / 22.7, 19.3 / 19.1.  With two on a CU, beyond 16 items, only chunks from
-// 128 elements on, of two K-contiguous operands (whose fragments take twice the reads) from
-// 256; execute alone, layouts NN, NT, TN, TT: 16 items of 32 4.4 / 4.4, 4.4 / 4.5, 4.6 / 4.5,
-// 4.6 / 4.4, of 128 6.3 / 5.3, 6.1 / 5.7, 6.4 / 4.9, 6.3 / 5.2; 21 items of 32 4.5 / 4.8, 4.5 / 5.0,
-// 4.6 / 4.6, 4.6 / 4.8, of 64 5.1 / 5.3, 4.9 / 5.5, 5.2 / 4.9, 5.1 / 5.3, of 128 6.4 / 6.1, 6.1 / 6.5,
-// 6.4 / 5.5, 6.3 / 6.1; 32 items of 64 5.5 / 5.7, 5.5 / 5.9, 5.5 / 5.6, 5.6 / 5.6, of 128 6.4 / 6.3,
-// 6.3 / 6.7, 6.5 / 5.7, 6.5 / 6.4, of 200 8.5 / 7.7, 8.3 / 8.4, 8.6 / 6.8, 8.5 / 7.7, of 384
-// 11.6 / 9.8, 11.5 / 11.1, 11.8 / 8.7, 11.7 / 10.0.  (The quarters' times are those of their
-// first form; since they read a step ahead they take 0.73-1.0 of them.)
+// Execute alone, us, 64 x 64 / quarters, operands in L2, layouts NN, NT, TN, TT (64 x 64 as it
+// runs: the form that reads ahead from eight steps on): 16 items of 32 of K 4.0 / 3.9, 3.8 / 3.8,
+// 4.1 / 3.8, 4.1 / 3.9, of 128 5.9 / 4.8, 5.7 / 4.9, 6.0 / 4.4, 6.0 / 4.8, of 512 12.4 / 8.1, 12.2 / 8.6,
+// 12.5 / 7.0, 12.2 / 8.1, of 2048 37 / 20.9, 37 / 22.9, 37 / 17.2, 37 / 21.2; 32 items of 32 4.1 / 4.4,
+// 3.9 / 4.4, 4.3 / 4.2, 4.2 / 4.4, of 64 4.8 / 4.7, 4.6 / 4.7, 4.9 / 4.5, 4.8 / 4.7, of 96 5.5 / 5.3,
+// 5.2 / 5.3, 5.6 / 5.0, 5.5 / 5.1, of 128 6.1 / 5.7, 5.9 / 5.9, 6.2 / 5.3, 6.1 / 5.6, of 160 6.8 / 6.1,
+// 6.6 / 6.4, 6.9 / 5.7, 6.8 / 6.1, of 256 8.4 / 7.3, 8.2 / 7.7, 8.6 / 6.6, 8.3 / 7.3, of 1024 20.9 / 16.6,
+// 20.8 / 19.0, 21.0 / 14.3, 20.8 / 17.0 (20 and 24 items as 32); 40 items of 256 8.5 / 8.6, 8.3 / 9.5,
+// 8.7 / 7.9, 8.4 / 8.6, of 1024 21.0 / 21.2, 21.0 / 24.3, 21.3 / 19.1, 21.0 / 21.8; 64 of 512 13.1 / 15.5,
+// 13.0 / 17.4, 13.2 / 13.9, 13.1 / 15.6.  With two on a CU, beyond 16 items, only chunks from 128
+// elements on, of two K-contiguous operands (whose fragments take twice the reads) from 256.  That
+// is on the safe side: the lines were drawn on forms of both that read nothing ahead, and below them the
+// quarters now gain too, from 160 on in NT, from 64 on in NN and TT (1 to 6 %), at any length in TN (2 to 15 %).
 // `whole`: that many 256 x 256 items of a subset (full launches of this kernel run
 // the all-small list), with `steps` whole K steps between them, that the kernel
 // could take as they are (bf16, both operands K-contiguous: six
@@ -589,12 +589,22 @@ cleave::ExecuteTile general_tile(int dtype, bool both_k, int64_t items, const cl
 // against 128 x 128 items with two stages, operands in L2 / from HBM, the largest of three
 // layouts, by K steps per item (256 CUs):
 //                    2 steps      4            8            16           24           48
+//    16 items parts  0.65 / 0.65  0.63 / 0.63  0.60 / 0.60  0.57 / 0.51  0.56 / 0.45  0.54 / 0.42
+//             deep   0.85 / 0.85  0.88 / 0.88  0.91 / 0.88  0.94 / 0.81  0.95 / 0.75  0.98 / 0.75
+//    64 items parts  0.70 / 0.70  0.67 / 0.67  0.64 / 0.62  0.61 / 0.56  0.59 / 0.53  0.49 / 0.48
+//             deep   0.87 / 0.86  0.89 / 0.88  0.92 / 0.86  0.94 / 0.83  0.96 / 0.83  0.81 / 0.79
+//   128 items parts  0.78 / 0.78  0.78 / 0.79  0.79 / 0.80  0.77 / 0.79  0.78 / 0.78  0.77 / 0.78
+//             deep   0.88 / 0.86  0.89 / 0.91  0.92 / 0.88  0.94 / 0.85  0.95 / 0.84  0.80 / 0.81
 //   130 items parts  0.92 / 0.95  0.94 / 0.94  0.98 / 0.93  1.01 / 0.88  0.88 / 0.89  0.86 / 0.81
 //             deep   0.88 / 0.87  0.91 / 0.91  0.92 / 0.86  0.93 / 0.80  0.78 / 0.78  0.72 / 0.72
 //   160 items parts  0.97 / 0.98  0.98 / 0.98  1.02 / 0.98  0.98 / 0.91  0.96 / 0.92  0.95 / 0.93
 //             deep   0.88 / 0.88  0.91 / 0.90  0.92 / 0.87  0.93 / 0.83  0.90 / 0.76  0.78 / 0.73
 //   224 items deep   0.89 / 0.89  0.92 / 0.91  0.92 / 0.88  0.93 / 0.82  0.83 / 0.76  0.83 / 0.74
 //   256 items deep   0.90 / 0.90  0.92 / 0.92  0.93 / 0.87  0.91 / 0.80  0.83 / 0.76  0.85 / 0.73
+// (Before its last steps were copies with constant waits the ring took 1.09 to 1.14 of the two-stage time
+// with operands in L2 at 4 and 8 steps, and ran from 16 on only.)  Two such launches at a time, on
+// two streams, 4 to 24 steps: deep 0.87 to 0.98 of two stages with 136 or 160 items each, 0.95 to 1.02
+// with 192, 1.11 to 1.17 with 256, when a CU would have held a two-stage workgroup of each.
 cleave::DirectShape direct_shape(int cls, int64_t items, int cus) {
   if (cls == cleave::kTileLarge) return cleave::kDirectLarge;
   if (items * 2 <= cus) return cleave::kDirectParts;

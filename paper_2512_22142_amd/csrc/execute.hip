@@ -23,7 +23,9 @@
 //     last 16 bytes that are inside and shift the wanted elements down.
 //   * Loads run SETS steps ahead in registers and LDS holds two steps, with one
 //     barrier per step: what bounds a launch with few workgroups is the latency
-//     of a step's loads, and SETS of them overlap.
+//     of a step's loads, and SETS of them overlap.  Where a wave is nearly alone on its
+//     SIMD (kAhead) fragments are read a step before they are multiplied: LDS is written
+//     two steps ahead then, and loads run four ahead.
 //     The waits on them count loads in flight, so the loads of a step past the
 //     last one are issued too (one line, already read) rather than skipped.
 //   * An operand whose rows hold less than 16 bytes is loaded one element at a
@@ -44,8 +46,8 @@
 // refill comes on top): the same with an odd leading dimension 620-640 TFLOP/s.
 // Execute + reduce against unaligned operands loaded by element, and one fp32 tile
 // of 256 x 256 or 128 x 128 with one step in flight: forward, dX and dW of 3001 x 1000
-// x 2500 bf16 in 4 splits 158 / 1173 us, of 2048 x 768 x 3072 fp32 257 / 403 us, 512^3
-// fp32 10.7 / 26.7 us (of the last, 4.5 us are host time saved by the native argument
+// x 2500 bf16 in 4 splits 155 / 1173 us, of 2048 x 768 x 3072 fp32 255 / 403 us, 512^3
+// fp32 10.3 / 26.7 us (of the last, 4.5 us are host time saved by the native argument
 // checks).
 #include <hip/hip_runtime.h>
 

@@ -766,12 +766,12 @@ hipError_t configure_shape() {
 //     second workgroup (4096 items of 16 steps 187 / 221 us);
 //   parts: a launch of few small items has one short-lived workgroup per CU, or
 //     none, and what bounds it is the time one K step takes a lone workgroup:
-//     0.62 us at 128 x 128, of which its matrix instructions are 0.21.  64 x 64
+//     0.40 us at 128 x 128, of which its matrix instructions are 0.21.  64 x 64
 //     parts (4 waves of 32 x 32) spread an item over four CUs, read and fill a
 //     third of the LDS per step, and four 16 KB stages keep three steps' loads
-//     in flight: 0.27 us per step.  Execute, 128 x 128 items -> parts: 24 items
-//     of 6 steps 7.0 -> 5.0 us, 64 of 64 39 -> 17, 72 of 64 42 -> 28, 128 of
-//     172 105 -> 73 us.  Full launches do better with the larger tile (4096
+//     in flight: 0.17 us per step.  Execute, 128 x 128 items -> parts: 32 items
+//     of 6 steps 6.8 -> 4.1 us, 64 of 48 30 -> 13.2, 96 of 48 31 -> 19.9, 128 of
+//     48 32 -> 22.8 us.  Full launches do better with the larger tile (4096
 //     items of 16 steps 164 / 237 us).
 using LargeShape = Shape<kLargeTileRows, kLargeTileCols, 2, 4, 64, 2, false>;
 using SmallShape = Shape<kSmallTileRows, kSmallTileCols, 2, 2, 64, 2, false>;
