@@ -35,8 +35,8 @@ PEAK_HBM_GBPS = 8000.0
 # dropped on a mismatch.
 COUNTER_TRAFFIC = {
     "workload": "c3",
-    "sources_sha256": "2c1344d81797e57fb68841947b06dc774ebc01d79b772e49b5f6e2fc2f3abf58",
-    "execute_bytes_per_launch": (2.0 * 206335 + 388642) * 1024,
+    "sources_sha256": "d19ea50cc69e6403985b8330a80a590db16400bd86602e63d7282ece4232d8b9",
+    "execute_bytes_per_launch": (2.0 * 217937 + 388640) * 1024,
     "reduce_bytes_per_launch": (2.0 * 196589 + 97134) * 1024,
 }
 
